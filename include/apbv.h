@@ -238,7 +238,8 @@ size_t apbv_query_attention_workspace_bytes(int batch, int n_q_heads, int head_d
  *   n_splits   0: chosen by the library from the shape; >= 1: requested number of key ranges (clipped to the number
  *              of 64-key tiles and to 256; 1 = no split, the call is then apbv_host_attention and needs no workspace)
  *   workspace / workspace_bytes   at least apbv_query_attention_workspace_bytes(...) bytes, 256-byte aligned; may be
- *              NULL / 0 when that is 0.  Contents need no initialisation and are garbage afterwards.
+ *              NULL / 0 when that is 0.  Contents need no initialisation and are garbage afterwards.  (With n_splits
+ *              0 a smaller workspace gives fewer ranges; one that does not hold a sensible number is refused.)
  */
 apbv_status apbv_query_attention(int batch, int n_q_heads, int n_kv_heads, int head_dim,
                                  apbv_tensor q_block,

@@ -11,13 +11,14 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libapbv.so")
-# source -> flags of its own.  attention.hip: no NaN can arise on its arithmetic paths (masked logits are -inf and
+# source -> flags of its own.  attention.hip, query_attention.hip: no NaN can arise on its arithmetic paths (masked logits are -inf and
 # every inf - inf is guarded), and telling the compiler so drops a canonicalising v_max in front of every maximum.
 SOURCES = {
     "api.hip": [],
     "attention.hip": ["-fno-honor-nans"],
     "compress.hip": [],
     "merge.hip": [],
+    "query_attention.hip": ["-fno-honor-nans"],
     "score_matrix.hip": [],
 }
 

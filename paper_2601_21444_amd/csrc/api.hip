@@ -182,11 +182,21 @@ apbv_status apbv_query_attention(int batch, int n_q_heads, int n_kv_heads, int h
                                         v_pass, k_local, v_local, softmax_scale, out, lse_out, p);
   if (st != APBV_OK) return st;
   if (n_splits < 0) return APBV_ERR_SHAPE;
-  const KeySplit ks = plan_key_split(batch, n_q_heads, p.L, p.s_kv, n_splits);
+  KeySplit ks;
+  if (n_splits > 0) {
+    ks = plan_key_split(batch, n_q_heads, p.L, p.s_kv, n_splits);
+  } else {
+    // the library's choice, or as many ranges as the workspace holds down to the least it accepts
+    ks = choose_key_split(batch, n_q_heads, n_kv_heads, p.L, p.s_kv);
+    const size_t fits = workspace == nullptr ? 0 : workspace_bytes / key_range_bytes(batch, n_q_heads, head_dim, p.L);
+    const KeySplit least = per_head_key_split(batch, n_q_heads, p.L, p.s_kv);
+    if (fits < (size_t)ks.n_splits && ks.n_splits > least.n_splits)
+      ks = key_split_of(fits > (size_t)least.n_splits ? (int64_t)fits : least.n_splits, key_tiles(p.s_kv));
+  }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (ks.n_splits == 1) return launch_host_attention(p, head_dim, stream);
 
-  const size_t need = apbv_query_attention_workspace_bytes(batch, n_q_heads, head_dim, p.L, p.s_kv, n_splits);
+  const size_t need = (size_t)ks.n_splits * key_range_bytes(batch, n_q_heads, head_dim, p.L);
   if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < need) return APBV_ERR_WORKSPACE;
   const size_t rows = (size_t)batch * (size_t)p.L * (size_t)n_q_heads;
   const size_t part_out_bytes = align256(rows * head_dim * sizeof(bf16_t));
@@ -201,7 +211,7 @@ apbv_status apbv_query_attention(int batch, int n_q_heads, int n_kv_heads, int h
   ps.tiles_per_split = ks.tiles_per_split;
   ps.split_stride_out = (int64_t)(part_out_bytes / sizeof(bf16_t));
   ps.split_stride_lse = (int64_t)(part_lse_bytes / sizeof(float));
-  const apbv_status sl = launch_host_attention(ps, head_dim, stream);
+  const apbv_status sl = launch_query_attention(ps, head_dim, stream);
   if (sl != APBV_OK) return sl;
 
   MergeParams m;

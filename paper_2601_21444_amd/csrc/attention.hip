@@ -49,179 +49,20 @@
 // linear workgroup id is decoded so that the G query heads that share a KV head run on the same XCD
 // (workgroup id modulo 8) back to back and stream the same K/V tiles through that XCD's L2.
 #include "apbv_common.h"
+#include "attention_tiles.h"
 
 namespace apbv {
 namespace {
 
 constexpr int kWaves = 8;          // waves per workgroup of the main variant: 256 query rows
 constexpr int kWavesNarrow = 2;    // of the variant for short query blocks: 64 query rows
+constexpr int kWavesShort = 4;     // of the key-split variant for short query blocks
 constexpr int kBM = 32 * kWaves;   // query rows per workgroup (main variant)
-constexpr int kBN = 32;            // keys per tile (one k-step of O^T)
 constexpr int kRing = 4;           // K tiles, and V tiles, resident in LDS
-constexpr int kXcds = 8;
-constexpr float kRescaleThreshold = 8.0f;   // log2 units
 
-#define APBV_LDS(T) __attribute__((address_space(3))) T*
-
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(8))) short s16x8;
-
-// Compile-time loop: f(std::integral_constant<int, 0>{}) ... f(std::integral_constant<int, N-1>{}).
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-template <int D, int W>
-struct Tile {
-  static constexpr int ROW_BYTES = D * 2;
-  static constexpr int KC = D / 8;                        // 16-byte chunks per row
-  static constexpr int RPI = 1024 / ROW_BYTES;            // rows covered by one wave-wide LDS-direct load
-  static constexpr int LOADS = kBN / RPI;                 // such loads per tile (per tensor)
-  static constexpr int IPW = (LOADS + W - 1) / W;         // ... per wave; wave w issues loads w*IPW + u while < LOADS
-  static constexpr int KSD = D / 32;                      // MFMA k-steps over the head dimension (S^T)
-  static constexpr int DBN = D / 16;                      // 16-row blocks of O^T
-  static constexpr int TILE_BYTES = kBN * ROW_BYTES;
-  // chunk swizzles (functions of the row within the tile), chosen so that the 16 rows x 16 bytes of a quarter of
-  // a K read and the 8 rows x 32 bytes of half a transposing V read cover the 64 LDS banks exactly once
-  __device__ static __forceinline__ int fk(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
-  __device__ static __forceinline__ int fv(int r) { return D == 128 ? ((r & 7) << 1) : (((r >> 1) & 3) << 1); }
-};
-
-struct Segs {
-  const char *b0, *b1, *b2;   // byte pointers of the three segments, already offset to (batch, kv head)
-  int64_t p0, p1, p2;         // bytes between consecutive tokens
-  int64_t e0, e1, e2;         // one past the last virtual key of each segment (starts are 0, e0, e1)
-};
-
-// Pick the fields of the segment that holds virtual key j (selects, no indexed access).
-__device__ __forceinline__ void seg_of(const Segs sg, int64_t j, const char*& base, int64_t& pitch, int64_t& start,
-                                       int64_t& end) {
-  const bool in0 = j < sg.e0, in1 = j < sg.e1;
-  base = in0 ? sg.b0 : (in1 ? sg.b1 : sg.b2);
-  pitch = in0 ? sg.p0 : (in1 ? sg.p1 : sg.p2);
-  start = in0 ? 0 : (in1 ? sg.e0 : sg.e1);
-  end = in0 ? sg.e0 : (in1 ? sg.e1 : sg.e2);
-}
-
-// LDS-direct 16-byte load: lane l's bytes land at lds_dst + 16*l (lds_dst uniform, in M0).  Issued through
-// inline assembly so that the kernel, not the compiler's wait-count insertion, orders these loads against
-// the LDS reads (one s_waitcnt vmcnt + barrier per tile).
-__device__ __forceinline__ const char* uniform_ptr(const char* p) {      // a wave-uniform pointer, provably so
-  const uint64_t v = (uint64_t)p;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (const char*)(((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ void dma16_uniform(const char* base_uniform, uint32_t lane_off, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_dst), "v"(lane_off), "s"(base_uniform)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void dma16_lane(const char* addr, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_dst), "v"(addr) : "memory", "m0");
-}
-__device__ __forceinline__ uint32_t lds_addr(const unsigned char* p) { return (uint32_t)(size_t)(APBV_LDS(const unsigned char))p; }
-
-// Sequential producer of the tiles of ONE tensor (K or V) along the virtual key axis.  While consecutive tiles
-// stay inside one segment ("run") a tile costs one 64-bit scalar add and its loads are  uniform tile base + a
-// per-lane 32-bit offset computed once per run; the tile that straddles a segment boundary (or the end of the
-// keys) takes a per-row lookup.
-template <int D, int W, bool kIsV>
-struct TileStream {
-  using T = Tile<D, W>;
-  Segs sg;
-  int64_t s_kv;
-  int t_next;              // next tile to issue
-  int run_end;             // tiles [t_next, run_end) lie inside one segment; base points at tile t_next
-  const char* base;
-  int64_t step;            // kBN * pitch
-  uint32_t off[T::IPW];
-  int wave, lane;
-
-  __device__ static __forceinline__ int swz(int r) { return kIsV ? T::fv(r) : T::fk(r); }
-  __device__ __forceinline__ int row(int u) const { return (wave * T::IPW + u) * T::RPI + lane / T::KC; }
-  __device__ __forceinline__ uint32_t ldst(int u) const { return (uint32_t)((wave * T::IPW + u) * T::RPI * T::ROW_BYTES); }
-
-  __device__ __forceinline__ void init(const Segs& s, int64_t skv, int w, int l, int t_first) {
-    sg = s;
-    s_kv = skv;
-    wave = w;
-    lane = l;
-    t_next = t_first;
-    run_end = t_first;
-    base = nullptr;
-    step = 0;
-#pragma unroll
-    for (int u = 0; u < T::IPW; ++u) off[u] = 0;
-  }
-
-  // Start a run at tile t_next if that tile lies inside one segment.
-  __device__ __forceinline__ void start_run() {
-    const int64_t j0 = (int64_t)t_next * kBN;
-    const char* b;
-    int64_t pitch, start, end;
-    seg_of(sg, j0, b, pitch, start, end);
-    if (j0 + kBN > end) return;                      // straddling tile: run stays empty
-    run_end = (int)(end / kBN);
-    base = b + (j0 - start) * pitch;
-    step = kBN * pitch;
-#pragma unroll
-    for (int u = 0; u < T::IPW; ++u) {
-      const int r = row(u);
-      off[u] = (uint32_t)r * (uint32_t)pitch + 16u * (uint32_t)((lane % T::KC) ^ swz(r));
-    }
-  }
-
-  // Whether load u of a tile is this wave's to issue (always, when the loads divide evenly among the waves).
-  __device__ __forceinline__ bool mine(int u) const { return W * T::IPW == T::LOADS || wave * T::IPW + u < T::LOADS; }
-
-  // Tiles that can still be issued from the current run without a lookup (after trying to start a run if none is open).
-  __device__ __forceinline__ int run_left() {
-    if (t_next >= run_end) start_run();
-    return run_end - t_next;
-  }
-  // Issue tile t_next, which the caller knows to lie inside the current run: no tests.
-  __device__ __forceinline__ void issue_in_run(uint32_t dst) {
-    const char* bu = uniform_ptr(base);
-#pragma unroll
-    for (int u = 0; u < T::IPW; ++u)
-      if (mine(u)) dma16_uniform(bu, off[u], dst + ldst(u));
-    base += step;
-    ++t_next;
-  }
-
-  // Issue this wave's share of the loads of tile t_next into the LDS tile at dst.
-  __device__ __forceinline__ void issue(uint32_t dst) {
-    if (t_next >= run_end) start_run();
-    if (t_next < run_end) {
-      const char* bu = uniform_ptr(base);
-#pragma unroll
-      for (int u = 0; u < T::IPW; ++u)
-        if (mine(u)) dma16_uniform(bu, off[u], dst + ldst(u));
-      base += step;
-    } else {
-      const int64_t j0 = (int64_t)t_next * kBN;
-#pragma unroll
-      for (int u = 0; u < T::IPW; ++u) {
-        if (!mine(u)) continue;
-        const int r = row(u);
-        int64_t j = j0 + r;
-        j = j < s_kv ? j : s_kv - 1;                 // rows past the end repeat the last key: always masked
-        const char* b;
-        int64_t pitch, sj, ej;
-        seg_of(sg, j, b, pitch, sj, ej);
-        dma16_lane(b + (j - sj) * pitch + 16 * ((lane % T::KC) ^ swz(r)), dst + ldst(u));
-      }
-    }
-    ++t_next;
-  }
-};
-
-// One workgroup's work: query tile `qt` of query head (kvh, g) of batch item b, key range `split`.
-template <int D, int W>
+// One workgroup's work: row tile `qt` of batch item b, key range `split`.  kPacked: the rows are those of KV head kvh,
+// row r = i * G + g being query i of head kvh * G + g (g unused); otherwise they are the queries of head (kvh, g).
+template <int D, int W, bool kPacked>
 __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const int qt, const int b, const int kvh,
                                                     const int g, const int split) {
   using T = Tile<D, W>;
@@ -230,17 +71,19 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   __shared__ __attribute__((aligned(1024))) unsigned char v_lds[kRing][T::TILE_BYTES];
   // the LDS destination of an LDS-direct load travels in M0, which addresses the first 64 KB of the workgroup's LDS
   static_assert(2 * kRing * T::TILE_BYTES <= 65536, "the K/V tile rings must lie below 64 KB of LDS");
-  const int h = kvh * p.group + g;
-
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps LDS tile addresses in SGPRs
   const int li = lane & 15;       // query column / A-operand row within a 16-block
   const int lg = lane >> 4;       // lane group: k-slots 8 lg .. 8 lg + 7, accumulator rows 4 lg .. 4 lg + 3
 
-  const int64_t i0 = (int64_t)qt * kRows;               // first query position of the workgroup
-  const int64_t iw = i0 + wave * 32;                    // first query position of the wave
-  const int64_t i_row[2] = {iw + li, iw + 16 + li};     // this lane's two query positions
+  // (packed rows are few enough for 32 bits: kQueryMaxTokens * 65535)
+  const int64_t n_rows = kPacked ? p.L * p.group : p.L;
+  auto query_of = [&](int64_t r) { return kPacked ? (int64_t)((uint32_t)r / (uint32_t)p.group) : r; };
+  auto head_of = [&](int64_t r) { return kvh * p.group + (kPacked ? (int)((uint32_t)r % (uint32_t)p.group) : g); };
+  const int64_t i0 = (int64_t)qt * kRows;               // first row of the workgroup
+  const int64_t iw = i0 + wave * 32;                    // first row of the wave
+  const int64_t i_row[2] = {iw + li, iw + 16 + li};     // this lane's two rows
 
   Segs ks, vs;
   {
@@ -261,7 +104,8 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   bf16x8 qf[T::KSD][2];
 #pragma unroll
   for (int nq = 0; nq < 2; ++nq) {
-    const bf16_t* qrow = p.q.ptr + (int64_t)b * p.q.sb + (int64_t)h * p.q.sh + (i_row[nq] < p.L ? i_row[nq] : p.L - 1) * p.q.st;
+    const int64_t r = i_row[nq] < n_rows ? i_row[nq] : n_rows - 1;
+    const bf16_t* qrow = p.q.ptr + (int64_t)b * p.q.sb + (int64_t)head_of(r) * p.q.sh + query_of(r) * p.q.st;
 #pragma unroll
     for (int c = 0; c < T::KSD; ++c) qf[c][nq] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + 32 * c + 8 * lg));
   }
@@ -300,18 +144,18 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   // Query i sees the virtual keys 0 .. min(i + n_vis, s_kv - 1); the second bound only matters when there is no
   // causal segment (s_kv == n_vis: every key visible to every query).
   auto last_key = [&](int64_t i) { return (i + p.n_vis < p.s_kv - 1) ? i + p.n_vis : p.s_kv - 1; };
-  const int64_t i_last_wg = (i0 + kRows - 1 < p.L - 1) ? i0 + kRows - 1 : p.L - 1;
-  const int n_tiles_vis = (int)(last_key(i_last_wg) / kBN) + 1;      // tiles the workgroup can see into
+  const int64_t i_last_wg = (i0 + kRows - 1 < n_rows - 1) ? i0 + kRows - 1 : n_rows - 1;
+  const int n_tiles_vis = (int)(last_key(query_of(i_last_wg)) / kBN) + 1;      // tiles the workgroup can see into
   // key split (partial results merged afterwards): this workgroup walks tiles [t_begin, n_tiles) only; the split is
   // planned in 64-key units
   const int64_t per_split = (int64_t)p.tiles_per_split * (64 / kBN);
   const int64_t t_begin64 = (int64_t)split * per_split;
   const int t_begin = (int)(t_begin64 < n_tiles_vis ? t_begin64 : n_tiles_vis);
   const int n_tiles = (int)(t_begin64 + per_split < n_tiles_vis ? t_begin64 + per_split : n_tiles_vis);
-  const int t_last_wave = (int)(last_key(iw + 31) / kBN);     // last tile any row of the wave can see into
+  const int t_last_wave = (int)(last_key(query_of(iw + 31)) / kBN);     // last tile any row of the wave can see into
   const int n_w = t_last_wave + 1 < n_tiles ? t_last_wave + 1 : n_tiles;     // the wave computes tiles [t_begin, n_w)
-  const int t_mask_wave = (int)((last_key(iw) + 1) / kBN);    // first tile with a key some row of the wave cannot see
-  const int jrel0[2] = {(int)last_key(i_row[0]), (int)last_key(i_row[1])};   // last visible virtual key of each query
+  const int t_mask_wave = (int)((last_key(query_of(iw)) + 1) / kBN);    // first tile with a key some row of the wave cannot see
+  const int jrel0[2] = {(int)last_key(query_of(i_row[0])), (int)last_key(query_of(i_row[1]))};   // last visible virtual key of each row
 
   typedef f32x4 STile[2][2];       // S^T of one tile: [16-key block][16-query block]
   typedef u32x4 PTile[2];          // P^T of one tile as the B operand of O^T: [16-query block], four 32-bit words
@@ -653,8 +497,10 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
       l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     }
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;     // a key split may leave a row without any visible key
-    if (i_row[nq] < p.L) {
-      bf16_t* orow = p.out + (int64_t)split * p.split_stride_out + (((int64_t)b * p.L + i_row[nq]) * p.hq + h) * D;
+    if (i_row[nq] < n_rows) {
+      const int64_t i = query_of(i_row[nq]);
+      const int h = head_of(i_row[nq]);
+      bf16_t* orow = p.out + (int64_t)split * p.split_stride_out + (((int64_t)b * p.L + i) * p.hq + h) * D;
 #pragma unroll
       for (int d = 0; d < T::DBN; ++d) {
         f32x2 x01 = {o[d][nq][0] * inv, o[d][nq][1] * inv};
@@ -667,7 +513,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
         *reinterpret_cast<u32x2*>(orow + 16 * d + 4 * lg) = w;
       }
       if (p.lse != nullptr && lg == 0)
-        p.lse[(int64_t)split * p.split_stride_lse + ((int64_t)b * p.hq + h) * p.L + i_row[nq]] =
+        p.lse[(int64_t)split * p.split_stride_lse + ((int64_t)b * p.hq + h) * p.L + i] =
             l_tot > 0.f ? (m_ref[nq] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f : -INFINITY;
     }
   }
@@ -702,7 +548,18 @@ __global__ __launch_bounds__(64 * W, 2) void host_attention_kernel(const AttnPar
   const int qt = n_qtiles - 1 - item / bh;       // heaviest query tiles first
   const int b = (item % bh) / p.hkv;
   const int kvh = (item % bh) % p.hkv;
-  attention_workgroup<D, W>(p, qt, b, kvh, g, split);
+  attention_workgroup<D, W, false>(p, qt, b, kvh, g, split);
+}
+
+// ---- key-split launches: the heads of a KV group packed into the rows.  The row tiles of one (batch item, KV head,
+// key range) read the same keys: they run back to back on one XCD.
+template <int D, int W>
+__global__ __launch_bounds__(64 * W, 2) void packed_attention_kernel(const AttnParams p, const int n_rtiles, const int n_ranges) {
+  const int slot = blockIdx.x / kXcds;
+  const int range = (slot / n_rtiles) * kXcds + blockIdx.x % kXcds;      // (batch item, KV head, split)
+  if (range >= n_ranges) return;
+  const int split = range % p.n_splits, bh = range / p.n_splits;
+  attention_workgroup<D, W, true>(p, slot % n_rtiles, bh / p.hkv, bh % p.hkv, 0, split);
 }
 
 // ---- several attention problems of different lengths in one launch (the two virtual hosts and the anchor
@@ -723,7 +580,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void host_attention_group_kernel(co
   // (a copy, so that the fields live in scalar registers like the single-problem kernel's by-value argument
   // instead of being fetched from the argument block where they are used)
   const AttnParams item = gp.item[m];
-  attention_workgroup<D, kWaves>(item, qt, 0, kvh, g, 0);
+  attention_workgroup<D, kWaves, false>(item, qt, 0, kvh, g, 0);
 }
 
 }  // namespace
@@ -753,6 +610,30 @@ apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t
   static_assert(kAttnQueryTile == kBM && kAttnNarrowQueryTile == 32 * kWavesNarrow, "tile sizes the host-side planning assumes");
   if (p.L <= kAttnNarrowMaxRows) return launch_variant<kWavesNarrow>(p, head_dim, stream);
   return launch_variant<kWaves>(p, head_dim, stream);
+}
+
+template <int W>
+static apbv_status launch_packed_variant(const AttnParams& p, int head_dim, hipStream_t stream) {
+  const int64_t n_rtiles = (p.L * p.group + 32 * W - 1) / (32 * W);
+  const int64_t n_ranges = (int64_t)p.batch * p.hkv * p.n_splits;
+  const int64_t n_blocks = (n_ranges + kXcds - 1) / kXcds * kXcds * n_rtiles;
+  if (n_blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
+  Launcher launch(stream);
+  if (head_dim == 128)
+    launch(packed_attention_kernel<128, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, p, (int)n_rtiles, (int)n_ranges);
+  else if (head_dim == 64)
+    launch(packed_attention_kernel<64, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, p, (int)n_rtiles, (int)n_ranges);
+  else
+    return APBV_ERR_UNSUPPORTED;
+  return launch.status();
+}
+
+// The rows of a KV group's heads together, in 128-row workgroups for short blocks (two fit a compute unit, and fewer of
+// the rows are padding), 256-row ones above.
+apbv_status launch_packed_attention(const AttnParams& p, int head_dim, hipStream_t stream) {
+  static_assert(kQueryShortRows == 32 * kWavesShort, "the tile size the host-side planning assumes");
+  if (p.L <= kQueryShortTokens) return launch_packed_variant<kWavesShort>(p, head_dim, stream);
+  return launch_packed_variant<kWaves>(p, head_dim, stream);
 }
 
 apbv_status launch_host_attention_group(AttnGroupParams& gp, int head_dim, hipStream_t stream) {

@@ -15,6 +15,10 @@ constexpr int kAttnKeyTile = 64;            // keys per tile of the attention ke
 constexpr int kAttnQueryTile = 256;         // query rows per workgroup
 constexpr int kAttnNarrowQueryTile = 64;    // ... of the variant used for query blocks of at most
 constexpr int kAttnNarrowMaxRows = 128;     // this many rows
+constexpr int kQueryMaxTokens = 2048;       // query blocks whose key-split launch packs the heads of a KV group into its rows
+constexpr int kQueryShortTokens = 128;      // ... in tiles of kQueryShortRows rows up to here, of kAttnQueryTile above
+constexpr int kQueryShortRows = 128;
+constexpr int kQueryWaveRows = 32;          // rows per KV head a single wave takes (the waves then split the keys)
 
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -105,29 +109,78 @@ inline apbv_status validate_merge(int n_parts, int64_t rows, int n_q_heads, int 
   return APBV_OK;
 }
 
-// Key split of the query-block attention: how many ranges of how many 64-key tiles.  With `requested` == 0 the
-// count is chosen so that (query tiles x heads x batch x splits) reaches about two workgroups per compute unit
-// while every range keeps at least four tiles; ranges are equal and none is empty.
+// Key split of the query-block attention: n_splits ranges of tiles_per_split 64-key tiles; ranges are equal and none
+// is empty.
 struct KeySplit {
   int n_splits, tiles_per_split;
 };
-inline KeySplit plan_key_split(int batch, int n_q_heads, int64_t n_q, int64_t n_keys, int requested) {
-  const int64_t n_tiles = (n_keys + kAttnKeyTile - 1) / kAttnKeyTile;
-  int64_t s = requested;
-  if (s <= 0) {
-    const int64_t tile = n_q <= kAttnNarrowMaxRows ? kAttnNarrowQueryTile : kAttnQueryTile;
-    const int64_t wgs = (n_q + tile - 1) / tile * n_q_heads * batch;
-    s = (512 + wgs - 1) / wgs;
-    const int64_t cap = n_tiles / 4 > 1 ? n_tiles / 4 : 1;
-    s = s < cap ? s : cap;
-  }
+inline KeySplit key_split_of(int64_t s, int64_t n_tiles) {
   s = s < n_tiles ? s : n_tiles;
   s = s < kMaxKeySplits ? s : kMaxKeySplits;
+  s = s > 1 ? s : 1;
   const int64_t per = (n_tiles + s - 1) / s;
   KeySplit ks;
   ks.tiles_per_split = (int)per;
   ks.n_splits = (int)((n_tiles + per - 1) / per);
   return ks;
+}
+inline int64_t key_tiles(int64_t n_keys) { return (n_keys + kAttnKeyTile - 1) / kAttnKeyTile; }
+
+// With one tile of query rows per query head: about two workgroups per compute unit, ranges of at least four tiles.
+// Blocks longer than kQueryMaxTokens are split like this; for shorter ones it is the fewest ranges the library's own
+// choice may be cut down to when the workspace holds no more.
+inline KeySplit per_head_key_split(int batch, int n_q_heads, int64_t n_q, int64_t n_keys) {
+  const int64_t tile = n_q <= kAttnNarrowMaxRows ? kAttnNarrowQueryTile : kAttnQueryTile;
+  const int64_t n_wg = (n_q + tile - 1) / tile * n_q_heads * batch;
+  const int64_t s = (512 + n_wg - 1) / n_wg;
+  const int64_t cap = key_tiles(n_keys) / 4 > 1 ? key_tiles(n_keys) / 4 : 1;
+  return key_split_of(s < cap ? s : cap, key_tiles(n_keys));
+}
+
+// The split a workspace is sized for: as requested, or (0) the most ranges choose_key_split() takes whatever the
+// number of KV heads, which the size query is not told.
+inline KeySplit plan_key_split(int batch, int n_q_heads, int64_t n_q, int64_t n_keys, int requested) {
+  if (requested > 0) return key_split_of(requested, key_tiles(n_keys));
+  if (n_q > kQueryMaxTokens) return per_head_key_split(batch, n_q_heads, n_q, n_keys);
+  const int64_t rows = n_q <= kQueryShortTokens ? kQueryShortRows : kAttnQueryTile;
+  const int64_t n_wg = (n_q * n_q_heads + rows - 1) / rows * batch;      // at least: with more KV heads there are more
+  const int64_t s = (512 + n_wg - 1) / n_wg;
+  const int64_t cap = key_tiles(n_keys) / 2 > 1 ? key_tiles(n_keys) / 2 : 1;
+  return key_split_of(s < cap ? s : cap, key_tiles(n_keys));
+}
+
+// The library's own choice for a block of at most kQueryMaxTokens queries, whose rows are packed per KV head.  For
+// these kernels' purposes one workgroup per compute unit runs at a time (a second one shares the matrix pipe or the
+// memory bandwidth), and the row tiles of a range run on one XCD of 32 compute units; a workgroup costs as much as kRangeOverhead key tiles before and after its keys (launch, cold
+// instruction cache, first loads, epilogue), and every range adds its partial results to the merge.  In units of one
+// 64-key tile (about 1 us): 64 queries of 16 / 2 heads over 16512 keys read 29.5 us at 16 ranges, 25.5 at 32, 27.8 at
+// 64, 35.5 at 128; one query over 131072 keys 52.5 us at 32, 28.6 at 128, 29.7 at 256.
+constexpr int kRangeOverhead = 8;
+inline KeySplit choose_key_split(int batch, int n_q_heads, int n_kv_heads, int64_t n_q, int64_t n_keys) {
+  const KeySplit most = plan_key_split(batch, n_q_heads, n_q, n_keys, 0);
+  if (n_q > kQueryMaxTokens) return most;
+  const int64_t rows = n_q * (n_q_heads / n_kv_heads);
+  const int64_t tile = n_q <= kQueryShortTokens ? kQueryShortRows : kAttnQueryTile;
+  const int64_t row_tiles = (rows + tile - 1) / tile, heads = (int64_t)n_kv_heads * batch;
+  const int64_t n_tiles = key_tiles(n_keys);
+  const double merge = (double)(rows * heads) / 5000.0;
+  double best = 0.0;
+  int64_t best_s = 1;
+  for (int64_t s = 1; s <= most.n_splits; ++s) {
+    const int64_t rounds = ((heads * s + 7) / 8 * row_tiles + 31) / 32;
+    const double cost = (double)(rounds * ((n_tiles + s - 1) / s + kRangeOverhead)) + (s > 1 ? 4.0 + merge * (double)s : 0.0);
+    if (s == 1 || cost < best) {
+      best = cost;
+      best_s = s;
+    }
+  }
+  return key_split_of(best_s, n_tiles);
+}
+
+// Workspace of one key range: its bf16 partial output and float32 log-sum-exps.
+inline size_t key_range_bytes(int batch, int n_q_heads, int head_dim, int64_t n_q) {
+  const size_t rows = (size_t)batch * (size_t)n_q * (size_t)n_q_heads;
+  return align256(rows * head_dim * 2) + align256(rows * sizeof(float));
 }
 
 inline size_t query_attention_workspace_bytes(int batch, int n_q_heads, int head_dim, int64_t n_q, int64_t n_keys,
@@ -136,9 +189,7 @@ inline size_t query_attention_workspace_bytes(int batch, int n_q_heads, int head
       n_q > kMaxTokens || n_keys > 3 * kMaxTokens)
     return 0;
   const KeySplit ks = plan_key_split(batch, n_q_heads, n_q, n_keys, n_splits);
-  if (ks.n_splits == 1) return 0;
-  const size_t rows = (size_t)batch * (size_t)n_q * (size_t)n_q_heads;
-  return (size_t)ks.n_splits * (align256(rows * head_dim * 2) + align256(rows * sizeof(float)));
+  return ks.n_splits == 1 ? 0 : (size_t)ks.n_splits * key_range_bytes(batch, n_q_heads, head_dim, n_q);
 }
 
 // ---- workspace of the compression call: [partial sums of the pooled query | scores | sort arrays of the exact

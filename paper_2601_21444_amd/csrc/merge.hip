@@ -88,6 +88,7 @@ static apbv_status launch_merge_variant(const MergeParams& p, hipStream_t stream
 }
 
 apbv_status launch_merge_lse(const MergeParams& p, hipStream_t stream) {
+  if (p.n_parts >= 64) return launch_merge_variant<32>(p, stream);
   return p.n_parts >= 8 ? launch_merge_variant<8>(p, stream) : launch_merge_variant<1>(p, stream);
 }
 
