@@ -133,6 +133,7 @@ constexpr size_t kStaticScratchBytes = APBV_NOALLOC_MAX_WORKSPACE_BYTES;   // si
 size_t compress_workspace_bytes(int batch, int hkv, int d, int64_t L, int64_t l_p);
 size_t matrix_scores_workspace_bytes(int reducer, int batch, int hkv, int64_t n_rows, int64_t L);
 apbv_status launch_compress(const CompressParams& p, hipStream_t stream);
+bool prepare_matrix_scores();      // per-device set-up of the kernels of score_matrix.hip
 apbv_status check_matrix_scores(const CompressParams& p);
 apbv_status launch_matrix_scores(const CompressParams& p, double* scores, void* stats_ws, hipStream_t stream);
 

@@ -649,6 +649,7 @@ apbv_status device_state(DeviceState& out) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(kLdsSortMax * 14)) != hipSuccess)
       return APBV_ERR_LAUNCH;
+    if (!prepare_matrix_scores()) return APBV_ERR_LAUNCH;
     void* ptr = nullptr;
     if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || ptr == nullptr) return APBV_ERR_LAUNCH;
     st.scratch_ptr = ptr;

@@ -332,6 +332,172 @@ __global__ __launch_bounds__(256, 3) void matrix_reduce_kernel(const RowsParams 
   }
 }
 
+// ---- kMass with the whole probe block in LDS.
+// matrix_reduce_kernel streams the probe rows past every 256 keys, behind a barrier per two tiles, and the scheduler
+// gathers the exponentials behind the matrix instructions.  Where the probe rows of a head fit the LDS nothing needs to
+// be streamed: a workgroup loads them once, and then every wave takes blocks of 64 keys of its own, straight from memory
+// into registers, and runs the probe tiles past them without a barrier, the matrix instructions of probe tile t+1 between
+// the scale, exponential and sum of tile t.  Bound by those three per logit, which issue on the port the matrix
+// instructions use.  Batch 16, 512 rows x 16384 keys x 2 heads: 86 -> 75 us (915 TFLOP/s); one item of 448 rows x 4
+// heads, the whole call: 49.1 -> 46.1 us.  With 64 rows (a fill per few tiles) it is no faster, and the maximum, whose
+// reduction is free, gains nothing (63 us either way): both stay with matrix_reduce_kernel.
+constexpr int kMinLdsProbe = 49152;       // bytes of probe rows: 192 rows of 128
+constexpr int kMaxLdsProbe = 131072;      // 512
+constexpr int kBlockKeys = 64;            // keys a wave holds at a time
+
+template <int N, typename F, int... I>
+__device__ __forceinline__ void unrolled_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  unrolled_impl<N>(f, std::make_integer_sequence<int, N>{});
+}
+
+// Grid (key groups, Hkv, batch): workgroup x takes the blocks of 64 keys from x * W * n_blocks, wave w every W-th.
+template <int D, int W>
+__global__ __launch_bounds__(64 * W, 2) void probe_resident_kernel(const RowsParams p, const int n_blocks) {
+  constexpr int KS = D / 16, KC = D / 8, ROW_BYTES = D * 2;
+  extern __shared__ __attribute__((aligned(16))) unsigned char probe[];        // [r_pad][D] swizzled, then [r_pad] c_r
+  const int v = blockIdx.y, b = blockIdx.z;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 31, hh = lane >> 5;
+  auto swz = [](int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
+  float* c_r = reinterpret_cast<float*>(probe + p.r_pad * ROW_BYTES);
+
+  const int64_t blk0 = (int64_t)blockIdx.x * W * n_blocks + wave;
+  const int64_t blk_all = (p.L + kBlockKeys - 1) / kBlockKeys;
+  // B operands: lane (c, hh) holds elements 8*hh + 16*kk .. +7 of keys c and 32 + c of the block
+  typedef bf16x8 KeyBlock[2][KS];
+  auto load_keys = [&](int64_t blk, KeyBlock& kf) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const bf16_t* row = key_row(p, b, v, blk * kBlockKeys + 32 * s + c) + 8 * hh;
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk) kf[s][kk] = *reinterpret_cast<const bf16x8*>(row + 16 * kk);
+    }
+  };
+  KeyBlock keys;
+  if (blk0 < blk_all) load_keys(blk0, keys);
+
+  // ---- the probe rows, 16 bytes a thread, sixteen loads in flight (four: 2 to 3 us more per launch)
+  {
+    constexpr int RPP = 64 * W / KC;         // rows per pass of the workgroup
+    ProbeCursor cur;
+    const int ch = tid % KC;
+    int r = tid / KC;
+    cur.init(p, b, v, r, 8 * ch, RPP);
+    for (; r < p.r_pad; r += 16 * RPP) {
+      u32x4 x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        x[u] = *reinterpret_cast<const u32x4*>(cur.get(p));
+        cur.advance(p);
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (r + u * RPP < p.r_pad) *reinterpret_cast<u32x4*>(probe + (r + u * RPP) * ROW_BYTES + 16 * (ch ^ swz(r + u * RPP))) = x[u];
+    }
+    const float* st = p.stats + ((int64_t)b * p.hkv + v) * p.r_pad;
+    for (int i = tid; i < p.r_pad; i += 64 * W) c_r[i] = st[i];
+  }
+  __syncthreads();
+
+  const int n_tiles = p.r_pad / 32;
+  int a_off[KS];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) a_off[kk] = c * ROW_BYTES + 16 * ((2 * kk + hh) ^ swz(c));
+  typedef f32x16 Acc[2];
+  bf16x8 af[KS];           // A fragments; at the top of a tile its first half has been requested
+#pragma unroll
+  for (int kk = 0; kk < KS / 2; ++kk) af[kk] = *reinterpret_cast<const bf16x8*>(probe + a_off[kk]);
+
+  for (int n = 0; n < n_blocks; ++n) {
+    const int64_t blk = blk0 + (int64_t)n * W;
+    if (blk >= blk_all) break;
+    float red[2] = {0.f, 0.f};
+    // One probe tile: its logits into `acc` on the matrix pipe, and (kPrev) the reduction of the previous tile's.  A
+    // slice is one matrix instruction with its share of the rest: the LDS read of a fragment for the other half of the
+    // k-steps (of the next tile, in the second half), and the scale, exponential and sum of logits two slices apart, so
+    // that nothing waits for what its own slice starts.  The slices are fenced: left alone, the scheduler gathers the
+    // exponentials behind the matrix instructions.
+    auto tile = [&](int t, Acc& acc, auto prev, const Acc& old) {
+      constexpr bool kPrev = decltype(prev)::value;
+      const unsigned char* here = probe + t * 32 * ROW_BYTES;
+      const unsigned char* after = probe + (t + 1 < n_tiles ? t + 1 : 0) * 32 * ROW_BYTES;
+      f32x4 cr[4];
+      if (kPrev) {
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) cr[i4] = *reinterpret_cast<const f32x4*>(&c_r[(t - 1) * 32 + 8 * i4 + 4 * hh]);
+      }
+      constexpr int kSlices = 2 * KS, kPer = 32 / kSlices;      // logits of the previous tile per slice, [s][16] in order
+      float x[32];
+      auto stage_f = [&](auto E) { constexpr int e = E; x[e] = __builtin_fmaf(old[e / 16][e % 16], p.scale_log2, -cr[e % 16 / 4][e % 4]); };
+      auto stage_e = [&](auto E) { constexpr int e = E; x[e] = __builtin_amdgcn_exp2f(x[e]); };
+      auto stage_a = [&](auto E) { constexpr int e = E; red[e / 16] += x[e]; };
+      unrolled<kSlices>([&](auto I) {
+        constexpr int i = I, h = i / KS, j = i % KS, kk = h * (KS / 2) + j / 2, s = j % 2;
+        acc[s] = mfma(af[kk], keys[s][kk], kk == 0 ? f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f} : acc[s]);
+        if constexpr (j < KS / 2) {
+          constexpr int kn = (h ^ 1) * (KS / 2) + j;
+          af[kn] = *reinterpret_cast<const bf16x8*>((h == 0 ? here : after) + a_off[kn]);
+        }
+        if constexpr (kPrev) {
+          unrolled<kPer>([&](auto J) {
+            constexpr int e = kPer * i + J;
+            stage_f(std::integral_constant<int, e>{});
+            if constexpr (e >= kPer) stage_e(std::integral_constant<int, e - kPer>{});
+            if constexpr (e >= 2 * kPer) stage_a(std::integral_constant<int, e - 2 * kPer>{});
+          });
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if constexpr (kPrev) {
+        unrolled<kPer>([&](auto J) { stage_e(std::integral_constant<int, 32 - kPer + J>{}); });
+        unrolled<2 * kPer>([&](auto J) { stage_a(std::integral_constant<int, 32 - 2 * kPer + J>{}); });
+      }
+    };
+    auto reduce = [&](int t, const Acc& acc) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const f32x4 cr = *reinterpret_cast<const f32x4*>(&c_r[t * 32 + 8 * i4 + 4 * hh]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) red[q] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[q][4 * i4 + e], p.scale_log2, -cr[e]));
+        }
+    };
+    Acc acc_a, acc_b;
+    tile(0, acc_a, std::false_type{}, acc_b);
+    int t = 1;
+    for (; t + 1 < n_tiles; t += 2) {
+      tile(t, acc_b, std::true_type{}, acc_a);
+      tile(t + 1, acc_a, std::true_type{}, acc_b);
+    }
+    if (t < n_tiles) {
+      tile(t, acc_b, std::true_type{}, acc_a);
+      acc_a[0] = acc_b[0];
+      acc_a[1] = acc_b[1];
+    }
+    // the next block's keys travel while the last tile is reduced (holding them beside this block's from its start
+    // takes 64 more registers: it spills)
+    if (n + 1 < n_blocks && blk + W < blk_all) load_keys(blk + W, keys);
+    reduce(n_tiles - 1, acc_a);
+
+    // the lane halves hold different probe rows of the same key
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const float r = red[s] + other_half(red[s]);
+      const int64_t i = blk * kBlockKeys + 32 * s + c;
+      if (hh == 0 && i < p.L) {
+        const int64_t at = ((int64_t)b * p.hkv + v) * p.L + i;
+        p.s_ws[at] = (double)r;
+        if (p.s_out) p.s_out[at] = (double)r;
+      }
+    }
+  }
+}
+
 // One wave per (batch, head, row): merge the chunks' statistics into c_r = maximum + log2(normaliser); padding rows
 // get +inf.  Every real row has at least one key, so its normaliser is positive.
 __global__ __launch_bounds__(256) void row_stats_combine_kernel(const RowsParams p, int batch) {
@@ -383,6 +549,50 @@ apbv_status check_matrix_scores(const CompressParams& cp) {
   return APBV_OK;
 }
 
+namespace {
+
+template <int D, int W>
+void launch_probe_resident(Launcher& launch, const RowsParams& p, int batch, int n_blocks) {
+  const int64_t blocks = (p.L + kBlockKeys - 1) / kBlockKeys;
+  const dim3 grid((unsigned)((blocks + W * n_blocks - 1) / (W * n_blocks)), p.hkv, batch);
+  launch(probe_resident_kernel<D, W>, grid, dim3(64 * W), (size_t)p.r_pad * (D * 2 + sizeof(float)), p, n_blocks);
+}
+
+template <int D>
+void launch_mass(Launcher& launch, const RowsParams& p, int batch) {
+  const int64_t probe_bytes = (int64_t)p.r_pad * D * 2;
+  if (probe_bytes < kMinLdsProbe || probe_bytes > kMaxLdsProbe) {
+    launch(matrix_reduce_kernel<D, kMass>, dim3((unsigned)((p.L + kResident - 1) / kResident), p.hkv, batch), dim3(256), (size_t)p.r_pad * sizeof(float), p);
+    return;
+  }
+  // Eight waves a workgroup, and as many blocks a wave as fill the rounds of the 256 compute units best; four waves if
+  // even single blocks leave half of them idle.
+  const int64_t blocks = (p.L + kBlockKeys - 1) / kBlockKeys;
+  const int64_t heads = (int64_t)p.hkv * batch;
+  if (heads * ((blocks + 7) / 8) <= 128) return launch_probe_resident<D, 4>(launch, p, batch, 1);
+  int best = 1;
+  int64_t best_cost = 0;
+  for (int n = 1; n <= 8; ++n) {
+    const int64_t cost = (heads * ((blocks + 8 * n - 1) / (8 * n)) + 255) / 256 * (4 * n + 1);   // a fill costs a quarter of a block
+    if (n == 1 || cost < best_cost) {
+      best = n;
+      best_cost = cost;
+    }
+  }
+  launch_probe_resident<D, 8>(launch, p, batch, best);
+}
+
+template <int D, int W>
+bool allow_lds() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&probe_resident_kernel<D, W>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             kMaxLdsProbe / (D * 2) * (D * 2 + (int)sizeof(float))) == hipSuccess;
+}
+
+}  // namespace
+
+// Dynamic-LDS limits of this file's kernels on the current device (part of the per-device set-up in compress.hip).
+bool prepare_matrix_scores() { return allow_lds<64, 4>() && allow_lds<64, 8>() && allow_lds<128, 4>() && allow_lds<128, 8>(); }
+
 apbv_status launch_matrix_scores(const CompressParams& cp, double* scores, void* stats_ws, hipStream_t stream) {
   const apbv_status ok = check_matrix_scores(cp);
   if (ok != APBV_OK) return ok;
@@ -412,9 +622,9 @@ apbv_status launch_matrix_scores(const CompressParams& cp, double* scores, void*
   p.stats = nullptr;
   p.s_ws = scores;
   p.s_out = cp.scores_out;
-  const dim3 grid((unsigned)((cp.L + kResident - 1) / kResident), cp.hkv, cp.batch);
   Launcher launch(stream);
   if (cp.reducer == APBV_REDUCE_MAX) {
+    const dim3 grid((unsigned)((cp.L + kResident - 1) / kResident), cp.hkv, cp.batch);
     if (cp.d == 128)
       launch(matrix_reduce_kernel<128, kMax>, grid, dim3(256), 0, p);
     else
@@ -433,11 +643,10 @@ apbv_status launch_matrix_scores(const CompressParams& cp, double* scores, void*
       launch(matrix_reduce_kernel<64, kStats>, sgrid, dim3(256), 0, p);
     const int64_t n_stat = (int64_t)cp.batch * cp.hkv * p.r_pad;
     launch(row_stats_combine_kernel, dim3((unsigned)((n_stat + 3) / 4)), dim3(256), 0, p, cp.batch);
-    const size_t lds = (size_t)p.r_pad * sizeof(float);
     if (cp.d == 128)
-      launch(matrix_reduce_kernel<128, kMass>, grid, dim3(256), lds, p);
+      launch_mass<128>(launch, p, cp.batch);
     else
-      launch(matrix_reduce_kernel<64, kMass>, grid, dim3(256), lds, p);
+      launch_mass<64>(launch, p, cp.batch);
   } else {
     return APBV_ERR_UNSUPPORTED;
   }
