@@ -7,13 +7,17 @@
 // one streaming pass over K, bound by HBM bandwidth.  Accumulation is in float64 so that the ranking
 // agrees with a float64 evaluation (float32 accumulation flips near-equal neighbours).
 //
-// Four launches on the caller's stream:
+// Launches on the caller's stream:
 //   pool_query_kernel   partial sums of q_bar (float64), up to 8 row ranges per pooled query
 //                                                                         [splits x Hkv x batch workgroups]
 //   score_kernel        s[v, j], 16-byte coalesced reads of K rows; adds the partial sums of q_bar as it starts;
 //                       scores stored through to memory as it runs         [L/64 x Hkv x batch]
-//   select_kernel       bucket sort by value of the scores above the l_p-th largest (exact fallback: radix select
-//                       + bitonic sort), into (score descending, index ascending) order   [Hkv x batch]
+// then, for a few heads of at most 16384 keys,
+//   select_gather_kernel  bucket sort by value of the scores above the l_p-th largest (exact fallback: radix select
+//                       + bitonic sort), into (score descending, index ascending) order; K_c, V_c rows
+//                                                                         [parts x Hkv x batch]
+// and otherwise the same as two launches
+//   select_kernel       the ordered indices                               [Hkv x batch]
 //   gather_kernel       K_c, V_c rows                                     [l_p*Hkv/.. x batch]
 #include <mutex>
 #include "apbv_common.h"
@@ -213,6 +217,7 @@ __device__ __forceinline__ bool precedes(uint64_t ka, uint32_t ia, uint64_t kb, 
 
 constexpr int kBins = 2048;                    // value buckets of the fast selection path
 
+constexpr int kResidentScores = 16 * kSelectThreads;     // scores a selection keeps in registers
 constexpr uint32_t kMaxBinRank = 128;          // largest bucket the rank-by-comparison step accepts
 
 struct SelectShared {
@@ -221,6 +226,7 @@ struct SelectShared {
   uint32_t fill[kBins];       // scatter cursor per bucket
   uint64_t prefix;
   uint32_t need, bucket, cnt, n_cand, t_bin, crowded;
+  int b_lo, b_hi;             // kParts: lowest and highest bucket of the part
   uint32_t wave_tot[kSelectThreads / 64];
   float red_lo[kSelectThreads / 64], red_hi[kSelectThreads / 64];
 };
@@ -276,15 +282,12 @@ __device__ __forceinline__ uint32_t block_scan_incl(uint32_t x, SelectShared& sh
   if (!kFresh) __syncthreads();         // wave_tot may still be read from a previous use
   if (lane == 63) sh.wave_tot[wave] = incl;
   __syncthreads();
-  uint32_t base = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < kSelectThreads / 64; ++w) {
-    const uint32_t t = sh.wave_tot[w];
-    if (w < wave) base += t;
-    tot += t;
-  }
-  *total = tot;
-  return incl + base;
+  // every wave scans the 16 totals itself, one a lane
+  constexpr int kSelectWaves = kSelectThreads / 64;
+  const uint32_t scan = wave_scan_incl(lane < kSelectWaves ? sh.wave_tot[lane] : 0u);
+  const int w = __builtin_amdgcn_readfirstlane(wave);
+  *total = (uint32_t)__builtin_amdgcn_readlane((int)scan, kSelectWaves - 1);
+  return incl + (w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)scan, w - 1) : 0u);
 }
 
 // Bitonic sort of n_sort (a power of two) entries into (key descending, index ascending) order.
@@ -320,12 +323,17 @@ __device__ __forceinline__ void bitonic_sort(uint64_t* skeys, uint32_t* sidx, in
 // map is monotone, bucket order followed by (key descending, index ascending) inside a bucket is the global order,
 // ties included.  Returns false (nothing written) if the candidates do not fit `cap` or a bucket is too crowded to
 // rank by comparison; the caller then takes the exact radix path.
+// kParts: n_parts workgroups share a head.  Each takes the buckets whose output offset lies in its share of the l_p
+// outputs, scatters and ranks those alone, and leaves their indices in sh.fill, outputs [*out_first, *out_first +
+// *n_out).  The histogram, and with it the decision to give up, is the same in every workgroup.
+template <bool kParts>
 __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s, int64_t L, int64_t l_p, int64_t cap,
                                                    uint64_t* skeys, uint32_t* sidx, uint16_t* sbin,
-                                                   int32_t* __restrict__ idx_out, SelectShared& sh) {
+                                                   int32_t* __restrict__ idx_out, SelectShared& sh, int part = 0,
+                                                   int n_parts = 1, uint32_t* out_first = nullptr, uint32_t* n_out = nullptr) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int kPer = 16;                                   // scores kept in registers per thread
-  const bool resident = L <= (int64_t)kPer * kSelectThreads;
+  constexpr int kPer = kResidentScores / kSelectThreads;
+  const bool resident = L <= kResidentScores;
   double sc[kPer];
   uint32_t bins[kPer];                                       // bucket | arrival order in the bucket << 11
   if (resident) {
@@ -362,13 +370,14 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
     sh.hist[i] = 0;
     sh.fill[i] = 0;
   }
-  if (tid == 0) sh.crowded = 0;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kSelectThreads / 64; ++w) {
-    lo = fminf(lo, sh.red_lo[w]);
-    hi = fmaxf(hi, sh.red_hi[w]);
+  if (tid == 0) {
+    sh.crowded = 0;
+    sh.b_lo = kBins;
+    sh.b_hi = -1;
   }
+  __syncthreads();
+  lo = wave_min(sh.red_lo[lane % (kSelectThreads / 64)]);     // (16 waves' values, one a lane: a loop over them costs 0.6 us)
+  hi = wave_max(sh.red_hi[lane % (kSelectThreads / 64)]);
   const float inv = (float)kBins / (hi - lo);
   if (!(inv > 0.0f) || !(inv < 1.0e30f)) return false;       // all scores equal in single precision (or range overflow)
   // rounding, subtraction of lo, multiplication by a positive constant and truncation are all monotone
@@ -399,6 +408,14 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
   const uint32_t excl = incl - (c0 + c1);
   sh.base[b0] = excl;
   sh.base[b1] = excl + c0;
+  if (kParts) {
+    const uint32_t from = (uint32_t)(l_p * part / n_parts), to = (uint32_t)(l_p * (part + 1) / n_parts);
+    const bool in0 = c0 != 0 && excl >= from && excl < to, in1 = c1 != 0 && excl + c0 >= from && excl + c0 < to;
+    if (in0 || in1) {
+      atomicMin(&sh.b_lo, in1 ? b1 : b0);
+      atomicMax(&sh.b_hi, in0 ? b0 : b1);
+    }
+  }
   if (excl < (uint32_t)l_p && (uint32_t)l_p <= incl) {
     const bool first = (uint32_t)l_p <= excl + c0;
     sh.t_bin = first ? b0 : b1;
@@ -410,9 +427,25 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
   if ((int64_t)n_cand > cap) return false;
   // a candidate bucket too crowded to rank by comparison: seen by every thread after the scatter's barrier
   if ((b0 >= t_bin && c0 > kMaxBinRank) || (b1 >= t_bin && c1 > kMaxBinRank)) sh.crowded = 1;
+  // the candidates this workgroup ranks: those of buckets [b_lo, b_hi], positions from `first` on
+  const int b_lo = kParts ? sh.b_lo : t_bin, b_hi = kParts ? sh.b_hi : kBins - 1;
+  const bool none = kParts && b_hi < 0;
+  const uint32_t first = kParts && !none ? sh.base[b_hi] : 0;
+  const uint32_t n_loc = none ? 0 : (kParts ? sh.base[b_lo] + sh.hist[b_lo] - first : n_cand);
   // scatter the candidates into bucket-grouped order.  Every wave walks all kPer iterations for the few lanes
   // that hold a candidate, so the body is two stores (index, raw score); key and bucket follow below.
-  if (resident) {
+  if (resident && kParts) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const uint32_t j = (uint32_t)tid + (uint32_t)u * kSelectThreads;
+      const int b = (int)(bins[u] & (uint32_t)(kBins - 1));
+      if (j < (uint32_t)L && b >= b_lo && b <= b_hi) {
+        const uint32_t pos = sh.base[b] - first + (bins[u] >> 11);
+        sidx[pos] = j;
+        skeys[pos] = (uint64_t)__double_as_longlong(sc[u]);
+      }
+    }
+  } else if (resident) {
     // Every bucket offset is fetched before the first store.  Lanes without a candidate all read one and the
     // same word (a broadcast), so that only the few candidates' reads can collide on an LDS bank.
     uint32_t pos[kPer];
@@ -433,8 +466,8 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
     for (int64_t j = tid; j < L; j += kSelectThreads) {
       const double x = s[j];
       const uint32_t b = bin_of(x);
-      if ((int)b >= t_bin) {
-        const uint32_t pos = sh.base[b] + atomicAdd(&sh.fill[b], 1u);
+      if ((int)b >= b_lo && (int)b <= b_hi) {
+        const uint32_t pos = sh.base[b] - first + atomicAdd(&sh.fill[b], 1u);
         sidx[pos] = (uint32_t)j;
         skeys[pos] = (uint64_t)__double_as_longlong(x);
       }
@@ -442,7 +475,7 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
   }
   __syncthreads();
   // the owner of a candidate position turns the raw score into its key and bucket, in place
-  for (uint32_t pos = tid; pos < n_cand; pos += kSelectThreads) {
+  for (uint32_t pos = tid; pos < n_loc; pos += kSelectThreads) {
     const double x = __longlong_as_double((long long)skeys[pos]);
     skeys[pos] = score_key(x);
     sbin[pos] = (uint16_t)bin_of(x);
@@ -450,15 +483,14 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
   __syncthreads();
   if (sh.crowded) return false;
   // rank inside the bucket, write the index at its final position
-  const int64_t out_base = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * l_p;
-  for (uint32_t pos = tid; pos < n_cand; pos += kSelectThreads) {
+  for (uint32_t pos = tid; pos < n_loc; pos += kSelectThreads) {
     const uint32_t b = sbin[pos];
-    const uint32_t first = sh.base[b], cnt = sh.hist[b];
+    const uint32_t begin = sh.base[b] - first, cnt = sh.hist[b];
     const uint64_t key = skeys[pos];
     const uint32_t idx = sidx[pos];
     uint32_t rank = 0;
-    const uint32_t end = first + cnt;                        // cnt >= 1: the entry itself
-    for (uint32_t q = first; q < end; q += 4) {              // four entries' reads in flight
+    const uint32_t end = begin + cnt;                        // cnt >= 1: the entry itself
+    for (uint32_t q = begin; q < end; q += 4) {              // four entries' reads in flight
       uint64_t kq[4];
       uint32_t iq[4];
 #pragma unroll
@@ -470,7 +502,14 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
 #pragma unroll
       for (int e = 0; e < 4; ++e) rank += (q + e < end && precedes(kq[e], iq[e], key, idx)) ? 1u : 0u;
     }
-    if (first + rank < (uint32_t)l_p) idx_out[out_base + first + rank] = (int32_t)idx;
+    if (first + begin + rank < (uint32_t)l_p) {
+      idx_out[first + begin + rank] = (int32_t)idx;
+      if (kParts) sh.fill[begin + rank] = idx;                // (the scatter's cursors are done with)
+    }
+  }
+  if (kParts) {
+    *out_first = first;
+    *n_out = first + n_loc < (uint32_t)l_p ? n_loc : (uint32_t)l_p - first;
   }
   return true;
 }
@@ -586,7 +625,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(const double* __
   }
 
   uint16_t* sbin = reinterpret_cast<uint16_t*>(sidx + cap);
-  if (bucket_rank_select(s, L, l_p, cap, skeys, sidx, sbin, idx_out, sh)) return;
+  if (bucket_rank_select<false>(s, L, l_p, cap, skeys, sidx, sbin, idx_out + head * l_p, sh)) return;
   radix_collect(s, L, l_p, skeys, sidx, sh);
   int64_t n_sort = 1;
   while (n_sort < l_p) n_sort <<= 1;
@@ -624,6 +663,64 @@ __global__ __launch_bounds__(256) void gather_kernel(View k, View v, const int32
   __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(v_c + dst));
 }
 
+// Selection and gather in one launch, n_parts workgroups per (KV head, batch item).  A head's selection alone leaves all
+// but one compute unit idle, and a gather launched behind it waits for the launch; here every workgroup repeats the part
+// that needs all scores (load, minimum and maximum, histogram, scan) and shares the rest: it scatters and ranks its own
+// buckets and copies the rows it has found.  The exact path, where it is needed, runs in every workgroup, each copying
+// its share of the rows.  Two heads of 16384 scores and 1024 rows: 9.8 + 2.4 us and the gap between -> 10.5 us, of which
+// 2.4 load the scores, 3.6 are minimum and maximum, histogram and scan (issue-bound, repeated), 0.8 the copy.
+constexpr int kMaxSelectParts = 16;
+constexpr int kMaxSharedHeads = 8;
+static_assert(kLdsSortMax / kMaxSelectParts + 1 + (int64_t)kMaxBinRank <= kBins && 64 + (int64_t)kMaxBinRank <= kBins,
+              "a part's share of the outputs and one bucket more fit sh.fill");
+
+template <int D>
+__global__ __launch_bounds__(kSelectThreads) void select_gather_kernel(const double* __restrict__ s_ws, View k, View v, int64_t L, int64_t l_p,
+                                                                       int64_t cap, int32_t* __restrict__ idx_out, int hkv,
+                                                                       bf16_t* __restrict__ k_c, bf16_t* __restrict__ v_c) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  __shared__ SelectShared sh;
+  constexpr int KC = D / 8;
+  const int part = blockIdx.x, n_parts = gridDim.x, head = blockIdx.y, b = blockIdx.z;
+  const int tid = threadIdx.x;
+  const int64_t h = (int64_t)b * hkv + head;
+  const double* s = s_ws + h * L;
+  int32_t* idx = idx_out + h * l_p;
+  uint64_t* skeys = reinterpret_cast<uint64_t*>(dyn);
+  uint32_t* sidx = reinterpret_cast<uint32_t*>(dyn + cap * sizeof(uint64_t));
+  uint16_t* sbin = reinterpret_cast<uint16_t*>(sidx + cap);
+  uint32_t first = 0, n_out = 0;
+  const uint32_t* rows = sh.fill;
+  if (!bucket_rank_select<true>(s, L, l_p, cap, skeys, sidx, sbin, idx, sh, part, n_parts, &first, &n_out)) {
+    radix_collect(s, L, l_p, skeys, sidx, sh);
+    int64_t n_sort = 1;
+    while (n_sort < l_p) n_sort <<= 1;
+    __syncthreads();
+    for (int64_t i = l_p + tid; i < n_sort; i += kSelectThreads) {   // padding sorts last
+      skeys[i] = 0;
+      sidx[i] = 0xffffffffu;
+    }
+    __syncthreads();
+    bitonic_sort(skeys, sidx, n_sort);
+    first = (uint32_t)(l_p * part / n_parts);
+    n_out = (uint32_t)(l_p * (part + 1) / n_parts) - first;
+    rows = sidx + first;
+    for (uint32_t i = tid; i < n_out; i += kSelectThreads) idx[first + i] = (int32_t)rows[i];
+  }
+  __syncthreads();
+  const bf16_t* kb = k.ptr + (int64_t)b * k.sb + (int64_t)head * k.sh;
+  const bf16_t* vb = v.ptr + (int64_t)b * v.sb + (int64_t)head * v.sh;
+  for (uint32_t item = tid; item < n_out * KC; item += kSelectThreads) {
+    const uint32_t i = item / KC, c = item % KC;
+    const int64_t j = rows[i];
+    const int64_t dst = (((int64_t)b * l_p + first + i) * hkv + head) * D + 8 * c;
+    const u32x4 kk = *reinterpret_cast<const u32x4*>(kb + j * k.st + 8 * c);
+    const u32x4 vv = *reinterpret_cast<const u32x4*>(vb + j * v.st + 8 * c);
+    __builtin_nontemporal_store(kk, reinterpret_cast<u32x4*>(k_c + dst));
+    __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(v_c + dst));
+  }
+}
+
 // Scratch of the entry point that takes no workspace (apbv_compress_kv_noalloc): a fixed array in the code object,
 // one copy per GPU at that GPU's own address.  In host code the array's name is only a handle for the symbol lookup
 // below; kernels and launch code use the looked-up device address.
@@ -648,6 +745,9 @@ apbv_status device_state(DeviceState& out) {
   if (!st.ready) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(kLdsSortMax * 14)) != hipSuccess)
+      return APBV_ERR_LAUNCH;
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_gather_kernel<64>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess ||
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&select_gather_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess)
       return APBV_ERR_LAUNCH;
     if (!prepare_matrix_scores()) return APBV_ERR_LAUNCH;
     void* ptr = nullptr;
@@ -717,7 +817,21 @@ apbv_status launch_compress(const CompressParams& p_in, hipStream_t stream) {
     else
       launch(score_kernel<64>, grid, dim3(256), 0, p.k, p.L, qbar, n_split, scores, p.scores_out, p.hkv, rows_per_block);
   }
-  if (p.l_p > 0) {
+  // A few heads' selection is shared by several workgroups each, in parts of at least 32 rows, and copies its rows too:
+  // one item of 2 heads x 16384 keys 18.5 -> 17.7 us (graph replay), of 4 heads 22.6 -> 21.9, 2 heads x 256 keys 13.5 ->
+  // 12.5; a launch less on the host as well.  With 16 heads it is even (32.6 and 32.9 us), with 32 slower (29.2 and 30.5),
+  // and beyond kResidentScores keys every workgroup would read the scores three times (8 x 4 heads x 30000: 72 and 86).
+  const int64_t heads = (int64_t)p.hkv * p.batch;
+  int64_t n_parts = p.l_p / 32 < kMaxSelectParts ? p.l_p / 32 : kMaxSelectParts;
+  n_parts = n_parts > 1 ? n_parts : 1;
+  if (p.l_p > 0 && !w.sort_in_global && heads <= kMaxSharedHeads && p.L <= kResidentScores) {
+    const dim3 grid((unsigned)n_parts, p.hkv, p.batch);
+    const size_t dyn = (size_t)w.n_sort * 14;
+    if (p.d == 128)
+      launch(select_gather_kernel<128>, grid, dim3(kSelectThreads), dyn, scores, p.k, p.v, p.L, p.l_p, w.n_sort, p.idx_out, p.hkv, p.k_c, p.v_c);
+    else
+      launch(select_gather_kernel<64>, grid, dim3(kSelectThreads), dyn, scores, p.k, p.v, p.L, p.l_p, w.n_sort, p.idx_out, p.hkv, p.k_c, p.v_c);
+  } else if (p.l_p > 0) {
     // select + order
     if (w.sort_in_global) {
       launch(select_kernel<true>, dim3(p.hkv, p.batch), dim3(kSelectThreads), 0, scores, p.L, p.l_p, w.n_sort, p.idx_out, reinterpret_cast<uint64_t*>(ws + w.sort_keys_off), reinterpret_cast<uint32_t*>(ws + w.sort_idx_off), p.hkv);
