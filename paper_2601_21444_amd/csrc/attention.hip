@@ -55,8 +55,8 @@ namespace apbv {
 namespace {
 
 constexpr int kWaves = 8;          // waves per workgroup of the main variant: 256 query rows
-constexpr int kWavesNarrow = 2;    // of the variant for short query blocks: 64 query rows
-constexpr int kWavesShort = 4;     // of the key-split variant for short query blocks
+constexpr int kWavesNarrow = 2;    // of the variants for less work than fills the chip with 256-row workgroups: 64
+constexpr int kWavesShort = 4;     // and 128 query rows
 constexpr int kBM = 32 * kWaves;   // query rows per workgroup (main variant)
 constexpr int kRing = 4;           // K tiles, and V tiles, resident in LDS
 
@@ -565,8 +565,8 @@ __global__ __launch_bounds__(64 * W, 2) void packed_attention_kernel(const AttnP
 // ---- several attention problems of different lengths in one launch (the two virtual hosts and the anchor
 // block of a physical host, Alg. 1 / Sec. 4.3): one workgroup per entry of the merged heaviest-first order of
 // all (problem, query tile) pairs, per KV head and group member.
-template <int D>
-__global__ __launch_bounds__(64 * kWaves, 2) void host_attention_group_kernel(const AttnGroupParams gp) {
+template <int D, int W>
+__global__ __launch_bounds__(64 * W, 2) void host_attention_group_kernel(const AttnGroupParams gp) {
   const int group = gp.item[0].group, hkv = gp.item[0].hkv;
   const int xcd = blockIdx.x % kXcds;
   const int slot = blockIdx.x / kXcds;
@@ -576,11 +576,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void host_attention_group_kernel(co
   const int entry = unit / hkv, kvh = unit % hkv;
   int m, qt;
   decode_group_entry(gp.sched, entry, m, qt);
-  if (m >= gp.n_items || qt < 0 || (int64_t)qt * kBM >= gp.item[m].L) return;      // never taken for a schedule the launcher built
+  if (m >= gp.n_items || qt < 0 || (int64_t)qt * 32 * W >= gp.item[m].L) return;      // never taken for a schedule the launcher built
   // (a copy, so that the fields live in scalar registers like the single-problem kernel's by-value argument
   // instead of being fetched from the argument block where they are used)
   const AttnParams item = gp.item[m];
-  attention_workgroup<D, kWaves, false>(item, qt, 0, kvh, g, 0);
+  attention_workgroup<D, W, false>(item, qt, 0, kvh, g, 0);
 }
 
 }  // namespace
@@ -595,20 +595,44 @@ static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t
   dim3 grid((unsigned)n_blocks);
   dim3 block(64 * W);
   Launcher launch(stream);
-  if (head_dim == 128)
+  if (head_dim == 128) {
     launch(host_attention_kernel<128, W>, grid, block, 0, p, n_qtiles, (int)n_items);
-  else if (head_dim == 64)
-    launch(host_attention_kernel<64, W>, grid, block, 0, p, n_qtiles, (int)n_items);
-  else
-    return APBV_ERR_UNSUPPORTED;
-  return launch.status();
+    return launch.status();
+  }
+  if constexpr (W != kWaves) {      // (head_dim 64 never takes the 256-row workgroups: attention_waves)
+    if (head_dim == 64) {
+      launch(host_attention_kernel<64, W>, grid, block, 0, p, n_qtiles, (int)n_items);
+      return launch.status();
+    }
+  }
+  return APBV_ERR_UNSUPPORTED;
 }
 
-// Query blocks of at most kAttnNarrowMaxRows rows take the 64-row workgroups: a 256-row tile would compute mostly
-// padding rows for them.
+// Waves per workgroup.  Every row's arithmetic is the same whatever the workgroup, so this is only a question of speed:
+// smaller workgroups cost K/V tile traffic, but spread over more compute units, and where two fit one, the start and
+// the end of one (about 10 us) run beside the other's key loop.  n_wg is the number of 256-row workgroups of the
+// launch, mean_keys the keys an average row of them sees.  Measured (us, 256 / 128 / 64 rows):
+//   d 128, 16 heads:  2048 rows (n_wg 128)  91 / 67 / 71     4096 (256)  152 / 135 / 167     8192 (512)  414 / 430 / 533
+//                     5000 (320, 4000 keys)  182 / 188       3 x 2048 (384, 2324 keys)  135 / 136
+//                     4 x 4096 (1024, 2248 keys)  318 / 330
+//   28 heads:         2 x 3001 (672, 2065 keys)  200 / 196   4 x 2048 (896, 1524 keys)  219 / 204
+//   d 64 (three 128-row workgroups fit a compute unit, one of 256 rows):
+//                     2 heads x 512 (4)  19.4 / 14.4 / 13.4  8 x 2048 (64)  44 / 31 / 28     8 x 8192 (256)  164 / 123 / 135
+//                     8 x 16384 (512)  370 / 345 / 400
+static int attention_waves(int head_dim, int64_t n_wg, int64_t mean_keys) {
+  if (head_dim == 64) return n_wg <= 64 ? kWavesNarrow : kWavesShort;
+  return n_wg <= 256 || mean_keys <= 2150 ? kWavesShort : kWaves;
+}
+
 apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t stream) {
   static_assert(kAttnQueryTile == kBM && kAttnNarrowQueryTile == 32 * kWavesNarrow, "tile sizes the host-side planning assumes");
+  // (a block of at most kAttnNarrowMaxRows rows is mostly padding in anything but 64-row workgroups)
   if (p.L <= kAttnNarrowMaxRows) return launch_variant<kWavesNarrow>(p, head_dim, stream);
+  const int64_t keys = (p.n_vis + (p.s_kv - p.n_vis) / 2) / p.n_splits;
+  switch (attention_waves(head_dim, (p.L + kBM - 1) / kBM * p.hq * p.batch * p.n_splits, keys)) {
+    case kWavesNarrow: return launch_variant<kWavesNarrow>(p, head_dim, stream);
+    case kWavesShort: return launch_variant<kWavesShort>(p, head_dim, stream);
+  }
   return launch_variant<kWaves>(p, head_dim, stream);
 }
 
@@ -636,32 +660,41 @@ apbv_status launch_packed_attention(const AttnParams& p, int head_dim, hipStream
   return launch_packed_variant<kWaves>(p, head_dim, stream);
 }
 
+template <int W>
+static apbv_status launch_group_variant(AttnGroupParams& gp, int head_dim, const int64_t* n_vis, const int64_t* rows, hipStream_t stream) {
+  static_assert(sizeof(AttnGroupParams) <= 4096, "kernel arguments are limited to 4 KB");
+  if (!build_group_schedule(gp.n_items, n_vis, rows, gp.sched, 32 * W)) return APBV_ERR_UNSUPPORTED;
+  const AttnParams& p0 = gp.item[0];
+  const int64_t n_units = (int64_t)gp.sched.n_entries * p0.hkv;
+  const int64_t n_blocks = (n_units + kXcds - 1) / kXcds * kXcds * p0.group;
+  if (n_blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
+  Launcher launch(stream);
+  if (head_dim == 128) {
+    launch(host_attention_group_kernel<128, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
+    return launch.status();
+  }
+  if constexpr (W != kWaves) {
+    if (head_dim == 64) {
+      launch(host_attention_group_kernel<64, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
+      return launch.status();
+    }
+  }
+  return APBV_ERR_UNSUPPORTED;
+}
+
 apbv_status launch_host_attention_group(AttnGroupParams& gp, int head_dim, hipStream_t stream) {
   static_assert(kGroupQueryTile == kBM, "the schedule's query tile is the kernel's");
-  static_assert(sizeof(AttnGroupParams) <= 4096, "kernel arguments are limited to 4 KB");
   const int n = gp.n_items;
   if (n < 1 || n > kMaxGroupItems) return APBV_ERR_UNSUPPORTED;
-  int64_t n_vis[kMaxGroupItems], rows[kMaxGroupItems];
+  int64_t n_vis[kMaxGroupItems], rows[kMaxGroupItems], tiles = 0, keys = 0;
   for (int m = 0; m < n; ++m) {
     n_vis[m] = gp.item[m].n_vis;
     rows[m] = gp.item[m].L;
+    tiles += (rows[m] + kBM - 1) / kBM;
+    keys += (rows[m] + kBM - 1) / kBM * (n_vis[m] + rows[m] / 2);
   }
-  if (!build_group_schedule(n, n_vis, rows, gp.sched)) return APBV_ERR_UNSUPPORTED;
-  const int64_t first = gp.sched.n_entries;
-  const AttnParams& p0 = gp.item[0];
-  const int64_t n_units = first * p0.hkv;
-  const int64_t n_blocks = (n_units + kXcds - 1) / kXcds * kXcds * p0.group;
-  if (n_blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
-  dim3 grid((unsigned)n_blocks);
-  dim3 block(64 * kWaves);
-  Launcher launch(stream);
-  if (head_dim == 128)
-    launch(host_attention_group_kernel<128>, grid, block, 0, gp);
-  else if (head_dim == 64)
-    launch(host_attention_group_kernel<64>, grid, block, 0, gp);
-  else
-    return APBV_ERR_UNSUPPORTED;
-  return launch.status();
+  if (attention_waves(head_dim, tiles * gp.item[0].hq, keys / tiles) == kWaves) return launch_group_variant<kWaves>(gp, head_dim, n_vis, rows, stream);
+  return launch_group_variant<kWavesShort>(gp, head_dim, n_vis, rows, stream);
 }
 
 }  // namespace apbv

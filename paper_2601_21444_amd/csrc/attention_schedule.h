@@ -1,8 +1,8 @@
 // Merged heaviest-first order of the query tiles of several attention problems (host side builds it, the
 // kernel decodes one entry per workgroup).  Plain C++: no HIP types, so host tests can compile it alone.
 //
-// Query tile qt (256 rows) of a problem with n_vis fully visible keys visits about (n_vis + 256 (qt+1)) / 64 key
-// tiles; its level is n_vis / 256 + qt, so one level is one query tile's worth of keys for every problem.
+// Query tile qt (256 rows, or another `tile`) of a problem with n_vis fully visible keys visits about (n_vis + 256 (qt+1))
+// / 64 key tiles; its level is n_vis / 256 + qt, so one level is one query tile's worth of keys for every problem.
 // Levels are walked from the highest down; inside a level the problems come in index order.  The level axis
 // is cut where a problem starts or ends, so inside a segment the set of active problems is fixed and an
 // entry index decodes with one division.
@@ -18,7 +18,7 @@
 namespace apbv {
 
 constexpr int kMaxGroupItems = 8;
-constexpr int kGroupQueryTile = 256;     // query rows per workgroup of the attention kernel
+constexpr int kGroupQueryTile = 256;     // query rows per workgroup of the attention kernel's main variant
 
 struct GroupSchedule {
   struct Segment {
@@ -32,15 +32,15 @@ struct GroupSchedule {
 };
 
 // rows[m] >= 1 query rows and n_vis[m] >= 0 fully visible keys of problem m.  False if the sizes do not fit.
-inline bool build_group_schedule(int n, const int64_t* n_vis, const int64_t* rows, GroupSchedule& s) {
+inline bool build_group_schedule(int n, const int64_t* n_vis, const int64_t* rows, GroupSchedule& s, int tile = kGroupQueryTile) {
   if (n < 1 || n > kMaxGroupItems) return false;
   int64_t lo[kMaxGroupItems], hi[kMaxGroupItems];      // level range [lo, hi) of every problem
   int64_t cuts[2 * kMaxGroupItems];
   int n_cuts = 0;
   for (int m = 0; m < n; ++m) {
     if (rows[m] < 1 || n_vis[m] < 0) return false;
-    lo[m] = n_vis[m] / kGroupQueryTile;
-    hi[m] = lo[m] + (rows[m] + kGroupQueryTile - 1) / kGroupQueryTile;
+    lo[m] = n_vis[m] / tile;
+    hi[m] = lo[m] + (rows[m] + tile - 1) / tile;
     if (hi[m] > 0x3fffffff) return false;
     s.level0[m] = (int)lo[m];
     cuts[n_cuts++] = lo[m];

@@ -1,0 +1,52 @@
+"""GPU parity of attention at both sides of the rule that picks the rows per workgroup (64, 128 or 256): the rows of one
+problem do not depend on the launch they are computed in.  Every case runs alone, where it takes small workgroups, and
+repeated in a batch, where it takes larger ones; the results are compared bit for bit and with the fp64 oracle."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2601_21444_amd as apbv
+from paper_2601_21444_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # hq, hkv, d, L, l_a, n_p, repeats
+    (2, 1, 64, 129, 0, 0, 40),           # 64-row workgroups alone (4 workgroups of 256 rows or fewer would do), 128 in the batch
+    (2, 1, 64, 700, 33, 95, 12),         # ragged tiles and segments
+    (4, 2, 128, 129, 7, 0, 3),           # just over the blocks that always take 64 rows
+    (4, 2, 128, 513, 40, 4000, 22),      # 128 rows alone; in the batch 264 workgroups of 256 rows with 4297 keys: 256
+    (3, 3, 128, 385, 0, 0, 90),          # in the batch 540 workgroups with few keys: 128
+]
+
+
+def bits(rng, shape):
+    return wl.f32_to_bf16_bits(rng.standard_normal(shape).astype(np.float32))
+
+
+def dev(b):
+    return torch.from_numpy(np.ascontiguousarray(b).view(np.int16)).view(torch.bfloat16).cuda()
+
+
+@pytest.mark.parametrize("hq,hkv,d,L,l_a,n_p,repeats", CASES)
+def test_rows_do_not_depend_on_the_workgroup(hq, hkv, d, L, l_a, n_p, repeats):
+    rng = np.random.default_rng((71, hq, L, n_p))
+    host = [bits(rng, (n, h, d)) for n, h in ((L, hq), (l_a, hkv), (l_a, hkv), (n_p, hkv), (n_p, hkv), (L, hkv), (L, hkv))]
+    args = [dev(x) for x in host]
+    scale = 1.0 / math.sqrt(d)
+    print(f"workgroups hq={hq} hkv={hkv} d={d} L={L} l_a={l_a} n_p={n_p} x {repeats}", flush=True)
+    out, lse = apbv.apbv_host_attention(*args, scale, return_lse=True)
+    many, lse_many = apbv.apbv_host_attention(*[x.unsqueeze(0).expand(repeats, *x.shape).contiguous() for x in args], scale, return_lse=True)
+    (grouped, lse_g), *_ = apbv.apbv_host_attention_group([tuple(args)] * 3, scale, return_lse=True)
+    torch.cuda.synchronize()
+    ref, lse_r = oracle.host_attention(*host, scale)
+    got = wl.bf16_bits_to_f32(out.cpu().view(torch.int16).numpy().view(np.uint16)).astype(np.float64)
+    diff = np.abs(got - ref)
+    assert diff.max() <= 2e-2 and diff.mean() / np.abs(ref).mean() <= 5e-3
+    np.testing.assert_allclose(lse.cpu().numpy().astype(np.float64), lse_r, atol=2e-3, rtol=0)
+    assert torch.equal(grouped.view(torch.int16), out.view(torch.int16)) and torch.equal(lse_g, lse)
+    for b in (0, repeats // 2, repeats - 1):
+        assert torch.equal(many[b].view(torch.int16), out.view(torch.int16)) and torch.equal(lse_many[b], lse)
