@@ -7,11 +7,13 @@ fallback path.
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 from typing import Optional, Tuple
 
 import torch
 
+_BF16 = torch.bfloat16
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libapbv.so")
 _lib = None
 
@@ -115,17 +117,23 @@ def apbv_compress_workspace_bytes(batch: int, n_kv_heads: int, head_dim: int, L:
 
 def tensor_view(t: torch.Tensor) -> Tuple[ApbvTensor, int]:
     """``[tokens, heads, d]`` or ``[batch, tokens, heads, d]`` bf16 tensor -> (apbv_tensor, batch)."""
-    if t.dtype != torch.bfloat16:
+    if t.dtype is not _BF16:
         raise TypeError("expected a bfloat16 tensor")
-    if t.dim() == 3:
-        t = t.unsqueeze(0)
-    if t.dim() != 4:
+    # (shape and strides are read once: a call makes up to seven of these, and for the smallest problems the interpreter's
+    # time is the call's)
+    shape, stride = t.shape, t.stride()
+    if len(shape) == 4:
+        b, n, _, _ = shape
+        sb, st, sh, sd = stride
+    elif len(shape) == 3:
+        n, _, _ = shape
+        st, sh, sd = stride
+        b, sb = 1, n * st
+    else:
         raise ValueError("expected [tokens, heads, d] or [batch, tokens, heads, d]")
-    if t.shape[1] > 0 and t.stride(3) != 1:
+    if n > 0 and sd != 1:
         raise ValueError("head_dim must be contiguous")
-    b, n, _, _ = t.shape
-    view = ApbvTensor(t.data_ptr() if n > 0 else None, n, t.stride(1), t.stride(2), t.stride(0))
-    return view, b
+    return ApbvTensor(t.data_ptr() if n > 0 else None, n, st, sh, sb), b
 
 
 def _check_buffer(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, shape, device) -> None:
@@ -134,20 +142,28 @@ def _check_buffer(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, shap
     the C ABI unchecked beyond that."""
     if t is None:
         return
-    need = int(shape) if isinstance(shape, int) else int(torch.Size(shape).numel())
-    if not isinstance(t, torch.Tensor) or t.dtype != dtype:
+    if not isinstance(t, torch.Tensor) or t.dtype is not dtype:
         raise TypeError(f"{name}: expected a {dtype} tensor")
     if not t.is_cuda or t.device != device:
         raise ValueError(f"{name}: must live on {device}")
     if not t.is_contiguous():
         raise ValueError(f"{name}: must be contiguous")
+    need = shape if isinstance(shape, int) else math.prod(shape)
     if t.numel() < need:
         raise ValueError(f"{name}: holds {t.numel()} elements, {need} are written")
 
 
+# The current device's current stream as a pointer, without the Stream object torch.cuda.current_stream() builds (2 us).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_ptr(stream: Optional[torch.cuda.Stream]) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is None:
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
+        stream = torch.cuda.current_stream()
+    return int(stream.cuda_stream)
 
 
 REDUCERS = {"sum": 0, "max": 1, "softmax_sum": 2}
@@ -175,8 +191,8 @@ def apbv_compress_kv(q_probe: torch.Tensor, k_local: torch.Tensor, v_local: torc
     vv, bv = tensor_view(v_local)
     if not (bq == b == bv):
         raise ValueError("batch sizes differ")
-    hq, d = q_probe.shape[-2], q_probe.shape[-1]
-    hkv, L = k_local.shape[-2], k_local.shape[-3]
+    hq, d = q_probe.shape[-2:]
+    L, hkv, _ = k_local.shape[-3:]
     dev = k_local.device
     _check_buffer(idx_out, "idx_out", torch.int32, (b, hkv, l_p), dev)
     _check_buffer(k_c_out, "k_c_out", torch.bfloat16, (b, l_p, hkv, d), dev)
@@ -226,8 +242,8 @@ def apbv_compress_kv_noalloc(q_probe: torch.Tensor, k_local: torch.Tensor, v_loc
     vv, bv = tensor_view(v_local)
     if not (bq == b == bv):
         raise ValueError("batch sizes differ")
-    hq, d = q_probe.shape[-2], q_probe.shape[-1]
-    hkv, L = k_local.shape[-2], k_local.shape[-3]
+    hq, d = q_probe.shape[-2:]
+    L, hkv, _ = k_local.shape[-3:]
     dev = k_local.device
     _check_buffer(idx_out, "idx_out", torch.int32, (b, hkv, l_p), dev)
     _check_buffer(k_c_out, "k_c_out", torch.bfloat16, (b, l_p, hkv, d), dev)
@@ -260,7 +276,7 @@ def apbv_host_attention(q_local: torch.Tensor, k_anchor: torch.Tensor, v_anchor:
         elif bt != b:
             raise ValueError("batch sizes differ")
         views.append(view)
-    L, hq, d = q_local.shape[-3], q_local.shape[-2], q_local.shape[-1]
+    L, hq, d = q_local.shape[-3:]
     hkv = k_anchor.shape[-2]
     dev = q_local.device
     _check_buffer(out, "out", torch.bfloat16, (b, L, hq, d), dev)
@@ -346,9 +362,8 @@ def apbv_query_attention(q_block: torch.Tensor, k_anchor: torch.Tensor, v_anchor
         elif bt != b:
             raise ValueError("batch sizes differ")
         views.append(view)
-    n_q, hq, d = q_block.shape[-3], q_block.shape[-2], q_block.shape[-1]
+    n_q, hq, d = q_block.shape[-3:]
     hkv = k_anchor.shape[-2]
-    n_keys = k_anchor.shape[-3] + k_pass.shape[-3] + k_local.shape[-3]
     dev = q_block.device
     _check_buffer(out, "out", torch.bfloat16, (b, n_q, hq, d), dev)
     _check_buffer(lse_out, "lse_out", torch.float32, (b, hq, n_q), dev)
@@ -358,6 +373,7 @@ def apbv_query_attention(q_block: torch.Tensor, k_anchor: torch.Tensor, v_anchor
     if return_lse and lse_out is None:
         lse_out = torch.empty((b, hq, n_q), dtype=torch.float32, device=dev)
     if workspace is None:
+        n_keys = k_anchor.shape[-3] + k_pass.shape[-3] + k_local.shape[-3]
         nbytes = apbv_query_attention_workspace_bytes(b, hq, d, n_q, max(n_keys, 1), n_splits)
         workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=dev)
     st = lib.apbv_query_attention(b, hq, hkv, d, *views, float(softmax_scale), int(n_splits), out.data_ptr(),
@@ -384,7 +400,9 @@ def apbv_merge_lse(parts_out: torch.Tensor, parts_lse: torch.Tensor, *, return_l
     n, rows, hq, d = parts_out.shape
     if parts_lse.shape != (n, hq, rows):
         raise ValueError("parts_lse must be [n_parts, Hq, rows]")
-    if not parts_out[0].is_contiguous() or not parts_lse[0].is_contiguous():
+    # (the strides of a part decide, which a tensor of all parts that is contiguous has; indexing a part out costs 2 us)
+    if not ((parts_out.is_contiguous() and n > 0) or parts_out[0].is_contiguous()) or \
+            not (parts_lse.is_contiguous() or parts_lse[0].is_contiguous()):
         raise ValueError("each part must be dense")
     _check_buffer(out, "out", torch.bfloat16, (rows, hq, d), parts_out.device)
     _check_buffer(lse_out, "lse_out", torch.float32, (hq, rows), parts_out.device)
