@@ -188,10 +188,11 @@ apbv_status apbv_query_attention(int batch, int n_q_heads, int n_kv_heads, int h
   } else {
     // the library's choice, or as many ranges as the workspace holds down to the least it accepts
     ks = choose_key_split(batch, n_q_heads, n_kv_heads, p.L, p.s_kv);
-    const size_t fits = workspace == nullptr ? 0 : workspace_bytes / key_range_bytes(batch, n_q_heads, head_dim, p.L);
     const KeySplit least = per_head_key_split(batch, n_q_heads, p.L, p.s_kv);
-    if (fits < (size_t)ks.n_splits && ks.n_splits > least.n_splits)
-      ks = key_split_of(fits > (size_t)least.n_splits ? (int64_t)fits : least.n_splits, key_tiles(p.s_kv));
+    const size_t usable = workspace == nullptr || !aligned(workspace, 256) ? 0 : workspace_bytes;
+    const size_t fits = usable / key_range_bytes(batch, n_q_heads, head_dim, p.L);
+    if (least.n_splits > 1 && fits < (size_t)least.n_splits) return APBV_ERR_WORKSPACE;
+    if (fits < (size_t)ks.n_splits) ks = key_split_of((int64_t)fits, key_tiles(p.s_kv));
   }
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (ks.n_splits == 1) return launch_host_attention(p, head_dim, stream);
