@@ -109,6 +109,27 @@ inline apbv_status validate_merge(int n_parts, int64_t rows, int n_q_heads, int 
   return APBV_OK;
 }
 
+// Lanes of the merge kernel that share one item (a 16-byte chunk of the output).  A lane that holds all its parts in
+// registers has their loads in flight at once, so with few items more lanes are faster; with many items the chip is full
+// anyway, and lanes reading one 16-byte piece of each part use a fraction of what a load fetches.  Measured (us; lanes
+// 1 / 2 / 4 / 8 / 16 / 64, items of head_dim 128; one lane holding eight parts):
+//   6 parts    4096 items  3.5 / 2.4 / 2.5 / 2.3 / 2.4 / 3.7     1048576  22 / 21 / 25 / 43 / 80 / 438
+//   16         4096        6.1 / 3.2 / 2.6 / 2.5 / 2.4 / 3.7     1048576  60 / 54 / 46 / 54 / 90 / 442
+//   64         1024        18 / 5.9 / 4.9 / 3.9 / 3.0 / 2.6      65536    41 / 14 / 15 / 18 / 17 / 34
+//   200        1024        53 / 14 / 11 / 7.7 / 6.4 / 3.1        65536    126 / 40 / 40 / 47 / 68 / 91
+//   (head_dim 64) 64 parts, 131072 items: 8 lanes 32, 4 lanes 43
+// A launch has fewer than 2^32 threads: beyond 2^28 items one lane takes an item.
+constexpr int kMergePartsPerLane = 4;
+inline int64_t merge_items(int batch, int64_t rows, int n_q_heads, int head_dim) {
+  return (int64_t)batch * rows * n_q_heads * (head_dim / 8);
+}
+inline int merge_lanes(int64_t items, int n_parts) {
+  if (items > (int64_t)1 << 28 || n_parts <= kMergePartsPerLane) return 1;
+  if (n_parts <= 2 * kMergePartsPerLane) return items <= 65536 ? 2 : 1;
+  if (n_parts <= 4 * kMergePartsPerLane) return 4;
+  return items <= 1024 ? 64 : (items <= 4096 ? 16 : 8);
+}
+
 // Key split of the query-block attention: n_splits ranges of tiles_per_split 64-key tiles; ranges are equal and none
 // is empty.
 struct KeySplit {

@@ -6,13 +6,11 @@
 // Every partial output is read once (16 bytes per lane per part), fp32 arithmetic.  The work is small and what bounds
 // it is the chain of dependent steps and a cold instruction cache, so: the parts' log-sum-exps and outputs are requested
 // together, indexes are 32-bit where they fit, and lanes are combined on the DPP path instead of through LDS.
-// 16 parts of 64 x 16 rows of 128: 3.8 -> 2.9 us; 128 parts of 16 rows: 6.1 -> 2.7 us; 16 parts of 512 x 28: 19.9 -> 12.8.
+// 16 parts of 64 x 16 rows of 128: 3.8 -> 2.8 us; 100 parts of 16 rows: 5.4 -> 2.6 us; 16 parts of 512 x 28: 19.9 -> 12.8.
 #include "apbv_common.h"
 
 namespace apbv {
 namespace {
-
-constexpr int kPartsPerLane = 4;     // parts a lane holds in registers at once
 
 // op over groups of LP consecutive lanes (LP a power of two), the result in every lane of the group.
 template <int LP, typename Op>
@@ -35,8 +33,9 @@ __device__ __forceinline__ float group_reduce(float x, Op op) {
   return x;
 }
 
-// LP lanes share one 16-byte output chunk: lane `sub` takes parts sub, sub + LP, ...
-template <int D, int LP>
+// LP lanes share one 16-byte output chunk: lane `sub` takes parts sub, sub + LP, ...; up to kPartsPerLane of them are held
+// in registers at once; with more the lanes loop over the parts (merge_lanes: how many lanes, and why).
+template <int D, int LP, int kPartsPerLane>
 __global__ __launch_bounds__(256) void merge_lse_kernel(const MergeParams p) {
   constexpr int KC = D / 8;
   const int64_t thread = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -120,16 +119,16 @@ __global__ __launch_bounds__(256) void merge_lse_kernel(const MergeParams p) {
   if (p.lse_out != nullptr && c == 0) p.lse_out[lse_idx] = wsum > 0.f ? m + __logf(wsum) : -INFINITY;
 }
 
-template <int LP>
+template <int LP, int kPartsPerLane = kMergePartsPerLane>
 apbv_status launch_merge_variant(const MergeParams& p, hipStream_t stream) {
-  const int64_t threads = (int64_t)p.batch * p.rows * p.hq * (p.d / 8) * LP;
+  const int64_t threads = merge_items(p.batch, p.rows, p.hq, p.d) * LP;
   const int64_t blocks = (threads + 255) / 256;
   if (blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
   Launcher launch(stream);
   if (p.d == 128)
-    launch(merge_lse_kernel<128, LP>, dim3((unsigned)blocks), dim3(256), 0, p);
+    launch(merge_lse_kernel<128, LP, kPartsPerLane>, dim3((unsigned)blocks), dim3(256), 0, p);
   else if (p.d == 64)
-    launch(merge_lse_kernel<64, LP>, dim3((unsigned)blocks), dim3(256), 0, p);
+    launch(merge_lse_kernel<64, LP, kPartsPerLane>, dim3((unsigned)blocks), dim3(256), 0, p);
   else
     return APBV_ERR_UNSUPPORTED;
   return launch.status();
@@ -137,14 +136,16 @@ apbv_status launch_merge_variant(const MergeParams& p, hipStream_t stream) {
 
 }  // namespace
 
-// As many lanes per item as leave a lane at most kPartsPerLane parts; beyond 64 lanes' worth the lanes loop.  (The 65535
-// heads x 2^24 rows the entry point accepts must stay launchable: with many rows one lane per item is enough threads.)
 apbv_status launch_merge_lse(const MergeParams& p, hipStream_t stream) {
-  if ((int64_t)p.batch * p.rows * p.hq * (p.d / 8) > ((int64_t)1 << 30)) return launch_merge_variant<1>(p, stream);
-  if (p.n_parts <= 1 * kPartsPerLane) return launch_merge_variant<1>(p, stream);
-  if (p.n_parts <= 4 * kPartsPerLane) return launch_merge_variant<4>(p, stream);
-  if (p.n_parts <= 16 * kPartsPerLane) return launch_merge_variant<16>(p, stream);
-  return launch_merge_variant<64>(p, stream);
+  switch (merge_lanes(merge_items(p.batch, p.rows, p.hq, p.d), p.n_parts)) {
+    case 1: return p.n_parts <= kMergePartsPerLane ? launch_merge_variant<1>(p, stream) : launch_merge_variant<1, 2 * kMergePartsPerLane>(p, stream);
+    case 2: return launch_merge_variant<2>(p, stream);
+    case 4: return launch_merge_variant<4>(p, stream);
+    case 8: return launch_merge_variant<8>(p, stream);
+    case 16: return launch_merge_variant<16>(p, stream);
+    case 64: return launch_merge_variant<64>(p, stream);
+  }
+  return APBV_ERR_UNSUPPORTED;
 }
 
 }  // namespace apbv

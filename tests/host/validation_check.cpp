@@ -102,6 +102,17 @@ int main() {
   EXPECT(validate_merge(3, 10, 4, 128, P(0x1000), 5120, static_cast<const float*>(P(0x2000)), 39, P(0x3000), nullptr) == APBV_ERR_SHAPE);
   EXPECT(validate_merge(3, 10, 4, 96, P(0x1000), 5120, static_cast<const float*>(P(0x2000)), 40, P(0x3000), nullptr) == APBV_ERR_UNSUPPORTED);
   EXPECT(validate_merge(3, 10, 4, 128, nullptr, 5120, static_cast<const float*>(P(0x2000)), 40, P(0x3000), nullptr) == APBV_ERR_NULL);
+  // lanes per item: a launch stays below 2^32 threads (blocks of 256) at every number of parts and items, and only a few
+  // items get more lanes than read 128 bytes of a part together
+  for (int64_t items = 8; items <= (int64_t)1 << 31; items += items / 3 + 1)
+    for (int n_parts = 1; n_parts <= 65536; n_parts += n_parts / 5 + 1) {
+      const int lanes = merge_lanes(items, n_parts);
+      EXPECT(lanes == 1 || lanes == 2 || lanes == 4 || lanes == 8 || lanes == 16 || lanes == 64);
+      EXPECT((items * lanes + 255) / 256 * 256 < (int64_t)1 << 32 && (lanes <= 8 || items <= 4096));
+      EXPECT(lanes > 1 || n_parts <= 8 || items > (int64_t)1 << 28);
+    }
+  EXPECT(merge_lanes(((int64_t)1 << 29) - 1, 65) == 1 && merge_lanes((int64_t)1 << 28, 17) == 8);
+  EXPECT(merge_items(2, 3, 5, 128) == 2 * 3 * 5 * 16 && merge_items(1, (int64_t)1 << 24, 65535, 64) == ((int64_t)65535 << 27));
   // ---- planners over a sweep: the key split covers every tile exactly once with no empty range; workspaces are
   // aligned, ordered and monotone in the batch
   for (int64_t n_keys = 1; n_keys < 300000; n_keys = n_keys * 3 + 7)

@@ -69,6 +69,37 @@ def test_merge_matches_oracle_and_handles_empty_parts():
     np.testing.assert_allclose(lse_g[fin], lse_r[fin], atol=1e-5)
 
 
+# Both sides of every number of parts and of items (rows x heads x head_dim / 8) at which the lanes that share an item
+# change, item counts that do not fill a block among them
+MANY_PARTS = [(n, d, rows, hq) for n in (1, 2, 4, 5, 8, 9, 16, 17, 32, 33, 64, 65, 256, 257, 300)
+              for d, rows, hq in ((128, 3, 7), (64, 41, 3), (64, 300, 1), (128, 77, 6))]
+MANY_PARTS += [(n, 128, 700, 6) for n in (5, 8, 9)] + [(n, 64, 1366, 6) for n in (5, 8)]      # more than 65536 items
+
+
+@pytest.mark.parametrize("n,d,rows,hq", MANY_PARTS)
+def test_merge_of_many_parts(n, d, rows, hq):
+    rng = np.random.default_rng((10, n, rows))
+    print(f"merge n={n} d={d} rows={rows} hq={hq}", flush=True)
+    outs = rand_bits(rng, (n, rows, hq, d))
+    lses = (rng.standard_normal((n, hq, rows)) * 3).astype(np.float32)
+    lses[n // 2, :, ::2] = -np.inf          # a part that saw no key of every other row
+    lses[: n - 1, 0, 1] = -np.inf           # a row whose keys are all in the last part
+    lses[:, hq - 1, 2] = -np.inf            # a row with no key anywhere
+    whole = torch.full((rows + 2, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")     # canary rows
+    out, lse = apbv.apbv_merge_lse(dev(outs), torch.from_numpy(lses).cuda(), return_lse=True, out=whole[1:rows + 1])
+    torch.cuda.synchronize()
+    ref, lse_r = oracle.merge_lse([wl.bf16_bits_to_f32(o).astype(np.float64) for o in outs], list(lses.astype(np.float64)))
+    got = to_f64(out)
+    # one rounding to bf16 (half an ulp, 2^-8 at most); float32 weights (up to 20 ulps each, the exponent's rounding) and a
+    # sum of n products of values below 8
+    np.testing.assert_allclose(got, ref, rtol=2.0 ** -8, atol=(n + 40) * 8 * 2.0 ** -24)
+    assert np.all(got[2, hq - 1] == 0) and torch.isnan(whole[0]).all() and torch.isnan(whole[-1]).all()
+    # float32 rounding of the n weights, their sum and its logarithm
+    np.testing.assert_array_equal(np.isneginf(lse.cpu().numpy()), np.isneginf(lse_r))
+    fin = np.isfinite(lse_r)
+    np.testing.assert_allclose(lse.cpu().numpy()[fin], lse_r[fin], atol=(n + 40) * 2.0 ** -23, rtol=0)
+
+
 def test_query_block_attention_end_to_end():
     """Eq. 5 on one GPU: H hosts each attend the query block to their anchor slice and context block (no causal
     segment), the last one also to the query block's own keys (causal); the merged result must equal
