@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import math
+import operator
 import os
 from typing import Optional, Tuple
 
@@ -142,13 +143,14 @@ def _check_buffer(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, shap
     the C ABI unchecked beyond that."""
     if t is None:
         return
+    # (as whole numbers: a size such as l_p that is none is refused here, not rounded at the call)
+    need = shape if isinstance(shape, int) else math.prod(map(operator.index, shape))
     if not isinstance(t, torch.Tensor) or t.dtype is not dtype:
         raise TypeError(f"{name}: expected a {dtype} tensor")
     if not t.is_cuda or t.device != device:
         raise ValueError(f"{name}: must live on {device}")
     if not t.is_contiguous():
         raise ValueError(f"{name}: must be contiguous")
-    need = shape if isinstance(shape, int) else math.prod(shape)
     if t.numel() < need:
         raise ValueError(f"{name}: holds {t.numel()} elements, {need} are written")
 

@@ -4,7 +4,9 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
+import torch
 
 import paper_2601_21444_amd as apbv
 from paper_2601_21444_amd.binding import ApbvTensor
@@ -131,6 +133,15 @@ def test_compress_reduced_rejects_bad_arguments_without_launching():
     need = ws("softmax_sum", 1, 4, 2, 128, 8, 4096, 64)
     assert call(ws_bytes=need - 1) == -4
     assert call(n_q=4200, ws_bytes=1 << 30) == -3                 # 8400 rows: more than the softmax-sum kernels stage
+
+
+@pytest.mark.parametrize("l_p,error", [(3.0, TypeError), (3.5, TypeError), (np.float64(3), TypeError), (3, ValueError), (np.int64(3), ValueError)])
+def test_output_buffers_are_sized_by_whole_numbers(l_p, error):
+    """A size that is no whole number is refused whatever buffers came with the call; a whole one gets as far as the
+    check of the buffer's device."""
+    import paper_2601_21444_amd.binding as b
+    with pytest.raises(error):
+        b._check_buffer(torch.empty(6, dtype=torch.int32), "idx_out", torch.int32, (1, 2, l_p), torch.device("cuda"))
 
 
 def test_merge_rejects_bad_arguments_without_launching():
