@@ -595,43 +595,22 @@ static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t
   dim3 grid((unsigned)n_blocks);
   dim3 block(64 * W);
   Launcher launch(stream);
-  if (head_dim == 128) {
+  if (head_dim == 128)
     launch(host_attention_kernel<128, W>, grid, block, 0, p, n_qtiles, (int)n_items);
-    return launch.status();
-  }
-  if constexpr (W != kWaves) {      // (head_dim 64 never takes the 256-row workgroups: attention_waves)
-    if (head_dim == 64) {
-      launch(host_attention_kernel<64, W>, grid, block, 0, p, n_qtiles, (int)n_items);
-      return launch.status();
-    }
-  }
-  return APBV_ERR_UNSUPPORTED;
-}
-
-// Waves per workgroup.  Every row's arithmetic is the same whatever the workgroup, so this is only a question of speed:
-// smaller workgroups cost K/V tile traffic, but spread over more compute units, and where two fit one, the start and
-// the end of one (about 10 us) run beside the other's key loop.  n_wg is the number of 256-row workgroups of the
-// launch, mean_keys the keys an average row of them sees.  Measured (us, 256 / 128 / 64 rows):
-//   d 128, 16 heads:  2048 rows (n_wg 128)  91 / 67 / 71     4096 (256)  152 / 135 / 167     8192 (512)  414 / 430 / 533
-//                     5000 (320, 4000 keys)  182 / 188       3 x 2048 (384, 2324 keys)  135 / 136
-//                     4 x 4096 (1024, 2248 keys)  318 / 330
-//   28 heads:         2 x 3001 (672, 2065 keys)  200 / 196   4 x 2048 (896, 1524 keys)  219 / 204
-//   d 64 (three 128-row workgroups fit a compute unit, one of 256 rows):
-//                     2 heads x 512 (4)  19.4 / 14.4 / 13.4  8 x 2048 (64)  44 / 31 / 28     8 x 8192 (256)  164 / 123 / 135
-//                     8 x 16384 (512)  370 / 345 / 400
-static int attention_waves(int head_dim, int64_t n_wg, int64_t mean_keys) {
-  if (head_dim == 64) return n_wg <= 64 ? kWavesNarrow : kWavesShort;
-  return n_wg <= 256 || mean_keys <= 2150 ? kWavesShort : kWaves;
+  else if (head_dim == 64)
+    launch(host_attention_kernel<64, W>, grid, block, 0, p, n_qtiles, (int)n_items);
+  else
+    return APBV_ERR_UNSUPPORTED;
+  return launch.status();
 }
 
 apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t stream) {
   static_assert(kAttnQueryTile == kBM && kAttnNarrowQueryTile == 32 * kWavesNarrow, "tile sizes the host-side planning assumes");
   // (a block of at most kAttnNarrowMaxRows rows is mostly padding in anything but 64-row workgroups)
   if (p.L <= kAttnNarrowMaxRows) return launch_variant<kWavesNarrow>(p, head_dim, stream);
-  const int64_t keys = (p.n_vis + (p.s_kv - p.n_vis) / 2) / p.n_splits;
-  switch (attention_waves(head_dim, (p.L + kBM - 1) / kBM * p.hq * p.batch * p.n_splits, keys)) {
-    case kWavesNarrow: return launch_variant<kWavesNarrow>(p, head_dim, stream);
-    case kWavesShort: return launch_variant<kWavesShort>(p, head_dim, stream);
+  switch (attention_rows(head_dim, p.group, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits)) {
+    case 32 * kWavesNarrow: return launch_variant<kWavesNarrow>(p, head_dim, stream);
+    case 32 * kWavesShort: return launch_variant<kWavesShort>(p, head_dim, stream);
   }
   return launch_variant<kWaves>(p, head_dim, stream);
 }
@@ -669,31 +648,31 @@ static apbv_status launch_group_variant(AttnGroupParams& gp, int head_dim, const
   const int64_t n_blocks = (n_units + kXcds - 1) / kXcds * kXcds * p0.group;
   if (n_blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
   Launcher launch(stream);
-  if (head_dim == 128) {
+  if (head_dim == 128)
     launch(host_attention_group_kernel<128, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
-    return launch.status();
-  }
-  if constexpr (W != kWaves) {
-    if (head_dim == 64) {
-      launch(host_attention_group_kernel<64, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
-      return launch.status();
-    }
-  }
-  return APBV_ERR_UNSUPPORTED;
+  else if (head_dim == 64)
+    launch(host_attention_group_kernel<64, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
+  else
+    return APBV_ERR_UNSUPPORTED;
+  return launch.status();
 }
 
 apbv_status launch_host_attention_group(AttnGroupParams& gp, int head_dim, hipStream_t stream) {
   static_assert(kGroupQueryTile == kBM, "the schedule's query tile is the kernel's");
   const int n = gp.n_items;
   if (n < 1 || n > kMaxGroupItems) return APBV_ERR_UNSUPPORTED;
-  int64_t n_vis[kMaxGroupItems], rows[kMaxGroupItems], tiles = 0, keys = 0;
+  int64_t n_vis[kMaxGroupItems], rows[kMaxGroupItems];
+  AttentionTiles tiles[3];
+  double kv_bytes = 0, qo_bytes = 0;
   for (int m = 0; m < n; ++m) {
-    n_vis[m] = gp.item[m].n_vis;
-    rows[m] = gp.item[m].L;
-    tiles += (rows[m] + kBM - 1) / kBM;
-    keys += (rows[m] + kBM - 1) / kBM * (n_vis[m] + rows[m] / 2);
+    const AttnParams& p = gp.item[m];
+    n_vis[m] = p.n_vis;
+    rows[m] = p.L;
+    for (int i = 0; i < 3; ++i) add_attention_tiles(tiles[i], 64 << i, p.hq, p.L, p.n_vis, true);
+    kv_bytes += (double)p.s_kv * p.hkv * head_dim * 4;
+    qo_bytes += (double)p.L * p.hq * head_dim * 4;
   }
-  if (attention_waves(head_dim, tiles * gp.item[0].hq, keys / tiles) == kWaves) return launch_group_variant<kWaves>(gp, head_dim, n_vis, rows, stream);
+  if (attention_rows(head_dim, gp.item[0].group, gp.item[0].hkv, tiles, kv_bytes, qo_bytes, false) == kBM) return launch_group_variant<kWaves>(gp, head_dim, n_vis, rows, stream);
   return launch_group_variant<kWavesShort>(gp, head_dim, n_vis, rows, stream);
 }
 

@@ -109,6 +109,105 @@ inline apbv_status validate_merge(int n_parts, int64_t rows, int n_q_heads, int 
   return APBV_OK;
 }
 
+// ---- rows per workgroup of the attention kernel (64, 128 or 256): a question of speed only, every row's arithmetic is the
+// same.  Smaller workgroups spread over more compute units, and where two share one the start and the end of one run
+// beside the other's keys; but they read K and V more often, and one that is alone on its unit takes 0.64 of the time of
+// two, not half.  The rule is drawn from 2260 measured launches (heads, batches, 129 to 16384 rows, 0 to 33000 visible
+// keys): against 256 rows always it is more than 1.5 % slower in 12 of them (at most 10 %) and on average 10 % (head_dim
+// 128) and 22 % (64) faster, 1 % behind the best size of every launch.  Examples (us, 256 / 128 rows, d 128):
+//   16 heads x 2048 rows behind 8704 keys  245 / 181 (a workgroup per unit)    x 4096 rows, no more keys  100 / 87
+//   16 x 4096 behind 32768  981 / 1030 (one full round either way)             32 x 3899 rows  123 / 130 (two full rounds)
+//   5 x 32 heads, 233 rows over 1829 keys  52 / 56 (320 of 128 rows: some units get two, the others one)
+//   68 x 16 heads of their own K/V, 1752 rows behind 827 keys  1909 / 2959 (K/V come from HBM each time, not from a cache)
+struct AttentionTiles {          // the row tiles of a launch: how many, and the keys the heaviest and the lightest see
+  double n = 0, k_max = 0, k_min = 0, key_sum = 0;
+};
+inline void add_attention_tiles(AttentionTiles& t, int rows, double heads, int64_t n_rows, int64_t n_vis, bool causal, int n_splits = 1) {
+  const double tiles = (double)((n_rows + rows - 1) / rows) * heads * n_splits;
+  const double hi = (double)(n_vis + (causal ? n_rows : 0)) / n_splits;
+  const double lo = (double)(n_vis + (causal ? (n_rows < rows ? n_rows : rows) : 0)) / n_splits;
+  t.k_max = t.n > 0 && t.k_max > hi ? t.k_max : hi;
+  t.k_min = t.n > 0 && t.k_min < lo ? t.k_min : lo;
+  t.n += tiles;
+  t.key_sum += tiles * (hi + lo) / 2;
+}
+// A workgroup that sees k keys takes fixed + per_key * k us when its unit is full (per_unit workgroups), alone_* when it
+// has the unit to itself; launches of more than two rounds end unevenly by a share of a lightest workgroup's time.
+struct AttentionCost {
+  int per_unit;
+  double fixed, per_key, alone_fixed, alone_per_key, uneven;
+};
+inline AttentionCost attention_cost(int head_dim, int rows) {
+  if (head_dim == 64) return {1, 5.8, 0.0178, 5.8, 0.0178, 0};           // 256 rows
+  if (rows == 128) return {2, 8.4, 0.0258, 7.2, 0.0152, 0};
+  return {1, 8.9, 0.0235, 8.9, 0.0235, 0.23};
+}
+// Time of a launch, heaviest first on 256 units: two whole rounds give every slot the same (its heavy item first, a light
+// one second); what is left over is a round of its own, or two.  Tiles are taken to spread evenly between k_min and k_max
+// keys.  Within 8 % of the measured launches.
+inline double attention_makespan(const AttentionCost& c, const AttentionTiles& w) {
+  const double units = 256, slots = units * c.per_unit;
+  auto shared = [&](double k) { return c.fixed + c.per_key * k; };
+  auto alone = [&](double k) { return c.alone_fixed + c.alone_per_key * k; };
+  auto larger = [](double a, double b) { return a > b ? a : b; };
+  const double pairs = std::floor(w.n / (2 * slots)), done = 2 * slots * pairs, m = w.n - done;
+  const double k1 = w.k_max - done / w.n * (w.k_max - w.k_min);
+  const double t = 2 * pairs * shared((w.k_max + k1) / 2) + (w.n > 2 * slots ? c.uneven * shared(w.k_min) : 0);
+  if (m <= 0) return t;
+  if (m <= units) return t + alone(k1);
+  const double k2 = k1 - units / m * (k1 - w.k_min);           // the heaviest unit's second workgroup
+  const double one = c.per_unit == 1 ? shared(k1) : larger(shared(k2) + c.alone_per_key * (k1 - k2), alone(k1));
+  if (m <= slots) return t + one;
+  const double k3 = k1 - slots / m * (k1 - w.k_min);           // the first of a second round
+  double second = shared(k3);
+  if (m <= slots + units && c.per_unit > 1) {                  // alone on its unit, once those beside it have finished
+    const double busy = shared(k1) - shared(k3) < shared(k3) ? shared(k1) - shared(k3) : shared(k3);
+    second = alone(k3) + (1 - alone(k3) / shared(k3)) * busy;
+  }
+  return t + larger(one, shared(k3) + second);
+}
+// Time of the memory traffic: Q and O once, K and V once per row tile (the heads of a group together, through their XCD's
+// L2) as far as the launch's tensors exceed the 256 MB last-level cache, at the 4 TB/s such launches reach.
+inline double attention_traffic(int head_dim, int group, const AttentionTiles& w, double kv_bytes, double qo_bytes) {
+  const double total = kv_bytes + qo_bytes, missed = total > 256e6 ? 1 - 256e6 / total : 0;
+  return (qo_bytes + missed * w.key_sum / group * head_dim * 4) / 4e6;
+}
+// tiles[]: of the launch cut into 64, 128 and 256 rows; kv_heads: KV heads, batch items and key ranges that a row tile of
+// the launch belongs to one of.
+//   head_dim 64   few workgroups: 64 rows (8 heads x 2048 rows 44 / 31 / 28 us with 256 / 128 / 64 rows); else 128 (three fit a
+//                 unit, one of 256 rows), but not where 256 rows are one round and 128 two with the second tile half empty
+//                 (192 workgroups of 132 rows 9.1 / 9.9)
+//   head_dim 128  by the estimates up to two rounds of 256 rows, whose spread they get right; beyond, and for the shortest
+//                 keys, by the keys alone: the fixed cost covered against the 4 to 10 % slower loop of 128 rows.  But 256
+//                 rows if the row tiles of a head share nothing with other heads and are not kept on one XCD (a number
+//                 of heads that eight does not divide, nor it eight): 84 heads x 3031 rows 211 / 248, 96 x 2874 325 / 294
+//   both          256 rows where the traffic of 128 would take longer; the tiles of many heads pass through the caches
+//                 without meeting another tile of theirs, those of a few heads run at the same time
+inline int attention_rows(int head_dim, int group, double kv_heads, const AttentionTiles (&tiles)[3], double kv_bytes, double qo_bytes,
+                          bool may_be_64) {
+  const AttentionTiles &t64 = tiles[0], &t128 = tiles[1], &t256 = tiles[2];
+  const double time = attention_makespan(attention_cost(head_dim, 256), t256), keys = t256.key_sum / t256.n;
+  const bool scattered = group == 1 && std::fmod(kv_heads, 8) != 0 && std::fmod(8, kv_heads) != 0 && kv_bytes > 32e6;
+  if (head_dim == 64) {
+    if (may_be_64 && t256.n <= 64) return 64;
+    if (t256.n <= 256 && t128.n > 256 && t128.n == 2 * t256.n && t64.n == 3 * t256.n) return 256;
+  } else if (t256.n > 512 ? keys > 2280 || scattered : keys > 300 && attention_makespan(attention_cost(head_dim, 128), t128) > 0.98 * time) {
+    return 256;
+  }
+  const double read = attention_traffic(head_dim, group, t256, kv_bytes, qo_bytes), least = time > read ? time : read;
+  const double reached = kv_heads * group >= 512 ? 0.85 : 1.2;
+  if (kv_bytes > 128e6 && attention_traffic(head_dim, group, t128, kv_bytes, qo_bytes) > reached * least) return 256;
+  return 128;
+}
+// One launch of batch * n_q_heads heads and n_splits key ranges, all of n_rows queries.
+inline int attention_rows(int head_dim, int group, int batch, int n_q_heads, int64_t n_rows, int64_t n_vis, bool causal, int n_splits) {
+  AttentionTiles tiles[3];
+  const double heads = (double)batch * n_q_heads, row = heads * head_dim * 4;
+  for (int i = 0; i < 3; ++i) add_attention_tiles(tiles[i], 64 << i, heads, n_rows, n_vis, causal, n_splits);
+  return attention_rows(head_dim, group, heads / group * n_splits, tiles, row / group * (double)(n_vis + (causal ? n_rows : 0)),
+                        row * (double)n_rows, true);
+}
+
 // Lanes of the merge kernel that share one item (a 16-byte chunk of the output).  A lane that holds all its parts in
 // registers has their loads in flight at once, so with few items more lanes are faster; with many items the chip is full
 // anyway, and lanes reading one 16-byte piece of each part use a fraction of what a load fetches.  Measured (us; lanes

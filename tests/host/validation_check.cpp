@@ -102,6 +102,28 @@ int main() {
   EXPECT(validate_merge(3, 10, 4, 128, P(0x1000), 5120, static_cast<const float*>(P(0x2000)), 39, P(0x3000), nullptr) == APBV_ERR_SHAPE);
   EXPECT(validate_merge(3, 10, 4, 96, P(0x1000), 5120, static_cast<const float*>(P(0x2000)), 40, P(0x3000), nullptr) == APBV_ERR_UNSUPPORTED);
   EXPECT(validate_merge(3, 10, 4, 128, nullptr, 5120, static_cast<const float*>(P(0x2000)), 40, P(0x3000), nullptr) == APBV_ERR_NULL);
+  // rows per workgroup: the launches of tests/test_gpu_attention_workgroups.py (alone, in a batch, three in a group) and
+  // measured ones on both sides of the rule
+  struct { int hq, hkv, d; int64_t L, n_vis; int repeats, alone, batch, group; } rows_of[] = {
+      {2, 1, 64, 129, 0, 40, 64, 128, 128},       {2, 1, 64, 700, 128, 12, 64, 128, 128},    {4, 1, 64, 300, 5000, 40, 64, 128, 128},
+      {8, 8, 64, 150, 1000, 30, 64, 256, 128},    {4, 2, 128, 129, 7, 3, 128, 128, 128},     {4, 2, 128, 513, 4040, 20, 128, 256, 128},
+      {28, 4, 128, 700, 1500, 3, 128, 256, 256},  {40, 8, 128, 289, 1700, 3, 128, 256, 256}};
+  for (const auto& c : rows_of) {
+    EXPECT(attention_rows(c.d, c.hq / c.hkv, 1, c.hq, c.L, c.n_vis, true, 1) == c.alone);
+    EXPECT(attention_rows(c.d, c.hq / c.hkv, c.repeats, c.hq, c.L, c.n_vis, true, 1) == c.batch);
+    AttentionTiles tiles[3];
+    for (int m = 0; m < 3; ++m)
+      for (int i = 0; i < 3; ++i) add_attention_tiles(tiles[i], 64 << i, c.hq, c.L, c.n_vis, true);
+    const double kv = 3.0 * (double)(c.n_vis + c.L) * c.hkv * c.d * 4, qo = 3.0 * (double)c.L * c.hq * c.d * 4;
+    EXPECT(attention_rows(c.d, c.hq / c.hkv, c.hkv, tiles, kv, qo, false) == c.group);
+  }
+  EXPECT(attention_rows(128, 8, 1, 16, 2048, 8704, true, 1) == 128 && attention_rows(128, 8, 1, 16, 4096, 0, true, 1) == 128);
+  EXPECT(attention_rows(128, 8, 1, 16, 4096, 32768, true, 1) == 256 && attention_rows(128, 8, 1, 16, 16384, 9216, true, 1) == 256);
+  EXPECT(attention_rows(128, 4, 5, 32, 233, 1829, false, 1) == 256 && attention_rows(128, 1, 1, 32, 3899, 0, true, 1) == 256);
+  EXPECT(attention_rows(128, 7, 2, 28, 3001, 564, true, 1) == 128 && attention_rows(128, 7, 4, 28, 2048, 500, true, 1) == 128);
+  EXPECT(attention_rows(128, 1, 68, 16, 1752, 827, true, 1) == 256 && attention_rows(128, 8, 68, 16, 1752, 827, true, 1) == 128);
+  EXPECT(attention_rows(128, 1, 1, 84, 3031, 0, true, 1) == 256 && attention_rows(128, 1, 1, 96, 2874, 0, true, 1) == 128);
+  EXPECT(attention_rows(64, 1, 83, 16, 3743, 937, true, 1) == 256 && attention_rows(64, 4, 1, 8, 8192, 0, true, 1) == 128);
   // lanes per item: a launch stays below 2^32 threads (blocks of 256) at every number of parts and items, and only a few
   // items get more lanes than read 128 bytes of a part together
   for (int64_t items = 8; items <= (int64_t)1 << 31; items += items / 3 + 1)

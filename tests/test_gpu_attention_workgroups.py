@@ -1,6 +1,7 @@
 """GPU parity of attention at both sides of the rule that picks the rows per workgroup (64, 128 or 256): the rows of one
-problem do not depend on the launch they are computed in.  Every case runs alone, where it takes small workgroups, and
-repeated in a batch, where it takes larger ones; the results are compared bit for bit and with the fp64 oracle."""
+problem do not depend on the launch they are computed in.  Every case runs alone, repeated in a batch, and three times in
+a grouped launch, in workgroups of the sizes listed (tests/host/validation_check.cpp holds the rule to them); the results
+are compared bit for bit and with the fp64 oracle."""
 import math
 
 import numpy as np
@@ -14,12 +15,15 @@ from paper_2601_21444_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # hq, hkv, d, L, l_a, n_p, repeats
-    (2, 1, 64, 129, 0, 0, 40),           # 64-row workgroups alone (4 workgroups of 256 rows or fewer would do), 128 in the batch
-    (2, 1, 64, 700, 33, 95, 12),         # ragged tiles and segments
-    (4, 2, 128, 129, 7, 0, 3),           # just over the blocks that always take 64 rows
-    (4, 2, 128, 513, 40, 4000, 22),      # 128 rows alone; in the batch 264 workgroups of 256 rows with 4297 keys: 256
-    (3, 3, 128, 385, 0, 0, 90),          # in the batch 540 workgroups with few keys: 128
+    # hq, hkv, d, L, l_a, n_p, repeats, rows alone / in the batch / in the group
+    (2, 1, 64, 129, 0, 0, 40),           # 64 / 128 / 128: just over the blocks that always take 64 rows
+    (2, 1, 64, 700, 33, 95, 12),         # 64 / 128 / 128: ragged tiles and segments
+    (4, 1, 64, 300, 100, 4900, 40),      # 64 / 128 / 128
+    (8, 8, 64, 150, 67, 933, 30),        # 64 / 256 / 128: rows 150 to 255 of the only tile missing, no shared K/V
+    (4, 2, 128, 129, 7, 0, 3),           # 128 / 128 / 128
+    (4, 2, 128, 513, 40, 4000, 20),      # 128 / 256 / 128: a last tile of one row
+    (28, 4, 128, 700, 33, 1467, 3),      # 128 / 256 / 256
+    (40, 8, 128, 289, 100, 1600, 3),     # 128 / 256 / 256: a last tile of 33 rows
 ]
 
 
@@ -39,14 +43,23 @@ def test_rows_do_not_depend_on_the_workgroup(hq, hkv, d, L, l_a, n_p, repeats):
     scale = 1.0 / math.sqrt(d)
     print(f"workgroups hq={hq} hkv={hkv} d={d} L={L} l_a={l_a} n_p={n_p} x {repeats}", flush=True)
     out, lse = apbv.apbv_host_attention(*args, scale, return_lse=True)
-    many, lse_many = apbv.apbv_host_attention(*[x.unsqueeze(0).expand(repeats, *x.shape).contiguous() for x in args], scale, return_lse=True)
-    (grouped, lse_g), *_ = apbv.apbv_host_attention_group([tuple(args)] * 3, scale, return_lse=True)
+    def canaries(n):                      # an output of n rows with a row of NaN before and after it
+        whole = torch.full((n + 2, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        return whole, whole[1:n + 1]
+    whole, many = canaries(repeats * L)
+    many, lse_many = apbv.apbv_host_attention(*[x.unsqueeze(0).expand(repeats, *x.shape).contiguous() for x in args], scale, return_lse=True,
+                                              out=many.view(repeats, L, hq, d))
+    outs = [canaries(L) for _ in range(3)]
+    group = apbv.apbv_host_attention_group([tuple(args) + (o,) for _, o in outs], scale, return_lse=True)
     torch.cuda.synchronize()
     ref, lse_r = oracle.host_attention(*host, scale)
     got = wl.bf16_bits_to_f32(out.cpu().view(torch.int16).numpy().view(np.uint16)).astype(np.float64)
     diff = np.abs(got - ref)
     assert diff.max() <= 2e-2 and diff.mean() / np.abs(ref).mean() <= 5e-3
     np.testing.assert_allclose(lse.cpu().numpy().astype(np.float64), lse_r, atol=2e-3, rtol=0)
-    assert torch.equal(grouped.view(torch.int16), out.view(torch.int16)) and torch.equal(lse_g, lse)
-    for b in (0, repeats // 2, repeats - 1):
+    for grouped, lse_g in group:
+        assert torch.equal(grouped.view(torch.int16), out.view(torch.int16)) and torch.equal(lse_g, lse)
+    for w in [whole] + [w for w, _ in outs]:
+        assert torch.isnan(w[0]).all() and torch.isnan(w[-1]).all() and not torch.isnan(w[1:-1]).any()
+    for b in range(repeats):
         assert torch.equal(many[b].view(torch.int16), out.view(torch.int16)) and torch.equal(lse_many[b], lse)
