@@ -84,9 +84,9 @@ struct AttnParams {
 };
 
 apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t stream);
-apbv_status launch_packed_attention(const AttnParams& p, int head_dim, hipStream_t stream);
-// short query blocks, heads of a KV group packed into the rows (query_attention.hip)
-apbv_status launch_query_attention(const AttnParams& p, int head_dim, hipStream_t stream);
+apbv_status launch_packed_attention(const AttnParams& p, int head_dim, int rows, hipStream_t stream);
+// a query block by one of the four kernels (query_attention.hip)
+apbv_status launch_query_attention(const AttnParams& p, int head_dim, QueryKernel kernel, hipStream_t stream);
 
 // Several attention problems (batch 1, one key range each, same head counts) in one launch.  The caller fills
 // item[] and n_items; the launcher fills the schedule.

@@ -182,20 +182,26 @@ apbv_status apbv_query_attention(int batch, int n_q_heads, int n_kv_heads, int h
                                         v_pass, k_local, v_local, softmax_scale, out, lse_out, p);
   if (st != APBV_OK) return st;
   if (n_splits < 0) return APBV_ERR_SHAPE;
-  KeySplit ks;
+  const QueryBlock block{batch, n_q_heads, n_kv_heads, head_dim, p.L, p.s_kv};
+  QueryPlan plan;
   if (n_splits > 0) {
-    ks = plan_key_split(batch, n_q_heads, p.L, p.s_kv, n_splits);
+    plan = choose_query_plan(block, n_splits, n_splits);
+    if (plan.split.n_splits == 1) plan.kernel = QueryKernel::kPerHead;      // no split asked for: apbv_host_attention
   } else {
-    // the library's choice, or as many ranges as the workspace holds down to the least it accepts
-    ks = choose_key_split(batch, n_q_heads, n_kv_heads, p.L, p.s_kv);
+    // the library's choice among as many ranges as the workspace holds, which are not fewer than the least it accepts
     const KeySplit least = per_head_key_split(batch, n_q_heads, p.L, p.s_kv);
     const size_t usable = workspace == nullptr || !aligned(workspace, 256) ? 0 : workspace_bytes;
     const size_t fits = usable / key_range_bytes(batch, n_q_heads, head_dim, p.L);
     if (least.n_splits > 1 && fits < (size_t)least.n_splits) return APBV_ERR_WORKSPACE;
-    if (fits < (size_t)ks.n_splits) ks = key_split_of((int64_t)fits, key_tiles(p.s_kv));
+    const int64_t most = plan_key_split(batch, n_q_heads, p.L, p.s_kv, 0).n_splits;
+    if (p.L > kQueryMaxTokens)
+      plan = {QueryKernel::kPerHead, least};
+    else
+      plan = choose_query_plan(block, 0, fits < (size_t)most ? (fits > 1 ? (int64_t)fits : 1) : most);
   }
+  const KeySplit ks = plan.split;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (ks.n_splits == 1) return launch_host_attention(p, head_dim, stream);
+  if (ks.n_splits == 1) return launch_query_attention(p, head_dim, plan.kernel, stream);
 
   const size_t need = (size_t)ks.n_splits * key_range_bytes(batch, n_q_heads, head_dim, p.L);
   if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < need) return APBV_ERR_WORKSPACE;
@@ -212,7 +218,7 @@ apbv_status apbv_query_attention(int batch, int n_q_heads, int n_kv_heads, int h
   ps.tiles_per_split = ks.tiles_per_split;
   ps.split_stride_out = (int64_t)(part_out_bytes / sizeof(bf16_t));
   ps.split_stride_lse = (int64_t)(part_lse_bytes / sizeof(float));
-  const apbv_status sl = launch_query_attention(ps, head_dim, stream);
+  const apbv_status sl = launch_query_attention(ps, head_dim, plan.kernel, stream);
   if (sl != APBV_OK) return sl;
 
   MergeParams m;

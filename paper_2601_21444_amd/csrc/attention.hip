@@ -631,12 +631,10 @@ static apbv_status launch_packed_variant(const AttnParams& p, int head_dim, hipS
   return launch.status();
 }
 
-// The rows of a KV group's heads together, in 128-row workgroups for short blocks (two fit a compute unit, and fewer of
-// the rows are padding), 256-row ones above.
-apbv_status launch_packed_attention(const AttnParams& p, int head_dim, hipStream_t stream) {
+// The rows of a KV group's heads together, in workgroups of 128 or 256.
+apbv_status launch_packed_attention(const AttnParams& p, int head_dim, int rows, hipStream_t stream) {
   static_assert(kQueryShortRows == 32 * kWavesShort, "the tile size the host-side planning assumes");
-  if (p.L <= kQueryShortTokens) return launch_packed_variant<kWavesShort>(p, head_dim, stream);
-  return launch_packed_variant<kWaves>(p, head_dim, stream);
+  return rows == kBM ? launch_packed_variant<kWaves>(p, head_dim, stream) : launch_packed_variant<kWavesShort>(p, head_dim, stream);
 }
 
 template <int W>

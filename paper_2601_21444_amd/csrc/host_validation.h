@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 #include <cmath>
+#include <initializer_list>
 #include "apbv.h"
 
 namespace apbv {
@@ -15,8 +16,8 @@ constexpr int kAttnKeyTile = 64;            // keys per tile of the attention ke
 constexpr int kAttnQueryTile = 256;         // query rows per workgroup
 constexpr int kAttnNarrowQueryTile = 64;    // ... of the variant used for query blocks of at most
 constexpr int kAttnNarrowMaxRows = 128;     // this many rows
-constexpr int kQueryMaxTokens = 2048;       // query blocks whose key-split launch packs the heads of a KV group into its rows
-constexpr int kQueryShortTokens = 128;      // ... in tiles of kQueryShortRows rows up to here, of kAttnQueryTile above
+constexpr int kQueryMaxTokens = 2048;       // query blocks whose launch may pack the heads of a KV group into its rows
+constexpr int kQueryShortTokens = 128;      // ... sized for tiles of kQueryShortRows rows up to here, of kAttnQueryTile above
 constexpr int kQueryShortRows = 128;
 constexpr int kQueryWaveRows = 32;          // rows per KV head a single wave takes (the waves then split the keys)
 
@@ -247,8 +248,8 @@ inline KeySplit key_split_of(int64_t s, int64_t n_tiles) {
 inline int64_t key_tiles(int64_t n_keys) { return (n_keys + kAttnKeyTile - 1) / kAttnKeyTile; }
 
 // With one tile of query rows per query head: about two workgroups per compute unit, ranges of at least four tiles.
-// Blocks longer than kQueryMaxTokens are split like this; for shorter ones it is the fewest ranges the library's own
-// choice may be cut down to when the workspace holds no more.
+// Blocks longer than kQueryMaxTokens are split like this; a call with a shorter one is refused if its workspace does not
+// hold the ranges of this split.
 inline KeySplit per_head_key_split(int batch, int n_q_heads, int64_t n_q, int64_t n_keys) {
   const int64_t tile = n_q <= kAttnNarrowMaxRows ? kAttnNarrowQueryTile : kAttnQueryTile;
   const int64_t n_wg = (n_q + tile - 1) / tile * n_q_heads * batch;
@@ -257,7 +258,7 @@ inline KeySplit per_head_key_split(int batch, int n_q_heads, int64_t n_q, int64_
   return key_split_of(s < cap ? s : cap, key_tiles(n_keys));
 }
 
-// The split a workspace is sized for: as requested, or (0) the most ranges choose_key_split() takes whatever the
+// The split a workspace is sized for: as requested, or (0) the most ranges choose_query_plan() takes whatever the
 // number of KV heads, which the size query is not told.
 inline KeySplit plan_key_split(int batch, int n_q_heads, int64_t n_q, int64_t n_keys, int requested) {
   if (requested > 0) return key_split_of(requested, key_tiles(n_keys));
@@ -269,32 +270,94 @@ inline KeySplit plan_key_split(int batch, int n_q_heads, int64_t n_q, int64_t n_
   return key_split_of(s < cap ? s : cap, key_tiles(n_keys));
 }
 
-// The library's own choice for a block of at most kQueryMaxTokens queries, whose rows are packed per KV head.  For
-// these kernels' purposes one workgroup per compute unit runs at a time (a second one shares the matrix pipe or the
-// memory bandwidth), and the row tiles of a range run on one XCD of 32 compute units; a workgroup costs as much as kRangeOverhead key tiles before and after its keys (launch, cold
-// instruction cache, first loads, epilogue), and every range adds its partial results to the merge.  In units of one
-// 64-key tile (about 1 us): 64 queries of 16 / 2 heads over 16512 keys read 29.5 us at 16 ranges, 25.5 at 32, 27.8 at
-// 64, 35.5 at 128; one query over 131072 keys 52.5 us at 32, 28.6 at 128, 29.7 at 256.
-constexpr int kRangeOverhead = 8;
-inline KeySplit choose_key_split(int batch, int n_q_heads, int n_kv_heads, int64_t n_q, int64_t n_keys) {
-  const KeySplit most = plan_key_split(batch, n_q_heads, n_q, n_keys, 0);
-  if (n_q > kQueryMaxTokens) return most;
-  const int64_t rows = n_q * (n_q_heads / n_kv_heads);
-  const int64_t tile = n_q <= kQueryShortTokens ? kQueryShortRows : kAttnQueryTile;
-  const int64_t row_tiles = (rows + tile - 1) / tile, heads = (int64_t)n_kv_heads * batch;
-  const int64_t n_tiles = key_tiles(n_keys);
-  const double merge = (double)(rows * heads) / 5000.0;
-  double best = 0.0;
-  int64_t best_s = 1;
-  for (int64_t s = 1; s <= most.n_splits; ++s) {
-    const int64_t rounds = ((heads * s + 7) / 8 * row_tiles + 31) / 32;
-    const double cost = (double)(rounds * ((n_tiles + s - 1) / s + kRangeOverhead)) + (s > 1 ? 4.0 + merge * (double)s : 0.0);
-    if (s == 1 || cost < best) {
-      best = cost;
-      best_s = s;
+// ---- kernel and ranges of a block of at most kQueryMaxTokens queries, from the time each would take.  There are four:
+// a workgroup per query head (attention.hip's own launch), workgroups of 128 or 256 rows packed per KV head, and a wave per
+// range for at most kQueryWaveRows packed rows.  Which is fastest turns on how many heads share K/V, how many workgroups
+// there are and how many keys each has (us: per query head / packed 128 / wave):
+//   120 decoding steps, 16 / 2 heads of 128, 1402 keys, one range      123 / 31.8 / 34.8
+//   5 steps, 28 / 4 heads of 128, 17629 keys, 16 ranges                120 / 41.0 / 36.6
+//   32 blocks of 7 queries, 16 / 16 heads of 64, 2194 keys, one range  47.9 / 50.1 / 54.4
+//   126 blocks of 78, 2 / 1 heads of 64, 26528 keys, one range         482 / 358, four 348 / 266 (two of a workgroup per head 289)
+//   603 queries, 16 / 1 heads of 128, 20814 keys, six ranges           115 / 161 (six ranges fill six XCDs of eight)
+enum class QueryKernel { kPerHead, kPacked128, kPacked256, kWave };
+struct QueryPlan {
+  QueryKernel kernel;
+  KeySplit split;
+};
+// Times in us, fitted to 18000 launches of 800 shapes (1 to 2048 queries, batches to 128, 64 to 200000 keys; within 9 %).
+// A workgroup with k keys takes alone + alone_per_key * k on a unit of its own, and every further one on the busiest unit
+// adds more + more_per_key * k, whether it runs beside the others or after them.
+struct QueryCost {
+  double alone, alone_per_key, more, more_per_key;
+};
+inline QueryCost query_cost(QueryKernel kernel, int head_dim, int per_head_rows) {
+  const bool wide = head_dim == 128;
+  switch (kernel) {
+    case QueryKernel::kWave: return wide ? QueryCost{7.4, 0.0103, 2.4, 0.0052} : QueryCost{6.0, 0.0029, 1.7, 0.0028};
+    case QueryKernel::kPacked256: return wide ? QueryCost{9.2, 0.0225, 2.4, 0.0258} : QueryCost{6.6, 0.0175, 1.9, 0.0187};
+    case QueryKernel::kPerHead:
+      if (per_head_rows == 256) return query_cost(QueryKernel::kPacked256, head_dim, 0);
+      if (per_head_rows == 64) return wide ? QueryCost{5.7, 0.0168, 1.5, 0.0084} : QueryCost{4.7, 0.0111, 0.7, 0.0045};
+      break;
+    case QueryKernel::kPacked128: break;
+  }
+  return wide ? QueryCost{5.4, 0.0164, 1.3, 0.0116} : QueryCost{4.8, 0.0114, 0.9, 0.0064};
+}
+struct QueryBlock {
+  int batch, n_q_heads, n_kv_heads, head_dim;
+  int64_t n_q, n_keys;
+};
+inline bool query_kernel_takes(QueryKernel kernel, const QueryBlock& q) {
+  const int64_t rows = q.n_q * (q.n_q_heads / q.n_kv_heads);
+  if (kernel == QueryKernel::kPerHead) return true;
+  if (q.n_q > kQueryMaxTokens) return false;
+  return kernel == QueryKernel::kWave ? rows <= kQueryWaveRows : kernel == QueryKernel::kPacked128 || rows > kAttnQueryTile;
+}
+inline double query_estimate(QueryKernel kernel, const QueryBlock& q, const KeySplit& ks) {
+  const int64_t rows = q.n_q * (q.n_q_heads / q.n_kv_heads), n_tiles = key_tiles(q.n_keys);
+  const int group = q.n_q_heads / q.n_kv_heads;
+  // Workgroups in whole rounds of eight XCDs: the row tiles of a range run on one of them, of a workgroup per query head
+  // those of a KV head's group.
+  int tile = kernel == QueryKernel::kPacked256 ? kAttnQueryTile : kQueryShortRows;
+  if (kernel == QueryKernel::kPerHead)
+    tile = q.n_q <= kAttnNarrowMaxRows ? kAttnNarrowQueryTile : attention_rows(q.head_dim, group, q.batch, q.n_q_heads, q.n_q, q.n_keys, false, ks.n_splits);
+  const int64_t ranges = (int64_t)q.n_kv_heads * q.batch * ks.n_splits, tiles = ((kernel == QueryKernel::kPerHead ? q.n_q : rows) + tile - 1) / tile;
+  const double n = kernel == QueryKernel::kPerHead ? (double)((ranges * tiles + 7) / 8 * 8 * group) : (double)((ranges + 7) / 8 * 8 * tiles);
+  const QueryCost c = query_cost(kernel, q.head_dim, tile);
+  const double keys = (double)ks.tiles_per_split * kAttnKeyTile, more = std::ceil(n / 256) - 1;
+  const double compute = c.alone + c.alone_per_key * keys + more * (c.more + c.more_per_key * keys);
+  // K and V at 5.5 TB/s, a little less with few waves to keep it busy; once, but by workgroups per head once per row tile if
+  // the 256 MB cache does not hold them.  A smooth maximum of the two.
+  const double kv = (double)q.batch * q.n_kv_heads * (double)n_tiles * kAttnKeyTile * q.head_dim * 4;
+  const double reads = kernel == QueryKernel::kWave ? 1 + 6.5 / n : kernel == QueryKernel::kPerHead && kv > 256e6 ? (double)tiles : 1;
+  const double memory = reads * kv / 5.5e6;
+  const double both = compute * compute * compute * compute + memory * memory * memory * memory;
+  const double parts = (double)ks.n_splits * q.batch * (double)q.n_q * q.n_q_heads * q.head_dim * 2;
+  return std::sqrt(std::sqrt(both)) + (ks.n_splits > 1 ? 1.84 + parts * 0.6e-6 + 0.3 / 64 * ks.n_splits : 0);
+}
+// The fastest kernel and, unless `requested` ranges are asked for (>= 1), number of ranges up to most_splits.  As the
+// estimates are good to 9 %, a workgroup per query head with its own split stays unless another plan promises 5 %, or with
+// the ranges requested 10 %.  Of 1900 calls outside the fit 11 were 2 to 17 % slower than with a workgroup per head, its own
+// split or the ranges requested; the mean was 0.67 of its time.
+inline QueryPlan choose_query_plan(const QueryBlock& q, int requested, int64_t most_splits) {
+  const int64_t n_tiles = key_tiles(q.n_keys);
+  const KeySplit own = per_head_key_split(q.batch, q.n_q_heads, q.n_q, q.n_keys);
+  QueryPlan best{QueryKernel::kPerHead, requested > 0 ? key_split_of(requested, n_tiles) : own.n_splits <= most_splits ? own : key_split_of(1, n_tiles)};
+  double least = (requested > 0 ? 0.9 : 0.95) * query_estimate(best.kernel, q, best.split);
+  for (QueryKernel kernel : {QueryKernel::kPerHead, QueryKernel::kPacked128, QueryKernel::kPacked256, QueryKernel::kWave}) {
+    if (!query_kernel_takes(kernel, q)) continue;
+    for (int64_t s = requested > 0 ? requested : 1;; s += s / 8 + 1) {       // (every count up to 8, then steps of about an eighth)
+      if (requested <= 0 && s > most_splits) s = most_splits;
+      const KeySplit ks = key_split_of(s, n_tiles);
+      const double t = query_estimate(kernel, q, ks) * (kernel == QueryKernel::kPerHead ? 0.98 : 1.0);
+      if (t < least) {
+        least = t;
+        best = {kernel, ks};
+      }
+      if (requested > 0 || s >= most_splits) break;
     }
   }
-  return key_split_of(best_s, n_tiles);
+  return best;
 }
 
 // Workspace of one key range: its bf16 partial output and float32 log-sum-exps.

@@ -358,9 +358,13 @@ apbv_status launch_query_rows(const AttnParams& p, hipStream_t stream) {
 
 }  // namespace
 
-apbv_status launch_query_attention(const AttnParams& p, int head_dim, hipStream_t stream) {
-  if (p.L > kQueryMaxTokens) return launch_host_attention(p, head_dim, stream);
-  if (p.L * p.group > kQueryWaveRows) return launch_packed_attention(p, head_dim, stream);
+apbv_status launch_query_attention(const AttnParams& p, int head_dim, QueryKernel kernel, hipStream_t stream) {
+  switch (kernel) {
+    case QueryKernel::kPerHead: return launch_host_attention(p, head_dim, stream);
+    case QueryKernel::kPacked128: return launch_packed_attention(p, head_dim, kQueryShortRows, stream);
+    case QueryKernel::kPacked256: return launch_packed_attention(p, head_dim, kAttnQueryTile, stream);
+    case QueryKernel::kWave: break;
+  }
   if (head_dim == 128) return launch_query_rows<128>(p, stream);
   if (head_dim == 64) return launch_query_rows<64>(p, stream);
   return APBV_ERR_UNSUPPORTED;

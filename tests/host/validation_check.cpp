@@ -148,6 +148,60 @@ int main() {
         const size_t ws = query_attention_workspace_bytes(1, 16, 128, n_q, n_keys, req);
         EXPECT(ws % 256 == 0 && (ks.n_splits == 1) == (ws == 0));
       }
+  // the query block's kernel and ranges: what was requested, or at most what the workspace is sized for and holds; every
+  // tile covered; a kernel only where it can run
+  for (int d : {64, 128})
+    for (int hq : {1, 2, 16, 28, 65535})
+      for (int g : {1, 2, 4, 7, 16, 65535})
+        for (int batch : {1, 5, 130, 65535})
+          for (int64_t n_q : {1, 2, 17, 128, 129, 700, 2048, 2049, 1 << 24})
+            for (int64_t n_keys : {1, 64, 500, 9000, 131072, 3 << 24}) {
+              if (hq % g) continue;
+              const QueryBlock q{batch, hq, hq / g, d, n_q, n_keys};
+              const int most = plan_key_split(batch, hq, n_q, n_keys, 0).n_splits;
+              for (int req : {0, 1, 3, 40, 1000})
+                for (int fits : {1, 2, 11, most}) {
+                  if (fits > most || (req > 0 && fits > 1)) continue;
+                  const QueryPlan plan = choose_query_plan(q, req, fits);
+                  const KeySplit ks = plan.split, asked = key_split_of(req, key_tiles(n_keys));
+                  EXPECT(query_kernel_takes(plan.kernel, q) && (plan.kernel == QueryKernel::kPerHead || n_q <= kQueryMaxTokens));
+                  EXPECT(plan.kernel != QueryKernel::kWave || n_q * g <= kQueryWaveRows);
+                  EXPECT(req == 0 ? ks.n_splits <= fits : ks.n_splits == asked.n_splits && ks.tiles_per_split == asked.tiles_per_split);
+                  EXPECT(ks.n_splits >= 1 && (int64_t)ks.n_splits * ks.tiles_per_split >= key_tiles(n_keys));
+                  EXPECT((int64_t)(ks.n_splits - 1) * ks.tiles_per_split < key_tiles(n_keys));
+                }
+            }
+  // the launches of tests/test_gpu_packed_query.py
+  struct { QueryKernel kernel; int ranges; QueryBlock q; int requested; } plans[] = {
+      {QueryKernel::kWave, 2, {1, 9, 1, 64, 2, 1007}, 2},          {QueryKernel::kWave, 1, {1, 16, 1, 64, 2, 449}, 0},
+      {QueryKernel::kWave, 3, {3, 16, 1, 64, 2, 5001}, 3},         {QueryKernel::kWave, 3, {4, 28, 4, 128, 4, 1344}, 3},
+      {QueryKernel::kWave, 1, {48, 28, 4, 128, 4, 1344}, 0},       {QueryKernel::kWave, 8, {24, 1, 1, 64, 1, 1500}, 0},
+      {QueryKernel::kWave, 21, {12, 32, 1, 128, 1, 9001}, 0},      {QueryKernel::kWave, 157, {1, 2, 1, 64, 1, 40001}, 0},
+      {QueryKernel::kPacked128, 1, {48, 8, 1, 128, 2, 64}, 0},     {QueryKernel::kPacked128, 3, {16, 7, 1, 128, 1, 134}, 3},
+      {QueryKernel::kPacked128, 2, {12, 11, 1, 128, 3, 320}, 2},   {QueryKernel::kPacked128, 4, {6, 16, 1, 128, 8, 908}, 4},
+      {QueryKernel::kPacked128, 6, {3, 4, 4, 128, 5, 712}, 0},     {QueryKernel::kPacked128, 3, {8, 6, 2, 128, 129, 469}, 3},
+      {QueryKernel::kPacked128, 3, {8, 8, 1, 64, 300, 640}, 3},    {QueryKernel::kPacked128, 1, {24, 16, 1, 64, 129, 329}, 0},
+      {QueryKernel::kPacked256, 3, {6, 16, 1, 128, 129, 2000}, 3}, {QueryKernel::kPacked256, 1, {40, 7, 1, 128, 150, 700}, 0},
+      {QueryKernel::kPacked256, 3, {8, 8, 1, 64, 257, 12000}, 3},
+      {QueryKernel::kPerHead, 6, {2, 2, 1, 64, 2049, 2249}, 7},    {QueryKernel::kPerHead, 2, {1, 8, 2, 128, 2100, 1000}, 2},
+      {QueryKernel::kPerHead, 4, {1, 12, 2, 128, 2100, 3640}, 4},
+      // ... with peaked logits
+      {QueryKernel::kWave, 3, {1, 16, 1, 64, 1, 5000}, 3},         {QueryKernel::kWave, 2, {1, 9, 1, 64, 2, 1005}, 2},
+      {QueryKernel::kPacked128, 4, {6, 16, 1, 128, 8, 900}, 4},    {QueryKernel::kPacked128, 3, {8, 8, 1, 64, 300, 340}, 3}};
+  for (const auto& c : plans) {
+    const int most = plan_key_split(c.q.batch, c.q.n_q_heads, c.q.n_q, c.q.n_keys, 0).n_splits;
+    const QueryPlan plan = choose_query_plan(c.q, c.requested, c.requested > 0 ? c.requested : most);
+    EXPECT(plan.kernel == c.kernel && plan.split.n_splits == c.ranges);
+  }
+  EXPECT(attention_rows(128, 4, 1, 8, 2100, 1000, false, 2) == 256 && attention_rows(128, 6, 1, 12, 2100, 1540, true, 4) == 256);
+  {  // measured shapes: one range goes through the packed kernels too, and a workgroup per head stays where it is faster
+    const QueryPlan steps = choose_query_plan({120, 16, 2, 128, 1, 1402}, 0, 4), ragged = choose_query_plan({126, 2, 1, 64, 78, 26528}, 0, 4);
+    EXPECT(steps.kernel != QueryKernel::kPerHead && ragged.kernel == QueryKernel::kPacked128 && ragged.split.n_splits > 1);
+    EXPECT(choose_query_plan({1, 16, 1, 128, 603, 20814}, 6, 6).kernel == QueryKernel::kPerHead);
+    const QueryPlan decode = choose_query_plan({1, 16, 2, 128, 1, 133121}, 0, 256), block = choose_query_plan({1, 16, 2, 128, 64, 16512}, 0, 64);
+    EXPECT(decode.kernel == QueryKernel::kWave && decode.split.n_splits >= 64);
+    EXPECT(block.kernel == QueryKernel::kPacked128 && block.split.n_splits >= 16);
+  }
   for (int64_t L = 1; L <= ((int64_t)1 << 24); L = L * 5 + 3)
     for (int64_t l_p = 0; l_p <= L; l_p = l_p * 7 + 1) {
       const CompressWorkspace w1 = plan_compress_workspace(1, 2, 128, L, l_p), w3 = plan_compress_workspace(3, 2, 128, L, l_p);

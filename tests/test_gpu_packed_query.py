@@ -32,9 +32,9 @@ def check(out_gpu, ref, what, max_abs=2e-2, mean_rel=5e-3):
     assert diff.max() <= max_abs and diff.mean() / np.abs(ref).mean() <= mean_rel
 
 
-# Rows of a KV group packed together, at the edges of their row tiles
-# (16, 32, 128, 256 rows; 128 and 2048 tokens), of the ranges' tiles (1 to 4 tiles a wave, odd counts, a last key alone)
-# and with a causal segment whose queries share a tile with others
+# Rows of a KV group packed together, at the edges of their row tiles (16, 32, 128, 256 rows; 128 and 2048 tokens), of the
+# ranges' tiles and with a causal segment whose queries share a tile with others.  Small as they are, most run in a
+# workgroup per query head; the same edges in the other kernels follow below.
 PACKED_CASES = [
     # hq, hkv, d, batch, n_q, l_a, n_c, local, n_splits
     (8, 1, 128, 1, 2, 0, 64, False, 2),            # 16 rows exactly; a range of one 64-key tile each
@@ -73,6 +73,87 @@ def test_packed_query_blocks(hq, hkv, d, batch, n_q, l_a, n_c, local, n_splits):
         np.testing.assert_allclose(lse[b].cpu().numpy().astype(np.float64), lse_r, atol=2e-3, rtol=0)
     if whole is not None:
         assert torch.isnan(whole[:, 0]).all() and torch.isnan(whole[:, -1]).all()
+
+
+# The same through the kernel named: batches of two items in turn, large enough that the plan takes it (held to it by
+# tests/host/validation_check.cpp).  One range writes the output itself, more go through the merge.
+KERNEL_CASES = [
+    # kernel, ranges, hq, hkv, d, batch, n_q, l_a, n_c, local, n_splits
+    ("wave", 2, 9, 1, 64, 1, 2, 5, 1000, True, 2),              # 18 rows: the second block of 16 two rows long
+    ("wave", 1, 16, 1, 64, 1, 2, 0, 449, False, 0),             # 32 rows exactly; a last key alone
+    ("wave", 3, 16, 1, 64, 3, 2, 0, 4999, True, 3),             # many tiles a wave, causal
+    ("wave", 3, 28, 4, 128, 4, 4, 0, 1344, False, 3),           # 28 rows; 7 64-key tiles a range: odd tile counts per wave
+    ("wave", 1, 28, 4, 128, 48, 4, 0, 1344, False, 0),
+    ("wave", 8, 1, 1, 64, 24, 1, 0, 1500, False, 0),            # one row
+    ("wave", 21, 32, 1, 128, 12, 1, 10, 8990, True, 0),
+    ("wave", 157, 2, 1, 64, 1, 1, 33, 39968, False, 0),         # more ranges than a lane of the merge holds; last key alone
+    ("packed128", 1, 8, 1, 128, 48, 2, 0, 64, False, 0),        # 16 rows of 128
+    ("packed128", 3, 7, 1, 128, 16, 1, 33, 100, True, 3),       # 7 rows; segments that meet inside a tile
+    ("packed128", 2, 11, 1, 128, 12, 3, 17, 300, True, 2),      # 33 rows
+    ("packed128", 4, 16, 1, 128, 6, 8, 0, 900, True, 4),        # 128 rows exactly
+    ("packed128", 6, 4, 4, 128, 3, 5, 7, 700, True, 0),         # no group
+    ("packed128", 3, 6, 2, 128, 8, 129, 40, 300, True, 3),      # 387 rows: four tiles
+    ("packed128", 3, 8, 1, 64, 8, 300, 40, 300, True, 3),
+    ("packed128", 1, 16, 1, 64, 24, 129, 0, 200, True, 0),
+    ("packed256", 3, 16, 1, 128, 6, 129, 0, 2000, False, 3),    # 2064 rows: a ninth tile of 16
+    ("packed256", 1, 7, 1, 128, 40, 150, 0, 700, False, 0),     # 1050 rows: a fifth tile of 26
+    ("packed256", 3, 8, 1, 64, 8, 257, 0, 12000, False, 3),
+    ("per_head", 6, 2, 1, 64, 2, 2049, 0, 200, True, 7),        # one query more than the largest packed block
+    ("per_head", 2, 8, 2, 128, 1, 2100, 0, 1000, False, 2),     # ... in 256-row workgroups
+    ("per_head", 4, 12, 2, 128, 1, 2100, 0, 1540, True, 4),
+]
+
+
+@pytest.mark.parametrize("kernel,ranges,hq,hkv,d,batch,n_q,l_a,n_c,local,n_splits", KERNEL_CASES)
+def test_every_kernel_of_the_query_block(kernel, ranges, hq, hkv, d, batch, n_q, l_a, n_c, local, n_splits):
+    rng = np.random.default_rng((79, hq, n_q, n_c))
+    n_l, distinct = n_q if local else 0, min(batch, 2)
+    host = [rand_bits(rng, (distinct, n, h, d)) for n, h in ((n_q, hq), (l_a, hkv), (l_a, hkv), (n_c, hkv), (n_c, hkv), (n_l, hkv), (n_l, hkv))]
+    pick = np.arange(batch) % distinct
+    scale = 1.0 / math.sqrt(d)
+    print(f"{kernel} x {ranges} hq={hq} hkv={hkv} d={d} batch={batch} n_q={n_q} keys={l_a}+{n_c}+{n_l} splits={n_splits}", flush=True)
+    whole = torch.full((batch * n_q + 2, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")       # a canary row on both sides
+    out, lse = apbv.apbv_query_attention(*[dev(x[pick]) for x in host], scale, n_splits=n_splits, return_lse=True,
+                                         out=whole[1:-1].view(batch, n_q, hq, d))
+    torch.cuda.synchronize()
+    assert torch.isnan(whole[0]).all() and torch.isnan(whole[-1]).all()
+    rows = np.unique(np.concatenate([np.arange(min(n_q, 40)), np.arange(max(0, n_q - 40), n_q), rng.integers(0, n_q, 100)]))
+    for i in range(distinct):
+        ref, lse_r = oracle.host_attention(*[x[i] for x in host], scale, rows=rows)
+        items = np.flatnonzero(pick == i)
+        check(to_f64(out[items[0]])[rows], ref, f"item {i}")
+        np.testing.assert_allclose(lse[items[0]].cpu().numpy().astype(np.float64)[:, rows], lse_r, atol=2e-3, rtol=0)
+        for b in items[1:]:
+            assert torch.equal(out[b].view(torch.int16), out[items[0]].view(torch.int16)) and torch.equal(lse[b], lse[items[0]])
+
+
+# Keys whose norms grow or fall along the axis and large logits: the reference maximum moves in most tiles, and waves and
+# ranges end with maxima far apart
+@pytest.mark.parametrize("gain", [8.0, 40.0])
+@pytest.mark.parametrize("order", ["ascending", "descending"])
+@pytest.mark.parametrize("hq,hkv,d,batch,n_q,n_c,n_splits", [(16, 1, 64, 1, 1, 5000, 3), (9, 1, 64, 1, 2, 1005, 2), (28, 4, 128, 4, 4, 1344, 3),
+                                                             (7, 1, 128, 24, 2, 1500, 0), (16, 1, 128, 6, 8, 900, 4), (8, 1, 64, 8, 300, 340, 3),
+                                                             (16, 1, 128, 6, 129, 2000, 3)])
+def test_peaked_logits_of_a_query_block(gain, order, hq, hkv, d, batch, n_q, n_c, n_splits):
+    rng = np.random.default_rng((80, hq, n_q, n_c))
+    ramp = np.linspace(0.05, 1.0, n_c, dtype=np.float32)[:: 1 if order == "ascending" else -1]
+    q, v = rand_bits(rng, (n_q, hq, d)), rand_bits(rng, (n_c, hkv, d))
+    k = wl.f32_to_bf16_bits(rng.standard_normal((n_c, hkv, d)).astype(np.float32) * ramp[:, None, None] * np.float32(gain))
+    e = np.empty((0, hkv, d), dtype=np.uint16)
+    scale = 1.0 / math.sqrt(d)
+    print(f"peaked query block gain={gain} {order} hq={hq} d={d} batch={batch} n_q={n_q} keys={n_c} splits={n_splits}", flush=True)
+    args = [dev(np.stack([x] * batch)) for x in (q, k, v, e, e, e, e)]
+    out, lse = apbv.apbv_query_attention(*args, scale, n_splits=n_splits, return_lse=True)
+    torch.cuda.synchronize()
+    ref, lse_r = oracle.host_attention(q, k, v, e, e, e, e, scale)
+    for b in (0, batch - 1):
+        got = to_f64(out[b])
+        assert np.all(np.isfinite(got))
+        diff = np.abs(got - ref)
+        # probabilities, partial results and the output rounded to bf16 (2^-9 each) of values up to 5; for the log-sum-exp
+        # the rounded probabilities (2^-9) and logits of up to 500 in float32
+        assert diff.max() <= 3 * 5 * 2.0 ** -9 and diff.mean() / np.abs(ref).mean() <= 5e-3
+        np.testing.assert_allclose(lse[b].cpu().numpy().astype(np.float64), lse_r, rtol=0, atol=5e-3)
 
 
 def test_query_attention_accepts_the_workspace_of_a_split_per_head():
