@@ -341,9 +341,7 @@ __global__ __launch_bounds__(256, 3) void matrix_reduce_kernel(const RowsParams 
 // instructions use.  Batch 16, 512 rows x 16384 keys x 2 heads: 86 -> 75 us (915 TFLOP/s); one item of 448 rows x 4
 // heads, the whole call: 49.1 -> 46.1 us.  With 64 rows (a fill per few tiles) it is no faster, and the maximum, whose
 // reduction is free, gains nothing (63 us either way): both stay with matrix_reduce_kernel.
-constexpr int kMinLdsProbe = 49152;       // bytes of probe rows: 192 rows of 128
-constexpr int kMaxLdsProbe = 131072;      // 512
-constexpr int kBlockKeys = 64;            // keys a wave holds at a time
+constexpr int kBlockKeys = kMassBlockKeys;     // keys a wave holds at a time
 
 template <int N, typename F, int... I>
 __device__ __forceinline__ void unrolled_impl(F&& f, std::integer_sequence<int, I...>) {
@@ -560,32 +558,19 @@ void launch_probe_resident(Launcher& launch, const RowsParams& p, int batch, int
 
 template <int D>
 void launch_mass(Launcher& launch, const RowsParams& p, int batch) {
-  const int64_t probe_bytes = (int64_t)p.r_pad * D * 2;
-  if (probe_bytes < kMinLdsProbe || probe_bytes > kMaxLdsProbe) {
+  const MassPlan plan = plan_mass(D, p.r_pad, p.L, (int64_t)p.hkv * batch);
+  if (plan.waves == 4)
+    launch_probe_resident<D, 4>(launch, p, batch, plan.n_blocks);
+  else if (plan.waves == 8)
+    launch_probe_resident<D, 8>(launch, p, batch, plan.n_blocks);
+  else
     launch(matrix_reduce_kernel<D, kMass>, dim3((unsigned)((p.L + kResident - 1) / kResident), p.hkv, batch), dim3(256), (size_t)p.r_pad * sizeof(float), p);
-    return;
-  }
-  // Eight waves a workgroup, and as many blocks a wave as fill the rounds of the 256 compute units best; four waves if
-  // even single blocks leave half of them idle.
-  const int64_t blocks = (p.L + kBlockKeys - 1) / kBlockKeys;
-  const int64_t heads = (int64_t)p.hkv * batch;
-  if (heads * ((blocks + 7) / 8) <= 128) return launch_probe_resident<D, 4>(launch, p, batch, 1);
-  int best = 1;
-  int64_t best_cost = 0;
-  for (int n = 1; n <= 8; ++n) {
-    const int64_t cost = (heads * ((blocks + 8 * n - 1) / (8 * n)) + 255) / 256 * (4 * n + 1);   // a fill costs a quarter of a block
-    if (n == 1 || cost < best_cost) {
-      best = n;
-      best_cost = cost;
-    }
-  }
-  launch_probe_resident<D, 8>(launch, p, batch, best);
 }
 
 template <int D, int W>
 bool allow_lds() {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&probe_resident_kernel<D, W>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             kMaxLdsProbe / (D * 2) * (D * 2 + (int)sizeof(float))) == hipSuccess;
+                             kMassMaxProbeBytes / (D * 2) * (D * 2 + (int)sizeof(float))) == hipSuccess;
 }
 
 }  // namespace

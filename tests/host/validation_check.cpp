@@ -210,6 +210,20 @@ int main() {
       EXPECT(w1.n_sort >= l_p && (w1.n_sort & (w1.n_sort - 1)) == 0 && w3.total >= w1.total);
       EXPECT(compress_workspace_bytes_checked(1, 2, 128, L, l_p) == w1.total);
     }
+  // attention-mass pass: resident only where the probe rows fit, with blocks for every key; measured shapes on both sides
+  for (int d : {64, 128})
+    for (int r_pad = 32; r_pad <= 2048; r_pad += 32)
+      for (int64_t L = 1; L <= ((int64_t)1 << 24); L = L * 3 + 1)
+        for (int64_t heads : {1, 7, 192, 65535 * 16}) {
+          const MassPlan m = plan_mass(d, r_pad, L, heads);
+          EXPECT(m.waves == 0 || ((m.waves == 4 || m.waves == 8) && m.n_blocks >= 1 && m.n_blocks <= 8));
+          EXPECT(m.waves == 0 || (r_pad * d * 2 >= kMassMinProbeBytes && r_pad * d * 2 <= kMassMaxProbeBytes));
+        }
+  EXPECT(plan_mass(64, 576, 20 * 64, 100).waves == 0 && plan_mass(128, 256, 1575, 192).waves == 0 && plan_mass(128, 512, 1266, 126).waves == 0);
+  // ... and those of tests/test_gpu_mass_shapes.py
+  EXPECT(plan_mass(128, 512, 63, 1).waves == 4 && plan_mass(128, 512, 65, 1).waves == 4 && plan_mass(128, 192, 70001, 1).waves == 8);
+  EXPECT(plan_mass(64, 384, 70001, 1).waves != 0 && plan_mass(64, 1024, 129, 1).waves == 4 && plan_mass(128, 512, 9000, 34).n_blocks == 3);
+  EXPECT(plan_mass(128, 512, 16384, 32).waves == 8 && plan_mass(128, 448, 16384, 4).waves != 0);
   // pooled-query partition: about 64 probe rows per range, at most kPoolSplitMax, no more ranges than fill the chip
   // twice over; and the partial sums of every partition fit the region the workspace plan reserves for them
   EXPECT(pool_splits(512, 2) == 8 && pool_splits(512, 192) == 2 && pool_splits(512, 1000) == 1 && pool_splits(10, 1) == 1);

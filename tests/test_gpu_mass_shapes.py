@@ -23,6 +23,14 @@ CASES = [
     (2, 2, 64, 384, 1, 257),        # rows of 64
     (1, 1, 64, 1024, 1, 129),
     (8, 2, 128, 64, 9, 16500),      # blocks that leave the last round of workgroups ragged
+    # (192 rows and few keys are streamed all the same, plan_mass; the same edges where the rows are resident)
+    (2, 1, 128, 256, 1, 63),        # 512 rows, less than one block of keys
+    (2, 1, 128, 256, 1, 64),        # one block
+    (1, 1, 128, 161, 1, 70001),     # 192 rows with padding, 1094 blocks
+    (1, 1, 128, 192, 1, 70001),     # 192 rows
+    (1, 1, 64, 384, 1, 70001),      # 384 rows of 64
+    (16, 2, 128, 64, 17, 9000),     # three blocks a wave, a last round of workgroups that is ragged
+    (4, 4, 64, 576, 25, 1280),      # and rows that would fit streamed: rounds that do not fill
 ]
 
 
