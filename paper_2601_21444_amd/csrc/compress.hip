@@ -282,6 +282,17 @@ __device__ __forceinline__ uint32_t block_scan_incl(uint32_t x, SelectShared& sh
   if (!kFresh) __syncthreads();         // wave_tot may still be read from a previous use
   if (lane == 63) sh.wave_tot[wave] = incl;
   __syncthreads();
+  if (!kFresh) {                        // (in the exact path; the scan below costs it 0.2 to 0.9 us of 20 to 50)
+    uint32_t base = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < kSelectThreads / 64; ++w) {
+      const uint32_t t = sh.wave_tot[w];
+      if (w < wave) base += t;
+      tot += t;
+    }
+    *total = tot;
+    return incl + base;
+  }
   // every wave scans the 16 totals itself, one a lane
   constexpr int kSelectWaves = kSelectThreads / 64;
   const uint32_t scan = wave_scan_incl(lane < kSelectWaves ? sh.wave_tot[lane] : 0u);
@@ -372,8 +383,10 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
   }
   if (tid == 0) {
     sh.crowded = 0;
-    sh.b_lo = kBins;
-    sh.b_hi = -1;
+    if (kParts) {
+      sh.b_lo = kBins;
+      sh.b_hi = -1;
+    }
   }
   __syncthreads();
   lo = wave_min(sh.red_lo[lane % (kSelectThreads / 64)]);     // (16 waves' values, one a lane: a loop over them costs 0.6 us)
