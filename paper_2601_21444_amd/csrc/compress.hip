@@ -217,8 +217,7 @@ __device__ __forceinline__ bool precedes(uint64_t ka, uint32_t ia, uint64_t kb, 
 
 constexpr int kBins = 2048;                    // value buckets of the fast selection path
 
-constexpr int kResidentScores = 16 * kSelectThreads;     // scores a selection keeps in registers
-constexpr uint32_t kMaxBinRank = 128;          // largest bucket the rank-by-comparison step accepts
+static_assert(kResidentScores == 16 * kSelectThreads, "sixteen scores a thread in registers");
 
 struct SelectShared {
   uint32_t hist[kBins];       // entries per bucket
@@ -683,7 +682,6 @@ __global__ __launch_bounds__(256) void gather_kernel(View k, View v, const int32
 // its share of the rows.  Two heads of 16384 scores and 1024 rows: 9.8 + 2.4 us and the gap between -> 10.5 us, of which
 // 2.4 load the scores, 3.6 are minimum and maximum, histogram and scan (issue-bound, repeated), 0.8 the copy.
 constexpr int kMaxSelectParts = 16;
-constexpr int kMaxSharedHeads = 8;
 static_assert(kLdsSortMax / kMaxSelectParts + 1 + (int64_t)kMaxBinRank <= kBins && 64 + (int64_t)kMaxBinRank <= kBins,
               "a part's share of the outputs and one bucket more fit sh.fill");
 
@@ -830,14 +828,10 @@ apbv_status launch_compress(const CompressParams& p_in, hipStream_t stream) {
     else
       launch(score_kernel<64>, grid, dim3(256), 0, p.k, p.L, qbar, n_split, scores, p.scores_out, p.hkv, rows_per_block);
   }
-  // A few heads' selection is shared by several workgroups each, in parts of at least 32 rows, and copies its rows too:
-  // one item of 2 heads x 16384 keys 18.5 -> 17.7 us (graph replay), of 4 heads 22.6 -> 21.9, 2 heads x 256 keys 13.5 ->
-  // 12.5; a launch less on the host as well.  With 16 heads it is even (32.6 and 32.9 us), with 32 slower (29.2 and 30.5),
-  // and beyond kResidentScores keys every workgroup would read the scores three times (8 x 4 heads x 30000: 72 and 86).
-  const int64_t heads = (int64_t)p.hkv * p.batch;
+  // (a few heads' selection is shared by several workgroups each, in parts of at least 32 rows, and copies its rows too)
   int64_t n_parts = p.l_p / 32 < kMaxSelectParts ? p.l_p / 32 : kMaxSelectParts;
   n_parts = n_parts > 1 ? n_parts : 1;
-  if (p.l_p > 0 && !w.sort_in_global && heads <= kMaxSharedHeads && p.L <= kResidentScores) {
+  if (share_selection((int64_t)p.hkv * p.batch, p.L, p.l_p, w)) {
     const dim3 grid((unsigned)n_parts, p.hkv, p.batch);
     const size_t dyn = (size_t)w.n_sort * 14;
     if (p.d == 128)

@@ -464,6 +464,20 @@ inline CompressWorkspace plan_compress_workspace(int batch, int hkv, int d, int6
   return w;
 }
 
+// Whether several workgroups share a head's selection and copy its rows in the same launch (compress.hip), or one selects
+// and another launch copies.  Shared: one item of 2 heads x 16384 keys, 1024 rows 18.0 -> 16.5 us (graph replay), 6000 rows
+// 29.8 -> 22.3, of 8 heads 41 -> 36; a launch less on the host as well.  Not with more heads (16 are even, 32.6 and 32.9 us,
+// 32 slower, 29.2 and 30.5), nor beyond kResidentScores keys, which every workgroup would read three times (8 x 4 heads x
+// 30000: 72 and 86); nor where most of a short block is selected (2000 of 2000 rows 14.9 and 15.7), nor without room for the
+// candidates beside the rows, where the bucket path gives up and all workgroups sort (8192 rows 158 and 164).
+constexpr int kResidentScores = 16384;         // scores a selection keeps in registers
+constexpr uint32_t kMaxBinRank = 128;          // largest bucket the bucket path accepts
+constexpr int kMaxSharedHeads = 8;
+inline bool share_selection(int64_t heads, int64_t L, int64_t l_p, const CompressWorkspace& w) {
+  return l_p > 0 && !w.sort_in_global && heads <= kMaxSharedHeads && L <= kResidentScores && (2 * l_p <= L || L > 4096) &&
+         (w.n_sort < kLdsSortMax || l_p + kMaxBinRank <= w.n_sort || L <= w.n_sort);
+}
+
 inline size_t compress_workspace_bytes_checked(int batch, int n_kv_heads, int head_dim, int64_t L, int64_t l_p) {
   if (batch < 1 || n_kv_heads < 1 || (head_dim != 64 && head_dim != 128) || L < 1 || L > kMaxTokens || l_p < 0 || l_p > L)
     return 0;

@@ -224,6 +224,11 @@ int main() {
   EXPECT(plan_mass(128, 512, 63, 1).waves == 4 && plan_mass(128, 512, 65, 1).waves == 4 && plan_mass(128, 192, 70001, 1).waves == 8);
   EXPECT(plan_mass(64, 384, 70001, 1).waves != 0 && plan_mass(64, 1024, 129, 1).waves == 4 && plan_mass(128, 512, 9000, 34).n_blocks == 3);
   EXPECT(plan_mass(128, 512, 16384, 32).waves == 8 && plan_mass(128, 448, 16384, 4).waves != 0);
+  // selection shared by several workgroups: few heads, resident scores, room for the candidates
+  auto shared = [](int heads, int64_t L, int64_t l_p) { return share_selection(heads, L, l_p, plan_compress_workspace(1, heads, 64, L, l_p)); };
+  EXPECT(shared(2, 16384, 1024) && shared(8, 16384, 6000) && shared(1, 16384, 8064) && shared(1, 8192, 8192) && shared(2, 700, 64));
+  EXPECT(!shared(9, 16384, 1024) && !shared(2, 16385, 1024) && !shared(2, 16384, 0) && !shared(1, 16384, 8193));
+  EXPECT(!shared(1, 16384, 8192) && !shared(2, 9000, 8100) && !shared(2, 2000, 2000) && !shared(1, 1, 1));
   // pooled-query partition: about 64 probe rows per range, at most kPoolSplitMax, no more ranges than fill the chip
   // twice over; and the partial sums of every partition fit the region the workspace plan reserves for them
   EXPECT(pool_splits(512, 2) == 8 && pool_splits(512, 192) == 2 && pool_splits(512, 1000) == 1 && pool_splits(10, 1) == 1);

@@ -23,7 +23,13 @@ CASES = [
     (2, 1, 5000, 2000, "pairs"),         # every score twice: ties inside and across the cut
     (1, 2, 4000, 600, "outlier"),        # one score far above the rest: crowded buckets, the exact path in every part
     (2, 1, 2000, 100, "equal"),          # all scores equal
-    (1, 1, 9000, 8192, "normal"),        # the largest sort the LDS holds
+    (1, 1, 9000, 8192, "normal"),        # the largest sort the LDS holds, no room for more candidates: two launches
+    (1, 1, 9000, 8064, "normal"),        # the largest that is shared
+    (1, 1, 8192, 8192, "normal"),        # everything of a block that is shared
+    (2, 1, 4097, 4097, "pairs"),
+    (1, 2, 2, 1, "normal"),              # the smallest
+    (2, 2, 16384, 4096, "equal"),        # the exact path with sixteen parts of 256 rows
+    (8, 1, 16384, 5000, "outlier"),
 ]
 
 
