@@ -343,7 +343,7 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
                                                    int n_parts = 1, uint32_t* out_first = nullptr, uint32_t* n_out = nullptr) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int kPer = kResidentScores / kSelectThreads;
-  const bool resident = L <= kResidentScores;
+  const bool resident = kParts || L <= kResidentScores;      // (heads are shared only where the scores are resident)
   double sc[kPer];
   uint32_t bins[kPer];                                       // bucket | arrival order in the bucket << 11
   if (resident) {
@@ -478,8 +478,8 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
     for (int64_t j = tid; j < L; j += kSelectThreads) {
       const double x = s[j];
       const uint32_t b = bin_of(x);
-      if ((int)b >= b_lo && (int)b <= b_hi) {
-        const uint32_t pos = sh.base[b] - first + atomicAdd(&sh.fill[b], 1u);
+      if ((int)b >= t_bin) {
+        const uint32_t pos = sh.base[b] + atomicAdd(&sh.fill[b], 1u);
         sidx[pos] = (uint32_t)j;
         skeys[pos] = (uint64_t)__double_as_longlong(x);
       }

@@ -1,5 +1,5 @@
-// Attention of a short query block over a long key axis for gfx950 (Eq. 5, and a decoding step): the key-split
-// launches of apbv_query_attention.  Operation, mask, softmax and MFMA mapping are those of attention.hip; what
+// Attention of a short query block over a long key axis for gfx950 (Eq. 5, and a decoding step): the launches of
+// apbv_query_attention other than attention.hip's own (choose_query_plan picks one of four).  Operation, mask, softmax and MFMA mapping are those of attention.hip; what
 // differs is how the work is cut.
 //
 // Rows.  The G query heads that share a KV head are G more rows of one problem: row r = i * G + g of (batch item, KV
@@ -10,11 +10,11 @@
 // WAVE walks its own range of the key axis with its own LDS rings (two 32-key tiles of K and of V, filled by LDS-direct
 // loads) and no barrier: the rings' order is kept by counting the wave's own loads.  The waves of a workgroup take
 // consecutive ranges of the same rows and combine their results in LDS at the end (float32), so a workgroup writes one
-// partial result per row.  One query over 131072 keys, 16 / 2 heads of 128 (136 MB): 94 -> 23.6 us, 5.8 TB/s.
+// partial result per row.  One query over 133121 keys, 16 / 2 heads of 128 (136 MB): 94 -> 23.6 us, 5.8 TB/s.
 //
 // More rows have matrix work to do and share their tiles among the waves: attention.hip's workgroups on packed rows.
-// 64 queries x 16 / 2 heads over 131072 keys 106 -> 94 us, 17 queries x 28 / 4 over 2 x 5000 keys 33 -> 18 us, 200
-// queries x 28 / 4 over 40000 keys 194 -> 132 us; this kernel with two blocks of rows per wave 125 us on the first.
+// 64 queries x 16 / 2 heads over 131072 keys 106 -> 94 us, 17 queries x 28 / 4 over 2 x 5000 keys 33 -> 18 us; this kernel
+// with two blocks of rows per wave 125 us on the first.
 #include "apbv_common.h"
 #include "attention_tiles.h"
 
@@ -29,10 +29,9 @@ struct QueryShape {
   static constexpr int kWaves = 65536 / kRingBytes;
 };
 
-// Work item: rows 16*NQ*rt .. of (batch item b, KV head kvh), key range `split`.
+// Work item: the at most 16*NQ rows of (batch item b, KV head kvh), key range `split`.
 template <int D, int NQ>
-__device__ __forceinline__ void query_workgroup(const AttnParams& p, const int rt, const int b, const int kvh,
-                                                const int split) {
+__device__ __forceinline__ void query_workgroup(const AttnParams& p, const int b, const int kvh, const int split) {
   using S = QueryShape<D>;
   using T = typename S::T;
   constexpr int W = S::kWaves;
@@ -45,9 +44,7 @@ __device__ __forceinline__ void query_workgroup(const AttnParams& p, const int r
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 15;
   const int lg = lane >> 4;
-  const int n_rows = (int)p.L * p.group;                   // at most kQueryMaxTokens * 65535
-  const int r0 = rt * kRows;
-  const int r_last = r0 + kRows < n_rows ? r0 + kRows - 1 : n_rows - 1;
+  const int n_rows = (int)p.L * p.group;                   // at most kRows
 
   Segs ks, vs;
   {
@@ -66,15 +63,14 @@ __device__ __forceinline__ void query_workgroup(const AttnParams& p, const int r
 
   // ---- the wave's tiles [tb, te): an equal share of the workgroup's range (planned in 64-key units)
   auto last_key = [&](int64_t i) { return (i + p.n_vis < p.s_kv - 1) ? i + p.n_vis : p.s_kv - 1; };
-  const int i_first = r0 / p.group, i_last = r_last / p.group;
-  const int64_t n_vis_tiles = last_key(i_last) / kBN + 1;
+  const int64_t n_vis_tiles = last_key(p.L - 1) / kBN + 1;
   const int64_t per_split = (int64_t)p.tiles_per_split * (64 / kBN);
   const int64_t s_begin = split * per_split < n_vis_tiles ? split * per_split : n_vis_tiles;
   const int64_t s_end = s_begin + per_split < n_vis_tiles ? s_begin + per_split : n_vis_tiles;
   const int per_wave = (int)((s_end - s_begin + W - 1) / W);
   const int tb = __builtin_amdgcn_readfirstlane((int)(s_begin + wave * per_wave < s_end ? s_begin + wave * per_wave : s_end));
   const int te = __builtin_amdgcn_readfirstlane((int)(tb + per_wave < s_end ? tb + per_wave : s_end));
-  const int t_mask = __builtin_amdgcn_readfirstlane((int)((last_key(i_first) + 1) / kBN));   // first tile with a key some row cannot see
+  const int t_mask = __builtin_amdgcn_readfirstlane((int)((last_key(0) + 1) / kBN));   // first tile with a key some row cannot see
 
   // ---- the rings: K(t), V(t) live in slot (t - tb) & 1
   TileStream<D, 1, false> kst;
@@ -93,12 +89,12 @@ __device__ __forceinline__ void query_workgroup(const AttnParams& p, const int r
     issue_v(0);
   }
 
-  // ---- Q^T fragments; this lane's rows r0 + 16*nq + li
+  // ---- Q^T fragments; this lane's rows 16*nq + li
   bf16x8 qf[T::KSD][NQ];
   int jlast[NQ];                                           // last visible virtual key of each row
 #pragma unroll
   for (int nq = 0; nq < NQ; ++nq) {
-    const int r = r0 + 16 * nq + li < n_rows ? r0 + 16 * nq + li : n_rows - 1;
+    const int r = 16 * nq + li < n_rows ? 16 * nq + li : n_rows - 1;
     const int i = r / p.group;
     const int h = kvh * p.group + r % p.group;
     jlast[nq] = (int)last_key(i);
@@ -286,7 +282,7 @@ __device__ __forceinline__ void query_workgroup(const AttnParams& p, const int r
       l = __builtin_fmaf(sw[kRows + 16 * nq + li], __builtin_amdgcn_exp2f(sw[16 * nq + li] - m0), l);
     }
     factor[nq] = l > 0.f ? __builtin_amdgcn_exp2f(m_ref[nq] - m0) / l : 0.f;
-    const int r = r0 + 16 * nq + li;
+    const int r = 16 * nq + li;
     if (p.lse != nullptr && wave == 0 && lg == 0 && r < n_rows) {
       const int i = r / p.group;
       const int h = kvh * p.group + r % p.group;
@@ -307,8 +303,7 @@ __device__ __forceinline__ void query_workgroup(const AttnParams& p, const int r
   __syncthreads();
   for (int item = threadIdx.x; item < kRows * (D / 8); item += 64 * W) {
     const int row = item / (D / 8), c = item % (D / 8);
-    const int r = r0 + row;
-    if (r >= n_rows) break;
+    if (row >= n_rows) break;
     f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < W; ++w) {
@@ -321,31 +316,25 @@ __device__ __forceinline__ void query_workgroup(const AttnParams& p, const int r
     y.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x0.z, x0.w}), bf16x2));
     y.z = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x1.x, x1.y}), bf16x2));
     y.w = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x1.z, x1.w}), bf16x2));
-    const int i = r / p.group;
-    const int h = kvh * p.group + r % p.group;
+    const int i = row / p.group;
+    const int h = kvh * p.group + row % p.group;
     *reinterpret_cast<u32x4*>(p.out + (int64_t)split * p.split_stride_out + (((int64_t)b * p.L + i) * p.hq + h) * D + 8 * c) = y;
   }
 }
 
-// The row tiles of one (batch item, KV head, key range) read the same keys: they run back to back on one XCD.
+// One workgroup per (batch item, KV head, key range).
 template <int D, int NQ>
-__global__ __launch_bounds__(64 * QueryShape<D>::kWaves, D == 128 ? 1 : 2) void query_attention_kernel(const AttnParams p, const int n_rtiles,
-                                                                                                    const int n_ranges) {
-  const int slot = blockIdx.x / kXcds;
-  const int range = (slot / n_rtiles) * kXcds + blockIdx.x % kXcds;      // (batch item, KV head, split)
-  if (range >= n_ranges) return;
-  const int split = range % p.n_splits, bh = range / p.n_splits;
-  query_workgroup<D, NQ>(p, slot % n_rtiles, bh / p.hkv, bh % p.hkv, split);
+__global__ __launch_bounds__(64 * QueryShape<D>::kWaves, D == 128 ? 1 : 2) void query_attention_kernel(const AttnParams p) {
+  const int split = blockIdx.x % p.n_splits, bh = blockIdx.x / p.n_splits;
+  query_workgroup<D, NQ>(p, bh / p.hkv, bh % p.hkv, split);
 }
 
 template <int D, int NQ>
 apbv_status launch_query_variant(const AttnParams& p, hipStream_t stream) {
-  const int64_t n_rtiles = (p.L * p.group + 16 * NQ - 1) / (16 * NQ);
-  const int64_t n_ranges = (int64_t)p.batch * p.hkv * p.n_splits;
-  const int64_t n_blocks = (n_ranges + kXcds - 1) / kXcds * kXcds * n_rtiles;
+  const int64_t n_blocks = (int64_t)p.batch * p.hkv * p.n_splits;
   if (n_blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
   Launcher launch(stream);
-  launch(query_attention_kernel<D, NQ>, dim3((unsigned)n_blocks), dim3(64 * QueryShape<D>::kWaves), 0, p, (int)n_rtiles, (int)n_ranges);
+  launch(query_attention_kernel<D, NQ>, dim3((unsigned)n_blocks), dim3(64 * QueryShape<D>::kWaves), 0, p);
   return launch.status();
 }
 
@@ -353,7 +342,8 @@ template <int D>
 apbv_status launch_query_rows(const AttnParams& p, hipStream_t stream) {
   const int64_t rows = p.L * p.group;
   if (rows <= 16) return launch_query_variant<D, 1>(p, stream);
-  return launch_query_variant<D, 2>(p, stream);
+  if (rows <= kQueryWaveRows) return launch_query_variant<D, 2>(p, stream);
+  return APBV_ERR_UNSUPPORTED;
 }
 
 }  // namespace

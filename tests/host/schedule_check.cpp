@@ -1,5 +1,5 @@
 // Host check of the merged query-tile schedule (csrc/attention_schedule.h), compiled with the plain C++ compiler:
-// for random groups, every (problem, query tile) pair must be decoded exactly once, levels never increase along
+// for random groups and both tile sizes, every (problem, query tile) pair must be decoded exactly once, levels never increase along
 // the order, and problems inside a level come in index order.
 #include <cstdio>
 #include <cstdlib>
@@ -17,27 +17,30 @@ static uint64_t rnd() {                       // splitmix64
   return z ^ (z >> 31);
 }
 
-static int check(int n, const int64_t* n_vis, const int64_t* rows) {
+static int check_tile(int n, const int64_t* n_vis, const int64_t* rows, int tile) {
   GroupSchedule s;
-  if (!build_group_schedule(n, n_vis, rows, s)) { std::printf("build failed\n"); return 1; }
+  if (!build_group_schedule(n, n_vis, rows, s, tile)) { std::printf("build failed\n"); return 1; }
   std::map<std::pair<int, int>, int> seen;
   long expected = 0;
-  for (int m = 0; m < n; ++m) expected += (rows[m] + 255) / 256;
+  for (int m = 0; m < n; ++m) expected += (rows[m] + tile - 1) / tile;
   if (s.n_entries != expected) { std::printf("n_entries %d != %ld\n", s.n_entries, expected); return 1; }
   long prev_level = -1;
   int prev_m = -1;
   for (int e = 0; e < s.n_entries; ++e) {
     int m, qt;
     decode_group_entry(s, e, m, qt);
-    if (m < 0 || m >= n || qt < 0 || qt >= (rows[m] + 255) / 256) { std::printf("entry %d -> (%d, %d) out of range\n", e, m, qt); return 1; }
+    if (m < 0 || m >= n || qt < 0 || qt >= (rows[m] + tile - 1) / tile) { std::printf("entry %d -> (%d, %d) out of range\n", e, m, qt); return 1; }
     if (seen[{m, qt}]++) { std::printf("entry %d -> (%d, %d) twice\n", e, m, qt); return 1; }
-    const long level = n_vis[m] / 256 + qt;
+    const long level = n_vis[m] / tile + qt;
     if (e > 0 && (level > prev_level || (level == prev_level && m <= prev_m))) { std::printf("order broken at entry %d\n", e); return 1; }
     prev_level = level;
     prev_m = m;
   }
   return 0;
 }
+
+// the two row tiles of the grouped launch
+static int check(int n, const int64_t* n_vis, const int64_t* rows) { return check_tile(n, n_vis, rows, 256) || check_tile(n, n_vis, rows, 128); }
 
 int main() {
   {  // a physical host of the 128K configuration: anchor block, virtual hosts 0 and 15
