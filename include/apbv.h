@@ -235,8 +235,11 @@ size_t apbv_query_attention_workspace_bytes(int batch, int n_q_heads, int head_d
  * and its log-sum-exp in the workspace, combined by the merge of apbv_merge_lse in a second kernel.  Partial
  * results pass through bf16, so the output can differ from apbv_host_attention's by bf16 rounding of the parts.
  *
- *   n_splits   0: chosen by the library from the shape; >= 1: requested number of key ranges (clipped to the number
- *              of 64-key tiles and to 256; 1 = no split, the call is then apbv_host_attention and needs no workspace)
+ *   n_splits   0: kernel and number of key ranges chosen by the library from the shape and the workspace (one range
+ *              included); >= 1: requested number of ranges (clipped to the number of 64-key tiles and to 256;
+ *              1 = no split, the call is then apbv_host_attention and needs no workspace).  Results are
+ *              repeatable, but their bf16 roundings depend on the ranges taken: with n_splits 0 therefore also on
+ *              the shape of the whole call and on workspace_bytes
  *   workspace / workspace_bytes   at least apbv_query_attention_workspace_bytes(...) bytes, 256-byte aligned; may be
  *              NULL / 0 when that is 0.  Contents need no initialisation and are garbage afterwards.  (With n_splits
  *              0 a smaller workspace gives fewer ranges; one that does not hold a sensible number is refused.)

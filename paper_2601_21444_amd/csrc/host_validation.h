@@ -114,7 +114,7 @@ inline apbv_status validate_merge(int n_parts, int64_t rows, int n_q_heads, int 
 // same.  Smaller workgroups spread over more compute units, and where two share one the start and the end of one run
 // beside the other's keys; but they read K and V more often, and one that is alone on its unit takes 0.64 of the time of
 // two, not half.  The rule is drawn from 2260 measured launches (heads, batches, 129 to 16384 rows, 0 to 33000 visible
-// keys): against 256 rows always it is more than 1.5 % slower in 12 of them (at most 10 %) and on average 10 % (head_dim
+// keys): against 256 rows always it is more than 1.5 % slower in 12 of them (at most 15 %) and on average 10 % (head_dim
 // 128) and 22 % (64) faster, 1 % behind the best size of every launch.  Examples (us, 256 / 128 rows, d 128):
 //   16 heads x 2048 rows behind 8704 keys  245 / 181 (a workgroup per unit)    x 4096 rows, no more keys  100 / 87
 //   16 x 4096 behind 32768  981 / 1030 (one full round either way)             32 x 3899 rows  123 / 130 (two full rounds)

@@ -1,6 +1,6 @@
 // Attention of a short query block over a long key axis for gfx950 (Eq. 5, and a decoding step): the launches of
-// apbv_query_attention other than attention.hip's own (choose_query_plan picks one of four).  Operation, mask, softmax and MFMA mapping are those of attention.hip; what
-// differs is how the work is cut.
+// apbv_query_attention other than attention.hip's own (choose_query_plan picks one of four).  Operation, mask, softmax
+// and MFMA mapping are those of attention.hip; what differs is how the work is cut.
 //
 // Rows.  The G query heads that share a KV head are G more rows of one problem: row r = i * G + g of (batch item, KV
 // head) is query i of head kvh * G + g.  A decoding step of one query then fills G of a 16-row MFMA block and reads
@@ -10,11 +10,11 @@
 // WAVE walks its own range of the key axis with its own LDS rings (two 32-key tiles of K and of V, filled by LDS-direct
 // loads) and no barrier: the rings' order is kept by counting the wave's own loads.  The waves of a workgroup take
 // consecutive ranges of the same rows and combine their results in LDS at the end (float32), so a workgroup writes one
-// partial result per row.  One query over 133121 keys, 16 / 2 heads of 128 (136 MB): 94 -> 23.6 us, 5.8 TB/s.
+// partial result per row.  One query over 133120 keys, 16 / 2 heads of 128 (136 MB): 94 -> 24.1 us, 5.7 TB/s.
 //
 // More rows have matrix work to do and share their tiles among the waves: attention.hip's workgroups on packed rows.
-// 64 queries x 16 / 2 heads over 131072 keys 106 -> 94 us, 17 queries x 28 / 4 over 2 x 5000 keys 33 -> 18 us; this kernel
-// with two blocks of rows per wave 125 us on the first.
+// With the merge: 64 queries x 16 / 2 heads over 131072 keys 88 -> 70 us, 17 queries x 28 / 4 over 2 x 5000 keys 32 -> 16 us;
+// this kernel with two blocks of rows per wave was slower than a workgroup per query head on the first (125 / 106 us).
 #include "apbv_common.h"
 #include "attention_tiles.h"
 

@@ -1,6 +1,6 @@
 // Host check of the merged query-tile schedule (csrc/attention_schedule.h), compiled with the plain C++ compiler:
-// for random groups and both tile sizes, every (problem, query tile) pair must be decoded exactly once, levels never increase along
-// the order, and problems inside a level come in index order.
+// for random groups and both tile sizes, every (problem, query tile) pair must be decoded exactly once, levels never
+// increase along the order, and problems inside a level come in index order.
 #include <cstdio>
 #include <cstdlib>
 #include <map>
