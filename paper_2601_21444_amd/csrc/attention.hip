@@ -62,11 +62,18 @@ constexpr int kRing = 4;           // K tiles, and V tiles, resident in LDS
 
 // One workgroup's work: row tile `qt` of batch item b, key range `split`.  kPacked: the rows are those of KV head kvh,
 // row r = i * G + g being query i of head kvh * G + g (g unused); otherwise they are the queries of head (kvh, g).
-template <int D, int W, bool kPacked>
+// kShare: waves per 32-row block.  With two, each finishes 16 of the rows (O, probabilities, row sums) and forms S^T of all
+// 32, because the reference maximum of a block moves for all its rows at once: the results are those of one wave, bit for
+// bit.  This is for launches that leave SIMDs empty: a wave alone on its SIMD does not overlap its matrix and vector
+// instructions (16 + 4.2 n cycles for one 16x16x32 and n vector instructions, measured), so its time is their sum, and
+// sharing takes a quarter of the first and half of the second off it.  us, 64-row workgroups of two waves / of four: 16
+// heads of 128 x 1024 rows behind 224 keys 29.3 / 22.2, 2 heads of 64 x 512 rows behind 160 12.8 / 10.9.
+template <int D, int W, bool kPacked, int kShare>
 __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const int qt, const int b, const int kvh,
                                                     const int g, const int split) {
   using T = Tile<D, W>;
-  constexpr int kRows = 32 * W;      // query rows of the workgroup
+  constexpr int kRows = 32 * W / kShare;      // query rows of the workgroup
+  constexpr int kOwn = 2 / kShare;            // 16-row query blocks this wave finishes: the first of its two
   __shared__ __attribute__((aligned(1024))) unsigned char k_lds[kRing][T::TILE_BYTES];
   __shared__ __attribute__((aligned(1024))) unsigned char v_lds[kRing][T::TILE_BYTES];
   // the LDS destination of an LDS-direct load travels in M0, which addresses the first 64 KB of the workgroup's LDS
@@ -82,8 +89,9 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   auto query_of = [&](int64_t r) { return kPacked ? (int64_t)((uint32_t)r / (uint32_t)p.group) : r; };
   auto head_of = [&](int64_t r) { return kvh * p.group + (kPacked ? (int)((uint32_t)r % (uint32_t)p.group) : g); };
   const int64_t i0 = (int64_t)qt * kRows;               // first row of the workgroup
-  const int64_t iw = i0 + wave * 32;                    // first row of the wave
-  const int64_t i_row[2] = {iw + li, iw + 16 + li};     // this lane's two rows
+  const int64_t iw = i0 + wave / kShare * 32;           // first row of the wave's block
+  const int first16 = kShare == 2 ? (wave & 1) * 16 : 0;                         // the 16 rows it finishes (first)
+  const int64_t i_row[2] = {iw + first16 + li, iw + (16 - first16) + li};        // this lane's two rows
 
   Segs ks, vs;
   {
@@ -129,15 +137,15 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   }
 
   // ---- online softmax state.  Per lane: two queries (nq = 0, 1); the four lane groups hold disjoint key subsets.
-  f32x4 o[T::DBN][2];
+  f32x4 o[T::DBN][kOwn];
 #pragma unroll
   for (int d = 0; d < T::DBN; ++d)
 #pragma unroll
-    for (int nq = 0; nq < 2; ++nq) o[d][nq] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int nq = 0; nq < kOwn; ++nq) o[d][nq] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_ref[2] = {-INFINITY, -INFINITY};   // reference maximum of the scaled (log2-domain) logits, whole row
   float m_sub[2] = {0.f, 0.f};               // what the exponent subtracts: m_ref, or 0 while m_ref = -inf
   float s_far[2] = {-INFINITY, -INFINITY};   // raw logits above this move the reference: (m_ref + threshold) / scale
-  float l_run[2] = {0.f, 0.f};               // running sum of the bf16-rounded exp2(. - m_ref), this lane's keys only
+  float l_run[kOwn] = {};                    // running sum of the bf16-rounded exp2(. - m_ref), this lane's keys only
   const float inv_scale_log2 = 1.0f / p.scale_log2;
 
   // Keys the workgroup / this wave can see at all.
@@ -158,7 +166,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   const int jrel0[2] = {(int)last_key(query_of(i_row[0])), (int)last_key(query_of(i_row[1]))};   // last visible virtual key of each row
 
   typedef f32x4 STile[2][2];       // S^T of one tile: [16-key block][16-query block]
-  typedef u32x4 PTile[2];          // P^T of one tile as the B operand of O^T: [16-query block], four 32-bit words
+  typedef u32x4 PTile[kOwn];         // P^T of one tile as the B operand of O^T: [16-query block], four 32-bit words
 
   auto read_k = [&](const unsigned char* kt, int mb, int c) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(kt + mb * 16 * T::ROW_BYTES + k_off[c]));
@@ -230,9 +238,11 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
         m_ref[nq] = m_new;
         m_sub[nq] = m_new > -INFINITY ? m_new : 0.f;
         s_far[nq] = (m_new + kRescaleThreshold) * inv_scale_log2;
-        l_run[nq] *= alpha;
+        if (nq < kOwn) {
+          l_run[nq] *= alpha;
 #pragma unroll
-        for (int d = 0; d < T::DBN; ++d) o[d][nq] *= alpha;
+          for (int d = 0; d < T::DBN; ++d) o[d][nq] *= alpha;
+        }
       }
     }
   };
@@ -259,7 +269,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     for (int d = 0; d < T::DBN; ++d) {
       const bf16x8 a = read_vt(vt, d);
 #pragma unroll
-      for (int nq = 0; nq < 2; ++nq)
+      for (int nq = 0; nq < kOwn; ++nq)
         o[d][nq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, pw[nq]), o[d][nq], 0, 0, 0);
     }
   };
@@ -274,8 +284,8 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   };
   auto finish = [&](const unsigned char* vt, const STile& s) {          // probabilities, O^T
     PTile pw;
-    exp_block(s, 0, pw);
-    exp_block(s, 1, pw);
+#pragma unroll
+    for (int nq = 0; nq < kOwn; ++nq) exp_block(s, nq, pw);
     pv(vt, pw);
   };
 
@@ -300,8 +310,9 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     // scheduler keeps that interleaving (pinning it with scheduling fences was measured 3 % slower).
     // exponential pipeline of tile t, one pair of probabilities at a time: pair pi = (nq, mb, first/second two rows);
     // stages F (scale and subtract), E (exp2), C (round to bf16 into the B operand word), D (row sum)
-    float xf[8][2];
-    uint32_t cw[8];
+    constexpr int kPairs = 4 * kOwn;
+    float xf[kPairs][2];
+    uint32_t cw[kPairs];
     PTile pw;
     auto stage_f = [&](int pi) {
       const int nq = pi >> 2, mb = (pi >> 1) & 1, e = 2 * (pi & 1);
@@ -330,8 +341,8 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
       constexpr int c = i / 4, nq = (i / 2) % 2, mb = i % 2;
       sn[mb][nq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[2 * c + mb], qf[c][nq],
                                                            c == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sn[mb][nq], 0, 0, 0);
-      // the 16 slices of the exponential pipeline are spread evenly over the nA matrix instructions
-      constexpr int s0 = (16 * i) / nA, s1 = (16 * (i + 1)) / nA;
+      // the slices of the exponential pipeline are spread evenly over the nA matrix instructions
+      constexpr int s0 = (2 * kPairs * i) / nA, s1 = (2 * kPairs * (i + 1)) / nA;
       static_for<s1 - s0>([&](auto J) {
         constexpr int sl = s0 + J, pi = sl / 2;
         if constexpr (sl % 2 == 0) {
@@ -352,14 +363,14 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
           vhi[d] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((APBV_LDS(s16x4))(vt + 16 * T::ROW_BYTES + v_off[d]));
       });
     });
-    stage_c(7);
-    stage_d(7);
+    stage_c(kPairs - 1);
+    stage_d(kPairs - 1);
     // ---- phase B: one slice per matrix instruction of O^T(t)
     float lm[2];
-    constexpr int nB = 2 * T::DBN, nK = kPrefetchK ? 2 * T::KSD : 0;
+    constexpr int nB = kOwn * T::DBN, nK = kPrefetchK ? 2 * T::KSD : 0;
     static_for<nB>([&](auto I) {
       constexpr int i = I;
-      constexpr int d = i / 2, nq = i % 2;
+      constexpr int d = i / kOwn, nq = i % kOwn;
       const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vlo[d], vhi[d], 0, 1, 2, 3, 4, 5, 6, 7));
       o[d][nq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, pw[nq]), o[d][nq], 0, 0, 0);
       // the K fragments of tile t+2
@@ -486,7 +497,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
 
   // ---- epilogue: normalise, round to bf16, store; optional log-sum-exp
 #pragma unroll
-  for (int nq = 0; nq < 2; ++nq) {
+  for (int nq = 0; nq < kOwn; ++nq) {
     float l_tot = l_run[nq];
     {
       auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(l_tot), __float_as_uint(l_tot), false, false);
@@ -534,7 +545,7 @@ __device__ __forceinline__ int deal(int row, int xcd, int period) {
 }
 
 // ---- workgroup -> (query tile, head, batch, key range); the heads of one KV group share an XCD
-template <int D, int W>
+template <int D, int W, int kShare = 1>
 __global__ __launch_bounds__(64 * W, 2) void host_attention_kernel(const AttnParams p, const int n_qtiles,
                                                                    const int n_items) {
   const int xcd = blockIdx.x % kXcds;
@@ -548,7 +559,7 @@ __global__ __launch_bounds__(64 * W, 2) void host_attention_kernel(const AttnPar
   const int qt = n_qtiles - 1 - item / bh;       // heaviest query tiles first
   const int b = (item % bh) / p.hkv;
   const int kvh = (item % bh) % p.hkv;
-  attention_workgroup<D, W, false>(p, qt, b, kvh, g, split);
+  attention_workgroup<D, W, false, kShare>(p, qt, b, kvh, g, split);
 }
 
 // ---- key-split launches: the heads of a KV group packed into the rows.  The row tiles of one (batch item, KV head,
@@ -559,13 +570,13 @@ __global__ __launch_bounds__(64 * W, 2) void packed_attention_kernel(const AttnP
   const int range = (slot / n_rtiles) * kXcds + blockIdx.x % kXcds;      // (batch item, KV head, split)
   if (range >= n_ranges) return;
   const int split = range % p.n_splits, bh = range / p.n_splits;
-  attention_workgroup<D, W, true>(p, slot % n_rtiles, bh / p.hkv, bh % p.hkv, 0, split);
+  attention_workgroup<D, W, true, 1>(p, slot % n_rtiles, bh / p.hkv, bh % p.hkv, 0, split);
 }
 
 // ---- several attention problems of different lengths in one launch (the two virtual hosts and the anchor
 // block of a physical host, Alg. 1 / Sec. 4.3): one workgroup per entry of the merged heaviest-first order of
 // all (problem, query tile) pairs, per KV head and group member.
-template <int D, int W>
+template <int D, int W, int kShare = 1>
 __global__ __launch_bounds__(64 * W, 2) void host_attention_group_kernel(const AttnGroupParams gp) {
   const int group = gp.item[0].group, hkv = gp.item[0].hkv;
   const int xcd = blockIdx.x % kXcds;
@@ -576,18 +587,18 @@ __global__ __launch_bounds__(64 * W, 2) void host_attention_group_kernel(const A
   const int entry = unit / hkv, kvh = unit % hkv;
   int m, qt;
   decode_group_entry(gp.sched, entry, m, qt);
-  if (m >= gp.n_items || qt < 0 || (int64_t)qt * 32 * W >= gp.item[m].L) return;      // never taken for a schedule the launcher built
+  if (m >= gp.n_items || qt < 0 || (int64_t)qt * (32 * W / kShare) >= gp.item[m].L) return;      // never taken for a schedule the launcher built
   // (a copy, so that the fields live in scalar registers like the single-problem kernel's by-value argument
   // instead of being fetched from the argument block where they are used)
   const AttnParams item = gp.item[m];
-  attention_workgroup<D, W, false>(item, qt, 0, kvh, g, 0);
+  attention_workgroup<D, W, false, kShare>(item, qt, 0, kvh, g, 0);
 }
 
 }  // namespace
 
-template <int W>
+template <int W, int kShare = 1>
 static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t stream) {
-  constexpr int kRows = 32 * W;
+  constexpr int kRows = 32 * W / kShare;
   const int n_qtiles = (int)((p.L + kRows - 1) / kRows);
   const int64_t n_items = (int64_t)n_qtiles * p.batch * p.hkv * p.n_splits;
   const int64_t n_blocks = (n_items + kXcds - 1) / kXcds * kXcds * p.group;
@@ -596,9 +607,9 @@ static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t
   dim3 block(64 * W);
   Launcher launch(stream);
   if (head_dim == 128)
-    launch(host_attention_kernel<128, W>, grid, block, 0, p, n_qtiles, (int)n_items);
+    launch(host_attention_kernel<128, W, kShare>, grid, block, 0, p, n_qtiles, (int)n_items);
   else if (head_dim == 64)
-    launch(host_attention_kernel<64, W>, grid, block, 0, p, n_qtiles, (int)n_items);
+    launch(host_attention_kernel<64, W, kShare>, grid, block, 0, p, n_qtiles, (int)n_items);
   else
     return APBV_ERR_UNSUPPORTED;
   return launch.status();
@@ -606,6 +617,7 @@ static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t
 
 apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t stream) {
   static_assert(kAttnQueryTile == kBM && kAttnNarrowQueryTile == 32 * kWavesNarrow, "tile sizes the host-side planning assumes");
+  if (attention_shares_blocks(head_dim, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits)) return launch_variant<kWavesShort, 2>(p, head_dim, stream);
   // (a block of at most kAttnNarrowMaxRows rows is mostly padding in anything but 64-row workgroups)
   if (p.L <= kAttnNarrowMaxRows) return launch_variant<kWavesNarrow>(p, head_dim, stream);
   switch (attention_rows(head_dim, p.group, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits)) {
@@ -637,19 +649,19 @@ apbv_status launch_packed_attention(const AttnParams& p, int head_dim, int rows,
   return rows == kBM ? launch_packed_variant<kWaves>(p, head_dim, stream) : launch_packed_variant<kWavesShort>(p, head_dim, stream);
 }
 
-template <int W>
+template <int W, int kShare = 1>
 static apbv_status launch_group_variant(AttnGroupParams& gp, int head_dim, const int64_t* n_vis, const int64_t* rows, hipStream_t stream) {
   static_assert(sizeof(AttnGroupParams) <= 4096, "kernel arguments are limited to 4 KB");
-  if (!build_group_schedule(gp.n_items, n_vis, rows, gp.sched, 32 * W)) return APBV_ERR_UNSUPPORTED;
+  if (!build_group_schedule(gp.n_items, n_vis, rows, gp.sched, 32 * W / kShare)) return APBV_ERR_UNSUPPORTED;
   const AttnParams& p0 = gp.item[0];
   const int64_t n_units = (int64_t)gp.sched.n_entries * p0.hkv;
   const int64_t n_blocks = (n_units + kXcds - 1) / kXcds * kXcds * p0.group;
   if (n_blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
   Launcher launch(stream);
   if (head_dim == 128)
-    launch(host_attention_group_kernel<128, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
+    launch(host_attention_group_kernel<128, W, kShare>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
   else if (head_dim == 64)
-    launch(host_attention_group_kernel<64, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
+    launch(host_attention_group_kernel<64, W, kShare>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
   else
     return APBV_ERR_UNSUPPORTED;
   return launch.status();
@@ -670,6 +682,7 @@ apbv_status launch_host_attention_group(AttnGroupParams& gp, int head_dim, hipSt
     kv_bytes += (double)p.s_kv * p.hkv * head_dim * 4;
     qo_bytes += (double)p.L * p.hq * head_dim * 4;
   }
+  if (attention_shares_blocks(head_dim, tiles)) return launch_group_variant<kWavesShort, 2>(gp, head_dim, n_vis, rows, stream);
   if (attention_rows(head_dim, gp.item[0].group, gp.item[0].hkv, tiles, kv_bytes, qo_bytes, false) == kBM) return launch_group_variant<kWaves>(gp, head_dim, n_vis, rows, stream);
   return launch_group_variant<kWavesShort>(gp, head_dim, n_vis, rows, stream);
 }

@@ -200,6 +200,25 @@ inline int attention_rows(int head_dim, int group, double kv_heads, const Attent
   if (kv_bytes > 128e6 && attention_traffic(head_dim, group, t128, kv_bytes, qo_bytes) > reached * least) return 256;
   return 128;
 }
+// Whether a launch takes 64-row workgroups of four waves, two to a block of 32 rows (kShare in attention.hip), instead: up to
+// a workgroup per unit always, with head_dim 64 (three fit a unit) up to three, and with head_dim 128 up to two where the
+// estimates say so.  Beyond, every wave's own reads of K and V from LDS cost more than the sharing saves (16 heads of 128
+// x 2048 rows behind 704 keys 50.6 / 50.4 us, 28 x 1500 behind 400 46.0 / 53.4).  Drawn from 700 measured launches: where it
+// is taken 1.18 times as fast on average, in one of 517 launches 3 % slower.  Blocks of at most kAttnNarrowMaxRows rows,
+// which take 64 rows either way: 400 launches, 1.13 times as fast, none slower.
+inline bool attention_shares_blocks(int head_dim, const AttentionTiles (&tiles)[3]) {
+  const AttentionTiles& t = tiles[0];
+  if (head_dim == 64) return t.n <= 768;
+  if (t.n <= 256) return true;
+  const double t128 = attention_makespan(attention_cost(128, 128), tiles[1]), t256 = attention_makespan(attention_cost(128, 256), tiles[2]);
+  return t.n <= 512 && attention_makespan(AttentionCost{2, 7.2, 0.018, 6.4, 0.0122, 0}, t) < (t128 < t256 ? t128 : t256);
+}
+inline bool attention_shares_blocks(int head_dim, int batch, int n_q_heads, int64_t n_rows, int64_t n_vis, bool causal, int n_splits) {
+  AttentionTiles tiles[3];
+  for (int i = 0; i < 3; ++i) add_attention_tiles(tiles[i], 64 << i, (double)batch * n_q_heads, n_rows, n_vis, causal, n_splits);
+  if (n_rows <= kAttnNarrowMaxRows) return tiles[0].n <= (head_dim == 64 ? 512 : 256);
+  return attention_shares_blocks(head_dim, tiles);
+}
 // One launch of batch * n_q_heads heads and n_splits key ranges, all of n_rows queries.
 inline int attention_rows(int head_dim, int group, int batch, int n_q_heads, int64_t n_rows, int64_t n_vis, bool causal, int n_splits) {
   AttentionTiles tiles[3];
