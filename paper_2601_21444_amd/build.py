@@ -18,6 +18,7 @@ SOURCES = {
     "attention.hip": ["-fno-honor-nans"],
     "compress.hip": [],
     "merge.hip": [],
+    "packed_attention.hip": ["-fno-honor-nans"],
     "query_attention.hip": ["-fno-honor-nans"],
     "score_matrix.hip": [],
 }

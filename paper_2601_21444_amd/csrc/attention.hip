@@ -60,15 +60,14 @@ constexpr int kWavesShort = 4;     // and 128 query rows
 constexpr int kBM = 32 * kWaves;   // query rows per workgroup (main variant)
 constexpr int kRing = 4;           // K tiles, and V tiles, resident in LDS
 
-// One workgroup's work: row tile `qt` of batch item b, key range `split`.  kPacked: the rows are those of KV head kvh,
-// row r = i * G + g being query i of head kvh * G + g (g unused); otherwise they are the queries of head (kvh, g).
+// One workgroup's work: row tile `qt` of batch item b and query head (kvh, g), key range `split`.
 // kShare: waves per 32-row block.  With two, each finishes 16 of the rows (O, probabilities, row sums) and forms S^T of all
 // 32, because the reference maximum of a block moves for all its rows at once: the results are those of one wave, bit for
 // bit.  This is for launches that leave SIMDs empty: a wave alone on its SIMD does not overlap its matrix and vector
 // instructions (16 + 4.2 n cycles for one 16x16x32 and n vector instructions, measured), so its time is their sum, and
 // sharing takes a quarter of the first and half of the second off it.  us, 64-row workgroups of two waves / of four: 16
 // heads of 128 x 1024 rows behind 224 keys 29.3 / 22.2, 2 heads of 64 x 512 rows behind 160 12.8 / 10.9.
-template <int D, int W, bool kPacked, int kShare>
+template <int D, int W, int kShare>
 __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const int qt, const int b, const int kvh,
                                                     const int g, const int split) {
   using T = Tile<D, W>;
@@ -84,36 +83,21 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   const int li = lane & 15;       // query column / A-operand row within a 16-block
   const int lg = lane >> 4;       // lane group: k-slots 8 lg .. 8 lg + 7, accumulator rows 4 lg .. 4 lg + 3
 
-  // (packed rows are few enough for 32 bits: kQueryMaxTokens * 65535)
-  const int64_t n_rows = kPacked ? p.L * p.group : p.L;
-  auto query_of = [&](int64_t r) { return kPacked ? (int64_t)((uint32_t)r / (uint32_t)p.group) : r; };
-  auto head_of = [&](int64_t r) { return kvh * p.group + (kPacked ? (int)((uint32_t)r % (uint32_t)p.group) : g); };
+  const int h = kvh * p.group + g;
   const int64_t i0 = (int64_t)qt * kRows;               // first row of the workgroup
   const int64_t iw = i0 + wave / kShare * 32;           // first row of the wave's block
   const int first16 = kShare == 2 ? (wave & 1) * 16 : 0;                         // the 16 rows it finishes (first)
   const int64_t i_row[2] = {iw + first16 + li, iw + (16 - first16) + li};        // this lane's two rows
 
   Segs ks, vs;
-  {
-    auto kbase = [&](int s) {
-      return reinterpret_cast<const char*>(p.k_seg[s].ptr + (int64_t)b * p.k_seg[s].sb + (int64_t)kvh * p.k_seg[s].sh);
-    };
-    auto vbase = [&](int s) {
-      return reinterpret_cast<const char*>(p.v_seg[s].ptr + (int64_t)b * p.v_seg[s].sb + (int64_t)kvh * p.v_seg[s].sh);
-    };
-    ks.b0 = kbase(0); ks.b1 = kbase(1); ks.b2 = kbase(2);
-    vs.b0 = vbase(0); vs.b1 = vbase(1); vs.b2 = vbase(2);
-    ks.p0 = p.k_seg[0].st * 2; ks.p1 = p.k_seg[1].st * 2; ks.p2 = p.k_seg[2].st * 2;
-    vs.p0 = p.v_seg[0].st * 2; vs.p1 = p.v_seg[1].st * 2; vs.p2 = p.v_seg[2].st * 2;
-    ks.e0 = vs.e0 = p.l_a; ks.e1 = vs.e1 = p.n_vis; ks.e2 = vs.e2 = p.s_kv;
-  }
+  key_segments(p, b, kvh, ks, vs);
 
   // ---- Q^T fragments (B operand of S^T), kept in registers for the whole key loop.
   bf16x8 qf[T::KSD][2];
 #pragma unroll
   for (int nq = 0; nq < 2; ++nq) {
-    const int64_t r = i_row[nq] < n_rows ? i_row[nq] : n_rows - 1;
-    const bf16_t* qrow = p.q.ptr + (int64_t)b * p.q.sb + (int64_t)head_of(r) * p.q.sh + query_of(r) * p.q.st;
+    const int64_t r = i_row[nq] < p.L ? i_row[nq] : p.L - 1;
+    const bf16_t* qrow = p.q.ptr + (int64_t)b * p.q.sb + (int64_t)h * p.q.sh + r * p.q.st;
 #pragma unroll
     for (int c = 0; c < T::KSD; ++c) qf[c][nq] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + 32 * c + 8 * lg));
   }
@@ -152,18 +136,18 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   // Query i sees the virtual keys 0 .. min(i + n_vis, s_kv - 1); the second bound only matters when there is no
   // causal segment (s_kv == n_vis: every key visible to every query).
   auto last_key = [&](int64_t i) { return (i + p.n_vis < p.s_kv - 1) ? i + p.n_vis : p.s_kv - 1; };
-  const int64_t i_last_wg = (i0 + kRows - 1 < n_rows - 1) ? i0 + kRows - 1 : n_rows - 1;
-  const int n_tiles_vis = (int)(last_key(query_of(i_last_wg)) / kBN) + 1;      // tiles the workgroup can see into
+  const int64_t i_last_wg = (i0 + kRows - 1 < p.L - 1) ? i0 + kRows - 1 : p.L - 1;
+  const int n_tiles_vis = (int)(last_key(i_last_wg) / kBN) + 1;      // tiles the workgroup can see into
   // key split (partial results merged afterwards): this workgroup walks tiles [t_begin, n_tiles) only; the split is
   // planned in 64-key units
   const int64_t per_split = (int64_t)p.tiles_per_split * (64 / kBN);
   const int64_t t_begin64 = (int64_t)split * per_split;
   const int t_begin = (int)(t_begin64 < n_tiles_vis ? t_begin64 : n_tiles_vis);
   const int n_tiles = (int)(t_begin64 + per_split < n_tiles_vis ? t_begin64 + per_split : n_tiles_vis);
-  const int t_last_wave = (int)(last_key(query_of(iw + 31)) / kBN);     // last tile any row of the wave can see into
+  const int t_last_wave = (int)(last_key(iw + 31) / kBN);     // last tile any row of the wave can see into
   const int n_w = t_last_wave + 1 < n_tiles ? t_last_wave + 1 : n_tiles;     // the wave computes tiles [t_begin, n_w)
-  const int t_mask_wave = (int)((last_key(query_of(iw)) + 1) / kBN);    // first tile with a key some row of the wave cannot see
-  const int jrel0[2] = {(int)last_key(query_of(i_row[0])), (int)last_key(query_of(i_row[1]))};   // last visible virtual key of each row
+  const int t_mask_wave = (int)((last_key(iw) + 1) / kBN);    // first tile with a key some row of the wave cannot see
+  const int jrel0[2] = {(int)last_key(i_row[0]), (int)last_key(i_row[1])};   // last visible virtual key of each row
 
   typedef f32x4 STile[2][2];       // S^T of one tile: [16-key block][16-query block]
   typedef u32x4 PTile[kOwn];         // P^T of one tile as the B operand of O^T: [16-query block], four 32-bit words
@@ -508,9 +492,8 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
       l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     }
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;     // a key split may leave a row without any visible key
-    if (i_row[nq] < n_rows) {
-      const int64_t i = query_of(i_row[nq]);
-      const int h = head_of(i_row[nq]);
+    if (i_row[nq] < p.L) {
+      const int64_t i = i_row[nq];
       bf16_t* orow = p.out + (int64_t)split * p.split_stride_out + (((int64_t)b * p.L + i) * p.hq + h) * D;
 #pragma unroll
       for (int d = 0; d < T::DBN; ++d) {
@@ -559,18 +542,7 @@ __global__ __launch_bounds__(64 * W, 2) void host_attention_kernel(const AttnPar
   const int qt = n_qtiles - 1 - item / bh;       // heaviest query tiles first
   const int b = (item % bh) / p.hkv;
   const int kvh = (item % bh) % p.hkv;
-  attention_workgroup<D, W, false, kShare>(p, qt, b, kvh, g, split);
-}
-
-// ---- key-split launches: the heads of a KV group packed into the rows.  The row tiles of one (batch item, KV head,
-// key range) read the same keys: they run back to back on one XCD.
-template <int D, int W>
-__global__ __launch_bounds__(64 * W, 2) void packed_attention_kernel(const AttnParams p, const int n_rtiles, const int n_ranges) {
-  const int slot = blockIdx.x / kXcds;
-  const int range = (slot / n_rtiles) * kXcds + blockIdx.x % kXcds;      // (batch item, KV head, split)
-  if (range >= n_ranges) return;
-  const int split = range % p.n_splits, bh = range / p.n_splits;
-  attention_workgroup<D, W, true, 1>(p, slot % n_rtiles, bh / p.hkv, bh % p.hkv, 0, split);
+  attention_workgroup<D, W, kShare>(p, qt, b, kvh, g, split);
 }
 
 // ---- several attention problems of different lengths in one launch (the two virtual hosts and the anchor
@@ -591,7 +563,7 @@ __global__ __launch_bounds__(64 * W, 2) void host_attention_group_kernel(const A
   // (a copy, so that the fields live in scalar registers like the single-problem kernel's by-value argument
   // instead of being fetched from the argument block where they are used)
   const AttnParams item = gp.item[m];
-  attention_workgroup<D, W, false, kShare>(item, qt, 0, kvh, g, 0);
+  attention_workgroup<D, W, kShare>(item, qt, 0, kvh, g, 0);
 }
 
 }  // namespace
@@ -625,28 +597,6 @@ apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t
     case 32 * kWavesShort: return launch_variant<kWavesShort>(p, head_dim, stream);
   }
   return launch_variant<kWaves>(p, head_dim, stream);
-}
-
-template <int W>
-static apbv_status launch_packed_variant(const AttnParams& p, int head_dim, hipStream_t stream) {
-  const int64_t n_rtiles = (p.L * p.group + 32 * W - 1) / (32 * W);
-  const int64_t n_ranges = (int64_t)p.batch * p.hkv * p.n_splits;
-  const int64_t n_blocks = (n_ranges + kXcds - 1) / kXcds * kXcds * n_rtiles;
-  if (n_blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
-  Launcher launch(stream);
-  if (head_dim == 128)
-    launch(packed_attention_kernel<128, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, p, (int)n_rtiles, (int)n_ranges);
-  else if (head_dim == 64)
-    launch(packed_attention_kernel<64, W>, dim3((unsigned)n_blocks), dim3(64 * W), 0, p, (int)n_rtiles, (int)n_ranges);
-  else
-    return APBV_ERR_UNSUPPORTED;
-  return launch.status();
-}
-
-// The rows of a KV group's heads together, in workgroups of 128 or 256.
-apbv_status launch_packed_attention(const AttnParams& p, int head_dim, int rows, hipStream_t stream) {
-  static_assert(kQueryShortRows == 32 * kWavesShort, "the tile size the host-side planning assumes");
-  return rows == kBM ? launch_packed_variant<kWaves>(p, head_dim, stream) : launch_packed_variant<kWavesShort>(p, head_dim, stream);
 }
 
 template <int W, int kShare = 1>

@@ -25,7 +25,9 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-template <int D, int W>
+// kWide: read by the 32x32x16 matrix instruction (32 rows x 16 bytes of K at once, 4 rows x 64 bytes of V) instead of the
+// 16x16x32 one; only the swizzle of V differs.
+template <int D, int W, bool kWide = false>
 struct Tile {
   static constexpr int ROW_BYTES = D * 2;
   static constexpr int KC = D / 8;                        // 16-byte chunks per row
@@ -38,7 +40,10 @@ struct Tile {
   // chunk swizzles (functions of the row within the tile), chosen so that the 16 rows x 16 bytes of a quarter of
   // a K read and the 8 rows x 32 bytes of half a transposing V read cover the 64 LDS banks exactly once
   __device__ static __forceinline__ int fk(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
-  __device__ static __forceinline__ int fv(int r) { return D == 128 ? ((r & 7) << 1) : (((r >> 1) & 3) << 1); }
+  __device__ static __forceinline__ int fv(int r) {
+    if (kWide) return D == 128 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2);
+    return D == 128 ? ((r & 7) << 1) : (((r >> 1) & 3) << 1);
+  }
 };
 
 struct Segs {
@@ -46,6 +51,16 @@ struct Segs {
   int64_t p0, p1, p2;         // bytes between consecutive tokens
   int64_t e0, e1, e2;         // one past the last virtual key of each segment (starts are 0, e0, e1)
 };
+
+// The three segments of K and of V for (batch item b, KV head kvh).
+__device__ __forceinline__ void key_segments(const AttnParams& p, int b, int kvh, Segs& ks, Segs& vs) {
+  auto base = [&](const View& t) { return reinterpret_cast<const char*>(t.ptr + (int64_t)b * t.sb + (int64_t)kvh * t.sh); };
+  ks.b0 = base(p.k_seg[0]); ks.b1 = base(p.k_seg[1]); ks.b2 = base(p.k_seg[2]);
+  vs.b0 = base(p.v_seg[0]); vs.b1 = base(p.v_seg[1]); vs.b2 = base(p.v_seg[2]);
+  ks.p0 = p.k_seg[0].st * 2; ks.p1 = p.k_seg[1].st * 2; ks.p2 = p.k_seg[2].st * 2;
+  vs.p0 = p.v_seg[0].st * 2; vs.p1 = p.v_seg[1].st * 2; vs.p2 = p.v_seg[2].st * 2;
+  ks.e0 = vs.e0 = p.l_a; ks.e1 = vs.e1 = p.n_vis; ks.e2 = vs.e2 = p.s_kv;
+}
 
 // Pick the fields of the segment that holds virtual key j (selects, no indexed access).
 __device__ __forceinline__ void seg_of(const Segs sg, int64_t j, const char*& base, int64_t& pitch, int64_t& start,
@@ -78,9 +93,9 @@ __device__ __forceinline__ uint32_t lds_addr(const unsigned char* p) { return (u
 // stay inside one segment ("run") a tile costs one 64-bit scalar add and its loads are  uniform tile base + a
 // per-lane 32-bit offset computed once per run; the tile that straddles a segment boundary (or the end of the
 // keys) takes a per-row lookup.
-template <int D, int W, bool kIsV>
+template <int D, int W, bool kIsV, bool kWide = false>
 struct TileStream {
-  using T = Tile<D, W>;
+  using T = Tile<D, W, kWide>;
   Segs sg;
   int64_t s_kv;
   int t_next;              // next tile to issue
@@ -140,6 +155,16 @@ struct TileStream {
       if (mine(u)) dma16_uniform(bu, off[u], dst + ldst(u));
     base += step;
     ++t_next;
+  }
+
+  // The u-th of the wave's IPW loads of tile t_next, which the caller knows to lie inside the current run; the last one moves
+  // on to the next tile.  From tile t_last on it is t_last that is loaded, again and again.
+  __device__ __forceinline__ void issue_in_run(uint32_t dst, int u, int t_last) {
+    if (mine(u)) dma16_uniform(uniform_ptr(base), off[u], dst + ldst(u));
+    if (u == T::IPW - 1) {
+      base += t_next < t_last ? step : 0;
+      ++t_next;
+    }
   }
 
   // issue(), staying on tile t_last once there: the callers' last requests repeat it instead of being left out, so that

@@ -303,7 +303,10 @@ struct QueryPlan {
   QueryKernel kernel;
   KeySplit split;
 };
-// Times in us, fitted to 18000 launches of 800 shapes (1 to 2048 queries, batches to 128, 64 to 200000 keys; within 9 %).
+// Times in us, fitted to 18000 launches of 800 shapes (1 to 2048 queries, batches to 128, 64 to 200000 keys; within 9 %) while
+// the packed workgroups used 16x16x32 matrix instructions.  They have become up to 14 % faster, a workgroup per head with
+// shared blocks up to 20 %; the order of the plans is the same: constants refitted to 70000 launches chose 0.5 % better on
+// average and worse by more than 5 % in 325 of 7702 shapes, so these stay.
 // A workgroup with k keys takes alone + alone_per_key * k on a unit of its own, and every further one on the busiest unit
 // adds more + more_per_key * k, whether it runs beside the others or after them.
 struct QueryCost {

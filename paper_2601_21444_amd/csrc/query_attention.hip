@@ -12,8 +12,8 @@
 // consecutive ranges of the same rows and combine their results in LDS at the end (float32), so a workgroup writes one
 // partial result per row.  One query over 133120 keys, 16 / 2 heads of 128 (136 MB): 94 -> 24.1 us, 5.7 TB/s.
 //
-// More rows have matrix work to do and share their tiles among the waves: attention.hip's workgroups on packed rows.
-// With the merge: 64 queries x 16 / 2 heads over 131072 keys 88 -> 70 us, 17 queries x 28 / 4 over 2 x 5000 keys 32 -> 16 us;
+// More rows have matrix work to do and share their tiles among the waves: packed_attention.hip.  With the merge, against a
+// workgroup per query head: 64 queries x 16 / 2 heads over 131072 keys 88 -> 70 us, 17 queries x 28 / 4 over 2 x 5000 keys 32 -> 15 us;
 // this kernel with two blocks of rows per wave was slower than a workgroup per query head on the first (125 / 106 us).
 #include "apbv_common.h"
 #include "attention_tiles.h"
@@ -47,19 +47,7 @@ __device__ __forceinline__ void query_workgroup(const AttnParams& p, const int b
   const int n_rows = (int)p.L * p.group;                   // at most kRows
 
   Segs ks, vs;
-  {
-    auto kbase = [&](int s) {
-      return reinterpret_cast<const char*>(p.k_seg[s].ptr + (int64_t)b * p.k_seg[s].sb + (int64_t)kvh * p.k_seg[s].sh);
-    };
-    auto vbase = [&](int s) {
-      return reinterpret_cast<const char*>(p.v_seg[s].ptr + (int64_t)b * p.v_seg[s].sb + (int64_t)kvh * p.v_seg[s].sh);
-    };
-    ks.b0 = kbase(0); ks.b1 = kbase(1); ks.b2 = kbase(2);
-    vs.b0 = vbase(0); vs.b1 = vbase(1); vs.b2 = vbase(2);
-    ks.p0 = p.k_seg[0].st * 2; ks.p1 = p.k_seg[1].st * 2; ks.p2 = p.k_seg[2].st * 2;
-    vs.p0 = p.v_seg[0].st * 2; vs.p1 = p.v_seg[1].st * 2; vs.p2 = p.v_seg[2].st * 2;
-    ks.e0 = vs.e0 = p.l_a; ks.e1 = vs.e1 = p.n_vis; ks.e2 = vs.e2 = p.s_kv;
-  }
+  key_segments(p, b, kvh, ks, vs);
 
   // ---- the wave's tiles [tb, te): an equal share of the workgroup's range (planned in 64-key units)
   auto last_key = [&](int64_t i) { return (i + p.n_vis < p.s_kv - 1) ? i + p.n_vis : p.s_kv - 1; };
