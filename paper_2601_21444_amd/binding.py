@@ -1,8 +1,12 @@
-"""Thin ctypes binding of libapbv.so: argument marshalling only.
+"""Thin binding of libapbv.so: argument marshalling only.
 
 Every step of the hot path runs inside the HIP library; PyTorch is used here for device memory and
 for the current HIP stream.  If the library has not been built the calls raise -- there is no
 fallback path.
+
+The plain call (every output and workspace passed, dense tensors of the right types, the current stream) is marshalled in
+native code (csrc/marshal.cpp), which looks at the same things as the code here and hands back what it does not take; the
+ctypes code here allocates what was left out and says what is wrong.
 """
 from __future__ import annotations
 
@@ -16,7 +20,9 @@ import torch
 
 _BF16 = torch.bfloat16
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libapbv.so")
+_MARSHAL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal.so")
 _lib = None
+_native = None
 
 
 class ApbvError(RuntimeError):
@@ -50,13 +56,15 @@ class ApbvAttentionItem(ctypes.Structure):
 
 def load_library() -> ctypes.CDLL:
     """Load libapbv.so (built in-tree by ``paper_2601_21444_amd.build``); raises if it is missing."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
         raise RuntimeError(
             f"{_LIB_PATH} is missing: build the HIP library first (python -m paper_2601_21444_amd.build). "
             "There is no CPU or PyTorch fallback for the APB-V hot path.")
+    if not os.path.exists(_MARSHAL_PATH):
+        raise RuntimeError(f"{_MARSHAL_PATH} is missing: build the library first (python -m paper_2601_21444_amd.build).")
     lib = ctypes.CDLL(_LIB_PATH)
     lib.apbv_status_string.restype = ctypes.c_char_p
     lib.apbv_status_string.argtypes = [ctypes.c_int]
@@ -100,6 +108,10 @@ def load_library() -> ctypes.CDLL:
     lib.apbv_host_attention_group.argtypes = [
         ctypes.c_int, ctypes.POINTER(ApbvAttentionItem), ctypes.c_int, ctypes.c_int, ctypes.c_int,
         ctypes.c_float, ctypes.c_void_p]
+    from . import _marshal
+    if _raw_stream is not None and _current_device is not None:
+        _marshal.use_stream(torch.cuda.is_initialized, _current_device, _raw_stream)
+    _native = _marshal
     _lib = lib
     return lib
 
@@ -177,6 +189,17 @@ def apbv_compress_reduced_workspace_bytes(reducer: str, batch: int, n_q_heads: i
                                                                     head_dim, n_q, L, l_p))
 
 
+def _compress_result(st: int, k_local, idx_out, k_c_out, v_c_out, scores_out, return_scores: bool):
+    if st != 0:
+        raise ApbvError(st, "apbv_compress_kv")
+    if k_local.dim() != 4:
+        idx_out, k_c_out, v_c_out = idx_out[0], k_c_out[0], v_c_out[0]
+        scores_out = scores_out[0] if scores_out is not None else None
+    if return_scores:
+        return idx_out, k_c_out, v_c_out, scores_out
+    return idx_out, k_c_out, v_c_out
+
+
 def apbv_compress_kv(q_probe: torch.Tensor, k_local: torch.Tensor, v_local: torch.Tensor, l_p: int, *,
                      reducer: str = "sum", softmax_scale: float = 0.0,
                      return_scores: bool = False, workspace: Optional[torch.Tensor] = None,
@@ -187,7 +210,10 @@ def apbv_compress_kv(q_probe: torch.Tensor, k_local: torch.Tensor, v_local: torc
     include/apbv.h.  Tensors are ``[tokens, heads, d]`` or batched ``[batch, tokens, heads, d]``.  A ``reducer``
     other than "sum" ("max", "softmax_sum") goes through apbv_compress_kv_reduced."""
     lib = load_library()
-    batched = k_local.dim() == 4
+    if stream is None and workspace is not None and type(reducer) is str and reducer in REDUCERS and not (return_scores and scores_out is None):
+        st = _native.compress_kv(q_probe, k_local, v_local, l_p, REDUCERS[reducer], softmax_scale, idx_out, k_c_out, v_c_out, scores_out, workspace)
+        if st is not None:
+            return _compress_result(st, k_local, idx_out, k_c_out, v_c_out, scores_out, return_scores)
     qv, bq = tensor_view(q_probe)
     kv, b = tensor_view(k_local)
     vv, bv = tensor_view(v_local)
@@ -220,14 +246,7 @@ def apbv_compress_kv(q_probe: torch.Tensor, k_local: torch.Tensor, v_local: torc
         v_c_out.data_ptr() if l_p > 0 else None,
         scores_out.data_ptr() if scores_out is not None else None,
         workspace.data_ptr(), workspace.numel() * workspace.element_size(), _stream_ptr(stream))
-    if st != 0:
-        raise ApbvError(st, "apbv_compress_kv")
-    if not batched:
-        idx_out, k_c_out, v_c_out = idx_out[0], k_c_out[0], v_c_out[0]
-        scores_out = scores_out[0] if scores_out is not None else None
-    if return_scores:
-        return idx_out, k_c_out, v_c_out, scores_out
-    return idx_out, k_c_out, v_c_out
+    return _compress_result(st, k_local, idx_out, k_c_out, v_c_out, scores_out, return_scores)
 
 
 NOALLOC_MAX_WORKSPACE_BYTES = 4194304      # APBV_NOALLOC_MAX_WORKSPACE_BYTES of include/apbv.h
@@ -239,6 +258,12 @@ def apbv_compress_kv_noalloc(q_probe: torch.Tensor, k_local: torch.Tensor, v_loc
     """apbv_compress_kv without a workspace (the library's static scratch array) and without any allocation here
     either: the caller passes every output.  See apbv_compress_kv_noalloc in include/apbv.h."""
     lib = load_library()
+    if stream is None:
+        st = _native.compress_kv(q_probe, k_local, v_local, l_p, -1, 0.0, idx_out, k_c_out, v_c_out, scores_out, None)
+        if st is not None:
+            if st != 0:
+                raise ApbvError(st, "apbv_compress_kv_noalloc")
+            return idx_out, k_c_out, v_c_out
     qv, bq = tensor_view(q_probe)
     kv, b = tensor_view(k_local)
     vv, bv = tensor_view(v_local)
@@ -261,6 +286,15 @@ def apbv_compress_kv_noalloc(q_probe: torch.Tensor, k_local: torch.Tensor, v_loc
     return idx_out, k_c_out, v_c_out
 
 
+def _attention_result(st: int, what: str, q: torch.Tensor, out: torch.Tensor, lse_out: Optional[torch.Tensor], return_lse: bool):
+    if st != 0:
+        raise ApbvError(st, what)
+    if q.dim() != 4:
+        out = out[0] if out.dim() == 4 else out
+        lse_out = lse_out[0] if (lse_out is not None and lse_out.dim() == 3) else lse_out
+    return (out, lse_out) if return_lse else out
+
+
 def apbv_host_attention(q_local: torch.Tensor, k_anchor: torch.Tensor, v_anchor: torch.Tensor,
                         k_pass: torch.Tensor, v_pass: torch.Tensor, k_local: torch.Tensor, v_local: torch.Tensor,
                         softmax_scale: float, *, return_lse: bool = False, out: Optional[torch.Tensor] = None,
@@ -268,7 +302,10 @@ def apbv_host_attention(q_local: torch.Tensor, k_anchor: torch.Tensor, v_anchor:
     """Fused host attention over [anchor | passing | local(causal)]; see apbv_host_attention in
     include/apbv.h.  Returns ``out [.., L, Hq, d]`` bf16 (and ``lse [.., Hq, L]`` fp32)."""
     lib = load_library()
-    batched = q_local.dim() == 4
+    if stream is None and out is not None and not (return_lse and lse_out is None):
+        st = _native.host_attention(q_local, k_anchor, v_anchor, k_pass, v_pass, k_local, v_local, softmax_scale, out, lse_out)
+        if st is not None:
+            return _attention_result(st, "apbv_host_attention", q_local, out, lse_out, return_lse)
     views = []
     b = None
     for t in (q_local, k_anchor, v_anchor, k_pass, v_pass, k_local, v_local):
@@ -289,12 +326,7 @@ def apbv_host_attention(q_local: torch.Tensor, k_anchor: torch.Tensor, v_anchor:
         lse_out = torch.empty((b, hq, L), dtype=torch.float32, device=dev)
     st = lib.apbv_host_attention(b, hq, hkv, d, *views, float(softmax_scale), out.data_ptr(),
                                  lse_out.data_ptr() if lse_out is not None else None, _stream_ptr(stream))
-    if st != 0:
-        raise ApbvError(st, "apbv_host_attention")
-    if not batched:
-        out = out[0] if out.dim() == 4 else out
-        lse_out = lse_out[0] if (lse_out is not None and lse_out.dim() == 3) else lse_out
-    return (out, lse_out) if return_lse else out
+    return _attention_result(st, "apbv_host_attention", q_local, out, lse_out, return_lse)
 
 
 def apbv_host_attention_group(problems, softmax_scale: float, *, return_lse: bool = False,
@@ -304,6 +336,12 @@ def apbv_host_attention_group(problems, softmax_scale: float, *, return_lse: boo
     ``[tokens, heads, d]`` tensors (optionally followed by preallocated ``out`` and ``lse_out``).  Returns the list of
     outputs (of ``(out, lse)`` pairs with ``return_lse``)."""
     lib = load_library()
+    if stream is None:
+        st = _native.attention_group(problems, softmax_scale, bool(return_lse))
+        if st is not None:
+            if st != 0:
+                raise ApbvError(st, "apbv_host_attention_group")
+            return [(p[7], p[8]) if return_lse else p[7] for p in problems]
     n = len(problems)
     items = (ApbvAttentionItem * max(n, 1))()
     results = []
@@ -354,7 +392,10 @@ def apbv_query_attention(q_block: torch.Tensor, k_anchor: torch.Tensor, v_anchor
     """Attention of a short query block with the key axis split over workgroups; see apbv_query_attention in
     include/apbv.h.  Same tensors and results as :func:`apbv_host_attention`."""
     lib = load_library()
-    batched = q_block.dim() == 4
+    if stream is None and out is not None and workspace is not None and not (return_lse and lse_out is None):
+        st = _native.query_attention(q_block, k_anchor, v_anchor, k_pass, v_pass, k_local, v_local, softmax_scale, n_splits, out, lse_out, workspace)
+        if st is not None:
+            return _attention_result(st, "apbv_query_attention", q_block, out, lse_out, return_lse)
     views = []
     b = None
     for t in (q_block, k_anchor, v_anchor, k_pass, v_pass, k_local, v_local):
@@ -382,12 +423,7 @@ def apbv_query_attention(q_block: torch.Tensor, k_anchor: torch.Tensor, v_anchor
                                   lse_out.data_ptr() if lse_out is not None else None,
                                   workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                   _stream_ptr(stream))
-    if st != 0:
-        raise ApbvError(st, "apbv_query_attention")
-    if not batched:
-        out = out[0] if out.dim() == 4 else out
-        lse_out = lse_out[0] if (lse_out is not None and lse_out.dim() == 3) else lse_out
-    return (out, lse_out) if return_lse else out
+    return _attention_result(st, "apbv_query_attention", q_block, out, lse_out, return_lse)
 
 
 def apbv_merge_lse(parts_out: torch.Tensor, parts_lse: torch.Tensor, *, return_lse: bool = False,
@@ -397,6 +433,12 @@ def apbv_merge_lse(parts_out: torch.Tensor, parts_lse: torch.Tensor, *, return_l
     ``parts_out [n_parts, rows, Hq, d]`` bf16 (parts may be strided along dim 0), ``parts_lse [n_parts, Hq, rows]``
     fp32.  Returns ``out [rows, Hq, d]`` bf16 (and ``lse [Hq, rows]`` fp32)."""
     lib = load_library()
+    if stream is None and out is not None and not (return_lse and lse_out is None):
+        st = _native.merge_lse(parts_out, parts_lse, out, lse_out)
+        if st is not None:
+            if st != 0:
+                raise ApbvError(st, "apbv_merge_lse")
+            return (out, lse_out) if return_lse else out
     if parts_out.dtype != torch.bfloat16 or parts_lse.dtype != torch.float32:
         raise TypeError("expected bfloat16 partial outputs and float32 log-sum-exps")
     n, rows, hq, d = parts_out.shape

@@ -1,9 +1,11 @@
-"""Build libapbv.so (gfx950) in-tree with hipcc.  `python -m paper_2601_21444_amd.build`."""
+"""Build libapbv.so (gfx950) in-tree with hipcc, and the native marshalling of the Python binding (_marshal.so) with the host
+compiler.  `python -m paper_2601_21444_amd.build`."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +13,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libapbv.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 # source -> flags of its own.  attention.hip, query_attention.hip: no NaN can arise on its arithmetic paths (masked logits are -inf and
 # every inf - inf is guarded), and telling the compiler so drops a canonicalising v_max in front of every maximum.
 SOURCES = {
@@ -32,8 +35,23 @@ FLAGS = [
 ]
 
 
+def marshal_commands():
+    """Compile and link command of _marshal.so; it calls the libapbv.so beside it."""
+    import torch
+    from torch.utils import cpp_extension
+    cxx = os.environ.get("CXX", "g++")
+    obj = os.path.join(OBJ, "marshal.o")
+    includes = [f for p in [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]] for f in ("-isystem", p)]
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return ([cxx, "-O2", "-std=c++17", "-fPIC", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *includes,
+             "-I", os.path.join(ROOT, "include"), "-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj],
+            [cxx, "-shared", obj, "-L", PKG, "-l:libapbv.so", "-Wl,-rpath,$ORIGIN", "-L", torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
+             "-o", MARSHAL])
+
+
 def build(verbose: bool = True, extra=()) -> str:
     os.makedirs(OBJ, exist_ok=True)
+    compile_marshal, link_marshal = marshal_commands()
 
     def compile_one(item):
         src, own = item
@@ -44,12 +62,15 @@ def build(verbose: bool = True, extra=()) -> str:
         subprocess.run(cmd, check=True)
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(len(SOURCES), 8)) as pool:
+    with ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, 8)) as pool:
+        marshal = pool.submit(subprocess.run, compile_marshal, check=True)
         objs = list(pool.map(compile_one, SOURCES.items()))
+        marshal.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    subprocess.run(link_marshal, check=True)
     return LIB
 
 
