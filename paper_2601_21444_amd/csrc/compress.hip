@@ -16,6 +16,9 @@
 //   select_gather_kernel  bucket sort by value of the scores above the l_p-th largest (exact fallback: radix select
 //                       + bitonic sort), into (score descending, index ascending) order; K_c, V_c rows
 //                                                                         [parts x Hkv x batch]
+// for a few heads of longer blocks
+//   coarse_histogram_kernel  counts of the scores per coarse bin          [n_hist x Hkv x batch]
+//   long_select_gather_kernel  as above, over the coarse bins of a part   [parts x Hkv x batch]
 // and otherwise the same as two launches
 //   select_kernel       the ordered indices                               [Hkv x batch]
 //   gather_kernel       K_c, V_c rows                                     [l_p*Hkv/.. x batch]
@@ -226,6 +229,7 @@ struct SelectShared {
   uint64_t prefix;
   uint32_t need, bucket, cnt, n_cand, t_bin, crowded;
   int b_lo, b_hi;             // kParts: lowest and highest bucket of the part
+  int order[2];
   uint32_t wave_tot[kSelectThreads / 64];
   float red_lo[kSelectThreads / 64], red_hi[kSelectThreads / 64];
 };
@@ -675,6 +679,24 @@ __global__ __launch_bounds__(256) void gather_kernel(View k, View v, const int32
   __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(v_c + dst));
 }
 
+// K_c, V_c rows first .. first + n_out - 1 of a head from the token indices in `rows` (LDS), by one workgroup.
+template <int D>
+__device__ __forceinline__ void copy_rows(const View& k, const View& v, const uint32_t* rows, uint32_t first, uint32_t n_out, int b, int head, int hkv, int64_t l_p,
+                                          bf16_t* __restrict__ k_c, bf16_t* __restrict__ v_c) {
+  constexpr int KC = D / 8;
+  const bf16_t* kb = k.ptr + (int64_t)b * k.sb + (int64_t)head * k.sh;
+  const bf16_t* vb = v.ptr + (int64_t)b * v.sb + (int64_t)head * v.sh;
+  for (uint32_t item = threadIdx.x; item < n_out * KC; item += kSelectThreads) {
+    const uint32_t i = item / KC, c = item % KC;
+    const int64_t j = rows[i];
+    const int64_t dst = (((int64_t)b * l_p + first + i) * hkv + head) * D + 8 * c;
+    const u32x4 kk = *reinterpret_cast<const u32x4*>(kb + j * k.st + 8 * c);
+    const u32x4 vv = *reinterpret_cast<const u32x4*>(vb + j * v.st + 8 * c);
+    __builtin_nontemporal_store(kk, reinterpret_cast<u32x4*>(k_c + dst));
+    __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(v_c + dst));
+  }
+}
+
 // Selection and gather in one launch, n_parts workgroups per (KV head, batch item).  A head's selection alone leaves all
 // but one compute unit idle, and a gather launched behind it waits for the launch; here every workgroup repeats the part
 // that needs all scores (load, minimum and maximum, histogram, scan) and shares the rest: it scatters and ranks its own
@@ -691,7 +713,6 @@ __global__ __launch_bounds__(kSelectThreads) void select_gather_kernel(const dou
                                                                        bf16_t* __restrict__ k_c, bf16_t* __restrict__ v_c) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   __shared__ SelectShared sh;
-  constexpr int KC = D / 8;
   const int part = blockIdx.x, n_parts = gridDim.x, head = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x;
   const int64_t h = (int64_t)b * hkv + head;
@@ -719,17 +740,299 @@ __global__ __launch_bounds__(kSelectThreads) void select_gather_kernel(const dou
     for (uint32_t i = tid; i < n_out; i += kSelectThreads) idx[first + i] = (int32_t)rows[i];
   }
   __syncthreads();
-  const bf16_t* kb = k.ptr + (int64_t)b * k.sb + (int64_t)head * k.sh;
-  const bf16_t* vb = v.ptr + (int64_t)b * v.sb + (int64_t)head * v.sh;
-  for (uint32_t item = tid; item < n_out * KC; item += kSelectThreads) {
-    const uint32_t i = item / KC, c = item % KC;
-    const int64_t j = rows[i];
-    const int64_t dst = (((int64_t)b * l_p + first + i) * hkv + head) * D + 8 * c;
-    const u32x4 kk = *reinterpret_cast<const u32x4*>(kb + j * k.st + 8 * c);
-    const u32x4 vv = *reinterpret_cast<const u32x4*>(vb + j * v.st + 8 * c);
-    __builtin_nontemporal_store(kk, reinterpret_cast<u32x4*>(k_c + dst));
-    __builtin_nontemporal_store(vv, reinterpret_cast<u32x4*>(v_c + dst));
+  copy_rows<D>(k, v, rows, first, n_out, b, head, hkv, l_p, k_c, v_c);
+}
+
+// ------------------------------------------------------------------------------------------------
+// Selection of long blocks (more scores than a workgroup keeps in registers), a few heads: a histogram by several workgroups
+// per head, then selection and gather by several.  One workgroup that reads a head's scores three times, and the gather, took
+// 46 of the call's 57 us (one item of 2 heads x 65536 keys, 2000 rows); these take 6.5 and 17, of which 8 read the scores
+// (512 KB at what one unit's cache delivers), 1.2 find the bins' bounds and 5 are the buckets, the ranking and the copy.
+//
+// The coarse map is linear between the smallest and a quarter past the largest of a fixed sample of the head's scores, clamped
+// at both ends: monotone, and the same in every workgroup without one that has seen all scores.  It looks at the upper 32
+// bits of a score only, so that a bin is a range of these, ordered as signed integers, and the many scores outside a
+// workgroup's bins cost one comparison each.
+constexpr int kSampleScores = 4096;            // in lines of sixteen
+constexpr int kSubBins = 8;                    // LDS bins per coarse bin while counting (fewer collisions)
+
+__device__ __forceinline__ int clamped_bin(float y, int bins) { return (int)fminf(fmaxf(y, 0.0f), (float)(bins - 1)); }      // NaN: 0
+
+// The upper half of a float64 and its place in the order of the scores (as a signed integer; the map is its own inverse).
+__device__ __forceinline__ int upper_order(int hi) { return hi ^ ((hi >> 31) & 0x7fffffff); }
+constexpr int kOrderInf = 0x7ff00000;          // of +infinity; above it lie NaNs, which the maps send to bin 0
+__device__ __forceinline__ float upper_value(int hi) { return (float)__hiloint2double(hi, 0); }
+
+// The smallest place in the order, up to kOrderInf + 1, whose coarse bin is at least b: 64 probes a round, one a lane.
+__device__ __forceinline__ int first_of_bin(int b, float lo, float inv) {
+  const int lane = threadIdx.x & 63;
+  int64_t a = upper_order((int)0xfff00000), z = (int64_t)kOrderInf + 1;      // from -infinity
+  while (a < z) {
+    const int64_t step = (z - a + 63) / 64, probe = a + lane * step;
+    const bool there = probe >= z || clamped_bin((upper_value(upper_order((int)probe)) - lo) * inv, kCoarseBins) >= b;
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(there);
+    if (mask == 0) {
+      a += 63 * step + 1;
+    } else {
+      const int n = __builtin_ctzll(mask);
+      const int64_t to = a + n * step;
+      if (n > 0) a += (n - 1) * step + 1;
+      z = to < z ? to : z;
+    }
   }
+  return (int)z;
+}
+
+// Smallest and largest of a value per thread over the workgroup, in every thread.
+__device__ __forceinline__ void block_range(float& lo, float& hi, float* red_lo, float* red_hi) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  lo = wave_min(lo);
+  hi = wave_max(hi);
+  if (lane == 0) {
+    red_lo[wave] = lo;
+    red_hi[wave] = hi;
+  }
+  __syncthreads();
+  lo = wave_min(red_lo[lane % (kSelectThreads / 64)]);
+  hi = wave_max(red_hi[lane % (kSelectThreads / 64)]);
+}
+
+// Counts of one part of a head's scores per coarse bin.  Grid (parts, Hkv, batch); a part has at most kResidentScores.
+__global__ __launch_bounds__(kSelectThreads) void coarse_histogram_kernel(const double* __restrict__ s_ws, int64_t L, int hkv, CoarseHistogram* __restrict__ out) {
+  __shared__ uint32_t hist[kCoarseBins * kSubBins];
+  __shared__ float red_lo[kSelectThreads / 64], red_hi[kSelectThreads / 64];
+  const int tid = threadIdx.x, part = blockIdx.x, n_parts = gridDim.x;
+  const int64_t head = (int64_t)blockIdx.z * hkv + blockIdx.y;
+  const double* s = s_ws + head * L;
+  const int64_t per = (L + n_parts - 1) / n_parts, begin = part * per, end = begin + per < L ? begin + per : L;
+  constexpr int kPer = kResidentScores / kSelectThreads, kSample = kSampleScores / kSelectThreads;
+  const int* upper = reinterpret_cast<const int*>(s) + 1;        // of score j: upper[2 * j]
+  int smp[kSample], sc[kPer];
+#pragma unroll
+  for (int u = 0; u < kSample; ++u) {
+    const int i = tid + u * kSelectThreads;
+    smp[u] = upper[2 * ((int64_t)(i / 16) * (L / (kSampleScores / 16)) + i % 16)];
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int64_t j = begin + tid + u * kSelectThreads;
+    sc[u] = j < end ? upper[2 * j] : 0;
+  }
+  for (int i = tid; i < kCoarseBins * kSubBins; i += kSelectThreads) hist[i] = 0;
+  float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < kSample; ++u) {
+    const float x = upper_value(smp[u]);
+    lo = fminf(lo, x);
+    hi = fmaxf(hi, x);
+  }
+  block_range(lo, hi, red_lo, red_hi);
+  float inv = (float)kCoarseBins / ((hi - lo) * 1.25f);
+  if (!(inv > 0.0f) || !(inv < 1.0e30f)) inv = 0.0f;            // equal, or not finite: no map
+#pragma unroll
+  for (int u = 0; u < kPer; ++u)
+    if (begin + tid + u * kSelectThreads < end) atomicAdd(&hist[clamped_bin((upper_value(sc[u]) - lo) * inv * (float)kSubBins, kCoarseBins * kSubBins)], 1u);
+  __syncthreads();
+  CoarseHistogram* o = out + head * n_parts + part;
+  if (tid < kCoarseBins) {
+    uint32_t n = 0;
+#pragma unroll
+    for (int i = 0; i < kSubBins; ++i) n += hist[tid * kSubBins + i];
+    o->count[tid] = (uint16_t)n;
+  }
+  if (tid == 0) {
+    o->lo = lo;
+    o->inv = inv;
+  }
+}
+
+// Grid (parts, Hkv, batch).  Every workgroup adds the parts' histograms and takes the coarse bins whose output offset lies in
+// its share of the l_p outputs; it collects the scores of those bins, all it has to know of the others being their number,
+// sorts them by buckets as bucket_rank_select does, over their own range, and copies the rows.  Where its scores are too many
+// or too alike for that it sorts the head's l_p largest exactly and takes its outputs from there.
+template <int D>
+__global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(const double* __restrict__ s_ws, View k, View v, int64_t L, int64_t l_p, int n_hist,
+                                                                            const CoarseHistogram* __restrict__ coarse, int32_t* __restrict__ idx_out, int hkv,
+                                                                            bf16_t* __restrict__ k_c, bf16_t* __restrict__ v_c) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
+  __shared__ SelectShared sh;
+  constexpr int kItems = (int)(kLdsSortMax / kSelectThreads);
+  const int part = blockIdx.x, n_parts = gridDim.x, head = blockIdx.y, b = blockIdx.z;
+  const int tid = threadIdx.x;
+  const int64_t h = (int64_t)b * hkv + head;
+  const double* s = s_ws + h * L;
+  int32_t* idx = idx_out + h * l_p;
+  uint64_t* skeys = reinterpret_cast<uint64_t*>(dyn);
+  uint32_t* sidx = reinterpret_cast<uint32_t*>(dyn + kLdsSortMax * sizeof(uint64_t));
+  uint16_t* sbin = reinterpret_cast<uint16_t*>(sidx + kLdsSortMax);
+
+  // ---- the upper halves of the scores, sixteen a thread at a time: the first travel while the bins are found
+  constexpr uint32_t kLoads = 16, kStep = kLoads * kSelectThreads;
+  const uint32_t n_keys = (uint32_t)L;                       // (32-bit offsets: 64-bit ones were most of the loop's instructions)
+  const char* upper = reinterpret_cast<const char*>(s) + 4;
+  int hi[kLoads];
+  auto load = [&](uint32_t j0) {                             // (past the end: the last score, not taken)
+#pragma unroll
+    for (uint32_t u = 0; u < kLoads; ++u) {
+      const uint32_t j = j0 + u * kSelectThreads;
+      hi[u] = *reinterpret_cast<const int*>(upper + (size_t)((j < n_keys ? j : n_keys - 1) * 8u));
+    }
+  };
+  load(tid);
+
+  // ---- the workgroup's coarse bins: thread t has bin kCoarseBins - 1 - t, descending
+  const CoarseHistogram* ch = coarse + h * n_hist;
+  const float lo = ch->lo, inv = ch->inv;
+  const uint32_t from = (uint32_t)(l_p * part / n_parts), to = (uint32_t)(l_p * (part + 1) / n_parts);
+  uint32_t first = from, n_out = to - from, n_loc = 0;
+  bool exact = !(inv > 0.0f);
+  if (tid == 0) {
+    sh.b_lo = kCoarseBins;
+    sh.b_hi = -1;
+    sh.cnt = 0;
+    sh.crowded = 0;
+  }
+  for (int i = tid; i < kBins; i += kSelectThreads) sh.hist[i] = 0;
+  uint32_t c = 0;
+  if (tid < kCoarseBins)
+    for (int q = 0; q < n_hist; ++q) c += ch[q].count[kCoarseBins - 1 - tid];
+  uint32_t total;
+  __syncthreads();
+  const uint32_t excl = block_scan_incl<true>(c, sh, &total) - c;
+  if (c != 0 && excl >= from && excl < to) {
+    atomicMin(&sh.b_lo, kCoarseBins - 1 - tid);
+    atomicMax(&sh.b_hi, kCoarseBins - 1 - tid);
+  }
+  if (tid < kCoarseBins) {
+    sh.base[kCoarseBins - 1 - tid] = excl;
+    sh.fill[kCoarseBins - 1 - tid] = excl + c;
+  }
+  __syncthreads();
+  const int b_lo = sh.b_lo, b_hi = sh.b_hi;
+  if (!exact) {
+    if (b_hi < 0) return;                                    // no bin begins in this share
+    first = sh.base[b_hi];
+    n_loc = sh.fill[b_lo] - first;
+    n_out = first + n_loc < (uint32_t)l_p ? n_loc : (uint32_t)l_p - first;
+    exact = n_loc > (uint32_t)kLdsSortMax;
+  }
+  __syncthreads();
+
+  if (!exact) {
+    // ---- collect the indices of the bins' scores, in any order
+    if (tid < 128) {
+      const int bound = first_of_bin(tid < 64 ? b_lo : b_hi + 1, lo, inv);
+      if ((tid & 63) == 0) sh.order[tid >> 6] = bound;
+    }
+    __syncthreads();
+    const int lowest = b_lo > 0 ? sh.order[0] : (int)0x80000000;
+    const uint32_t width = (uint32_t)((b_hi < kCoarseBins - 1 ? sh.order[1] : kOrderInf + 1) - lowest);
+    for (uint32_t j0 = tid; j0 < n_keys; j0 += kStep) {
+      uint32_t hits = 0;                                     // (few: their stores are one short loop behind the comparisons)
+#pragma unroll
+      for (uint32_t u = 0; u < kLoads; ++u) {
+        const int order = upper_order(hi[u]);
+        hits |= (uint32_t)((uint32_t)(order - lowest) < width || (b_lo == 0 && order > kOrderInf)) << u;
+      }
+      const uint32_t left = (n_keys - j0 + kSelectThreads - 1) / kSelectThreads;
+      if (left < kLoads) hits &= (1u << left) - 1;
+      if (j0 + kStep < n_keys) load(j0 + kStep);              // travels while the hits are stored
+      while (hits != 0) {
+        const uint32_t pos = atomicAdd(&sh.cnt, 1u);
+        if (pos < n_loc) sidx[pos] = j0 + (uint32_t)__builtin_ctz(hits) * kSelectThreads;      // (always: the same map counted them)
+        hits &= hits - 1;
+      }
+    }
+    __syncthreads();
+    // ---- buckets of equal width over the collected scores; every thread holds up to kItems of them
+    double x[kItems];
+    uint32_t ix[kItems], bin[kItems];                        // bucket | arrival order << 11
+    float lo2 = INFINITY, hi2 = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kItems; ++u) {
+      const uint32_t pos = tid + u * kSelectThreads;
+      x[u] = 0.0;
+      ix[u] = bin[u] = 0;
+      if (pos < n_loc) {
+        ix[u] = sidx[pos];
+        x[u] = s[ix[u]];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kItems; ++u) {
+      if (tid + u * kSelectThreads < n_loc) {
+        lo2 = fminf(lo2, (float)x[u]);
+        hi2 = fmaxf(hi2, (float)x[u]);
+      }
+    }
+    block_range(lo2, hi2, sh.red_lo, sh.red_hi);
+    float inv2 = (float)kBins / (hi2 - lo2);
+    if (!(inv2 > 0.0f) || !(inv2 < 1.0e30f)) inv2 = 0.0f;    // all alike: one bucket
+#pragma unroll
+    for (int u = 0; u < kItems; ++u)
+      if (tid + u * kSelectThreads < n_loc) {
+        const uint32_t q = (uint32_t)clamped_bin(((float)x[u] - lo2) * inv2, kBins);
+        bin[u] = q | (atomicAdd(&sh.hist[q], 1u) << 11);
+      }
+    __syncthreads();
+    const int b0 = kBins - 1 - 2 * tid, b1 = kBins - 2 - 2 * tid;
+    const uint32_t c0 = sh.hist[b0], c1 = sh.hist[b1];
+    const uint32_t before = block_scan_incl<true>(c0 + c1, sh, &total) - (c0 + c1);
+    sh.base[b0] = before;
+    sh.base[b1] = before + c0;
+    if (c0 > kMaxBinRank || c1 > kMaxBinRank) sh.crowded = 1;
+    __syncthreads();
+    exact = sh.crowded != 0;
+    if (!exact) {
+#pragma unroll
+      for (int u = 0; u < kItems; ++u)
+        if (tid + u * kSelectThreads < n_loc) {
+          const uint32_t q = bin[u] & (uint32_t)(kBins - 1), pos = sh.base[q] + (bin[u] >> 11);
+          skeys[pos] = score_key(x[u]);
+          sidx[pos] = ix[u];
+          sbin[pos] = (uint16_t)q;
+        }
+      __syncthreads();
+      uint32_t out_pos[kItems];
+#pragma unroll
+      for (int u = 0; u < kItems; ++u) {
+        const uint32_t pos = tid + u * kSelectThreads;
+        out_pos[u] = n_out;
+        if (pos >= n_loc) continue;
+        const uint32_t q = sbin[pos], begin = sh.base[q], end = begin + sh.hist[q];
+        const uint64_t key = skeys[pos];
+        const uint32_t index = sidx[pos];
+        uint32_t rank = 0;
+        for (uint32_t e = begin; e < end; ++e) rank += precedes(skeys[e], sidx[e], key, index) ? 1u : 0u;
+        out_pos[u] = begin + rank;
+        ix[u] = index;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kItems; ++u)
+        if (out_pos[u] < n_out) {
+          sidx[out_pos[u]] = ix[u];
+          idx[first + out_pos[u]] = (int32_t)ix[u];
+        }
+    }
+  }
+  const uint32_t* rows = sidx;
+  if (exact) {
+    radix_collect(s, L, l_p, skeys, sidx, sh);
+    int64_t n_sort = 1;
+    while (n_sort < l_p) n_sort <<= 1;
+    __syncthreads();
+    for (int64_t i = l_p + tid; i < n_sort; i += kSelectThreads) {   // padding sorts last
+      skeys[i] = 0;
+      sidx[i] = 0xffffffffu;
+    }
+    __syncthreads();
+    bitonic_sort(skeys, sidx, n_sort);
+    rows = sidx + first;
+    for (uint32_t i = tid; i < n_out; i += kSelectThreads) idx[first + i] = (int32_t)rows[i];
+  }
+  __syncthreads();
+  copy_rows<D>(k, v, rows, first, n_out, b, head, hkv, l_p, k_c, v_c);
 }
 
 // Scratch of the entry point that takes no workspace (apbv_compress_kv_noalloc): a fixed array in the code object,
@@ -759,6 +1062,9 @@ apbv_status device_state(DeviceState& out) {
       return APBV_ERR_LAUNCH;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_gather_kernel<64>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(&select_gather_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess)
+      return APBV_ERR_LAUNCH;
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&long_select_gather_kernel<64>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess ||
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&long_select_gather_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess)
       return APBV_ERR_LAUNCH;
     if (!prepare_matrix_scores()) return APBV_ERR_LAUNCH;
     void* ptr = nullptr;
@@ -838,6 +1144,16 @@ apbv_status launch_compress(const CompressParams& p_in, hipStream_t stream) {
       launch(select_gather_kernel<128>, grid, dim3(kSelectThreads), dyn, scores, p.k, p.v, p.L, p.l_p, w.n_sort, p.idx_out, p.hkv, p.k_c, p.v_c);
     else
       launch(select_gather_kernel<64>, grid, dim3(kSelectThreads), dyn, scores, p.k, p.v, p.L, p.l_p, w.n_sort, p.idx_out, p.hkv, p.k_c, p.v_c);
+  } else if (const LongSelection plan = plan_long_selection((int64_t)p.hkv * p.batch, p.d, p.L, p.l_p, w); plan.n_parts > 0) {
+    // the histograms lie where the partial sums of the pooled queries were
+    CoarseHistogram* coarse = reinterpret_cast<CoarseHistogram*>(ws + w.qbar_off);
+    launch(coarse_histogram_kernel, dim3((unsigned)plan.n_hist, p.hkv, p.batch), dim3(kSelectThreads), 0, scores, p.L, p.hkv, coarse);
+    const dim3 grid((unsigned)plan.n_parts, p.hkv, p.batch);
+    const size_t dyn = (size_t)kLdsSortMax * 14;
+    if (p.d == 128)
+      launch(long_select_gather_kernel<128>, grid, dim3(kSelectThreads), dyn, scores, p.k, p.v, p.L, p.l_p, plan.n_hist, coarse, p.idx_out, p.hkv, p.k_c, p.v_c);
+    else
+      launch(long_select_gather_kernel<64>, grid, dim3(kSelectThreads), dyn, scores, p.k, p.v, p.L, p.l_p, plan.n_hist, coarse, p.idx_out, p.hkv, p.k_c, p.v_c);
   } else if (p.l_p > 0) {
     // select + order
     if (w.sort_in_global) {

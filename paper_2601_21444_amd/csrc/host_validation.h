@@ -500,6 +500,33 @@ inline bool share_selection(int64_t heads, int64_t L, int64_t l_p, const Compres
          (w.n_sort < kLdsSortMax || l_p + kMaxBinRank <= w.n_sort || L <= w.n_sort);
 }
 
+// Long blocks, a few heads: the scores' histogram by n_hist workgroups a head, selection and gather by n_parts (compress.hip);
+// n_parts = 0: a workgroup per head and a gather launch.  The histograms take the place of the partial sums of the pooled
+// query, kPoolSplitMax * head_dim * 8 bytes a head, which bounds the length; every part reads all of a head's scores, which
+// bounds the heads.  Whole call, a workgroup per head / this (us, graph replay): 2 heads x 20000 keys 24.1 / 24.0, x 32768
+// 32.6 / 26.0, x 65536 57.7 / 35.7, x 250000 188 / 81; 16 x 65536 95.7 / 78.0; 32 x 30000 71.6 / 69.7; 48 x 20000 79.7 / 81.8.
+// From 8192 - kMaxBinRank rows on the bucket path of the one workgroup has no room and it sorts: 1 x 65536, 8192 rows 269 / 33.
+constexpr int kCoarseBins = 252;
+constexpr int kMaxLongHeads = 32, kLongScores = 24576;
+struct CoarseHistogram {         // of one part of a head's scores: counts (at most kResidentScores), and the map of all parts
+  uint16_t count[kCoarseBins];
+  float lo, inv;
+};
+static_assert(sizeof(CoarseHistogram) == 512, "eight to the partial sums of a pooled query of 64");
+struct LongSelection {
+  int n_hist, n_parts;
+};
+inline LongSelection plan_long_selection(int64_t heads, int head_dim, int64_t L, int64_t l_p, const CompressWorkspace& w) {
+  const int64_t most = (int64_t)kPoolSplitMax * head_dim * (int64_t)sizeof(double) / (int64_t)sizeof(CoarseHistogram);
+  if (l_p < 1 || w.sort_in_global || L <= kResidentScores || L > most * kResidentScores || heads > kMaxLongHeads) return {0, 0};
+  if (L < kLongScores && (w.n_sort < kLdsSortMax || l_p + (int64_t)kMaxBinRank <= w.n_sort)) return {0, 0};
+  int64_t n_hist = (L + kResidentScores / 2 - 1) / (kResidentScores / 2);
+  n_hist = n_hist < most ? n_hist : most;
+  int64_t n_parts = l_p / 32 < 16 ? l_p / 32 : 16;
+  n_parts = n_parts * heads <= 256 ? n_parts : 256 / heads;
+  return {(int)n_hist, (int)(n_parts > 1 ? n_parts : 1)};
+}
+
 inline size_t compress_workspace_bytes_checked(int batch, int n_kv_heads, int head_dim, int64_t L, int64_t l_p) {
   if (batch < 1 || n_kv_heads < 1 || (head_dim != 64 && head_dim != 128) || L < 1 || L > kMaxTokens || l_p < 0 || l_p > L)
     return 0;

@@ -1,0 +1,33 @@
+// Host check of the rule for the selection of long blocks (plan_long_selection): which calls of tests/test_gpu_long_select.py
+// take it, and for every call that does, that the histograms fit the pooled query's region and their counts, and the parts
+// have outputs.
+#include <cstdio>
+#include "host_validation.h"
+
+using namespace apbv;
+
+#define EXPECT(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+
+static LongSelection plan(int hkv, int batch, int d, int64_t L, int64_t l_p) {
+  return plan_long_selection((int64_t)hkv * batch, d, L, l_p, plan_compress_workspace(batch, hkv, d, L, l_p));
+}
+
+int main() {
+  struct { int hkv, batch, d; int64_t L, l_p; int n_parts; } cases[] = {
+      {1, 1, 64, 24576, 1, 1},     {1, 1, 64, 24575, 1, 0},     {2, 1, 64, 24577, 513, 16},  {2, 1, 128, 65536, 2000, 16}, {1, 2, 64, 40001, 8192, 16},
+      {1, 1, 64, 40001, 8193, 0},  {1, 1, 64, 17000, 8065, 16}, {1, 1, 64, 131072, 700, 16}, {1, 1, 64, 131073, 700, 0},   {1, 1, 128, 140000, 64, 2},
+      {2, 1, 64, 30000, 33, 1},    {4, 8, 64, 25000, 200, 6},   {3, 11, 64, 25000, 200, 0},  {2, 1, 128, 16384, 500, 0},   {1, 1, 64, 30000, 0, 0}};
+  for (const auto& c : cases) EXPECT(plan(c.hkv, c.batch, c.d, c.L, c.l_p).n_parts == c.n_parts);
+  for (int d : {64, 128})
+    for (int heads = 1; heads <= 40; heads += heads / 4 + 1)
+      for (int64_t L = 16000; L < 300000; L += L / 5 + 1)
+        for (int64_t l_p = 1; l_p <= 8200 && l_p <= L; l_p += l_p / 3 + 1) {
+          const CompressWorkspace w = plan_compress_workspace(1, heads, d, L, l_p);
+          const LongSelection s = plan_long_selection(heads, d, L, l_p, w);
+          if (s.n_parts == 0) continue;
+          EXPECT(w.qbar_off + (size_t)heads * s.n_hist * sizeof(CoarseHistogram) <= w.scores_off && w.n_sort <= kLdsSortMax);
+          EXPECT((L + s.n_hist - 1) / s.n_hist <= kResidentScores && s.n_parts <= l_p && s.n_parts * heads <= 256);
+        }
+  std::printf("long selection ok\n");
+  return 0;
+}
