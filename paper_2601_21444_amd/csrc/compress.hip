@@ -10,8 +10,9 @@
 // Launches on the caller's stream:
 //   pool_query_kernel   partial sums of q_bar (float64), up to 8 row ranges per pooled query
 //                                                                         [splits x Hkv x batch workgroups]
-//   score_kernel        s[v, j], 16-byte coalesced reads of K rows; adds the partial sums of q_bar as it starts;
-//                       scores stored through to memory as it runs         [L/64 x Hkv x batch]
+//   score_kernel        s[v, j], 16-byte coalesced reads of K rows; adds the partial sums of q_bar as it starts, or (few
+//                       probe rows) the rows, without the launch in front; scores stored through to memory as it runs
+//                                                                         [L/64 x Hkv x batch]
 // then, for a few heads of at most 16384 keys,
 //   select_gather_kernel  bucket sort by value of the scores above the l_p-th largest (exact fallback: radix select
 //                       + bitonic sort), into (score descending, index ascending) order; K_c, V_c rows
@@ -118,10 +119,12 @@ __global__ __launch_bounds__(T) void pool_query_kernel(View q, int64_t n_q, int 
 // ------------------------------------------------------------------------------------------------
 // s[b, v, j] = q_bar[b, v, :] . K[b, j, v, :].  D/8 lanes per key row, each lane 8 elements (one
 // 16-byte load), fixed summation order per row so identical rows get identical scores.
-template <int D>
+// kPool: every workgroup adds the few probe rows of its pooled query itself, behind its key loads, and there is no launch
+// for it (pools_in_scores: where).
+template <int D, bool kPool>
 __global__ __launch_bounds__(256) void score_kernel(View k, int64_t L, const double* __restrict__ qpart, int n_split,
                                                     double* __restrict__ s_ws, double* __restrict__ s_out,
-                                                    int hkv, int rows_per_block) {
+                                                    int hkv, int rows_per_block, View q, int group) {
   constexpr int LPR = D / 8;               // lanes per row
   constexpr int RPS = 256 / LPR;           // rows per step of the workgroup
   constexpr int UNROLL = 4;
@@ -130,7 +133,8 @@ __global__ __launch_bounds__(256) void score_kernel(View k, int64_t L, const dou
   const int c = threadIdx.x % LPR;
   const int rsub = threadIdx.x / LPR;
   __shared__ double qs[D];
-  const double* qb = qpart + ((int64_t)b * hkv + v) * n_split * D;      // n_split partial sums of the pooled query
+  __shared__ double rows[kPool ? RPS : 1][kPool ? D : 1];
+  const double* qb = kPool ? nullptr : qpart + ((int64_t)b * hkv + v) * n_split * D;      // n_split partial sums of the pooled query
   const bf16_t* base = k.ptr + (int64_t)b * k.sb + (int64_t)v * k.sh + 8 * c;
   const int64_t out_base = ((int64_t)b * hkv + v) * L;
   const int64_t r_begin = (int64_t)blockIdx.x * rows_per_block;
@@ -147,7 +151,40 @@ __global__ __launch_bounds__(256) void score_kernel(View k, int64_t L, const dou
     }
     // The pooled query reaches the lanes through LDS -- one 16-byte load by D/2 lanes per workgroup, behind the
     // key loads, instead of four loads per lane in front of them.
-    if (r0 == r_begin) {
+    if (kPool && r0 == r_begin) {
+      const bf16_t* qrow = q.ptr + (int64_t)b * q.sb + (int64_t)v * group * q.sh + 8 * c;
+      const int n_rows = (int)q.tokens * group;
+      double sum[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sum[e] = 0.0;
+      for (int r = rsub; r < n_rows; r += 4 * RPS) {
+        u32x4 y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int rr = r + u * RPS, t = rr / group;
+          y[u] = u32x4{0u, 0u, 0u, 0u};                      // +0.0: adds nothing
+          if (rr < n_rows) y[u] = *reinterpret_cast<const u32x4*>(qrow + (int64_t)t * q.st + (int64_t)(rr - t * group) * q.sh);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            sum[2 * e] += bf16_to_f64(y[u][e] & 0xffffu);
+            sum[2 * e + 1] += bf16_to_f64(y[u][e] >> 16);
+          }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) rows[rsub][8 * c + e] = sum[e];
+      __syncthreads();
+      if (threadIdx.x < D) {
+        double t = 0.0;
+#pragma unroll
+        for (int r = 0; r < RPS; ++r) t += rows[r][threadIdx.x];
+        qs[threadIdx.x] = t;
+      }
+      __syncthreads();
+    }
+    if (!kPool && r0 == r_begin) {
       if (threadIdx.x < D / 2) {
         // all partial sums are fetched before the first addition (independent loads), then added in index order
         double2 part[kPoolSplitMax];
@@ -1113,26 +1150,31 @@ apbv_status launch_compress(const CompressParams& p_in, hipStream_t stream) {
     const apbv_status st = launch_matrix_scores(p, scores, ws + stats_off, stream);
     if (st != APBV_OK) return st;
   } else {
-    // pooled query, as n_split partial sums
-    const int n_split = pool_splits(p.q_probe.tokens * p.group, (int64_t)p.batch * p.hkv);
-    const int64_t rows_per_split = (p.q_probe.tokens * p.group + n_split - 1) / n_split;
-    const bool wide = rows_per_split >= 4 * 1024 / (p.d / 8);
-    const dim3 pool_grid(n_split, p.hkv, p.batch);
-    if (p.d == 128 && wide)
-      launch(pool_query_kernel<128, 1024>, pool_grid, dim3(1024), 0, p.q_probe, p.q_probe.tokens, p.group, qbar, p.hkv, n_split);
-    else if (p.d == 128)
-      launch(pool_query_kernel<128, 256>, pool_grid, dim3(256), 0, p.q_probe, p.q_probe.tokens, p.group, qbar, p.hkv, n_split);
-    else if (wide)
-      launch(pool_query_kernel<64, 1024>, pool_grid, dim3(1024), 0, p.q_probe, p.q_probe.tokens, p.group, qbar, p.hkv, n_split);
-    else
-      launch(pool_query_kernel<64, 256>, pool_grid, dim3(256), 0, p.q_probe, p.q_probe.tokens, p.group, qbar, p.hkv, n_split);
+    const int64_t n_rows = p.q_probe.tokens * p.group;
+    const bool pooled = pools_in_scores(n_rows, p.d, (int64_t)p.hkv * p.batch, p.L);
+    const int n_split = pool_splits(n_rows, (int64_t)p.batch * p.hkv);
+    if (!pooled) {
+      // pooled query, as n_split partial sums
+      const int64_t rows_per_split = (n_rows + n_split - 1) / n_split;
+      const bool wide = rows_per_split >= 4 * 1024 / (p.d / 8);
+      const dim3 pool_grid(n_split, p.hkv, p.batch);
+      if (p.d == 128 && wide)
+        launch(pool_query_kernel<128, 1024>, pool_grid, dim3(1024), 0, p.q_probe, p.q_probe.tokens, p.group, qbar, p.hkv, n_split);
+      else if (p.d == 128)
+        launch(pool_query_kernel<128, 256>, pool_grid, dim3(256), 0, p.q_probe, p.q_probe.tokens, p.group, qbar, p.hkv, n_split);
+      else if (wide)
+        launch(pool_query_kernel<64, 1024>, pool_grid, dim3(1024), 0, p.q_probe, p.q_probe.tokens, p.group, qbar, p.hkv, n_split);
+      else
+        launch(pool_query_kernel<64, 256>, pool_grid, dim3(256), 0, p.q_probe, p.q_probe.tokens, p.group, qbar, p.hkv, n_split);
+    }
     // scores: one outer iteration per workgroup: 4 rows in flight per thread, many small workgroups
     const int rows_per_block = 4 * 256 / (p.d / 8);
     dim3 grid((unsigned)((p.L + rows_per_block - 1) / rows_per_block), p.hkv, p.batch);
+    auto score = [&](auto kernel) { launch(kernel, grid, dim3(256), 0, p.k, p.L, qbar, n_split, scores, p.scores_out, p.hkv, rows_per_block, p.q_probe, p.group); };
     if (p.d == 128)
-      launch(score_kernel<128>, grid, dim3(256), 0, p.k, p.L, qbar, n_split, scores, p.scores_out, p.hkv, rows_per_block);
+      pooled ? score(score_kernel<128, true>) : score(score_kernel<128, false>);
     else
-      launch(score_kernel<64>, grid, dim3(256), 0, p.k, p.L, qbar, n_split, scores, p.scores_out, p.hkv, rows_per_block);
+      pooled ? score(score_kernel<64, true>) : score(score_kernel<64, false>);
   }
   // (a few heads' selection is shared by several workgroups each, in parts of at least 32 rows, and copies its rows too)
   int64_t n_parts = p.l_p / 32 < kMaxSelectParts ? p.l_p / 32 : kMaxSelectParts;

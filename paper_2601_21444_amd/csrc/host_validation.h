@@ -451,6 +451,16 @@ inline int pool_splits(int64_t n_rows, int64_t n_pooled) {
   return (int)(s < 1 ? 1 : (s > kPoolSplitMax ? kPoolSplitMax : s));
 }
 
+// Whether the scoring workgroups add up the pooled query themselves (compress.hip) instead of a launch in front of them, which
+// costs about 2.5 us: few probe rows (16-byte loads a thread) read again by few workgroups.  Whole call, with the launch /
+// without (us, graph replay): 16 rows of 64, 4 workgroups 11.4 / 9.6; 64 rows of 128, 64 workgroups 13.4 / 11.7, 512 15.1 /
+// 13.6, 1504 16.8 / 17.7; 96 rows, 512 15.0 / 14.4; 160 rows, 250 14.1 / 13.5, 512 14.9 / 15.6; 512 rows, 64 14.1 / 17.3;
+// 256 rows of 64, 256 14.6 / 13.6, 1024 16.3 / 18.0.
+inline bool pools_in_scores(int64_t n_rows, int head_dim, int64_t heads, int64_t L) {
+  const double loads = (double)n_rows * head_dim / 2048, workgroups = (double)heads * (double)((L * head_dim + 8191) / 8192);
+  return loads <= 10 && workgroups / 256 * (loads + 1) <= 17;
+}
+
 inline int64_t pow2_ceil(int64_t x) {
   int64_t n = 1;
   while (n < x) n <<= 1;

@@ -1,6 +1,7 @@
-// Host check of the rule for the selection of long blocks (plan_long_selection): which calls of tests/test_gpu_long_select.py
-// take it, and for every call that does, that the histograms fit the pooled query's region and their counts, and the parts
-// have outputs.
+// Host checks of two rules of the compression.  Selection of long blocks (plan_long_selection): which calls of
+// tests/test_gpu_long_select.py take it, and for every call that does, that the histograms fit the pooled query's region and
+// their counts, and the parts have outputs.  Pooled query without a launch of its own (pools_in_scores): both sides of the
+// line, among them the calls of tests/test_gpu_pooled_scores.py.
 #include <cstdio>
 #include "host_validation.h"
 
@@ -28,6 +29,12 @@ int main() {
           EXPECT(w.qbar_off + (size_t)heads * s.n_hist * sizeof(CoarseHistogram) <= w.scores_off && w.n_sort <= kLdsSortMax);
           EXPECT((L + s.n_hist - 1) / s.n_hist <= kResidentScores && s.n_parts <= l_p && s.n_parts * heads <= 256);
         }
-  std::printf("long selection ok\n");
+  EXPECT(pools_in_scores(64, 128, 2, 16384) && !pools_in_scores(160, 128, 2, 16384) && pools_in_scores(160, 128, 2, 8000));
+  EXPECT(pools_in_scores(256, 64, 2, 16384) && !pools_in_scores(256, 64, 8, 16384) && !pools_in_scores(64, 128, 8, 12000));
+  EXPECT(!pools_in_scores(512, 128, 2, 2000) && !pools_in_scores(512, 128, 1, 1) && pools_in_scores(1, 64, 1, 1));
+  for (int64_t rows : {1, 15, 16, 17, 64, 65, 160}) EXPECT(pools_in_scores(rows, 128, 2, 700));
+  for (int64_t rows : {31, 33, 128, 129, 320}) EXPECT(pools_in_scores(rows, 64, 2, 700));
+  EXPECT(!pools_in_scores(161, 128, 2, 700) && !pools_in_scores(321, 64, 2, 700));
+  std::printf("compression rules ok\n");
   return 0;
 }
