@@ -377,21 +377,20 @@ __device__ __forceinline__ void bitonic_sort(uint64_t* skeys, uint32_t* sidx, in
 // kParts: n_parts workgroups share a head.  Each takes the buckets whose output offset lies in its share of the l_p
 // outputs, scatters and ranks those alone, and leaves their indices in sh.fill, outputs [*out_first, *out_first +
 // *n_out).  The histogram, and with it the decision to give up, is the same in every workgroup.
-template <bool kParts>
+template <bool kParts, int kPer = kResidentScores / kSelectThreads>
 __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s, int64_t L, int64_t l_p, int64_t cap,
                                                    uint64_t* skeys, uint32_t* sidx, uint16_t* sbin,
                                                    int32_t* __restrict__ idx_out, SelectShared& sh, int part = 0,
                                                    int n_parts = 1, uint32_t* out_first = nullptr, uint32_t* n_out = nullptr) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int kPer = kResidentScores / kSelectThreads;
   const bool resident = kParts || L <= kResidentScores;      // (heads are shared only where the scores are resident)
   double sc[kPer];
   uint32_t bins[kPer];                                       // bucket | arrival order in the bucket << 11
   if (resident) {
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
-      const int64_t j = tid + (int64_t)u * kSelectThreads;
-      sc[u] = j < L ? s[j] : 0.0;
+      const uint32_t j = (uint32_t)tid + (uint32_t)u * kSelectThreads;
+      sc[u] = j < (uint32_t)L ? *reinterpret_cast<const double*>(reinterpret_cast<const char*>(s) + (size_t)(j * 8u)) : 0.0;
     }
   }
   // minimum and maximum, in single precision (the conversion is monotone, which is all the map needs)
@@ -740,11 +739,14 @@ __device__ __forceinline__ void copy_rows(const View& k, const View& v, const ui
 // buckets and copies the rows it has found.  The exact path, where it is needed, runs in every workgroup, each copying
 // its share of the rows.  Two heads of 16384 scores and 1024 rows: 9.8 + 2.4 us and the gap between -> 10.5 us, of which
 // 2.4 load the scores, 3.6 are minimum and maximum, histogram and scan (issue-bound, repeated), 0.8 the copy.
+// kPer: scores a thread holds.  Every loop over them is unrolled, and steps without a score are neither free to issue nor to
+// fetch, so short blocks take a shorter body: whole call with 16 a thread / as many as it takes (us, graph replay): 512 keys
+// 9.9 / 8.0, 1000 (8 heads) 11.4 / 9.6, 2048 13.3 / 11.8, 4096 14.0 / 12.7, 8192 14.3 / 13.5.
 constexpr int kMaxSelectParts = 16;
 static_assert(kLdsSortMax / kMaxSelectParts + 1 + (int64_t)kMaxBinRank <= kBins && 64 + (int64_t)kMaxBinRank <= kBins,
               "a part's share of the outputs and one bucket more fit sh.fill");
 
-template <int D>
+template <int D, int kPer>
 __global__ __launch_bounds__(kSelectThreads) void select_gather_kernel(const double* __restrict__ s_ws, View k, View v, int64_t L, int64_t l_p,
                                                                        int64_t cap, int32_t* __restrict__ idx_out, int hkv,
                                                                        bf16_t* __restrict__ k_c, bf16_t* __restrict__ v_c) {
@@ -760,7 +762,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_gather_kernel(const dou
   uint16_t* sbin = reinterpret_cast<uint16_t*>(sidx + cap);
   uint32_t first = 0, n_out = 0;
   const uint32_t* rows = sh.fill;
-  if (!bucket_rank_select<true>(s, L, l_p, cap, skeys, sidx, sbin, idx, sh, part, n_parts, &first, &n_out)) {
+  if (!bucket_rank_select<true, kPer>(s, L, l_p, cap, skeys, sidx, sbin, idx, sh, part, n_parts, &first, &n_out)) {
     radix_collect(s, L, l_p, skeys, sidx, sh);
     int64_t n_sort = 1;
     while (n_sort < l_p) n_sort <<= 1;
@@ -1087,6 +1089,15 @@ struct DeviceState {
 std::mutex g_state_mutex;
 DeviceState g_state[kMaxDevices];
 
+template <int D>
+bool allow_select_lds() {
+  for (const void* f : {reinterpret_cast<const void*>(&select_gather_kernel<D, 1>), reinterpret_cast<const void*>(&select_gather_kernel<D, 2>),
+                        reinterpret_cast<const void*>(&select_gather_kernel<D, 4>), reinterpret_cast<const void*>(&select_gather_kernel<D, 8>),
+                        reinterpret_cast<const void*>(&select_gather_kernel<D, 12>), reinterpret_cast<const void*>(&select_gather_kernel<D, 16>)})
+    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess) return false;
+  return true;
+}
+
 apbv_status device_state(DeviceState& out) {
   int device = -1;
   if (hipGetDevice(&device) != hipSuccess || device < 0) return APBV_ERR_LAUNCH;
@@ -1097,9 +1108,7 @@ apbv_status device_state(DeviceState& out) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(kLdsSortMax * 14)) != hipSuccess)
       return APBV_ERR_LAUNCH;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&select_gather_kernel<64>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&select_gather_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess)
-      return APBV_ERR_LAUNCH;
+    if (!allow_select_lds<64>() || !allow_select_lds<128>()) return APBV_ERR_LAUNCH;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&long_select_gather_kernel<64>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(&long_select_gather_kernel<128>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsSortMax * 14)) != hipSuccess)
       return APBV_ERR_LAUNCH;
@@ -1182,10 +1191,19 @@ apbv_status launch_compress(const CompressParams& p_in, hipStream_t stream) {
   if (share_selection((int64_t)p.hkv * p.batch, p.L, p.l_p, w)) {
     const dim3 grid((unsigned)n_parts, p.hkv, p.batch);
     const size_t dyn = (size_t)w.n_sort * 14;
-    if (p.d == 128)
-      launch(select_gather_kernel<128>, grid, dim3(kSelectThreads), dyn, scores, p.k, p.v, p.L, p.l_p, w.n_sort, p.idx_out, p.hkv, p.k_c, p.v_c);
-    else
-      launch(select_gather_kernel<64>, grid, dim3(kSelectThreads), dyn, scores, p.k, p.v, p.L, p.l_p, w.n_sort, p.idx_out, p.hkv, p.k_c, p.v_c);
+    auto select = [&](auto kernel) { launch(kernel, grid, dim3(kSelectThreads), dyn, scores, p.k, p.v, p.L, p.l_p, w.n_sort, p.idx_out, p.hkv, p.k_c, p.v_c); };
+    auto select_up_to = [&](auto per) {
+      constexpr int kPer = decltype(per)::value;
+      p.d == 128 ? select(select_gather_kernel<128, kPer>) : select(select_gather_kernel<64, kPer>);
+    };
+    switch ((p.L + kSelectThreads - 1) / kSelectThreads) {
+      case 1: select_up_to(std::integral_constant<int, 1>{}); break;
+      case 2: select_up_to(std::integral_constant<int, 2>{}); break;
+      case 3: case 4: select_up_to(std::integral_constant<int, 4>{}); break;
+      case 5: case 6: case 7: case 8: select_up_to(std::integral_constant<int, 8>{}); break;
+      case 9: case 10: case 11: case 12: select_up_to(std::integral_constant<int, 12>{}); break;
+      default: select_up_to(std::integral_constant<int, 16>{});
+    }
   } else if (const LongSelection plan = plan_long_selection((int64_t)p.hkv * p.batch, p.d, p.L, p.l_p, w); plan.n_parts > 0) {
     // the histograms lie where the partial sums of the pooled queries were
     CoarseHistogram* coarse = reinterpret_cast<CoarseHistogram*>(ws + w.qbar_off);
