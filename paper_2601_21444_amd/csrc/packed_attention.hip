@@ -13,7 +13,7 @@
 //                   A = V^T by two transposing reads of four consecutive keys each.
 // Bound by the sum of what a lone wave issues (about 750 cycles a tile of 32 keys from resident LDS, 1100 with the loads and
 // barriers, of which 520 are matrix instructions) and the start and end of the workgroups (6 to 7 us).  Per call with the merge, workgroups of
-// 16x16x32 / these (us): 64 queries x 16 / 2 heads of 128 over 16512 keys 22.7 / 20.9, 17 x 28 / 4 over 2 x 4150 17.3 / 15.1,
+// 16x16x32 / these (us): 64 queries x 16 / 2 heads of 128 over 16512 keys 22.7 / 20.4, 17 x 28 / 4 over 2 x 4150 17.3 / 15.1,
 // 64 x 8 / 2 of 64 over 16512 13.2 / 11.6, 300 x 8 / 2 of 64, two items, over 5100 21.2 / 19.0; where HBM or power bounds
 // them they are equal (512 x 16 / 2 over 100000 338 / 337).  Results against float64 are as before (same stages and widths).
 #include "apbv_common.h"
@@ -259,7 +259,7 @@ __device__ __forceinline__ void packed_workgroup(const AttnParams& p, const int 
   const int t_pipe_end = n_w < t_mask ? n_w : t_mask;
   while (t < n_tiles) {
     int n_hot = 0;
-    if (((t - t_begin) & 2) == 0 && t + 4 < t_pipe_end && kst.t_next == t + 3 && vst.t_next == t + 2) {
+    if (t + 4 < t_pipe_end && kst.t_next == t + 3 && vst.t_next == t + 2) {
       // whole rounds that start at t' with t' + 4 < t_pipe_end; their loads K(t'+3..t'+6), V(t'+2..t'+5) must lie in the
       // streams' current runs, or past the last tile, which is then loaded again (into slots nobody reads)
       n_hot = (t_pipe_end - 1 - t) / 4;
@@ -284,13 +284,8 @@ __device__ __forceinline__ void packed_workgroup(const AttnParams& p, const int 
       advance_reference(lm);
     }
     if (t >= n_tiles) break;
-    // two tiles of the general kind; past the wave's last tile S^T is formed from whatever the slot holds, and not used
-    arrive();
-    const int o0 = ((t - t_begin) & 2) * T::TILE_BYTES, o2 = o0 ^ (2 * T::TILE_BYTES);
-    if (t + 3 < n_tiles) kst.issue(k_ring + o2 + T::TILE_BYTES);
-    if (t + 4 < n_tiles) kst.issue(k_ring + o0);
-    if (t + 2 < n_tiles) vst.issue(v_ring + o2);
-    if (t + 3 < n_tiles) vst.issue(v_ring + o2 + T::TILE_BYTES);
+    // one round of the general kind; past the wave's last tile S^T is formed from whatever the slot holds, and not used (ring
+    // slots computed instead of written out were 4 % slower, 64 queries x 16 / 2 heads over 16512 keys 20.4 -> 21.3 us)
     auto step = [&](int tt, const unsigned char* kt_next, const unsigned char* vt, f32x16& sc, f32x16& sn) {
       if (tt >= n_w) return;
       load_k(kt_next, kf);
@@ -303,9 +298,22 @@ __device__ __forceinline__ void packed_workgroup(const AttnParams& p, const int 
         advance_reference(lm);
       }
     };
-    step(t, k_lds[0] + o0 + T::TILE_BYTES, v_lds[0] + o0, s_a, s_b);
-    step(t + 1, k_lds[0] + o2, v_lds[0] + o0 + T::TILE_BYTES, s_b, s_a);
-    t += 2;
+    arrive();
+    if (t + 3 < n_tiles) kst.issue(k_ring + 3 * T::TILE_BYTES);
+    if (t + 4 < n_tiles) kst.issue(k_ring);
+    if (t + 2 < n_tiles) vst.issue(v_ring + 2 * T::TILE_BYTES);
+    if (t + 3 < n_tiles) vst.issue(v_ring + 3 * T::TILE_BYTES);
+    step(t, k_lds[1], v_lds[0], s_a, s_b);
+    step(t + 1, k_lds[2], v_lds[1], s_b, s_a);
+    if (t + 2 >= n_tiles) break;
+    arrive();
+    if (t + 5 < n_tiles) kst.issue(k_ring + T::TILE_BYTES);
+    if (t + 6 < n_tiles) kst.issue(k_ring + 2 * T::TILE_BYTES);
+    if (t + 4 < n_tiles) vst.issue(v_ring);
+    if (t + 5 < n_tiles) vst.issue(v_ring + T::TILE_BYTES);
+    step(t + 2, k_lds[3], v_lds[2], s_a, s_b);
+    step(t + 3, k_lds[0], v_lds[3], s_b, s_a);
+    t += 4;
   }
 
   // ---- normalise, round, store.  A lane holds 4 of every 8 columns of its row; the halves exchange so that each stores 16
