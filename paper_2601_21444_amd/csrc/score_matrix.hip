@@ -290,11 +290,11 @@ __global__ __launch_bounds__(256, 3) void matrix_reduce_kernel(const RowsParams 
 
   // Tile t lives in ring slot t % 4.  One barrier per two tiles: after the barrier in front of tiles t, t+1 both have
   // landed and everyone is done with tiles t-2, t-1, whose slots take the loads of tiles t+2, t+3.
-  // Everything loaded so far with ordinary loads (the resident operands) has arrived: vmcnt 0, said with the builtin
-  // so that the compiler's own wait-count bookkeeping knows it; from here on only tile loads are outstanding.
-  __builtin_amdgcn_s_waitcnt(0x0F70);
+  // The first tiles travel beside the resident operands.  Then everything has arrived: vmcnt 0, said with the builtin so
+  // that the compiler's own wait-count bookkeeping knows it; from here on only tile loads are outstanding.
   issue(0);
   if (str0 + TR < str_end) issue(1);
+  __builtin_amdgcn_s_waitcnt(0x0F70);
   arrive();
   int slot = 0;
   for (int64_t tile0 = str0; tile0 < str_end; tile0 += 2 * TR, slot ^= 2) {
@@ -496,33 +496,47 @@ __global__ __launch_bounds__(64 * W, 2) void probe_resident_kernel(const RowsPar
   }
 }
 
-// One wave per (batch, head, row): merge the chunks' statistics into c_r = maximum + log2(normaliser); padding rows
-// get +inf.  Every real row has at least one key, so its normaliser is positive.
-__global__ __launch_bounds__(256) void row_stats_combine_kernel(const RowsParams p, int batch) {
-  const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (w >= (int64_t)batch * p.hkv * p.r_pad) return;
-  const int r = (int)(w % p.r_pad);
-  const int64_t bv = w / p.r_pad;
-  float cr = INFINITY;
-  if (r < p.n_rows) {
-    const float2* part = p.partial + bv * p.n_chunks * p.r_pad + r;
-    float m = -INFINITY;
-    for (int ch = lane; ch < p.n_chunks; ch += 64) m = fmaxf(m, part[(int64_t)ch * p.r_pad].x);
+// Merge the chunks' statistics of a row into c_r = maximum + log2(normaliser); padding rows get +inf.  Every real row has at
+// least one key, so its normaliser is positive.  A workgroup takes 64 rows of a (batch item, head), a wave every sixteenth chunk
+// of them, eight at once: lanes side by side read rows side by side, and a launch is one wait for memory (a wave per row, its
+// lanes over the chunks, read 8 bytes of a line each: 16 x 2 heads x 512 rows x 32 chunks 6.5 -> 4.7 us, the
+// call 176.4 -> 171.8 with the first tiles of the matrix passes requested beside their resident operands).
+constexpr int kCombineWaves = 16;
+__global__ __launch_bounds__(64 * kCombineWaves) void row_stats_combine_kernel(const RowsParams p) {
+  __shared__ float part_m[kCombineWaves][64], part_z[kCombineWaves][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = blockIdx.x * 64 + lane;
+  const int64_t bv = (int64_t)blockIdx.z * p.hkv + blockIdx.y;
+  const float2* part = p.partial + bv * p.n_chunks * p.r_pad + (r < p.r_pad ? r : p.r_pad - 1);
+  float m = -INFINITY, z = 0.f;
+  for (int c0 = wave; c0 < p.n_chunks; c0 += 8 * kCombineWaves) {
+    float2 s[8];
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));
-    float z = 0.f;
-    for (int ch = lane; ch < p.n_chunks; ch += 64) {
-      const float2 s = part[(int64_t)ch * p.r_pad];
-      z += s.y * __builtin_amdgcn_exp2f(s.x - m);
+    for (int u = 0; u < 8; ++u) {
+      const int ch = c0 + u * kCombineWaves;
+      s[u] = float2{-INFINITY, 0.f};
+      if (ch < p.n_chunks) s[u] = part[(int64_t)ch * p.r_pad];
     }
+    float m_new = m;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) z += __shfl_xor(z, d);
-    cr = m + __builtin_amdgcn_logf(z);      // v_log_f32 is a base-2 logarithm
+    for (int u = 0; u < 8; ++u) m_new = fmaxf(m_new, s[u].x);
+    const float m_sub = m_new > -INFINITY ? m_new : 0.f;   // (chunks of nothing but -inf logits)
+    z *= __builtin_amdgcn_exp2f(m - m_sub);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) z += s[u].y * __builtin_amdgcn_exp2f(s[u].x - m_sub);
+    m = m_new;
   }
-  if (lane == 0) p.stats[w] = cr;
+  part_m[wave][lane] = m;
+  part_z[wave][lane] = z;
+  __syncthreads();
+  if (wave != 0 || r >= p.r_pad) return;
+  float m_all = m, z_all = 0.f;
+#pragma unroll
+  for (int w = 1; w < kCombineWaves; ++w) m_all = fmaxf(m_all, part_m[w][lane]);
+#pragma unroll
+  for (int w = 0; w < kCombineWaves; ++w) z_all += part_z[w][lane] * __builtin_amdgcn_exp2f(part_m[w][lane] - m_all);
+  p.stats[bv * p.r_pad + r] = r < p.n_rows ? m_all + __builtin_amdgcn_logf(z_all) : INFINITY;      // v_log_f32 is a base-2 logarithm
 }
-
 
 }  // namespace
 
@@ -626,8 +640,7 @@ apbv_status launch_matrix_scores(const CompressParams& cp, double* scores, void*
       launch(matrix_reduce_kernel<128, kStats>, sgrid, dim3(256), 0, p);
     else
       launch(matrix_reduce_kernel<64, kStats>, sgrid, dim3(256), 0, p);
-    const int64_t n_stat = (int64_t)cp.batch * cp.hkv * p.r_pad;
-    launch(row_stats_combine_kernel, dim3((unsigned)((n_stat + 3) / 4)), dim3(256), 0, p, cp.batch);
+    launch(row_stats_combine_kernel, dim3((unsigned)((p.r_pad + 63) / 64), cp.hkv, cp.batch), dim3(64 * kCombineWaves), 0, p);
     if (cp.d == 128)
       launch_mass<128>(launch, p, cp.batch);
     else
