@@ -497,10 +497,11 @@ __global__ __launch_bounds__(64 * W, 2) void probe_resident_kernel(const RowsPar
 }
 
 // Merge the chunks' statistics of a row into c_r = maximum + log2(normaliser); padding rows get +inf.  Every real row has at
-// least one key, so its normaliser is positive.  A workgroup takes 64 rows of a (batch item, head), a wave every sixteenth chunk
-// of them, eight at once: lanes side by side read rows side by side, and a launch is one wait for memory (a wave per row, its
-// lanes over the chunks, read 8 bytes of a line each: 16 x 2 heads x 512 rows x 32 chunks 6.5 -> 4.7 us, the
-// call 176.4 -> 171.8 with the first tiles of the matrix passes requested beside their resident operands).
+// least one key, so its normaliser is positive.  A workgroup takes 64 rows of a (batch item, head); wave w has four consecutive
+// chunks of every 64 of them: lanes side by side read rows side by side, and up to 64 chunks are one wait for memory (a wave
+// per row, its lanes over the chunks, read 8 bytes of a line each: 16 x 2 heads x 512 rows x 32 chunks 6.5 -> 4.7 us, the
+// call 176.4 -> 171.8 with the first tiles of the matrix passes requested beside their resident operands).  Chunks 64 apart
+// are added in turn, then neighbours, then pairs of neighbours and so on: scores an ulp off would change places.
 constexpr int kCombineWaves = 16;
 __global__ __launch_bounds__(64 * kCombineWaves) void row_stats_combine_kernel(const RowsParams p) {
   __shared__ float part_m[kCombineWaves][64], part_z[kCombineWaves][64];
@@ -508,34 +509,46 @@ __global__ __launch_bounds__(64 * kCombineWaves) void row_stats_combine_kernel(c
   const int r = blockIdx.x * 64 + lane;
   const int64_t bv = (int64_t)blockIdx.z * p.hkv + blockIdx.y;
   const float2* part = p.partial + bv * p.n_chunks * p.r_pad + (r < p.r_pad ? r : p.r_pad - 1);
-  float m = -INFINITY, z = 0.f;
-  for (int c0 = wave; c0 < p.n_chunks; c0 += 8 * kCombineWaves) {
-    float2 s[8];
+  auto load = [&](int c0, float2 (&s)[4]) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int ch = c0 + u * kCombineWaves;
-      s[u] = float2{-INFINITY, 0.f};
-      if (ch < p.n_chunks) s[u] = part[(int64_t)ch * p.r_pad];
+    for (int e = 0; e < 4; ++e) {
+      s[e] = float2{-INFINITY, 0.f};
+      if (c0 + e < p.n_chunks) s[e] = part[(int64_t)(c0 + e) * p.r_pad];
     }
-    float m_new = m;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) m_new = fmaxf(m_new, s[u].x);
-    const float m_sub = m_new > -INFINITY ? m_new : 0.f;   // (chunks of nothing but -inf logits)
-    z *= __builtin_amdgcn_exp2f(m - m_sub);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) z += s[u].y * __builtin_amdgcn_exp2f(s[u].x - m_sub);
-    m = m_new;
+  };
+  auto largest = [](float m, const float2 (&s)[4]) { return fmaxf(fmaxf(m, fmaxf(s[0].x, s[1].x)), fmaxf(s[2].x, s[3].x)); };
+  float2 s[4];
+  load(4 * wave, s);
+  float m = largest(-INFINITY, s);
+  for (int c0 = 4 * wave + 64; c0 < p.n_chunks; c0 += 64) {
+    float2 more[4];
+    load(c0, more);
+    m = largest(m, more);
   }
   part_m[wave][lane] = m;
-  part_z[wave][lane] = z;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kCombineWaves; ++w) m = fmaxf(m, part_m[w][lane]);
+  float z[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) z[e] = 4 * wave + e < p.n_chunks ? s[e].y * __builtin_amdgcn_exp2f(s[e].x - m) : 0.f;
+  for (int c0 = 4 * wave + 64; c0 < p.n_chunks; c0 += 64) {
+    load(c0, s);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c0 + e < p.n_chunks) z[e] += s[e].y * __builtin_amdgcn_exp2f(s[e].x - m);
+  }
+  part_z[wave][lane] = (z[0] + z[1]) + (z[2] + z[3]);
   __syncthreads();
   if (wave != 0 || r >= p.r_pad) return;
-  float m_all = m, z_all = 0.f;
+  float t[kCombineWaves];
 #pragma unroll
-  for (int w = 1; w < kCombineWaves; ++w) m_all = fmaxf(m_all, part_m[w][lane]);
+  for (int w = 0; w < kCombineWaves; ++w) t[w] = part_z[w][lane];
 #pragma unroll
-  for (int w = 0; w < kCombineWaves; ++w) z_all += part_z[w][lane] * __builtin_amdgcn_exp2f(part_m[w][lane] - m_all);
-  p.stats[bv * p.r_pad + r] = r < p.n_rows ? m_all + __builtin_amdgcn_logf(z_all) : INFINITY;      // v_log_f32 is a base-2 logarithm
+  for (int n = kCombineWaves / 2; n > 0; n /= 2)
+#pragma unroll
+    for (int w = 0; w < n; ++w) t[w] = t[2 * w] + t[2 * w + 1];
+  p.stats[bv * p.r_pad + r] = r < p.n_rows ? m + __builtin_amdgcn_logf(t[0]) : INFINITY;      // v_log_f32 is a base-2 logarithm
 }
 
 }  // namespace
