@@ -592,10 +592,8 @@ apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t
   if (attention_shares_blocks(head_dim, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits)) return launch_variant<kWavesShort, 2>(p, head_dim, stream);
   // (a block of at most kAttnNarrowMaxRows rows is mostly padding in anything but 64-row workgroups)
   if (p.L <= kAttnNarrowMaxRows) return launch_variant<kWavesNarrow>(p, head_dim, stream);
-  switch (attention_rows(head_dim, p.group, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits)) {
-    case 32 * kWavesNarrow: return launch_variant<kWavesNarrow>(p, head_dim, stream);
-    case 32 * kWavesShort: return launch_variant<kWavesShort>(p, head_dim, stream);
-  }
+  // (its 64 rows are for launches that share blocks)
+  if (attention_rows(head_dim, p.group, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits) != kBM) return launch_variant<kWavesShort>(p, head_dim, stream);
   return launch_variant<kWaves>(p, head_dim, stream);
 }
 

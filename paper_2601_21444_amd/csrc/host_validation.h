@@ -175,7 +175,8 @@ inline double attention_traffic(int head_dim, int group, const AttentionTiles& w
 }
 // tiles[]: of the launch cut into 64, 128 and 256 rows; kv_heads: KV heads, batch items and key ranges that a row tile of
 // the launch belongs to one of.
-//   head_dim 64   few workgroups: 64 rows (8 heads x 2048 rows 44 / 31 / 28 us with 256 / 128 / 64 rows); else 128 (three fit a
+//   head_dim 64   few workgroups: 64 rows (8 heads x 2048 rows 44 / 31 / 28 us with 256 / 128 / 64 rows; these launches share
+//                 their blocks between two waves, attention_shares_blocks: 22); else 128 (three fit a
 //                 unit, one of 256 rows), but not where 256 rows are one round and 128 two with the second tile half empty
 //                 (192 workgroups of 132 rows 9.1 / 9.9)
 //   head_dim 128  by the estimates up to two rounds of 256 rows, whose spread they get right; beyond, and for the shortest
