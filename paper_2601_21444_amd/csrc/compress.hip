@@ -797,9 +797,6 @@ constexpr int kSubBins = 8;                    // LDS bins per coarse bin while 
 
 __device__ __forceinline__ int clamped_bin(float y, int bins) { return (int)fminf(fmaxf(y, 0.0f), (float)(bins - 1)); }      // NaN: 0
 
-// The upper half of a float64 and its place in the order of the scores (as a signed integer; the map is its own inverse).
-__device__ __forceinline__ int upper_order(int hi) { return hi ^ ((hi >> 31) & 0x7fffffff); }
-constexpr int kOrderInf = 0x7ff00000;          // of +infinity; above it lie NaNs, which the maps send to bin 0
 __device__ __forceinline__ float upper_value(int hi) { return (float)__hiloint2double(hi, 0); }
 
 // The smallest place in the order, up to kOrderInf + 1, whose coarse bin is at least b: 64 probes a round, one a lane.
@@ -965,13 +962,13 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
     }
     __syncthreads();
     const int lowest = b_lo > 0 ? sh.order[0] : (int)0x80000000;
-    const uint32_t width = (uint32_t)((b_hi < kCoarseBins - 1 ? sh.order[1] : kOrderInf + 1) - lowest);
+    const uint32_t width = order_distance(lowest, b_hi < kCoarseBins - 1 ? sh.order[1] : kOrderInf + 1);
     for (uint32_t j0 = tid; j0 < n_keys; j0 += kStep) {
       uint32_t hits = 0;                                     // (few: their stores are one short loop behind the comparisons)
 #pragma unroll
       for (uint32_t u = 0; u < kLoads; ++u) {
         const int order = upper_order(hi[u]);
-        hits |= (uint32_t)((uint32_t)(order - lowest) < width || (b_lo == 0 && order > kOrderInf)) << u;
+        hits |= (uint32_t)(order_distance(lowest, order) < width || (b_lo == 0 && order > kOrderInf)) << u;
       }
       const uint32_t left = (n_keys - j0 + kSelectThreads - 1) / kSelectThreads;
       if (left < kLoads) hits &= (1u << left) - 1;

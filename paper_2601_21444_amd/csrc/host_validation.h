@@ -538,6 +538,13 @@ inline LongSelection plan_long_selection(int64_t heads, int head_dim, int64_t L,
   return {(int)n_hist, (int)(n_parts > 1 ? n_parts : 1)};
 }
 
+// The upper half of a float64 and its place in the order of the scores (as a signed integer; the map is its own inverse).
+constexpr int upper_order(int hi) { return hi ^ ((hi >> 31) & 0x7fffffff); }
+constexpr int kOrderInf = 0x7ff00000;          // of +infinity; above it lie NaNs, which the maps send to bin 0
+// How far `to` lies above `from` in that order, modulo 2^32 (in unsigned arithmetic: the places of negative and of positive
+// scores are further apart than an int holds).  `to` lies in [from, past) where its distance is below that of `past`.
+constexpr uint32_t order_distance(int from, int to) { return (uint32_t)to - (uint32_t)from; }
+
 inline size_t compress_workspace_bytes_checked(int batch, int n_kv_heads, int head_dim, int64_t L, int64_t l_p) {
   if (batch < 1 || n_kv_heads < 1 || (head_dim != 64 && head_dim != 128) || L < 1 || L > kMaxTokens || l_p < 0 || l_p > L)
     return 0;

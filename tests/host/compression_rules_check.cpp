@@ -1,8 +1,10 @@
-// Host checks of two rules of the compression.  Selection of long blocks (plan_long_selection): which calls of
-// tests/test_gpu_long_select.py take it, and for every call that does, that the histograms fit the pooled query's region and
-// their counts, and the parts have outputs.  Pooled query without a launch of its own (pools_in_scores): both sides of the
-// line, among them the calls of tests/test_gpu_pooled_scores.py.
+// Host checks of two rules of the compression, and of the comparison that collects the scores of a long block.  Selection of
+// long blocks (plan_long_selection): which calls of tests/test_gpu_long_select.py take it, and for every call that does, that
+// the histograms fit the pooled query's region and their counts, and the parts have outputs.  Pooled query without a launch
+// of its own (pools_in_scores): both sides of the line, among them the calls of tests/test_gpu_pooled_scores.py.
+#include <cmath>
 #include <cstdio>
+#include <cstring>
 #include "host_validation.h"
 
 using namespace apbv;
@@ -29,6 +31,23 @@ int main() {
           EXPECT(w.qbar_off + (size_t)heads * s.n_hist * sizeof(CoarseHistogram) <= w.scores_off && w.n_sort <= kLdsSortMax);
           EXPECT((L + s.n_hist - 1) / s.n_hist <= kResidentScores && s.n_parts <= l_p && s.n_parts * heads <= 256);
         }
+  // the test that collects the scores of a range of bins, [lowest, past) in the order of their upper halves
+  const double values[] = {-INFINITY, -1e300, -1234.5, -1.0, -1e-300, -0.0, 0.0, 1e-300, 1.0, 1234.5, 1e300, INFINITY};
+  auto order_of = [](double x) {
+    int64_t bits;
+    std::memcpy(&bits, &x, sizeof bits);
+    return upper_order((int)(bits >> 32));
+  };
+  for (double a : values) {
+    EXPECT(upper_order(upper_order(order_of(a))) == order_of(a));
+    for (double b : values) {
+      EXPECT(!(a < b) || order_of(a) < order_of(b));
+      for (int past : {order_of(b), kOrderInf + 1})
+        for (double x : values)
+          if (order_of(a) <= past)
+            EXPECT((order_distance(order_of(a), order_of(x)) < order_distance(order_of(a), past)) == (order_of(a) <= order_of(x) && order_of(x) < past));
+    }
+  }
   EXPECT(pools_in_scores(64, 128, 2, 16384) && !pools_in_scores(160, 128, 2, 16384) && pools_in_scores(160, 128, 2, 8000));
   EXPECT(pools_in_scores(256, 64, 2, 16384) && !pools_in_scores(256, 64, 8, 16384) && !pools_in_scores(64, 128, 8, 12000));
   EXPECT(!pools_in_scores(512, 128, 2, 2000) && !pools_in_scores(512, 128, 1, 1) && pools_in_scores(1, 64, 1, 1));
