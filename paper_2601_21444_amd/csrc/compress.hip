@@ -799,7 +799,8 @@ __device__ __forceinline__ int clamped_bin(float y, int bins) { return (int)fmin
 
 __device__ __forceinline__ float upper_value(int hi) { return (float)__hiloint2double(hi, 0); }
 
-// The smallest place in the order, up to kOrderInf + 1, whose coarse bin is at least b: 64 probes a round, one a lane.
+// The smallest place in the order whose coarse bin is at least b, kOrderInf + 1 for the one past the last: 64 probes a round,
+// one a lane.
 __device__ __forceinline__ int first_of_bin(int b, float lo, float inv) {
   const int lane = threadIdx.x & 63;
   int64_t a = upper_order((int)0xfff00000), z = (int64_t)kOrderInf + 1;      // from -infinity
@@ -955,21 +956,20 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
   __syncthreads();
 
   if (!exact) {
-    // ---- collect the indices of the bins' scores, in any order
+    // ---- collect the indices of the bins' scores, in any order.  Bin 0, where NaNs are counted too, is never one of them: a part
+    // that holds it has every score from its first output down, which are more than the LDS sorts.
+    static_assert(kResidentScores >= 2 * kLdsSortMax, "L > kResidentScores, l_p <= kLdsSortMax: at least L - l_p + 1 scores");
     if (tid < 128) {
       const int bound = first_of_bin(tid < 64 ? b_lo : b_hi + 1, lo, inv);
       if ((tid & 63) == 0) sh.order[tid >> 6] = bound;
     }
     __syncthreads();
-    const int lowest = b_lo > 0 ? sh.order[0] : (int)0x80000000;
-    const uint32_t width = order_distance(lowest, b_hi < kCoarseBins - 1 ? sh.order[1] : kOrderInf + 1);
+    const int lowest = sh.order[0];
+    const uint32_t width = order_distance(lowest, sh.order[1]);
     for (uint32_t j0 = tid; j0 < n_keys; j0 += kStep) {
       uint32_t hits = 0;                                     // (few: their stores are one short loop behind the comparisons)
 #pragma unroll
-      for (uint32_t u = 0; u < kLoads; ++u) {
-        const int order = upper_order(hi[u]);
-        hits |= (uint32_t)(order_distance(lowest, order) < width || (b_lo == 0 && order > kOrderInf)) << u;
-      }
+      for (uint32_t u = 0; u < kLoads; ++u) hits |= (uint32_t)(order_distance(lowest, upper_order(hi[u])) < width) << u;
       const uint32_t left = (n_keys - j0 + kSelectThreads - 1) / kSelectThreads;
       if (left < kLoads) hits &= (1u << left) - 1;
       if (j0 + kStep < n_keys) load(j0 + kStep);              // travels while the hits are stored

@@ -30,6 +30,7 @@ int main() {
           if (s.n_parts == 0) continue;
           EXPECT(w.qbar_off + (size_t)heads * s.n_hist * sizeof(CoarseHistogram) <= w.scores_off && w.n_sort <= kLdsSortMax);
           EXPECT((L + s.n_hist - 1) / s.n_hist <= kResidentScores && s.n_parts <= l_p && s.n_parts * heads <= 256);
+          EXPECT(L - l_p + 1 > kLdsSortMax);      // a part with bin 0, which its collecting loop does not take, has as many
         }
   // the test that collects the scores of a range of bins, [lowest, past) in the order of their upper halves
   const double values[] = {-INFINITY, -1e300, -1234.5, -1.0, -1e-300, -0.0, 0.0, 1e-300, 1.0, 1234.5, 1e300, INFINITY};
