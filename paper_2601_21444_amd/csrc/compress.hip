@@ -885,8 +885,9 @@ __global__ __launch_bounds__(kSelectThreads) void coarse_histogram_kernel(const 
 
 // Grid (parts, Hkv, batch).  Every workgroup adds the parts' histograms and takes the coarse bins whose output offset lies in
 // its share of the l_p outputs; it collects the scores of those bins, all it has to know of the others being their number,
-// sorts them by buckets as bucket_rank_select does, over their own range, and copies the rows.  Where its scores are too many
-// or too alike for that it sorts the head's l_p largest exactly and takes its outputs from there.
+// sorts them by buckets as bucket_rank_select does, over their own range, and copies the rows.  Where they are too alike for
+// that it sorts them whole; where they are too many for the LDS it sorts the head's l_p largest, and takes its outputs from
+// there.
 template <int D>
 __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(const double* __restrict__ s_ws, View k, View v, int64_t L, int64_t l_p, int n_hist,
                                                                             const CoarseHistogram* __restrict__ coarse, int32_t* __restrict__ idx_out, int hkv,
@@ -922,6 +923,7 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
   const float lo = ch->lo, inv = ch->inv;
   const uint32_t from = (uint32_t)(l_p * part / n_parts), to = (uint32_t)(l_p * (part + 1) / n_parts);
   uint32_t first = from, n_out = to - from, n_loc = 0;
+  uint32_t n_sort = 0;                                       // entries left to sort by comparison exchanges, if any
   bool exact = !(inv > 0.0f);
   if (tid == 0) {
     sh.b_lo = kCoarseBins;
@@ -1018,8 +1020,15 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
     sh.base[b1] = before + c0;
     if (c0 > kMaxBinRank || c1 > kMaxBinRank) sh.crowded = 1;
     __syncthreads();
-    exact = sh.crowded != 0;
-    if (!exact) {
+    if (sh.crowded != 0) {
+      // too many alike to rank by comparison: what was collected is sorted as it is
+#pragma unroll
+      for (int u = 0; u < kItems; ++u) {
+        const uint32_t pos = tid + u * kSelectThreads;
+        if (pos < n_loc) skeys[pos] = score_key(x[u]);       // (sidx[pos] is ix[u])
+      }
+      n_sort = n_loc;
+    } else {
 #pragma unroll
       for (int u = 0; u < kItems; ++u)
         if (tid + u * kSelectThreads < n_loc) {
@@ -1055,16 +1064,19 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
   const uint32_t* rows = sidx;
   if (exact) {
     radix_collect(s, L, l_p, skeys, sidx, sh);
-    int64_t n_sort = 1;
-    while (n_sort < l_p) n_sort <<= 1;
+    n_sort = (uint32_t)l_p;
+    rows = sidx + first;
+  }
+  if (n_sort > 0) {
+    int64_t n_padded = 1;
+    while (n_padded < n_sort) n_padded <<= 1;
     __syncthreads();
-    for (int64_t i = l_p + tid; i < n_sort; i += kSelectThreads) {   // padding sorts last
+    for (int64_t i = n_sort + tid; i < n_padded; i += kSelectThreads) {   // padding sorts last
       skeys[i] = 0;
       sidx[i] = 0xffffffffu;
     }
     __syncthreads();
-    bitonic_sort(skeys, sidx, n_sort);
-    rows = sidx + first;
+    bitonic_sort(skeys, sidx, n_padded);
     for (uint32_t i = tid; i < n_out; i += kSelectThreads) idx[first + i] = (int32_t)rows[i];
   }
   __syncthreads();

@@ -89,3 +89,46 @@ def test_long_selection_of_matrix_scores(reducer):
         np.testing.assert_array_equal(idx[h].cpu().numpy(), order)
         rows = torch.from_numpy(order.copy()).cuda()
         assert torch.equal(k_c[:, h], k[rows, h]) and torch.equal(v_c[:, h], v[rows, h])
+
+
+def keys_of_scores(scores):
+    """Key rows whose scores under a probe of ones are exactly these float32 values: the sum of three bfloat16 pieces."""
+    k = np.zeros(scores.shape + (64,), dtype=np.uint16)
+    rest = scores.astype(np.float32)
+    for i in range(3):
+        k[..., i] = wl.f32_to_bf16_bits(rest)
+        rest = rest - wl.bf16_bits_to_f32(k[..., i])
+    assert not rest.any()
+    return k
+
+
+CROWDS = [
+    # L, l_p, distinct scores on top, how many alike below them, distinct ones below those: the rest lies far below
+    (30000, 500, 0, 128, 0),            # as many as a bucket ranks
+    (30000, 500, 0, 129, 0),            # one more: its part sorts what it collected
+    (30000, 500, 300, 4096, 0),         # a power of two to sort, and a cut among the alike
+    (30000, 5000, 700, 4097, 900),      # distinct outputs on both sides
+    (40000, 33, 5, 6000, 0),            # one part
+    (40000, 8192, 100, 5000, 4000),
+    (24576, 8192, 0, 7000, 3000),
+]
+
+
+@pytest.mark.parametrize("L,l_p,above,alike,below", CROWDS)
+def test_alike_scores_of_a_long_block(L, l_p, above, alike, below):
+    rng = np.random.default_rng((71, L, l_p, alike))
+    hkv = 2
+    scores = np.stack([rng.permutation(np.concatenate([9 + rng.random(above), np.full(alike, 8.5), 8 + 0.4 * rng.random(below),
+                                                       rng.standard_normal(L - above - alike - below) - 9])) for _ in range(hkv)]).astype(np.float32)
+    k = np.ascontiguousarray(keys_of_scores(scores).transpose(1, 0, 2))
+    q = wl.f32_to_bf16_bits(np.ones((1, hkv, 64), dtype=np.float32))
+    v = rng.integers(0, 1 << 15, k.shape, dtype=np.uint16)
+    dev = lambda x: torch.from_numpy(x.view(np.int16)).view(torch.bfloat16).cuda()
+    print(f"alike scores {L} {l_p}: {above} above {alike} above {below}", flush=True)
+    idx, k_c, v_c = apbv.apbv_compress_kv(dev(q), dev(k), dev(v), l_p)
+    torch.cuda.synchronize()
+    idx_r, kc_r, vc_r, s_r = oracle.compress_kv(q, k, v, l_p)
+    assert np.array_equal(s_r, scores)
+    bits = lambda t: t.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+    np.testing.assert_array_equal(idx.cpu().numpy(), idx_r)
+    assert np.array_equal(bits(k_c), kc_r) and np.array_equal(bits(v_c), vc_r)
