@@ -314,25 +314,12 @@ __device__ __forceinline__ float wave_max(float x) {
 }
 
 // Inclusive scan of one value per thread over the whole workgroup (1024 threads); returns the
-// inclusive prefix, *total gets the workgroup sum.  kFresh: wave_tot has not been used since the last barrier.
-template <bool kFresh = false>
+// inclusive prefix, *total gets the workgroup sum.  (wave_tot must not have been used since the last barrier.)
 __device__ __forceinline__ uint32_t block_scan_incl(uint32_t x, SelectShared& sh, uint32_t* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t incl = wave_scan_incl(x);
-  if (!kFresh) __syncthreads();         // wave_tot may still be read from a previous use
   if (lane == 63) sh.wave_tot[wave] = incl;
   __syncthreads();
-  if (!kFresh) {                        // (in the exact path; the scan below costs it 0.2 to 0.9 us of 20 to 50)
-    uint32_t base = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < kSelectThreads / 64; ++w) {
-      const uint32_t t = sh.wave_tot[w];
-      if (w < wave) base += t;
-      tot += t;
-    }
-    *total = tot;
-    return incl + base;
-  }
   // every wave scans the 16 totals itself, one a lane
   constexpr int kSelectWaves = kSelectThreads / 64;
   const uint32_t scan = wave_scan_incl(lane < kSelectWaves ? sh.wave_tot[lane] : 0u);
@@ -456,7 +443,7 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
   const int b0 = kBins - 1 - 2 * tid, b1 = kBins - 2 - 2 * tid;
   const uint32_t c0 = sh.hist[b0], c1 = sh.hist[b1];
   uint32_t total;
-  const uint32_t incl = block_scan_incl<true>(c0 + c1, sh, &total);
+  const uint32_t incl = block_scan_incl(c0 + c1, sh, &total);
   const uint32_t excl = incl - (c0 + c1);
   sh.base[b0] = excl;
   sh.base[b1] = excl + c0;
@@ -629,27 +616,42 @@ __device__ __forceinline__ void radix_collect(const double* __restrict__ s, int6
       }
     }
   } else {
-    // more equal keys than needed: take the `need` lowest indices.  Each thread scans a contiguous
-    // index range; an exclusive scan of the per-thread tie counts gives each tie its rank by index.
-    const int64_t chunk = (L + kSelectThreads - 1) / kSelectThreads;
-    const int64_t lo = (int64_t)tid * chunk, hi = (lo + chunk < L) ? lo + chunk : L;
+    // more equal keys than needed: take the `need` lowest indices.  Each wave takes a contiguous range, 64 keys side by side
+    // at a time; the waves' tie counts give each tie its rank by index.  (A range per thread read a line a lane.  Equal
+    // scores, us a call: 2 heads x 65536, 2000 rows 558 -> 529, 32 x 131072, 1000 rows 1343 -> 1140, 2 x 16384, 1024 rows
+    // 154 -> 147.)
+    constexpr int kWaves = kSelectThreads / 64;
+    const int64_t span = (L + kSelectThreads - 1) / kSelectThreads * 64;
+    const int64_t lo = wave * span, hi = lo + span < L ? lo + span : L;
     uint32_t n_eq = 0;
-    for (int64_t j = lo; j < hi; ++j) n_eq += (score_key(s[j]) == kth);
-    uint32_t total;
-    uint32_t rank = block_scan_incl(n_eq, sh, &total) - n_eq;
-    for (int64_t j = lo; j < hi; ++j) {
-      const uint64_t key = score_key(s[j]);
+#pragma unroll 8
+    for (int64_t j0 = lo; j0 < hi; j0 += 64) {
+      const int64_t j = j0 + lane;
+      n_eq += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(j < hi && score_key(s[j]) == kth));
+    }
+    if (lane == 0) sh.wave_tot[wave] = n_eq;
+    __syncthreads();
+    uint32_t rank = 0;                          // ties in front of the range, then of its next 64 keys
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) rank += w < wave ? sh.wave_tot[w] : 0u;
+#pragma unroll 8
+    for (int64_t j0 = lo; j0 < hi; j0 += 64) {
+      const int64_t j = j0 + lane;
+      const uint64_t key = j < hi ? score_key(s[j]) : 0;
+      const bool tie = j < hi && key == kth;
+      const uint64_t ties = __builtin_amdgcn_ballot_w64(tie);
       if (key > kth) {
         const uint32_t pos = atomicAdd(&sh.cnt, 1u);
         skeys[pos] = key;
         sidx[pos] = (uint32_t)j;
-      } else if (key == kth) {
-        if (rank < need) {
-          skeys[n_gt + rank] = key;
-          sidx[n_gt + rank] = (uint32_t)j;
+      } else if (tie) {
+        const uint32_t at = rank + __builtin_amdgcn_mbcnt_hi((uint32_t)(ties >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ties, 0u));
+        if (at < need) {
+          skeys[n_gt + at] = key;
+          sidx[n_gt + at] = (uint32_t)j;
         }
-        ++rank;
       }
+      rank += (uint32_t)__builtin_popcountll(ties);
     }
   }
 }
@@ -937,7 +939,7 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
     for (int q = 0; q < n_hist; ++q) c += ch[q].count[kCoarseBins - 1 - tid];
   uint32_t total;
   __syncthreads();
-  const uint32_t excl = block_scan_incl<true>(c, sh, &total) - c;
+  const uint32_t excl = block_scan_incl(c, sh, &total) - c;
   if (c != 0 && excl >= from && excl < to) {
     atomicMin(&sh.b_lo, kCoarseBins - 1 - tid);
     atomicMax(&sh.b_hi, kCoarseBins - 1 - tid);
@@ -1015,7 +1017,7 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
     __syncthreads();
     const int b0 = kBins - 1 - 2 * tid, b1 = kBins - 2 - 2 * tid;
     const uint32_t c0 = sh.hist[b0], c1 = sh.hist[b1];
-    const uint32_t before = block_scan_incl<true>(c0 + c1, sh, &total) - (c0 + c1);
+    const uint32_t before = block_scan_incl(c0 + c1, sh, &total) - (c0 + c1);
     sh.base[b0] = before;
     sh.base[b1] = before + c0;
     if (c0 > kMaxBinRank || c1 > kMaxBinRank) sh.crowded = 1;

@@ -60,3 +60,26 @@ def test_shared_selection(hkv, batch, L, l_p, kind):
         np.testing.assert_array_equal(idx[b].numpy(), idx_r)
         np.testing.assert_array_equal(k_c[b].view(torch.int16).numpy().view(np.uint16), kc_r)
         np.testing.assert_array_equal(v_c[b].view(torch.int16).numpy().view(np.uint16), vc_r)
+
+
+@pytest.mark.parametrize("L", [1, 63, 64, 65, 1023, 1024, 1025, 4097, 16384, 16385, 24577])
+def test_alike_scores_are_taken_in_index_order(L):
+    """The exact path's collection of equal scores, a range of keys a wave: ranges that end within 64 keys, are empty, or hold
+    one tie each; one workgroup a head (2 and 12 heads), shared selection, long blocks."""
+    for hkv, kind in ((2, "all"), (2, "few"), (12, "all")):
+        rng = np.random.default_rng((89, L, hkv))
+        l_p = max(1, L // 3)
+        bits = lambda *shape: wl.f32_to_bf16_bits(rng.standard_normal(shape).astype(np.float32))
+        dev = lambda x: torch.from_numpy(np.ascontiguousarray(x).view(np.int16)).view(torch.bfloat16).cuda()
+        k, q = np.repeat(bits(1, hkv, 64), L, axis=0), bits(2, hkv, 64)
+        if kind == "few":                       # some above the rest, the last key of each run of 64 among them
+            better = wl.f32_to_bf16_bits(np.sign(wl.bf16_bits_to_f32(q).sum(0)) * 4)
+            k[63::64] = better
+            k[-1] = better
+        v = rng.integers(0, 1 << 15, (L, hkv, 64), dtype=np.uint16)
+        print(f"alike L={L} hkv={hkv} {kind}", flush=True)
+        idx, k_c, v_c = (x.cpu() for x in apbv.apbv_compress_kv(dev(q), dev(k), dev(v), l_p))
+        idx_r, kc_r, vc_r, _ = oracle.compress_kv(q, k, v, l_p)
+        np.testing.assert_array_equal(idx.numpy(), idx_r)
+        np.testing.assert_array_equal(k_c.view(torch.int16).numpy().view(np.uint16), kc_r)
+        np.testing.assert_array_equal(v_c.view(torch.int16).numpy().view(np.uint16), vc_r)
