@@ -264,9 +264,10 @@ struct SelectShared {
   uint32_t base[kBins];       // entries in higher buckets (output offset of the bucket)
   uint32_t fill[kBins];       // scatter cursor per bucket
   uint64_t prefix;
-  uint32_t need, bucket, cnt, n_cand, t_bin, crowded;
+  uint32_t need, bucket, cnt, n_cand, t_bin, crowded, divided;
   int b_lo, b_hi;             // kParts: lowest and highest bucket of the part
-  int order[2];
+  int order[2];               // long blocks: a part's range in the order of the scores, of the outputs
+  uint32_t share[2];
   uint32_t wave_tot[kSelectThreads / 64];
   float red_lo[kSelectThreads / 64], red_hi[kSelectThreads / 64];
 };
@@ -888,8 +889,8 @@ __global__ __launch_bounds__(kSelectThreads) void coarse_histogram_kernel(const 
 // Grid (parts, Hkv, batch).  Every workgroup adds the parts' histograms and takes the coarse bins whose output offset lies in
 // its share of the l_p outputs; it collects the scores of those bins, all it has to know of the others being their number,
 // sorts them by buckets as bucket_rank_select does, over their own range, and copies the rows.  Where they are too alike for
-// that it sorts them whole; where they are too many for the LDS it sorts the head's l_p largest, and takes its outputs from
-// there.
+// that it sorts them whole; where a bin of its share may be too large for the LDS (most_of_a_bin) it sorts the head's l_p
+// largest, and takes its outputs from there.
 template <int D>
 __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(const double* __restrict__ s_ws, View k, View v, int64_t L, int64_t l_p, int n_hist,
                                                                             const CoarseHistogram* __restrict__ coarse, int32_t* __restrict__ idx_out, int hkv,
@@ -924,12 +925,10 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
   const CoarseHistogram* ch = coarse + h * n_hist;
   const float lo = ch->lo, inv = ch->inv;
   const uint32_t from = (uint32_t)(l_p * part / n_parts), to = (uint32_t)(l_p * (part + 1) / n_parts);
-  uint32_t first = from, n_out = to - from, n_loc = 0;
-  uint32_t n_sort = 0;                                       // entries left to sort by comparison exchanges, if any
-  bool exact = !(inv > 0.0f);
   if (tid == 0) {
     sh.b_lo = kCoarseBins;
     sh.b_hi = -1;
+    sh.divided = 0;
     sh.cnt = 0;
     sh.crowded = 0;
   }
@@ -939,29 +938,29 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
     for (int q = 0; q < n_hist; ++q) c += ch[q].count[kCoarseBins - 1 - tid];
   uint32_t total;
   __syncthreads();
-  const uint32_t excl = block_scan_incl(c, sh, &total) - c;
-  if (c != 0 && excl >= from && excl < to) {
-    atomicMin(&sh.b_lo, kCoarseBins - 1 - tid);
-    atomicMax(&sh.b_hi, kCoarseBins - 1 - tid);
+  const uint32_t excl = block_scan_incl(c, sh, &total) - c, most = most_of_a_bin(l_p, n_parts);
+  if (c != 0) {                                              // (output l_p lies in a bin too: L > l_p)
+    if (excl <= from && from < excl + c) sh.share[0] = first_of_share(from, excl, c, most);
+    if (excl <= to && to < excl + c) sh.share[1] = first_of_share(to, excl, c, most);
+    if (c > most && excl < to && from < excl + c) sh.divided = 1;
+    if (excl >= from && excl < to) {
+      atomicMin(&sh.b_lo, kCoarseBins - 1 - tid);
+      atomicMax(&sh.b_hi, kCoarseBins - 1 - tid);
+    }
   }
-  if (tid < kCoarseBins) {
-    sh.base[kCoarseBins - 1 - tid] = excl;
-    sh.fill[kCoarseBins - 1 - tid] = excl + c;
-  }
+  if (tid < kCoarseBins) sh.fill[kCoarseBins - 1 - tid] = excl + c;
   __syncthreads();
   const int b_lo = sh.b_lo, b_hi = sh.b_hi;
-  if (!exact) {
-    if (b_hi < 0) return;                                    // no bin begins in this share
-    first = sh.base[b_hi];
-    n_loc = sh.fill[b_lo] - first;
-    n_out = first + n_loc < (uint32_t)l_p ? n_loc : (uint32_t)l_p - first;
-    exact = n_loc > (uint32_t)kLdsSortMax;
-  }
+  const bool exact = sh.divided != 0;                        // (always where there is no map: all scores are in bin 0)
+  const uint32_t first = sh.share[0], end = sh.share[1] < (uint32_t)l_p ? sh.share[1] : (uint32_t)l_p;
+  if (first >= end) return;                                  // all of the share lies in a bin that begins before it
+  const uint32_t n_out = end - first, n_loc = exact ? 0 : sh.fill[b_lo] - first;      // at most kLdsSortMax
+  uint32_t n_sort = 0;                                       // entries left to sort by comparison exchanges, if any
   __syncthreads();
 
   if (!exact) {
-    // ---- collect the indices of the bins' scores, in any order.  Bin 0, where NaNs are counted too, is never one of them: a part
-    // that holds it has every score from its first output down, which are more than the LDS sorts.
+    // ---- collect the indices of the bins' scores, in any order.  Bin 0, where NaNs are counted too, is never one of them: with
+    // an output it has at least L - l_p + 1 scores, more than the LDS sorts.
     static_assert(kResidentScores >= 2 * kLdsSortMax, "L > kResidentScores, l_p <= kLdsSortMax: at least L - l_p + 1 scores");
     if (tid < 128) {
       const int bound = first_of_bin(tid < 64 ? b_lo : b_hi + 1, lo, inv);

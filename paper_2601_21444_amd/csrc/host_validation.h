@@ -538,6 +538,14 @@ inline LongSelection plan_long_selection(int64_t heads, int head_dim, int64_t L,
   return {(int)n_hist, (int)(n_parts > 1 ? n_parts : 1)};
 }
 
+// Which outputs a part takes.  Output x lies in the coarse bin of the outputs [excl, excl + c); a bin belongs to the part in
+// whose share [l_p * part / n_parts, l_p * (part + 1) / n_parts) it begins, so that a part's outputs begin where a bin does.
+// But a bin that may not fit the LDS beside the others of its part is divided where the shares are: every part that has some
+// of it sorts the head's l_p largest (taken whole by one part, which then copied all its rows, us a call: 2 heads x 20000 keys
+// of two values, 8100 rows 355 -> 271, 65536, 8000 rows 727 -> 593).
+constexpr uint32_t most_of_a_bin(int64_t l_p, int n_parts) { return (uint32_t)(kLdsSortMax - (l_p + n_parts - 1) / n_parts); }
+constexpr uint32_t first_of_share(uint32_t x, uint32_t excl, uint32_t c, uint32_t most) { return x == excl || c > most ? x : excl + c; }
+
 // The upper half of a float64 and its place in the order of the scores (as a signed integer; the map is its own inverse).
 constexpr int upper_order(int hi) { return hi ^ ((hi >> 31) & 0x7fffffff); }
 constexpr int kOrderInf = 0x7ff00000;          // of +infinity; above it lie NaNs, which the maps send to bin 0

@@ -1,18 +1,59 @@
 // Host checks of two rules of the compression, and of the comparison that collects the scores of a long block.  Selection of
 // long blocks (plan_long_selection): which calls of tests/test_gpu_long_select.py take it, and for every call that does, that
-// the histograms fit the pooled query's region and their counts, and the parts have outputs.  Pooled query without a launch
+// the histograms fit the pooled query's region and their counts, and the parts have outputs and divide them.  Pooled query without a launch
 // of its own (pools_in_scores): both sides of the line, among them the calls of tests/test_gpu_pooled_scores.py.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <random>
+#include <vector>
 #include "host_validation.h"
 
 using namespace apbv;
 
-#define EXPECT(x) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return 1; } } while (0)
+#define EXPECT_OR(x, result) do { if (!(x)) { std::printf("line %d: %s\n", __LINE__, #x); return result; } } while (0)
+#define EXPECT(x) EXPECT_OR(x, 1)
 
 static LongSelection plan(int hkv, int batch, int d, int64_t L, int64_t l_p) {
   return plan_long_selection((int64_t)hkv * batch, d, L, l_p, plan_compress_workspace(batch, hkv, d, L, l_p));
+}
+
+// The shares of long_select_gather_kernel over random bins, from one score to nearly all in one: every output belongs to one
+// part, a part that collects has whole bins (the last cut at l_p) that fit the LDS, and the others are those of large bins.
+static bool shares_fit(int64_t L, int64_t l_p, int n_parts) {
+  static std::mt19937_64 rng(5);
+  const uint32_t most = most_of_a_bin(l_p, n_parts);
+  for (int trial = 0; trial < 6; ++trial) {
+    std::vector<uint32_t> begin{0};                       // first output of every bin, then L
+    while (begin.back() < L) {
+      const uint32_t sizes[] = {1, 40, 500, most, most + 1, 9000, (uint32_t)L};
+      const uint32_t n = 1 + (uint32_t)(rng() % sizes[rng() % (trial + 2)]);
+      begin.push_back((uint32_t)std::min<int64_t>(L, (int64_t)begin.back() + (rng() % 4 ? n : sizes[rng() % 7])));
+    }
+    uint32_t next = 0;
+    for (int part = 0; part < n_parts; ++part) {
+      const uint32_t from = (uint32_t)(l_p * part / n_parts), to = (uint32_t)(l_p * (part + 1) / n_parts);
+      uint32_t share[2] = {0, 0}, last = 0;
+      bool divided = false;
+      for (size_t i = 0; i + 1 < begin.size(); ++i) {
+        const uint32_t excl = begin[i], c = begin[i + 1] - excl;
+        if (excl <= from && from < excl + c) share[0] = first_of_share(from, excl, c, most);
+        if (excl <= to && to < excl + c) share[1] = first_of_share(to, excl, c, most);
+        if (c > most && excl < to && from < excl + c) divided = true;
+        if (excl >= from && excl < to) last = excl + c;
+      }
+      const uint32_t first = share[0], end = std::min<uint32_t>(share[1], (uint32_t)l_p);
+      if (first >= end) continue;
+      EXPECT_OR(first == next, false);
+      next = end;
+      if (divided) continue;
+      const bool begins = std::binary_search(begin.begin(), begin.end(), first), ends = std::binary_search(begin.begin(), begin.end(), end) || end == l_p;
+      EXPECT_OR(begins && ends && last >= end && last - first <= kLdsSortMax, false);
+    }
+    EXPECT_OR(next == l_p, false);
+  }
+  return true;
 }
 
 int main() {
@@ -30,7 +71,8 @@ int main() {
           if (s.n_parts == 0) continue;
           EXPECT(w.qbar_off + (size_t)heads * s.n_hist * sizeof(CoarseHistogram) <= w.scores_off && w.n_sort <= kLdsSortMax);
           EXPECT((L + s.n_hist - 1) / s.n_hist <= kResidentScores && s.n_parts <= l_p && s.n_parts * heads <= 256);
-          EXPECT(L - l_p + 1 > kLdsSortMax);      // a part with bin 0, which its collecting loop does not take, has as many
+          EXPECT(L - l_p + 1 > kLdsSortMax);      // bin 0, if it has an output: the collecting loop does not take it
+          if (!shares_fit(L, l_p, s.n_parts)) return 1;
         }
   // the test that collects the scores of a range of bins, [lowest, past) in the order of their upper halves
   const double values[] = {-INFINITY, -1e300, -1234.5, -1.0, -1e-300, -0.0, 0.0, 1e-300, 1.0, 1234.5, 1e300, INFINITY};

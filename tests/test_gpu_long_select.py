@@ -111,6 +111,14 @@ CROWDS = [
     (40000, 33, 5, 6000, 0),            # one part
     (40000, 8192, 100, 5000, 4000),
     (24576, 8192, 0, 7000, 3000),
+    # bins that may not fit beside the others of their part, whose outputs the parts divide: from 8193 - l_p / 16 scores on
+    (30000, 8192, 100, 7680, 4000),     # the largest bin one part takes whole
+    (30000, 8192, 100, 7681, 4000),     # one more; outputs on both sides of it
+    (30000, 8000, 100, 7700, 150),      # it ends inside the last part's share
+    (30000, 8192, 511, 7681, 1),        # it begins at the last output of the first share
+    (30000, 1000, 999, 20000, 0),       # the last output alone
+    (30000, 1024, 128, 9000, 0),        # it begins at a share of its own
+    (40000, 40, 3, 9000, 0),            # one part
 ]
 
 
@@ -118,7 +126,7 @@ CROWDS = [
 def test_alike_scores_of_a_long_block(L, l_p, above, alike, below):
     rng = np.random.default_rng((71, L, l_p, alike))
     hkv = 2
-    scores = np.stack([rng.permutation(np.concatenate([9 + rng.random(above), np.full(alike, 8.5), 8 + 0.4 * rng.random(below),
+    scores = np.stack([rng.permutation(np.concatenate([9 + rng.random(above), np.full(alike, 8.5), 8 + 0.2 * rng.random(below),
                                                        rng.standard_normal(L - above - alike - below) - 9])) for _ in range(hkv)]).astype(np.float32)
     k = np.ascontiguousarray(keys_of_scores(scores).transpose(1, 0, 2))
     q = wl.f32_to_bf16_bits(np.ones((1, hkv, 64), dtype=np.float32))
