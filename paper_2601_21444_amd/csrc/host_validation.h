@@ -546,6 +546,20 @@ inline LongSelection plan_long_selection(int64_t heads, int head_dim, int64_t L,
 constexpr uint32_t most_of_a_bin(int64_t l_p, int n_parts) { return (uint32_t)(kLdsSortMax - (l_p + n_parts - 1) / n_parts); }
 constexpr uint32_t first_of_share(uint32_t x, uint32_t excl, uint32_t c, uint32_t most) { return x == excl || c > most ? x : excl + c; }
 
+// Workgroup -> head and part.  The parts of a head read the same scores, where they sort the head's largest ten times over, so
+// they run on one of the eight XCDs (workgroup number modulo eight) and share its L2: rows of eight heads, one an XCD.  Fewer
+// heads than a row are spread, as a single XCD's L2 would feed all parts.  us a call, parts of a head on several XCDs / on one:
+// a key in 11 equal and on top, 32 heads x 131072 keys of 64, 1000 rows 683 / 497, 8 x 200000 of 128, 4000 rows 918 / 599
+// (one workgroup a head took 601 and 718); normal scores 155 / 132, 121 / 121.
+struct HeadPart {
+  int head, part;
+};
+constexpr HeadPart head_and_part(int workgroup, int n_parts, int n_heads) {
+  const int in_rows = n_heads / 8 * 8 * n_parts;
+  if (workgroup >= in_rows) return {workgroup / n_parts, workgroup % n_parts};
+  return {workgroup / (8 * n_parts) * 8 + workgroup % 8, workgroup / 8 % n_parts};
+}
+
 // The upper half of a float64 and its place in the order of the scores (as a signed integer; the map is its own inverse).
 constexpr int upper_order(int hi) { return hi ^ ((hi >> 31) & 0x7fffffff); }
 constexpr int kOrderInf = 0x7ff00000;          // of +infinity; above it lie NaNs, which the maps send to bin 0

@@ -74,6 +74,16 @@ int main() {
           EXPECT(L - l_p + 1 > kLdsSortMax);      // bin 0, if it has an output: the collecting loop does not take it
           if (!shares_fit(L, l_p, s.n_parts)) return 1;
         }
+  // every part of every head once, those of a whole row of heads on one XCD
+  for (int heads = 1; heads <= kMaxLongHeads; ++heads)
+    for (int parts = 1; parts <= 16; ++parts) {
+      std::vector<int> seen(heads * parts, 0);
+      for (int w = 0; w < heads * parts; ++w) {
+        const HeadPart at = head_and_part(w, parts, heads);
+        EXPECT(at.head >= 0 && at.head < heads && at.part >= 0 && at.part < parts && seen[at.head * parts + at.part]++ == 0);
+        EXPECT(at.head >= heads / 8 * 8 || at.head % 8 == w % 8);
+      }
+    }
   // the test that collects the scores of a range of bins, [lowest, past) in the order of their upper halves
   const double values[] = {-INFINITY, -1e300, -1234.5, -1.0, -1e-300, -0.0, 0.0, 1e-300, 1.0, 1234.5, 1e300, INFINITY};
   auto order_of = [](double x) {

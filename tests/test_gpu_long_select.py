@@ -25,6 +25,7 @@ CASES = [
     (1, 1, 128, 140000, 64, "normal"),       # longer with head_dim 128, two parts
     (2, 1, 64, 30000, 33, "normal"),         # one part
     (4, 8, 64, 25000, 200, "normal"),        # the most heads
+    (3, 4, 64, 25000, 70, "normal"),         # a row of eight heads and four more
     (3, 11, 64, 25000, 200, "normal"),       # one more
     (2, 1, 64, 30000, 2500, "pairs"),        # every score twice: ties inside and across bins and the cut
     (2, 1, 64, 30000, 900, "ascending"),     # the sample and the parts see different ranges
