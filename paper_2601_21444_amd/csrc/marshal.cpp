@@ -86,21 +86,21 @@ bool whole(PyObject* o, int64_t& x) {
   return overflow == 0;
 }
 
-// The current device's current stream; false (no error set) if CUDA is not initialised in this process.
+// The current device's current stream; false if CUDA is not initialised in this process, or with what was raised (by a signal's
+// handler, say: these functions run Python code).
 bool current_stream(void*& stream) {
   PyObject* ok = PyObject_CallNoArgs(g_is_initialized);
   const bool ready = ok == Py_True;
   Py_XDECREF(ok);
-  PyObject *dev = nullptr, *raw = nullptr;
-  if (ready && (dev = PyObject_CallNoArgs(g_current_device)) != nullptr) raw = PyObject_CallOneArg(g_raw_stream, dev);
-  Py_XDECREF(dev);
-  if (raw != nullptr) stream = PyLong_AsVoidPtr(raw);
-  Py_XDECREF(raw);
-  if (PyErr_Occurred()) {
-    PyErr_Clear();
-    return false;
-  }
-  return raw != nullptr;
+  if (!ready) return false;
+  PyObject* dev = PyObject_CallNoArgs(g_current_device);
+  if (dev == nullptr) return false;
+  PyObject* raw = PyObject_CallOneArg(g_raw_stream, dev);
+  Py_DECREF(dev);
+  if (raw == nullptr) return false;
+  stream = PyLong_AsVoidPtr(raw);
+  Py_DECREF(raw);
+  return PyErr_Occurred() == nullptr;
 }
 
 int to_int(int64_t x) { return x > 0x7fffffff ? 0x7fffffff : (int)x; }      // sizes the library refuses either way
@@ -116,8 +116,8 @@ PyObject* guarded(F&& f) {
   } catch (...) {
     taken = false;
   }
-  if (!taken) return not_taken();
-  return PyLong_FromLong(status);
+  if (taken) return PyLong_FromLong(status);
+  return PyErr_Occurred() ? nullptr : not_taken();
 }
 
 // merge_lse(parts_out, parts_lse, out, lse_out)
@@ -278,12 +278,11 @@ PyObject* use_stream(PyObject*, PyObject* const* a, Py_ssize_t n) {
     PyErr_SetString(PyExc_TypeError, "use_stream takes three functions");
     return nullptr;
   }
-  Py_INCREF(a[0]);
-  Py_INCREF(a[1]);
-  Py_INCREF(a[2]);
-  g_is_initialized = a[0];
-  g_current_device = a[1];
-  g_raw_stream = a[2];
+  PyObject** const kept[3] = {&g_is_initialized, &g_current_device, &g_raw_stream};
+  for (int i = 0; i < 3; ++i) {
+    Py_INCREF(a[i]);
+    Py_XSETREF(*kept[i], a[i]);
+  }
   Py_RETURN_NONE;
 }
 

@@ -123,3 +123,24 @@ def test_merge_and_refusals_agree():
                 case(**s)
             said.append((err.type, str(err.value)))
         assert said[0] == said[1]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("asked", [0, 1, 2])
+def test_what_is_raised_while_the_stream_is_asked_for_is_not_lost(asked):
+    """The functions that name the stream run Python code, where a signal's handler may raise: the call ends with it."""
+    binding.load_library()
+    parts, lse, out = bf(3, 7, 4, 64), torch.randn(3, 4, 7, device="cuda"), torch.full((7, 4, 64), 5.0, device="cuda", dtype=torch.bfloat16)
+    functions = [torch.cuda.is_initialized, binding._current_device, binding._raw_stream]
+
+    def interrupted(*_):
+        raise KeyboardInterrupt
+    try:
+        binding._native.use_stream(*[interrupted if i == asked else f for i, f in enumerate(functions)])
+        with pytest.raises(KeyboardInterrupt):
+            apbv.apbv_merge_lse(parts, lse, out=out)
+    finally:
+        binding._native.use_stream(*functions)
+    torch.cuda.synchronize()
+    assert (out == 5.0).all()
+    assert binding._native.merge_lse(parts, lse, out, None) == 0
