@@ -65,7 +65,8 @@ typedef struct {
 /* Host, pure.  Static string naming a status code. */
 const char* apbv_status_string(apbv_status s);
 
-/* Host, pure.  Library version, major*10000 + minor*100 + patch. */
+/* Library version, major*10000 + minor*100 + patch: of this header, and (host, pure) of the library. */
+#define APBV_VERSION 215
 int apbv_version(void);
 
 /* Host, pure.  Bytes of workspace apbv_compress_kv needs for this shape (0 on invalid arguments).

@@ -6,21 +6,22 @@ fallback path.
 
 The plain call (every output and workspace passed, dense tensors of the right types, the current stream) is marshalled in
 native code (csrc/marshal.cpp), which looks at the same things as the code here and hands back what it does not take; the
-ctypes code here allocates what was left out and says what is wrong.
+ctypes code here allocates what was left out and says what is wrong, and serves every call where that extension is missing.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import math
 import operator
 import os
+import warnings
 from typing import Optional, Tuple
 
 import torch
 
 _BF16 = torch.bfloat16
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libapbv.so")
-_MARSHAL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal.so")
 _lib = None
 _native = None
 
@@ -54,6 +55,33 @@ class ApbvAttentionItem(ctypes.Structure):
     ]
 
 
+class _NoMarshal:
+    """In place of the native marshalling where there is none: no call is the plain one."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_marshal(lib: ctypes.CDLL):
+    """The native marshalling if it was built with this library, for this interpreter and this torch."""
+    try:
+        native = importlib.import_module(__package__ + "._marshal")
+    except ModuleNotFoundError:
+        return _NoMarshal()
+    except ImportError as e:
+        why = str(e)
+    else:
+        # the version of apbv.h it was compiled with, and where the apbv_version lies that it calls
+        built = (getattr(native, "version", None), getattr(native, "library", None))
+        if built == (lib.apbv_version(), ctypes.cast(lib.apbv_version, ctypes.c_void_p).value):
+            if _raw_stream is not None and _current_device is not None:
+                native.use_stream(torch.cuda.is_initialized, _current_device, _raw_stream)
+            return native
+        why = "it belongs to another build of the library"
+    warnings.warn(f"the native marshalling is not used ({why}); calls are marshalled by ctypes", RuntimeWarning, stacklevel=3)
+    return _NoMarshal()
+
+
 def load_library() -> ctypes.CDLL:
     """Load libapbv.so (built in-tree by ``paper_2601_21444_amd.build``); raises if it is missing."""
     global _lib, _native
@@ -63,8 +91,6 @@ def load_library() -> ctypes.CDLL:
         raise RuntimeError(
             f"{_LIB_PATH} is missing: build the HIP library first (python -m paper_2601_21444_amd.build). "
             "There is no CPU or PyTorch fallback for the APB-V hot path.")
-    if not os.path.exists(_MARSHAL_PATH):
-        raise RuntimeError(f"{_MARSHAL_PATH} is missing: build the library first (python -m paper_2601_21444_amd.build).")
     lib = ctypes.CDLL(_LIB_PATH)
     lib.apbv_status_string.restype = ctypes.c_char_p
     lib.apbv_status_string.argtypes = [ctypes.c_int]
@@ -108,10 +134,7 @@ def load_library() -> ctypes.CDLL:
     lib.apbv_host_attention_group.argtypes = [
         ctypes.c_int, ctypes.POINTER(ApbvAttentionItem), ctypes.c_int, ctypes.c_int, ctypes.c_int,
         ctypes.c_float, ctypes.c_void_p]
-    from . import _marshal
-    if _raw_stream is not None and _current_device is not None:
-        _marshal.use_stream(torch.cuda.is_initialized, _current_device, _raw_stream)
-    _native = _marshal
+    _native = _load_marshal(lib)
     _lib = lib
     return lib
 

@@ -293,4 +293,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+// The module says what it was built against and linked to: the version of apbv.h, the address of the library's apbv_version.
+PyMODINIT_FUNC PyInit__marshal() {
+  PyObject* m = PyModule_Create(&module);
+  PyObject* library = PyLong_FromVoidPtr(reinterpret_cast<void*>(&apbv_version));
+  if (m == nullptr || library == nullptr || PyModule_AddIntConstant(m, "version", APBV_VERSION) != 0 || PyModule_AddObjectRef(m, "library", library) != 0)
+    Py_CLEAR(m);
+  Py_XDECREF(library);
+  return m;
+}

@@ -1,6 +1,9 @@
 """The native marshalling of the binding: what is not the plain call is handed back untouched (CPU), and the plain call gives
 the results, errors and outputs of the general way (GPU), which an explicit stream takes."""
 import math
+import sys
+import sysconfig
+import types
 
 import pytest
 import torch
@@ -42,6 +45,58 @@ def test_other_than_plain_calls_are_handed_back():
         apbv.apbv_merge_lse(parts, lse, out=out)
     with pytest.raises(TypeError):
         apbv.apbv_host_attention(q.float(), k, k, k, k, k, k, 1.0, out=out)
+
+
+def loaded_again(monkeypatch, module):
+    """The binding's native part after loading the library with this module as the extension (None: there is none)."""
+    monkeypatch.setitem(sys.modules, "paper_2601_21444_amd._marshal", module)
+    monkeypatch.delattr(apbv, "_marshal", raising=False)
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_native", None)
+    assert apbv.load_library() is not None and apbv.apbv_version() >= 100
+    return binding._native
+
+
+def test_the_library_loads_without_the_extension(monkeypatch):
+    """... and every call goes the general way, whose messages these are."""
+    native = loaded_again(monkeypatch, None)
+    parts, lse, out, q, k = cpu_args()
+    assert native.merge_lse(parts, lse, out, None) is None
+    with pytest.raises(ValueError, match="must live on"):
+        apbv.apbv_merge_lse(parts, lse, out=out)
+    with pytest.raises(ValueError, match="must live on"):
+        apbv.apbv_host_attention(q, k, k, k, k, k, k, 1.0, out=out.new_zeros(1, 5, 2, 64))
+    assert native.attention_group([], 1.0, False) is None and native.compress_kv() is None and native.query_attention() is None
+
+
+def test_an_extension_of_another_build_is_not_used(monkeypatch):
+    apbv.load_library()
+    real = binding._native
+    for other in (dict(version=real.version + 1, library=real.library), dict(version=real.version, library=real.library + 8), {}):
+        module = types.ModuleType("paper_2601_21444_amd._marshal")
+        module.merge_lse = lambda *a: pytest.fail("called")
+        for name, value in other.items():
+            setattr(module, name, value)
+        with pytest.warns(RuntimeWarning, match="marshalling"):
+            assert loaded_again(monkeypatch, module).merge_lse(1, 2, 3, 4) is None
+
+
+def test_the_library_is_built_without_what_the_extension_needs(monkeypatch, tmp_path, capsys):
+    from paper_2601_21444_amd import build as b
+    ran = []
+    monkeypatch.setattr(b, "OBJ", str(tmp_path))
+    monkeypatch.setattr(b.subprocess, "run", lambda cmd, **kw: ran.append(cmd))
+    b.build(verbose=False)
+    assert any(cmd[-1] == b.LIB for cmd in ran) and any(str(cmd[-1]).endswith(sysconfig.get_config_var("EXT_SUFFIX")) for cmd in ran)
+    for lacks in ("torch", "CXX"):
+        ran.clear()
+        with monkeypatch.context() as m:
+            if lacks == "torch":
+                m.setitem(sys.modules, "torch", None)
+            else:
+                m.setenv("CXX", str(tmp_path / "no-compiler"))
+            b.build(verbose=False)
+        assert [cmd[-1] for cmd in ran if "-shared" in cmd] == [b.LIB] and "not built" in capsys.readouterr().out
 
 
 def bf(*s):
