@@ -103,14 +103,38 @@ def bf(*s):
     return torch.randn(s, device="cuda", dtype=torch.bfloat16)
 
 
-def both(call, args, outs, **kw):
-    """The outputs of the native and of the general way, the buffers filled with different values before each."""
+class Recorder:
+    """The native marshalling with a note of what each of its functions said."""
+
+    def __init__(self, native):
+        self.native, self.said = native, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.said.append(getattr(self.native, name)(*args))
+            return self.said[-1]
+        return call
+
+
+@pytest.fixture
+def native(monkeypatch):
+    apbv.load_library()
+    recorder = Recorder(binding._native)
+    monkeypatch.setattr(binding, "_native", recorder)
+    return recorder
+
+
+def both(native, call, args, outs, said=0, **kw):
+    """The outputs of the native and of the general way, the buffers filled with different values before each; `said`: what the
+    native function returns in the call that asks it (None: handed back)."""
     got = []
     for fill, extra in ((1, {}), (3, {"stream": torch.cuda.current_stream()})):
         for t in outs.values():
             t.fill_(fill)
+        native.said.clear()
         result = call(*args, **outs, **kw, **extra)
         torch.cuda.synchronize()
+        assert native.said == ([] if extra else [said])
         flat = result if isinstance(result, tuple) else (result,)
         got.append(([tuple(t.shape) for t in flat], [t.clone() for t in outs.values() if t.dtype != torch.uint8]))
     assert got[0][0] == got[1][0]
@@ -121,7 +145,7 @@ def both(call, args, outs, **kw):
 @pytest.mark.gpu
 @pytest.mark.parametrize("batched", [False, True])
 @pytest.mark.parametrize("form", ["dense", "strided", "empty segments"])
-def test_native_and_general_marshalling_agree(batched, form):
+def test_native_and_general_marshalling_agree(native, batched, form):
     b, L, hq, hkv, d, nv = 2, 150, 4, 2, 64, 40
     lead = (b,) if batched else ()
     n_b = b if batched else 1
@@ -135,23 +159,21 @@ def test_native_and_general_marshalling_agree(batched, form):
     scale = 1 / math.sqrt(d)
     new = lambda *s, dtype=torch.bfloat16: torch.empty((n_b,) + s, device="cuda", dtype=dtype)
     print("marshal", batched, form, flush=True)
-    binding.load_library()
-    assert binding._native.host_attention(q, ka, va, e, e, k, v, scale, new(L, hq, d), None) == 0
-    both(apbv.apbv_host_attention, (q, ka, va, e, e, k, v, scale), dict(out=new(L, hq, d), lse_out=new(hq, L, dtype=torch.float32)), return_lse=True)
-    both(apbv.apbv_host_attention, (q, ka, va, e, e, k, v, scale), dict(out=new(L, hq, d)))
+    both(native, apbv.apbv_host_attention, (q, ka, va, e, e, k, v, scale), dict(out=new(L, hq, d), lse_out=new(hq, L, dtype=torch.float32)), return_lse=True)
+    both(native, apbv.apbv_host_attention, (q, ka, va, e, e, k, v, scale), dict(out=new(L, hq, d)))
     ws = torch.empty(max(256, apbv.apbv_query_attention_workspace_bytes(n_b, hq, d, 9, L + nv, 2)), dtype=torch.uint8, device="cuda")
-    both(apbv.apbv_query_attention, (q[..., :9, :, :], ka, va, k, v, e, e, scale), dict(out=new(9, hq, d), lse_out=new(hq, 9, dtype=torch.float32), workspace=ws), n_splits=2, return_lse=True)
+    both(native, apbv.apbv_query_attention, (q[..., :9, :, :], ka, va, k, v, e, e, scale), dict(out=new(9, hq, d), lse_out=new(hq, 9, dtype=torch.float32), workspace=ws), n_splits=2, return_lse=True)
     for reducer in ("sum", "max", "softmax_sum"):
         ws = torch.empty(apbv.apbv_compress_reduced_workspace_bytes(reducer, n_b, hq, hkv, d, 9, L, 33), dtype=torch.uint8, device="cuda")
         outs = dict(idx_out=new(hkv, 33, dtype=torch.int32), k_c_out=new(33, hkv, d), v_c_out=new(33, hkv, d), scores_out=new(hkv, L, dtype=torch.float64), workspace=ws)
-        both(apbv.apbv_compress_kv, (q[..., :9, :, :], k, v, 33), outs, reducer=reducer, softmax_scale=scale, return_scores=True)
+        both(native, apbv.apbv_compress_kv, (q[..., :9, :, :], k, v, 33), outs, reducer=reducer, softmax_scale=scale, return_scores=True)
     del outs["workspace"], outs["scores_out"]
-    both(apbv.apbv_compress_kv_noalloc, (q[..., :9, :, :], k, v, 33), outs)
+    both(native, apbv.apbv_compress_kv_noalloc, (q[..., :9, :, :], k, v, 33), outs)
     if not batched:
         group = [(q, ka, va, e, e, k, v, new(L, hq, d)[0], new(hq, L, dtype=torch.float32)[0]) for _ in range(2)]
-        assert binding._native.attention_group(group, scale, True) == 0
-        native = apbv.apbv_host_attention_group(group, scale, return_lse=True)
-        kept = [(o.clone(), s.clone()) for o, s in native]
+        native.said.clear()
+        kept = [(o.clone(), s.clone()) for o, s in apbv.apbv_host_attention_group(group, scale, return_lse=True)]
+        assert native.said == [0]
         general = apbv.apbv_host_attention_group([list(g) for g in group], scale, return_lse=True, stream=torch.cuda.current_stream())
         torch.cuda.synchronize()
         for (o, s), (o2, s2) in zip(kept, general):
@@ -159,11 +181,11 @@ def test_native_and_general_marshalling_agree(batched, form):
 
 
 @pytest.mark.gpu
-def test_merge_and_refusals_agree():
+def test_merge_and_refusals_agree(native):
     parts, lse = bf(3, 7, 4, 64), torch.randn(3, 4, 7, device="cuda")
     outs = dict(out=torch.empty(7, 4, 64, device="cuda", dtype=torch.bfloat16), lse_out=torch.empty(4, 7, device="cuda"))
-    both(apbv.apbv_merge_lse, (parts, lse), outs, return_lse=True)
-    both(apbv.apbv_merge_lse, (bf(3, 14, 4, 64)[:, :7], lse), outs)        # strided parts: the general way both times
+    both(native, apbv.apbv_merge_lse, (parts, lse), outs, return_lse=True)
+    both(native, apbv.apbv_merge_lse, (bf(3, 14, 4, 64)[:, :7], lse), outs, said=None)        # strided parts: handed back
     q, k, e = bf(9, 4, 64), bf(9, 2, 64), bf(0, 2, 64)
     cases = [lambda **s: apbv.apbv_merge_lse(bf(3, 7, 4, 96), lse, out=torch.empty(7 * 4 * 96, device="cuda", dtype=torch.bfloat16), **s),
              lambda **s: apbv.apbv_host_attention(q, e, e, e, e, k, k, -1.0, out=torch.empty_like(q), **s),
@@ -171,12 +193,15 @@ def test_merge_and_refusals_agree():
              lambda **s: apbv.apbv_host_attention(q, e, e, e, e, k, k, 1.0, out=torch.empty(3, device="cuda", dtype=torch.bfloat16), **s),
              lambda **s: apbv.apbv_compress_kv(q, k, k, 10, workspace=torch.empty(1 << 20, dtype=torch.uint8, device="cuda"), idx_out=torch.empty(20, dtype=torch.int32, device="cuda"),
                                                k_c_out=torch.empty(2000, dtype=torch.bfloat16, device="cuda"), v_c_out=torch.empty(2000, dtype=torch.bfloat16, device="cuda"), **s)]
-    for case in cases:
+    # what the library refuses is refused by it either way; a buffer or a size that the binding refuses is handed back
+    for case, status in zip(cases, (-3, -2, -2, None, None)):
         said = []
         for s in ({}, {"stream": torch.cuda.current_stream()}):
+            native.said.clear()
             with pytest.raises(Exception) as err:
                 case(**s)
             said.append((err.type, str(err.value)))
+            assert native.said == ([] if s else [status])
         assert said[0] == said[1]
 
 
