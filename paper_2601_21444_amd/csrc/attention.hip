@@ -589,11 +589,12 @@ static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t
 
 apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t stream) {
   static_assert(kAttnQueryTile == kBM && kAttnNarrowQueryTile == 32 * kWavesNarrow, "tile sizes the host-side planning assumes");
-  if (attention_shares_blocks(head_dim, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits)) return launch_variant<kWavesShort, 2>(p, head_dim, stream);
-  // (a block of at most kAttnNarrowMaxRows rows is mostly padding in anything but 64-row workgroups)
-  if (p.L <= kAttnNarrowMaxRows) return launch_variant<kWavesNarrow>(p, head_dim, stream);
-  // (its 64 rows are for launches that share blocks)
-  if (attention_rows(head_dim, p.group, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits) != kBM) return launch_variant<kWavesShort>(p, head_dim, stream);
+  switch (attention_kernel(head_dim, p.group, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits)) {
+    case AttentionKernel::kShared64: return launch_variant<kWavesShort, 2>(p, head_dim, stream);
+    case AttentionKernel::kNarrow64: return launch_variant<kWavesNarrow>(p, head_dim, stream);
+    case AttentionKernel::k128: return launch_variant<kWavesShort>(p, head_dim, stream);
+    case AttentionKernel::k256: break;
+  }
   return launch_variant<kWaves>(p, head_dim, stream);
 }
 
@@ -620,19 +621,15 @@ apbv_status launch_host_attention_group(AttnGroupParams& gp, int head_dim, hipSt
   const int n = gp.n_items;
   if (n < 1 || n > kMaxGroupItems) return APBV_ERR_UNSUPPORTED;
   int64_t n_vis[kMaxGroupItems], rows[kMaxGroupItems];
-  AttentionTiles tiles[3];
-  double kv_bytes = 0, qo_bytes = 0;
   for (int m = 0; m < n; ++m) {
-    const AttnParams& p = gp.item[m];
-    n_vis[m] = p.n_vis;
-    rows[m] = p.L;
-    for (int i = 0; i < 3; ++i) add_attention_tiles(tiles[i], 64 << i, p.hq, p.L, p.n_vis, true);
-    kv_bytes += (double)p.s_kv * p.hkv * head_dim * 4;
-    qo_bytes += (double)p.L * p.hq * head_dim * 4;
+    n_vis[m] = gp.item[m].n_vis;
+    rows[m] = gp.item[m].L;
   }
-  if (attention_shares_blocks(head_dim, tiles)) return launch_group_variant<kWavesShort, 2>(gp, head_dim, n_vis, rows, stream);
-  if (attention_rows(head_dim, gp.item[0].group, gp.item[0].hkv, tiles, kv_bytes, qo_bytes, false) == kBM) return launch_group_variant<kWaves>(gp, head_dim, n_vis, rows, stream);
-  return launch_group_variant<kWavesShort>(gp, head_dim, n_vis, rows, stream);
+  switch (attention_group_kernel(head_dim, gp.item[0].hq, gp.item[0].hkv, n, n_vis, rows)) {
+    case AttentionKernel::kShared64: return launch_group_variant<kWavesShort, 2>(gp, head_dim, n_vis, rows, stream);
+    case AttentionKernel::k256: return launch_group_variant<kWaves>(gp, head_dim, n_vis, rows, stream);
+    default: return launch_group_variant<kWavesShort>(gp, head_dim, n_vis, rows, stream);
+  }
 }
 
 }  // namespace apbv

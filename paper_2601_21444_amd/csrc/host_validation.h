@@ -229,6 +229,30 @@ inline int attention_rows(int head_dim, int group, int batch, int n_q_heads, int
                         row * (double)n_rows, true);
 }
 
+// The workgroups of a launch: 64 rows by four waves, two to a block of 32, or by two waves; 128 or 256 rows.
+enum class AttentionKernel { kShared64, kNarrow64, k128, k256 };
+// One launch of batch * n_q_heads heads and n_splits key ranges, all of n_rows queries.
+inline AttentionKernel attention_kernel(int head_dim, int group, int batch, int n_q_heads, int64_t n_rows, int64_t n_vis, bool causal, int n_splits) {
+  if (attention_shares_blocks(head_dim, batch, n_q_heads, n_rows, n_vis, causal, n_splits)) return AttentionKernel::kShared64;
+  // (a block of at most kAttnNarrowMaxRows rows is mostly padding in anything but 64-row workgroups)
+  if (n_rows <= kAttnNarrowMaxRows) return AttentionKernel::kNarrow64;
+  // (64 of attention_rows are for launches that share blocks)
+  return attention_rows(head_dim, group, batch, n_q_heads, n_rows, n_vis, causal, n_splits) == kAttnQueryTile ? AttentionKernel::k256 : AttentionKernel::k128;
+}
+// One launch of n problems with rows[m] queries behind n_vis[m] keys, each with its causal segment.
+inline AttentionKernel attention_group_kernel(int head_dim, int n_q_heads, int n_kv_heads, int n, const int64_t* n_vis, const int64_t* rows) {
+  AttentionTiles tiles[3];
+  double kv_bytes = 0, qo_bytes = 0;
+  for (int m = 0; m < n; ++m) {
+    for (int i = 0; i < 3; ++i) add_attention_tiles(tiles[i], 64 << i, n_q_heads, rows[m], n_vis[m], true);
+    kv_bytes += (double)(n_vis[m] + rows[m]) * n_kv_heads * head_dim * 4;
+    qo_bytes += (double)rows[m] * n_q_heads * head_dim * 4;
+  }
+  if (attention_shares_blocks(head_dim, tiles)) return AttentionKernel::kShared64;
+  const int tile = attention_rows(head_dim, n_q_heads / n_kv_heads, n_kv_heads, tiles, kv_bytes, qo_bytes, false);
+  return tile == kAttnQueryTile ? AttentionKernel::k256 : AttentionKernel::k128;
+}
+
 // Lanes of the merge kernel that share one item (a 16-byte chunk of the output).  A lane that holds all its parts in
 // registers has their loads in flight at once, so with few items more lanes are faster; with many items the chip is full
 // anyway, and lanes reading one 16-byte piece of each part use a fraction of what a load fetches.  Measured (us; lanes
@@ -341,6 +365,8 @@ inline double query_estimate(QueryKernel kernel, const QueryBlock& q, const KeyS
   const int group = q.n_q_heads / q.n_kv_heads;
   // Workgroups in whole rounds of eight XCDs: the row tiles of a range run on one of them, of a workgroup per query head
   // those of a KV head's group.
+  // (A workgroup per query head of more than kAttnNarrowMaxRows queries counts as attention_rows cuts it, without the shared
+  // blocks and after its own 64 rows: the launches that query_cost was fitted to.)
   int tile = kernel == QueryKernel::kPacked256 ? kAttnQueryTile : kQueryShortRows;
   if (kernel == QueryKernel::kPerHead)
     tile = q.n_q <= kAttnNarrowMaxRows ? kAttnNarrowQueryTile : attention_rows(q.head_dim, group, q.batch, q.n_q_heads, q.n_q, q.n_keys, false, ks.n_splits);

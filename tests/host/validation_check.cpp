@@ -102,8 +102,8 @@ int main() {
   EXPECT(validate_merge(3, 10, 4, 128, P(0x1000), 5120, static_cast<const float*>(P(0x2000)), 39, P(0x3000), nullptr) == APBV_ERR_SHAPE);
   EXPECT(validate_merge(3, 10, 4, 96, P(0x1000), 5120, static_cast<const float*>(P(0x2000)), 40, P(0x3000), nullptr) == APBV_ERR_UNSUPPORTED);
   EXPECT(validate_merge(3, 10, 4, 128, nullptr, 5120, static_cast<const float*>(P(0x2000)), 40, P(0x3000), nullptr) == APBV_ERR_NULL);
-  // rows per workgroup: the launches of tests/test_gpu_attention_workgroups.py (alone, in a batch, three in a group) and
-  // measured ones on both sides of the rule
+  // rows per workgroup where blocks are not shared (tests/host/shared_blocks_check.cpp has the launches): problems alone, in a
+  // batch and three in a group, and measured ones on both sides of the rule
   struct { int hq, hkv, d; int64_t L, n_vis; int repeats, alone, batch, group; } rows_of[] = {
       {2, 1, 64, 129, 0, 40, 64, 128, 128},       {2, 1, 64, 700, 128, 12, 64, 128, 128},    {4, 1, 64, 300, 5000, 40, 64, 128, 128},
       {8, 8, 64, 150, 1000, 30, 64, 256, 128},    {4, 2, 128, 129, 7, 3, 128, 128, 128},     {4, 2, 128, 513, 4040, 20, 128, 256, 128},

@@ -1,7 +1,7 @@
-"""GPU parity of attention at both sides of the rule that picks the rows per workgroup (64, 128 or 256): the rows of one
-problem do not depend on the launch they are computed in.  Every case runs alone, repeated in a batch, and three times in
-a grouped launch, in workgroups of the sizes listed (tests/host/validation_check.cpp holds the rule to them); the results
-are compared bit for bit and with the fp64 oracle."""
+"""GPU parity of attention at both sides of the rules that pick the workgroups (64 rows of shared blocks, 64, 128 or 256): the
+rows of one problem do not depend on the launch they are computed in.  Every case runs alone, repeated in a batch, and three
+times in a grouped launch, in the workgroups listed (tests/host/shared_blocks_check.cpp holds the launches to them); the
+results are compared bit for bit and with the fp64 oracle."""
 import math
 
 import numpy as np
@@ -15,15 +15,21 @@ from paper_2601_21444_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # hq, hkv, d, L, l_a, n_p, repeats, rows alone / in the batch / in the group
-    (2, 1, 64, 129, 0, 0, 40),           # 64 / 128 / 128: just over the blocks that always take 64 rows
-    (2, 1, 64, 700, 33, 95, 12),         # 64 / 128 / 128: ragged tiles and segments
-    (4, 1, 64, 300, 100, 4900, 40),      # 64 / 128 / 128
-    (8, 8, 64, 150, 67, 933, 30),        # 64 / 256 / 128: rows 150 to 255 of the only tile missing, no shared K/V
-    (4, 2, 128, 129, 7, 0, 3),           # 128 / 128 / 128
-    (4, 2, 128, 513, 40, 4000, 20),      # 128 / 256 / 128: a last tile of one row
+    # hq, hkv, d, L, l_a, n_p, repeats, rows alone / in the batch / in the group (s: of shared blocks)
+    (2, 1, 64, 129, 0, 0, 40),           # s64 / s64 / s64: just over the blocks that always take 64 rows
+    (2, 1, 64, 700, 33, 95, 12),         # s64 / s64 / s64: ragged tiles and segments
+    (4, 1, 64, 300, 100, 4900, 40),      # s64 / 128 / s64
+    (8, 8, 64, 150, 67, 933, 30),        # s64 / s64 / s64: rows 150 to 191 of the last tile missing, no shared K/V
+    (4, 2, 128, 129, 7, 0, 3),           # s64 / s64 / s64
+    (4, 2, 128, 513, 40, 4000, 20),      # s64 / 256 / s64: a last tile of one row
     (28, 4, 128, 700, 33, 1467, 3),      # 128 / 256 / 256
-    (40, 8, 128, 289, 100, 1600, 3),     # 128 / 256 / 256: a last tile of 33 rows
+    (40, 8, 128, 289, 100, 1600, 3),     # s64 / 256 / 256: a last tile of 33 rows
+    # the other workgroups of either head_dim
+    (8, 4, 64, 77, 20, 50, 40),          # s64 / 64 / s64
+    (8, 2, 128, 100, 20, 50, 20),        # s64 / 64 / s64
+    (16, 4, 64, 1700, 0, 60, 2),         # s64 / 128 / 128
+    (16, 2, 128, 1200, 30, 70, 2),       # s64 / 128 / 128
+    (8, 8, 64, 1500, 100, 100, 83),      # s64 / 256 / s64: K and V exceed the caches
 ]
 
 

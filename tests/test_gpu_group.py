@@ -79,6 +79,41 @@ def test_group_matches_oracle_and_separate_calls(hq, hkv, d, shapes):
             assert torch.isnan(whole[0]).all() and torch.isnan(whole[-1]).all()   # nothing written outside the problem's rows
 
 
+LARGE = [
+    # hq, hkv, d, [(L, l_a, n_p), ...]: launches of 128 and of 256 rows a workgroup (tests/host/shared_blocks_check.cpp)
+    (16, 2, 128, [(900, 64, 0), (1300, 64, 200), (333, 0, 50)]),                                  # 128
+    (16, 8, 128, [(1900, 64, 0), (1300, 64, 200), (333, 0, 50)]),                                 # 128
+    (32, 4, 64, [(700, 64, 0), (640, 0, 100), (333, 10, 5)]),                                     # 128
+    (28, 4, 128, [(700, 33, 1467), (901, 33, 1700), (1000, 333, 0)]),                             # 128
+    (27, 27, 64, [(5250 - 37 * m, 500 - 40 * m, 11500 + 141 * m) for m in range(5)]),             # 256: K and V exceed the caches
+]
+
+
+@pytest.mark.parametrize("hq,hkv,d,shapes", LARGE)
+def test_group_of_unequal_problems_in_longer_workgroups(hq, hkv, d, shapes):
+    g = torch.Generator(device="cuda").manual_seed(hq + d)
+    scale = 1.0 / math.sqrt(d)
+    print(f"group of long workgroups hq={hq} hkv={hkv} d={d} shapes={shapes}", flush=True)
+    probs, whole = [], []
+    for L, l_a, n_p in shapes:
+        probs.append([torch.randn((n, h, d), generator=g, device="cuda", dtype=torch.bfloat16)
+                      for n, h in ((L, hq), (l_a, hkv), (l_a, hkv), (n_p, hkv), (n_p, hkv), (L, hkv), (L, hkv))])
+        whole.append(torch.full((L + 2, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda"))
+    res = apbv.apbv_host_attention_group([tuple(p) + (w[1:-1],) for p, w in zip(probs, whole)], scale, return_lse=True)
+    torch.cuda.synchronize()
+    for p, w, (out, lse) in zip(probs, whole, res):
+        plain, lse_p = apbv.apbv_host_attention(*p, scale, return_lse=True)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), plain.view(torch.int16)) and torch.equal(lse, lse_p)
+        assert torch.isnan(w[0]).all() and torch.isnan(w[-1]).all() and not torch.isnan(out).any()
+        # the first KV head and its query heads against the oracle, on rows at the edges of the tiles
+        L, n = out.shape[0], hq // hkv
+        rows = np.array([0, 127, 128, 255, 256, L - 1])
+        host = [x[:, :n if i == 0 else 1].contiguous().view(torch.int16).cpu().numpy().view(np.uint16) for i, x in enumerate(p)]
+        ref, _ = oracle.host_attention(*host, scale, rows=rows)
+        check(to_f64(out[:, :n])[rows], ref, f"L={L}, sampled rows")
+
+
 def test_group_physical_host_full_size():
     """Physical host 0 of 8 at the 128K configuration: anchor block (2048), virtual host 0 (no passing keys) and
     virtual host 15 (15 passing blocks of 1024), 16384 local tokens each; bit-identical to separate calls, sampled
