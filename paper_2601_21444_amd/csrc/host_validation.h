@@ -175,10 +175,9 @@ inline double attention_traffic(int head_dim, int group, const AttentionTiles& w
 }
 // tiles[]: of the launch cut into 64, 128 and 256 rows; kv_heads: KV heads, batch items and key ranges that a row tile of
 // the launch belongs to one of.
-//   head_dim 64   few workgroups: 64 rows (8 heads x 2048 rows 44 / 31 / 28 us with 256 / 128 / 64 rows; these launches share
-//                 their blocks between two waves, attention_shares_blocks: 22); else 128 (three fit a
-//                 unit, one of 256 rows), but not where 256 rows are one round and 128 two with the second tile half empty
-//                 (192 workgroups of 132 rows 9.1 / 9.9)
+//   head_dim 64   128 (three fit a unit, one of 256 rows).  Its two exceptions, 64 rows for few workgroups and 256 where these
+//                 are one round and 128 two with the second tile half empty, lie where launches share blocks
+//                 (attention_shares_blocks): no launch takes them any more, only query_estimate
 //   head_dim 128  by the estimates up to two rounds of 256 rows, whose spread they get right; beyond, and for the shortest
 //                 keys, by the keys alone: the fixed cost covered against the 4 to 10 % slower loop of 128 rows.  But 256
 //                 rows if the row tiles of a head share nothing with other heads and are not kept on one XCD (a number
@@ -205,8 +204,10 @@ inline int attention_rows(int head_dim, int group, double kv_heads, const Attent
 // a workgroup per unit always, with head_dim 64 (three fit a unit) up to three, and with head_dim 128 up to two where the
 // estimates say so.  Beyond, every wave's own reads of K and V from LDS cost more than the sharing saves (16 heads of 128
 // x 2048 rows behind 704 keys 50.6 / 50.4 us, 28 x 1500 behind 400 46.0 / 53.4).  Drawn from 700 measured launches: where it
-// is taken 1.18 times as fast on average, in one of 517 launches 3 % slower.  Blocks of at most kAttnNarrowMaxRows rows,
-// which take 64 rows either way: 400 launches, 1.13 times as fast, none slower.
+// is taken 1.18 times as fast on average, in one of 517 launches 3 % slower; of 150 others at the upper end of the ranges
+// (250 workgroups and more) one is 3 % slower, and 32 heads of 64 with their own K/V x 1436 rows (736) 5 %.  Blocks of at most
+// kAttnNarrowMaxRows rows, which take 64 rows either way, up to 256 workgroups, or 512 with head_dim 64: 400 launches, 1.13
+// times as fast, none slower; of 150 others one 3 %.
 inline bool attention_shares_blocks(int head_dim, const AttentionTiles (&tiles)[3]) {
   const AttentionTiles& t = tiles[0];
   if (head_dim == 64) return t.n <= 768;
@@ -328,10 +329,13 @@ struct QueryPlan {
   QueryKernel kernel;
   KeySplit split;
 };
-// Times in us, fitted to 18000 launches of 800 shapes (1 to 2048 queries, batches to 128, 64 to 200000 keys; within 9 %) while
-// the packed workgroups used 16x16x32 matrix instructions.  They have become up to 14 % faster, a workgroup per head with
-// shared blocks up to 20 %; the order of the plans is the same: constants refitted to 70000 launches chose 0.5 % better on
-// average and worse by more than 5 % in 325 of 7702 shapes, so these stay.
+// Times in us, fitted to 18000 launches of 800 shapes (1 to 2048 queries, batches to 128, 64 to 200000 keys; then within 9 %)
+// while the packed workgroups used 16x16x32 matrix instructions and no blocks were shared.  Packed workgroups have become up
+// to 14 % faster, a workgroup per head with shared blocks up to 20 %: of 320 shapes drawn over these ranges the plans chosen
+// now take 1.03 times the estimate in the median, 0.91 to 1.26 between the 5th and 95th in 100 (medians: a wave per range
+// 1.04, packed rows in 128 1.02, in 256 1.15, a workgroup per head with shared blocks 1.02, of 128 rows 1.22).  The order of
+// the plans has changed less: constants refitted to 70000 launches chose 0.5 % better on average and worse by more than 5 % in 325 of 7702
+// shapes, so these stay.
 // A workgroup with k keys takes alone + alone_per_key * k on a unit of its own, and every further one on the busiest unit
 // adds more + more_per_key * k, whether it runs beside the others or after them.
 struct QueryCost {
@@ -385,8 +389,8 @@ inline double query_estimate(QueryKernel kernel, const QueryBlock& q, const KeyS
   return std::sqrt(std::sqrt(both)) + (ks.n_splits > 1 ? 1.84 + parts * 0.6e-6 + 0.3 / 64 * ks.n_splits : 0);
 }
 // The fastest kernel and, unless `requested` ranges are asked for (>= 1), number of ranges up to most_splits.  As the
-// estimates are good to 9 %, a workgroup per query head with its own split stays unless another plan promises 5 %, or with
-// the ranges requested 10 %.  Of 1900 calls outside the fit 11 were 2 to 17 % slower than with a workgroup per head, its own
+// estimates are no better than that, a workgroup per query head with its own split stays unless another plan promises 5 %,
+// or with the ranges requested 10 %.  Of 1900 calls outside the fit 11 were 2 to 17 % slower than with a workgroup per head, its own
 // split or the ranges requested; the mean was 0.67 of its time.
 inline QueryPlan choose_query_plan(const QueryBlock& q, int requested, int64_t most_splits) {
   const int64_t n_tiles = key_tiles(q.n_keys);
@@ -541,8 +545,9 @@ inline bool share_selection(int64_t heads, int64_t L, int64_t l_p, const Compres
 // n_parts = 0: a workgroup per head and a gather launch.  The histograms take the place of the partial sums of the pooled
 // query, kPoolSplitMax * head_dim * 8 bytes a head, which bounds the length; every part reads all of a head's scores, which
 // bounds the heads.  Whole call, a workgroup per head / this (us, graph replay): 2 heads x 20000 keys 24.1 / 24.0, x 32768
-// 32.6 / 26.0, x 65536 57.7 / 35.7, x 250000 188 / 81; 16 x 65536 95.7 / 78.0; 32 x 30000 71.6 / 69.7; 48 x 20000 79.7 / 81.8.
-// From 8192 - kMaxBinRank rows on the bucket path of the one workgroup has no room and it sorts: 1 x 65536, 8192 rows 269 / 33.
+// 33.4 / 25.7, x 65536 56.7 / 35.6, x 250000 182 / 79; 16 x 65536 95.8 / 76.5; 32 x 30000 75.5 / 70.3; 48 x 20000 79.7 / 81.8
+// (before the parts of a head shared an XCD).  From 8192 - kMaxBinRank rows on the bucket path of the one workgroup has no room
+// and it sorts: 1 x 65536, 8192 rows 272 / 36.5.
 constexpr int kCoarseBins = 252;
 constexpr int kMaxLongHeads = 32, kLongScores = 24576;
 struct CoarseHistogram {         // of one part of a head's scores: counts (at most kResidentScores), and the map of all parts
