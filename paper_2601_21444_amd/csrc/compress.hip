@@ -556,6 +556,12 @@ __device__ __forceinline__ bool bucket_rank_select(const double* __restrict__ s,
 
 // Exact path for any input: radix select of the l_p-th largest key, most significant byte first, then
 // collection of the l_p winners (ties at the threshold by ascending index).
+// kByWaves: where ties have to be told apart by index, each wave reads a range of keys, instead of each thread, which reads a
+// line of memory a lane.  For long blocks, whose exact path runs in many workgroups at once: equal scores, us a call, 2 heads
+// x 65536, 2000 rows 558 -> 529, 32 x 131072, 1000 rows 1343 -> 1140.  In the other kernels, whose exact path lies in the
+// midst of code that is fetched once, it moves what lies behind: 154 -> 147 for 2 x 16384 equal scores, but up to 2 % of every
+// call of blocks of 4000 keys.
+template <bool kByWaves>
 __device__ __forceinline__ void radix_collect(const double* __restrict__ s, int64_t L, int64_t l_p, uint64_t* skeys,
                                               uint32_t* sidx, SelectShared& sh) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -616,11 +622,31 @@ __device__ __forceinline__ void radix_collect(const double* __restrict__ s, int6
         sidx[pos] = (uint32_t)j;
       }
     }
+  } else if constexpr (!kByWaves) {
+    // more equal keys than needed: take the `need` lowest indices.  Each thread scans a contiguous
+    // index range; an exclusive scan of the per-thread tie counts gives each tie its rank by index.
+    const int64_t chunk = (L + kSelectThreads - 1) / kSelectThreads;
+    const int64_t lo = (int64_t)tid * chunk, hi = (lo + chunk < L) ? lo + chunk : L;
+    uint32_t n_eq = 0;
+    for (int64_t j = lo; j < hi; ++j) n_eq += (score_key(s[j]) == kth);
+    uint32_t total;
+    uint32_t rank = block_scan_incl(n_eq, sh, &total) - n_eq;
+    for (int64_t j = lo; j < hi; ++j) {
+      const uint64_t key = score_key(s[j]);
+      if (key > kth) {
+        const uint32_t pos = atomicAdd(&sh.cnt, 1u);
+        skeys[pos] = key;
+        sidx[pos] = (uint32_t)j;
+      } else if (key == kth) {
+        if (rank < need) {
+          skeys[n_gt + rank] = key;
+          sidx[n_gt + rank] = (uint32_t)j;
+        }
+        ++rank;
+      }
+    }
   } else {
-    // more equal keys than needed: take the `need` lowest indices.  Each wave takes a contiguous range, 64 keys side by side
-    // at a time; the waves' tie counts give each tie its rank by index.  (A range per thread read a line a lane.  Equal
-    // scores, us a call: 2 heads x 65536, 2000 rows 558 -> 529, 32 x 131072, 1000 rows 1343 -> 1140, 2 x 16384, 1024 rows
-    // 154 -> 147.)
+    // more equal keys than needed: as above, a contiguous range per wave, 64 keys side by side
     constexpr int kWaves = kSelectThreads / 64;
     const int64_t span = (L + kSelectThreads - 1) / kSelectThreads * 64;
     const int64_t lo = wave * span, hi = lo + span < L ? lo + span : L;
@@ -679,7 +705,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(const double* __
 
   uint16_t* sbin = reinterpret_cast<uint16_t*>(sidx + cap);
   if (bucket_rank_select<false>(s, L, l_p, cap, skeys, sidx, sbin, idx_out + head * l_p, sh)) return;
-  radix_collect(s, L, l_p, skeys, sidx, sh);
+  radix_collect<false>(s, L, l_p, skeys, sidx, sh);
   int64_t n_sort = 1;
   while (n_sort < l_p) n_sort <<= 1;
   __syncthreads();
@@ -763,9 +789,8 @@ __global__ __launch_bounds__(kSelectThreads) void select_gather_kernel(const dou
   uint16_t* sbin = reinterpret_cast<uint16_t*>(sidx + cap);
   uint32_t first = 0, n_out = 0;
   const uint32_t* rows = sh.fill;
-  // (the exact path behind the rest of the code: between its halves it cost blocks of up to 1024 keys 0.1 to 0.2 us)
-  if (__builtin_expect(!bucket_rank_select<true, kPer>(s, L, l_p, cap, skeys, sidx, sbin, idx, sh, part, n_parts, &first, &n_out), 0)) {
-    radix_collect(s, L, l_p, skeys, sidx, sh);
+  if (!bucket_rank_select<true, kPer>(s, L, l_p, cap, skeys, sidx, sbin, idx, sh, part, n_parts, &first, &n_out)) {
+    radix_collect<false>(s, L, l_p, skeys, sidx, sh);
     int64_t n_sort = 1;
     while (n_sort < l_p) n_sort <<= 1;
     __syncthreads();
@@ -1070,7 +1095,7 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
   }
   const uint32_t* rows = sidx;
   if (__builtin_expect(exact, 0)) {
-    radix_collect(s, L, l_p, skeys, sidx, sh);
+    radix_collect<true>(s, L, l_p, skeys, sidx, sh);
     n_sort = (uint32_t)l_p;
     rows = sidx + first;
   }

@@ -64,8 +64,8 @@ def test_shared_selection(hkv, batch, L, l_p, kind):
 
 @pytest.mark.parametrize("L", [1, 63, 64, 65, 1023, 1024, 1025, 4097, 16384, 16385, 24577])
 def test_alike_scores_are_taken_in_index_order(L):
-    """The exact path's collection of equal scores, a range of keys a wave: ranges that end within 64 keys, are empty, or hold
-    one tie each; one workgroup a head (2 and 12 heads), shared selection, long blocks."""
+    """The exact path's collection of equal scores, a range of keys a thread or a wave: ranges that end within 64 keys, are
+    empty, or hold one tie each; one workgroup a head (2 and 12 heads), shared selection, long blocks."""
     for hkv, kind in ((2, "all"), (2, "few"), (12, "all")):
         rng = np.random.default_rng((89, L, hkv))
         l_p = max(1, L // 3)
