@@ -32,6 +32,11 @@
 // Softmax.  exp2 domain with the scale folded in.  The reference maximum m_ref of a query only moves when
 // some logit exceeds it by more than 2^8 (then O and l are rescaled): probabilities stay <= 2^8, and the
 // common path needs only each lane's own maximum over its 8 keys per query -- no cross-lane exchange.
+// Row sums are one more matrix instruction per query block and tile, with ones in place of V^T: it adds the probabilities
+// P^T of all 32 keys to what every lane of the row holds.  Eight two-element dot products on the vector ALU did it before,
+// of about 60 vector instructions a tile, and exchanges between the lane groups at the end.  us, dot products / this: 28
+// heads of 128, three problems of up to 16384 rows 6243 / 6188, 2 x 28 heads x 3001 rows 185.1 / 182.3, 2 heads of 64, three
+// problems of 16219 rows 270.5 / 258.6.
 //
 // Software pipeline.  The steps of a tile form a chain (S^T -> maximum -> exp -> P^T -> O^T); done tile
 // after tile a wave alternates between the matrix pipe and the vector ALU, and every LDS fragment read
@@ -129,7 +134,10 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   float m_ref[2] = {-INFINITY, -INFINITY};   // reference maximum of the scaled (log2-domain) logits, whole row
   float m_sub[2] = {0.f, 0.f};               // what the exponent subtracts: m_ref, or 0 while m_ref = -inf
   float s_far[2] = {-INFINITY, -INFINITY};   // raw logits above this move the reference: (m_ref + threshold) / scale
-  float l_run[kOwn] = {};                    // running sum of the bf16-rounded exp2(. - m_ref), this lane's keys only
+  f32x4 l_run[kOwn];                         // [0]: running sum of the bf16-rounded exp2(. - m_ref) over the row's keys (the other three are not used)
+#pragma unroll
+  for (int nq = 0; nq < kOwn; ++nq) l_run[nq] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
   const float inv_scale_log2 = 1.0f / p.scale_log2;
 
   // Keys the workgroup / this wave can see at all.
@@ -223,7 +231,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
         m_sub[nq] = m_new > -INFINITY ? m_new : 0.f;
         s_far[nq] = (m_new + kRescaleThreshold) * inv_scale_log2;
         if (nq < kOwn) {
-          l_run[nq] *= alpha;
+          l_run[nq][0] *= alpha;
 #pragma unroll
           for (int d = 0; d < T::DBN; ++d) o[d][nq] *= alpha;
         }
@@ -232,7 +240,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   };
 
   // ---- probabilities of the tile for query block nq: exp2 of the scaled logits minus the reference, rounded to bf16
-  // (the PV operand) with the rounded values added into the row sum two at a time.  (A row that has not seen a
+  // (the PV operand).  (A row that has not seen a
   // visible key yet -- possible in a key split -- has m_ref = -inf: subtract 0, every probability is exp2(-inf) = 0.)
   auto exp_block = [&](const STile& s, int nq, PTile& pw) {
 #pragma unroll
@@ -242,13 +250,19 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
         f32x2 xy = {__builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][nq][e], p.scale_log2, -m_sub[nq])),
                     __builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][nq][e + 1], p.scale_log2, -m_sub[nq]))};
         const bf16x2 c = __builtin_convertvector(xy, bf16x2);
-        l_run[nq] = __builtin_amdgcn_fdot2_f32_bf16(c, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, l_run[nq], false);
         pw[nq][2 * mb + (e >> 1)] = __builtin_bit_cast(uint32_t, c);
       }
   };
 
+  // ---- row sums += 1 P^T
+  auto add_sums = [&](int nq, const u32x4& pw) {
+    l_run[nq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, __builtin_bit_cast(bf16x8, pw), l_run[nq], 0, 0, 0);
+  };
+
   // ---- O^T += V^T P^T for the 32 keys of the tile
   auto pv = [&](const unsigned char* vt, const PTile& pw) {
+#pragma unroll
+    for (int nq = 0; nq < kOwn; ++nq) add_sums(nq, pw[nq]);
 #pragma unroll
     for (int d = 0; d < T::DBN; ++d) {
       const bf16x8 a = read_vt(vt, d);
@@ -293,10 +307,9 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     // The source lists each matrix instruction with its share of the vector and LDS instructions; the compiler's own
     // scheduler keeps that interleaving (pinning it with scheduling fences was measured 3 % slower).
     // exponential pipeline of tile t, one pair of probabilities at a time: pair pi = (nq, mb, first/second two rows);
-    // stages F (scale and subtract), E (exp2), C (round to bf16 into the B operand word), D (row sum)
+    // stages F (scale and subtract), E (exp2), C (round to bf16 into the B operand word)
     constexpr int kPairs = 4 * kOwn;
     float xf[kPairs][2];
-    uint32_t cw[kPairs];
     PTile pw;
     auto stage_f = [&](int pi) {
       const int nq = pi >> 2, mb = (pi >> 1) & 1, e = 2 * (pi & 1);
@@ -310,12 +323,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     auto stage_c = [&](int pi) {
       const int nq = pi >> 2, mb = (pi >> 1) & 1;
       f32x2 xy = {xf[pi][0], xf[pi][1]};
-      cw[pi] = __builtin_bit_cast(uint32_t, __builtin_convertvector(xy, bf16x2));
-      pw[nq][2 * mb + (pi & 1)] = cw[pi];
-    };
-    auto stage_d = [&](int pi) {
-      const int nq = pi >> 2;
-      l_run[nq] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, cw[pi]), bf16x2{(__bf16)1.0f, (__bf16)1.0f}, l_run[nq], false);
+      pw[nq][2 * mb + (pi & 1)] = __builtin_bit_cast(uint32_t, __builtin_convertvector(xy, bf16x2));
     };
     // ---- phase A: one slice per matrix instruction of S^T(t+1)
     s16x4 vlo[T::DBN], vhi[T::DBN];
@@ -334,7 +342,6 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
           if constexpr (pi > 0) stage_c(pi - 1);
         } else {
           stage_e(pi);
-          if constexpr (pi > 0) stage_d(pi - 1);
         }
       });
       // ... and the 2 DBN transposing reads of the V^T operands of phase B
@@ -348,13 +355,13 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
       });
     });
     stage_c(kPairs - 1);
-    stage_d(kPairs - 1);
     // ---- phase B: one slice per matrix instruction of O^T(t)
     float lm[2];
     constexpr int nB = kOwn * T::DBN, nK = kPrefetchK ? 2 * T::KSD : 0;
     static_for<nB>([&](auto I) {
       constexpr int i = I;
       constexpr int d = i / kOwn, nq = i % kOwn;
+      if constexpr (d == 0) add_sums(nq, pw[nq]);
       const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vlo[d], vhi[d], 0, 1, 2, 3, 4, 5, 6, 7));
       o[d][nq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, pw[nq]), o[d][nq], 0, 0, 0);
       // the K fragments of tile t+2
@@ -482,15 +489,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   // ---- epilogue: normalise, round to bf16, store; optional log-sum-exp
 #pragma unroll
   for (int nq = 0; nq < kOwn; ++nq) {
-    float l_tot = l_run[nq];
-    {
-      auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(l_tot), __float_as_uint(l_tot), false, false);
-      l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    }
-    {
-      auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_tot), __float_as_uint(l_tot), false, false);
-      l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-    }
+    const float l_tot = l_run[nq][0];
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;     // a key split may leave a row without any visible key
     if (i_row[nq] < p.L) {
       const int64_t i = i_row[nq];
