@@ -29,9 +29,18 @@
 //                  bytes addressed by lanes i/4, 4+i/4, 8+i/4, 12+i/4), each delivering 4 consecutive
 //                  keys of one head-dim column.
 //
-// Softmax.  exp2 domain with the scale folded in.  The reference maximum m_ref of a query only moves when
-// some logit exceeds it by more than 2^8 (then O and l are rescaled): probabilities stay <= 2^8, and the
-// common path needs only each lane's own maximum over its 8 keys per query -- no cross-lane exchange.
+// Softmax.  exp2 domain with the scale folded in.  The exponents of a row are taken against a reference that only moves when
+// some logit of its 16-row block exceeds its row's by more than 2^5; then the references of the block become their rows'
+// maxima, and O and the row sums are rescaled.  What is subtracted lies kReferenceBias above the reference, so that such a
+// logit's probability is 2 or more, and nothing but the probabilities has to be looked at: bit 14 of a bf16 says so, and
+// the words that hold a tile's are or-ed together (six instructions a tile; the maxima of the logits, which told it before,
+// took fourteen).  If a bit is set, the probabilities are formed again from the logits, which are kept until then.  bf16
+// and float32 have the exponents to spare: what underflows is 2^-121 of the row's maximum.  us, maxima of the logits / this:
+// 28 heads of 128, three problems of up to 16384 rows 6064 / 5910, 16 heads x 16384 rows behind 9216 keys 1859 / 1807, 2 x 28
+// heads x 3001 rows 181.1 / 179.4, 2 heads of 64, three problems of 16219 rows 255.5 / 247.3.  A probability equal to the
+// reference is not rounded, so the sooner it moves the closer the results: relative errors against float64 of 300 rows of
+// unit-variance logits with 2^2, 2^5, 2^8 1.86e-3, 2.03e-3, 2.11e-3 (2^8 for 32 rows at a time, as it was: 2.11e-3); every
+// move costs, and times grow from 2^4 down (28 heads of 128 as above, moves at 2^2 / 2^3 / 2^4 / 2^5 / 2^8: 6142 / 6077 / 6039 / 6036 / 6014).
 // Row sums are one more matrix instruction per query block and tile, with ones in place of V^T: it adds the probabilities
 // P^T of all 32 keys to what every lane of the row holds.  Eight two-element dot products on the vector ALU did it before,
 // of about 60 vector instructions a tile, and exchanges between the lane groups at the end.  us, dot products / this: 28
@@ -42,7 +51,7 @@
 // after tile a wave alternates between the matrix pipe and the vector ALU, and every LDS fragment read
 // is waited for where it is issued.  Here, while the matrix pipe computes S^T of tile t+1, the vector
 // ALU exponentiates tile t and the V^T operands of tile t are read; while it accumulates O^T of tile t,
-// the vector ALU takes the maxima of tile t+1 and the K fragments of tile t+2 are read.  K therefore
+// the K fragments of tile t+2 are read.  K therefore
 // runs one tile ahead of V in LDS, and no LDS read is consumed in the phase that issues it.  Tiles that
 // touch the mask diagonal, and the few rounds around a segment boundary, take the plain sequence.
 //
@@ -63,21 +72,21 @@ constexpr int kWaves = 8;          // waves per workgroup of the main variant: 2
 constexpr int kWavesNarrow = 2;    // of the variants for less work than fills the chip with 256-row workgroups: 64
 constexpr int kWavesShort = 4;     // and 128 query rows
 constexpr int kBM = 32 * kWaves;   // query rows per workgroup (main variant)
+constexpr float kNoReference = -3.402823466e38f;      // what is subtracted in a row that has seen no visible key: below every logit
 constexpr int kRing = 4;           // K tiles, and V tiles, resident in LDS
 
 // One workgroup's work: row tile `qt` of batch item b and query head (kvh, g), key range `split`.
-// kShare: waves per 32-row block.  With two, each finishes 16 of the rows (O, probabilities, row sums) and forms S^T of all
-// 32, because the reference maximum of a block moves for all its rows at once: the results are those of one wave, bit for
-// bit.  This is for launches that leave SIMDs empty: a wave alone on its SIMD does not overlap its matrix and vector
-// instructions (16 + 4.2 n cycles for one 16x16x32 and n vector instructions, measured), so its time is their sum, and
-// sharing takes a quarter of the first and half of the second off it.  us, 64-row workgroups of two waves / of four: 16
-// heads of 128 x 1024 rows behind 224 keys 29.3 / 22.2, 2 heads of 64 x 512 rows behind 160 12.8 / 10.9.
-template <int D, int W, int kShare>
+// kOwn: 16-row blocks per wave.  Two share every K and V fragment that is read; one is for launches that leave SIMDs empty: a
+// wave alone on its SIMD does not overlap its matrix and vector instructions (16 + 4.2 n cycles for one 16x16x32 and n vector
+// instructions, measured), so its time is their sum, half of what it is with two.  Results are the same bit for bit.  Four
+// waves of one block, against two waves of two blocks / two waves that finish 16 rows each but form S^T of all 32 (as the
+// reference was one for a block before) / now (us): 16 heads of 128 x 1024 rows behind 224 keys 29.3 / 22.2 / 19.1, 2 heads
+// of 64 x 512 rows behind 160 12.8 / 10.9 / 9.4.
+template <int D, int W, int kOwn>
 __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const int qt, const int b, const int kvh,
                                                     const int g, const int split) {
   using T = Tile<D, W>;
-  constexpr int kRows = 32 * W / kShare;      // query rows of the workgroup
-  constexpr int kOwn = 2 / kShare;            // 16-row query blocks this wave finishes: the first of its two
+  constexpr int kRows = 16 * kOwn * W;        // query rows of the workgroup
   __shared__ __attribute__((aligned(1024))) unsigned char k_lds[kRing][T::TILE_BYTES];
   __shared__ __attribute__((aligned(1024))) unsigned char v_lds[kRing][T::TILE_BYTES];
   // the LDS destination of an LDS-direct load travels in M0, which addresses the first 64 KB of the workgroup's LDS
@@ -90,18 +99,16 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
 
   const int h = kvh * p.group + g;
   const int64_t i0 = (int64_t)qt * kRows;               // first row of the workgroup
-  const int64_t iw = i0 + wave / kShare * 32;           // first row of the wave's block
-  const int first16 = kShare == 2 ? (wave & 1) * 16 : 0;                         // the 16 rows it finishes (first)
-  const int64_t i_row[2] = {iw + first16 + li, iw + (16 - first16) + li};        // this lane's two rows
+  const int64_t iw = i0 + wave * 16 * kOwn;             // first row of the wave
 
   Segs ks, vs;
   key_segments(p, b, kvh, ks, vs);
 
   // ---- Q^T fragments (B operand of S^T), kept in registers for the whole key loop.
-  bf16x8 qf[T::KSD][2];
+  bf16x8 qf[T::KSD][kOwn];
 #pragma unroll
-  for (int nq = 0; nq < 2; ++nq) {
-    const int64_t r = i_row[nq] < p.L ? i_row[nq] : p.L - 1;
+  for (int nq = 0; nq < kOwn; ++nq) {
+    const int64_t i = iw + 16 * nq + li, r = i < p.L ? i : p.L - 1;
     const bf16_t* qrow = p.q.ptr + (int64_t)b * p.q.sb + (int64_t)h * p.q.sh + r * p.q.st;
 #pragma unroll
     for (int c = 0; c < T::KSD; ++c) qf[c][nq] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qrow + 32 * c + 8 * lg));
@@ -125,20 +132,20 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     }
   }
 
-  // ---- online softmax state.  Per lane: two queries (nq = 0, 1); the four lane groups hold disjoint key subsets.
+  // ---- online softmax state.  Per lane: kOwn queries; the four lane groups hold disjoint key subsets.
   f32x4 o[T::DBN][kOwn];
 #pragma unroll
   for (int d = 0; d < T::DBN; ++d)
 #pragma unroll
     for (int nq = 0; nq < kOwn; ++nq) o[d][nq] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_ref[2] = {-INFINITY, -INFINITY};   // reference maximum of the scaled (log2-domain) logits, whole row
-  float m_sub[2] = {0.f, 0.f};               // what the exponent subtracts: m_ref, or 0 while m_ref = -inf
-  float s_far[2] = {-INFINITY, -INFINITY};   // raw logits above this move the reference: (m_ref + threshold) / scale
-  f32x4 l_run[kOwn];                         // [0]: running sum of the bf16-rounded exp2(. - m_ref) over the row's keys (the other three are not used)
+  float m_sub[kOwn];                         // what the exponent subtracts: the row's reference + kReferenceBias
+  f32x4 l_run[kOwn];                         // [0]: running sum of the bf16-rounded probabilities of the row (the other three are not used)
 #pragma unroll
-  for (int nq = 0; nq < kOwn; ++nq) l_run[nq] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int nq = 0; nq < kOwn; ++nq) {
+    m_sub[nq] = kNoReference;
+    l_run[nq] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
   const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
-  const float inv_scale_log2 = 1.0f / p.scale_log2;
 
   // Keys the workgroup / this wave can see at all.
   // Query i sees the virtual keys 0 .. min(i + n_vis, s_kv - 1); the second bound only matters when there is no
@@ -152,12 +159,14 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   const int64_t t_begin64 = (int64_t)split * per_split;
   const int t_begin = (int)(t_begin64 < n_tiles_vis ? t_begin64 : n_tiles_vis);
   const int n_tiles = (int)(t_begin64 + per_split < n_tiles_vis ? t_begin64 + per_split : n_tiles_vis);
-  const int t_last_wave = (int)(last_key(iw + 31) / kBN);     // last tile any row of the wave can see into
+  const int t_last_wave = (int)(last_key(iw + 16 * kOwn - 1) / kBN);     // last tile any row of the wave can see into
   const int n_w = t_last_wave + 1 < n_tiles ? t_last_wave + 1 : n_tiles;     // the wave computes tiles [t_begin, n_w)
   const int t_mask_wave = (int)((last_key(iw) + 1) / kBN);    // first tile with a key some row of the wave cannot see
-  const int jrel0[2] = {(int)last_key(i_row[0]), (int)last_key(i_row[1])};   // last visible virtual key of each row
+  int jrel0[kOwn];                                            // last visible virtual key of each row
+#pragma unroll
+  for (int nq = 0; nq < kOwn; ++nq) jrel0[nq] = (int)last_key(iw + 16 * nq + li);
 
-  typedef f32x4 STile[2][2];       // S^T of one tile: [16-key block][16-query block]
+  typedef f32x4 STile[2][kOwn];      // S^T of one tile: [16-key block][16-query block]
   typedef u32x4 PTile[kOwn];         // P^T of one tile as the B operand of O^T: [16-query block], four 32-bit words
 
   auto read_k = [&](const unsigned char* kt, int mb, int c) {
@@ -177,7 +186,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
       for (int mb = 0; mb < 2; ++mb) {
         const bf16x8 a = read_k(kt, mb, c);
 #pragma unroll
-        for (int nq = 0; nq < 2; ++nq)
+        for (int nq = 0; nq < kOwn; ++nq)
           s[mb][nq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[c][nq], c == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[mb][nq], 0, 0, 0);
       }
   };
@@ -185,7 +194,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   // ---- mask of a tile that reaches above the wave's first diagonal element
   auto apply_mask = [&](STile& s, int t) {
 #pragma unroll
-    for (int nq = 0; nq < 2; ++nq) {
+    for (int nq = 0; nq < kOwn; ++nq) {
       const int jrel_max = jrel0[nq] - t * kBN;          // last visible key of this query, tile-relative
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
@@ -195,53 +204,8 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     }
   };
 
-  // ---- this lane's largest logit per query
-  auto lane_max = [&](const STile& s, float (&lm)[2]) {
-#pragma unroll
-    for (int nq = 0; nq < 2; ++nq) {
-      float mx = __builtin_fmaxf(s[0][nq][0], s[0][nq][1]);
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int r = (mb == 0 ? 2 : 0); r < 4; ++r) mx = __builtin_fmaxf(mx, s[mb][nq][r]);
-      lm[nq] = mx;
-    }
-  };
-
-  // ---- lazy rescaling: the reference maximum moves only when some logit of the tile exceeds it by more than the
-  // threshold; then it becomes the exact row maximum so far and O, l are rescaled.  (m_ref = -inf before the first
-  // visible key: alpha = 0; a row still without one keeps its zeros.  The test is a NaN-free comparison of raw
-  // logits: s_far = -inf while m_ref = -inf, so the first finite logit moves the reference.)
-  auto advance_reference = [&](const float (&lm)[2]) {
-    if ((__builtin_amdgcn_ballot_w64(lm[0] > s_far[0]) | __builtin_amdgcn_ballot_w64(lm[1] > s_far[1])) != 0) {
-#pragma unroll
-      for (int nq = 0; nq < 2; ++nq) {
-        float mx = lm[nq];
-        {
-          auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-          mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-        }
-        {
-          auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-          mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-        }
-        const float m_new = fmaxf(m_ref[nq], mx * p.scale_log2);
-        const float alpha = m_new > -INFINITY ? __builtin_amdgcn_exp2f(m_ref[nq] - m_new) : 1.f;
-        m_ref[nq] = m_new;
-        m_sub[nq] = m_new > -INFINITY ? m_new : 0.f;
-        s_far[nq] = (m_new + kRescaleThreshold) * inv_scale_log2;
-        if (nq < kOwn) {
-          l_run[nq][0] *= alpha;
-#pragma unroll
-          for (int d = 0; d < T::DBN; ++d) o[d][nq] *= alpha;
-        }
-      }
-    }
-  };
-
   // ---- probabilities of the tile for query block nq: exp2 of the scaled logits minus the reference, rounded to bf16
-  // (the PV operand).  (A row that has not seen a
-  // visible key yet -- possible in a key split -- has m_ref = -inf: subtract 0, every probability is exp2(-inf) = 0.)
+  // (the PV operand).
   auto exp_block = [&](const STile& s, int nq, PTile& pw) {
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
@@ -249,9 +213,43 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
       for (int e = 0; e < 4; e += 2) {
         f32x2 xy = {__builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][nq][e], p.scale_log2, -m_sub[nq])),
                     __builtin_amdgcn_exp2f(__builtin_fmaf(s[mb][nq][e + 1], p.scale_log2, -m_sub[nq]))};
-        const bf16x2 c = __builtin_convertvector(xy, bf16x2);
-        pw[nq][2 * mb + (e >> 1)] = __builtin_bit_cast(uint32_t, c);
+        pw[nq][2 * mb + (e >> 1)] = __builtin_bit_cast(uint32_t, __builtin_convertvector(xy, bf16x2));
       }
+  };
+
+  // ---- lazy rescaling: where a probability of a 16-row block is 2 or more, the references of the block's rows become their
+  // largest logits of the tile, where these are larger, and the probabilities are formed again.  (A row that has not seen a
+  // visible key has kNoReference: hidden keys give exp2(-inf) = 0, the first visible one +inf.)  Both blocks take the same
+  // steps, the one that stays with its references as they are: branches around them take 40 bytes of scratch.
+  auto settle_reference = [&](const STile& s, PTile& pw) {
+    uint32_t any[kOwn], all = 0;
+#pragma unroll
+    for (int nq = 0; nq < kOwn; ++nq) all |= any[nq] = pw[nq][0] | pw[nq][1] | pw[nq][2] | pw[nq][3];
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64((all & 0x40004000u) != 0) == 0, 1)) return;
+#pragma unroll
+    for (int nq = 0; nq < kOwn; ++nq) {
+      const bool moves = __builtin_amdgcn_ballot_w64((any[nq] & 0x40004000u) != 0) != 0;
+      float mx = s[0][nq][0];
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int r = (mb == 0 ? 1 : 0); r < 4; ++r) mx = __builtin_fmaxf(mx, s[mb][nq][r]);
+      {
+        auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+      }
+      {
+        auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+      }
+      const float m_new = moves ? fmaxf(m_sub[nq], __builtin_fmaf(mx, p.scale_log2, kReferenceBias)) : m_sub[nq];
+      const float alpha = __builtin_amdgcn_exp2f(m_sub[nq] - m_new);
+      m_sub[nq] = m_new;
+      l_run[nq][0] *= alpha;
+#pragma unroll
+      for (int d = 0; d < T::DBN; ++d) o[d][nq] *= alpha;
+      exp_block(s, nq, pw);
+    }
   };
 
   // ---- row sums += 1 P^T
@@ -273,17 +271,15 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   };
 
   // ---- plain sequence, for the first tile and for tiles on the mask diagonal
-  auto prepare = [&](const unsigned char* kt, int t, STile& s) {       // S^T, mask, reference
+  auto prepare = [&](const unsigned char* kt, int t, STile& s) {       // S^T, mask
     qk(kt, s);
     if (t >= t_mask_wave) apply_mask(s, t);
-    float lm[2];
-    lane_max(s, lm);
-    advance_reference(lm);
   };
-  auto finish = [&](const unsigned char* vt, const STile& s) {          // probabilities, O^T
+  auto finish = [&](const unsigned char* vt, const STile& s) {          // probabilities, reference, O^T
     PTile pw;
 #pragma unroll
     for (int nq = 0; nq < kOwn; ++nq) exp_block(s, nq, pw);
+    settle_reference(s, pw);
     pv(vt, pw);
   };
 
@@ -291,9 +287,9 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
   // in kf, S^T into sn).  No LDS read is waited for where it is issued: the K fragments of a tile are read one phase
   // ahead, the V^T operands of phase B during phase A.
   //   phase A: S^T(t+1) on the matrix pipe from kf; the exponentials of tile t on the vector ALU; the V^T operands of
-  //            tile t read into vf
-  //   phase B: O^T(t) from vf; the lane maxima of tile t+1; with kPrefetchK the K fragments of tile t+2 (at
-  //            kt_after, landed since the last barrier) read into kf
+  //            tile t read into vf; then the reference, should a probability ask for it
+  //   phase B: O^T(t) from vf; with kPrefetchK the K fragments of tile t+2 (at kt_after, landed since the
+  //            last barrier) read into kf
   typedef bf16x8 KFrags[2 * T::KSD];        // [c][mb]
   auto load_k = [&](const unsigned char* kt, KFrags& kf) {
 #pragma unroll
@@ -327,10 +323,10 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     };
     // ---- phase A: one slice per matrix instruction of S^T(t+1)
     s16x4 vlo[T::DBN], vhi[T::DBN];
-    constexpr int nA = 4 * T::KSD;                 // matrix instructions of phase A
+    constexpr int nA = 2 * kOwn * T::KSD;          // matrix instructions of phase A
     static_for<nA>([&](auto I) {
       constexpr int i = I;
-      constexpr int c = i / 4, nq = (i / 2) % 2, mb = i % 2;
+      constexpr int c = i / (2 * kOwn), nq = (i / 2) % kOwn, mb = i % 2;
       sn[mb][nq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[2 * c + mb], qf[c][nq],
                                                            c == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sn[mb][nq], 0, 0, 0);
       // the slices of the exponential pipeline are spread evenly over the nA matrix instructions
@@ -355,8 +351,8 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
       });
     });
     stage_c(kPairs - 1);
+    settle_reference(sc, pw);
     // ---- phase B: one slice per matrix instruction of O^T(t)
-    float lm[2];
     constexpr int nB = kOwn * T::DBN, nK = kPrefetchK ? 2 * T::KSD : 0;
     static_for<nB>([&](auto I) {
       constexpr int i = I;
@@ -370,17 +366,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
         constexpr int k = k0 + J;
         kf[k] = read_k(kt_after, k % 2, k / 2);
       });
-      // the lane maxima of tile t+1: 8 instructions
-      constexpr int m0 = (8 * i) / nB, m1 = (8 * (i + 1)) / nB;
-      static_for<m1 - m0>([&](auto J) {
-        constexpr int m = m0 + J, nqm = m / 4, st = m % 4;
-        if constexpr (st == 0) lm[nqm] = __builtin_fmaxf(sn[0][nqm][0], sn[0][nqm][1]);
-        if constexpr (st == 1) lm[nqm] = __builtin_fmaxf(lm[nqm], __builtin_fmaxf(sn[0][nqm][2], sn[0][nqm][3]));
-        if constexpr (st == 2) lm[nqm] = __builtin_fmaxf(lm[nqm], __builtin_fmaxf(sn[1][nqm][0], sn[1][nqm][1]));
-        if constexpr (st == 3) lm[nqm] = __builtin_fmaxf(lm[nqm], __builtin_fmaxf(sn[1][nqm][2], sn[1][nqm][3]));
-      });
     });
-    advance_reference(lm);
   };
 
   // One tile step of the wave in the plain sequence: K(t+1) is at kt_next, V(t) at vt, S^T(t) in sc; leaves S^T(t+1)
@@ -486,13 +472,15 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     t += 4;
   }
 
-  // ---- epilogue: normalise, round to bf16, store; optional log-sum-exp
+  // ---- epilogue: normalise, round to bf16, store; optional log-sum-exp.  (The lane's place is asked for anew, so that no
+  // register holds it through the key loop.)
+  const int lane_out = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), lg_out = lane_out >> 4;
 #pragma unroll
   for (int nq = 0; nq < kOwn; ++nq) {
     const float l_tot = l_run[nq][0];
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;     // a key split may leave a row without any visible key
-    if (i_row[nq] < p.L) {
-      const int64_t i = i_row[nq];
+    const int64_t i = iw + 16 * nq + (lane_out & 15);
+    if (i < p.L) {
       bf16_t* orow = p.out + (int64_t)split * p.split_stride_out + (((int64_t)b * p.L + i) * p.hq + h) * D;
 #pragma unroll
       for (int d = 0; d < T::DBN; ++d) {
@@ -503,11 +491,11 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
         u32x2 w;
         w.x = __builtin_bit_cast(uint32_t, c01);
         w.y = __builtin_bit_cast(uint32_t, c23);
-        *reinterpret_cast<u32x2*>(orow + 16 * d + 4 * lg) = w;
+        *reinterpret_cast<u32x2*>(orow + 16 * d + 4 * lg_out) = w;
       }
-      if (p.lse != nullptr && lg == 0)
+      if (p.lse != nullptr && lg_out == 0)
         p.lse[(int64_t)split * p.split_stride_lse + ((int64_t)b * p.hq + h) * p.L + i] =
-            l_tot > 0.f ? (m_ref[nq] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f : -INFINITY;
+            l_tot > 0.f ? (m_sub[nq] + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f : -INFINITY;
     }
   }
 }
@@ -527,7 +515,7 @@ __device__ __forceinline__ int deal(int row, int xcd, int period) {
 }
 
 // ---- workgroup -> (query tile, head, batch, key range); the heads of one KV group share an XCD
-template <int D, int W, int kShare = 1>
+template <int D, int W, int kOwn = 2>
 __global__ __launch_bounds__(64 * W, 2) void host_attention_kernel(const AttnParams p, const int n_qtiles,
                                                                    const int n_items) {
   const int xcd = blockIdx.x % kXcds;
@@ -541,13 +529,13 @@ __global__ __launch_bounds__(64 * W, 2) void host_attention_kernel(const AttnPar
   const int qt = n_qtiles - 1 - item / bh;       // heaviest query tiles first
   const int b = (item % bh) / p.hkv;
   const int kvh = (item % bh) % p.hkv;
-  attention_workgroup<D, W, kShare>(p, qt, b, kvh, g, split);
+  attention_workgroup<D, W, kOwn>(p, qt, b, kvh, g, split);
 }
 
 // ---- several attention problems of different lengths in one launch (the two virtual hosts and the anchor
 // block of a physical host, Alg. 1 / Sec. 4.3): one workgroup per entry of the merged heaviest-first order of
 // all (problem, query tile) pairs, per KV head and group member.
-template <int D, int W, int kShare = 1>
+template <int D, int W, int kOwn = 2>
 __global__ __launch_bounds__(64 * W, 2) void host_attention_group_kernel(const AttnGroupParams gp) {
   const int group = gp.item[0].group, hkv = gp.item[0].hkv;
   const int xcd = blockIdx.x % kXcds;
@@ -558,18 +546,18 @@ __global__ __launch_bounds__(64 * W, 2) void host_attention_group_kernel(const A
   const int entry = unit / hkv, kvh = unit % hkv;
   int m, qt;
   decode_group_entry(gp.sched, entry, m, qt);
-  if (m >= gp.n_items || qt < 0 || (int64_t)qt * (32 * W / kShare) >= gp.item[m].L) return;      // never taken for a schedule the launcher built
+  if (m >= gp.n_items || qt < 0 || (int64_t)qt * (16 * kOwn * W) >= gp.item[m].L) return;      // never taken for a schedule the launcher built
   // (a copy, so that the fields live in scalar registers like the single-problem kernel's by-value argument
   // instead of being fetched from the argument block where they are used)
   const AttnParams item = gp.item[m];
-  attention_workgroup<D, W, kShare>(item, qt, 0, kvh, g, 0);
+  attention_workgroup<D, W, kOwn>(item, qt, 0, kvh, g, 0);
 }
 
 }  // namespace
 
-template <int W, int kShare = 1>
+template <int W, int kOwn = 2>
 static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t stream) {
-  constexpr int kRows = 32 * W / kShare;
+  constexpr int kRows = 16 * kOwn * W;
   const int n_qtiles = (int)((p.L + kRows - 1) / kRows);
   const int64_t n_items = (int64_t)n_qtiles * p.batch * p.hkv * p.n_splits;
   const int64_t n_blocks = (n_items + kXcds - 1) / kXcds * kXcds * p.group;
@@ -578,9 +566,9 @@ static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t
   dim3 block(64 * W);
   Launcher launch(stream);
   if (head_dim == 128)
-    launch(host_attention_kernel<128, W, kShare>, grid, block, 0, p, n_qtiles, (int)n_items);
+    launch(host_attention_kernel<128, W, kOwn>, grid, block, 0, p, n_qtiles, (int)n_items);
   else if (head_dim == 64)
-    launch(host_attention_kernel<64, W, kShare>, grid, block, 0, p, n_qtiles, (int)n_items);
+    launch(host_attention_kernel<64, W, kOwn>, grid, block, 0, p, n_qtiles, (int)n_items);
   else
     return APBV_ERR_UNSUPPORTED;
   return launch.status();
@@ -589,7 +577,7 @@ static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t
 apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t stream) {
   static_assert(kAttnQueryTile == kBM && kAttnNarrowQueryTile == 32 * kWavesNarrow, "tile sizes the host-side planning assumes");
   switch (attention_kernel(head_dim, p.group, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits)) {
-    case AttentionKernel::kShared64: return launch_variant<kWavesShort, 2>(p, head_dim, stream);
+    case AttentionKernel::kShared64: return launch_variant<kWavesShort, 1>(p, head_dim, stream);
     case AttentionKernel::kNarrow64: return launch_variant<kWavesNarrow>(p, head_dim, stream);
     case AttentionKernel::k128: return launch_variant<kWavesShort>(p, head_dim, stream);
     case AttentionKernel::k256: break;
@@ -597,19 +585,19 @@ apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t
   return launch_variant<kWaves>(p, head_dim, stream);
 }
 
-template <int W, int kShare = 1>
+template <int W, int kOwn = 2>
 static apbv_status launch_group_variant(AttnGroupParams& gp, int head_dim, const int64_t* n_vis, const int64_t* rows, hipStream_t stream) {
   static_assert(sizeof(AttnGroupParams) <= 4096, "kernel arguments are limited to 4 KB");
-  if (!build_group_schedule(gp.n_items, n_vis, rows, gp.sched, 32 * W / kShare)) return APBV_ERR_UNSUPPORTED;
+  if (!build_group_schedule(gp.n_items, n_vis, rows, gp.sched, 16 * kOwn * W)) return APBV_ERR_UNSUPPORTED;
   const AttnParams& p0 = gp.item[0];
   const int64_t n_units = (int64_t)gp.sched.n_entries * p0.hkv;
   const int64_t n_blocks = (n_units + kXcds - 1) / kXcds * kXcds * p0.group;
   if (n_blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
   Launcher launch(stream);
   if (head_dim == 128)
-    launch(host_attention_group_kernel<128, W, kShare>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
+    launch(host_attention_group_kernel<128, W, kOwn>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
   else if (head_dim == 64)
-    launch(host_attention_group_kernel<64, W, kShare>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
+    launch(host_attention_group_kernel<64, W, kOwn>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);
   else
     return APBV_ERR_UNSUPPORTED;
   return launch.status();
@@ -625,7 +613,7 @@ apbv_status launch_host_attention_group(AttnGroupParams& gp, int head_dim, hipSt
     rows[m] = gp.item[m].L;
   }
   switch (attention_group_kernel(head_dim, gp.item[0].hq, gp.item[0].hkv, n, n_vis, rows)) {
-    case AttentionKernel::kShared64: return launch_group_variant<kWavesShort, 2>(gp, head_dim, n_vis, rows, stream);
+    case AttentionKernel::kShared64: return launch_group_variant<kWavesShort, 1>(gp, head_dim, n_vis, rows, stream);
     case AttentionKernel::k256: return launch_group_variant<kWaves>(gp, head_dim, n_vis, rows, stream);
     default: return launch_group_variant<kWavesShort>(gp, head_dim, n_vis, rows, stream);
   }

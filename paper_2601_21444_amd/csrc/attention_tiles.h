@@ -8,6 +8,7 @@ namespace {
 
 constexpr int kBN = 32;                     // keys per tile (one k-step of O^T)
 constexpr float kRescaleThreshold = 8.0f;   // log2 units
+constexpr float kReferenceBias = 4.0f;      // log2 units between a row's reference and what attention.hip subtracts
 constexpr int kXcds = 8;                    // accelerator dies with an L2 of their own; workgroup id modulo 8
 
 #define APBV_LDS(T) __attribute__((address_space(3))) T*
