@@ -514,12 +514,17 @@ __device__ __forceinline__ int deal(int row, int xcd, int period) {
   return row * kXcds + xcd;
 }
 
+template <int D, int W, int kOwn>
+__device__ constexpr int workgroups_per_unit() {      // by LDS with head_dim 128, by registers with 64
+  return D == 128 ? (W == 8 ? 1 : 2) : (W == 8 ? 1 : kOwn == 1 ? 4 : 3);
+}
+
 // ---- workgroup -> (query tile, head, batch, key range); the heads of one KV group share an XCD
 template <int D, int W, int kOwn = 2>
 __global__ __launch_bounds__(64 * W, 2) void host_attention_kernel(const AttnParams p, const int n_qtiles,
                                                                    const int n_items) {
   const int xcd = blockIdx.x % kXcds;
-  const int slot = blockIdx.x / kXcds;
+  const int slot = arrange_workgroup(blockIdx.x / kXcds, gridDim.x / kXcds, workgroups_per_unit<D, W, kOwn>());
   const int item_split = deal(slot / p.group, xcd, p.batch * p.hkv * p.n_splits);
   if (item_split >= n_items) return;
   const int split = item_split % p.n_splits;     // key ranges of one item share nothing: spread them over the XCDs
@@ -539,7 +544,7 @@ template <int D, int W, int kOwn = 2>
 __global__ __launch_bounds__(64 * W, 2) void host_attention_group_kernel(const AttnGroupParams gp) {
   const int group = gp.item[0].group, hkv = gp.item[0].hkv;
   const int xcd = blockIdx.x % kXcds;
-  const int slot = blockIdx.x / kXcds;
+  const int slot = arrange_workgroup(blockIdx.x / kXcds, gridDim.x / kXcds, workgroups_per_unit<D, W, kOwn>());
   const int unit = deal(slot / group, xcd, hkv);
   if (unit >= gp.sched.n_entries * hkv) return;
   const int g = slot % group;
