@@ -20,6 +20,8 @@
 // for a few heads of longer blocks
 //   coarse_histogram_kernel  counts of the scores per coarse bin          [n_hist x Hkv x batch]
 //   long_select_gather_kernel  as above, over the coarse bins of a part   [parts x Hkv x batch]
+// for many heads of at most 1024 keys, instead of all of these,
+//   short_compress_kernel  every step in one launch                       [parts x Hkv x batch]
 // and otherwise the same as two launches
 //   select_kernel       the ordered indices                               [Hkv x batch]
 //   gather_kernel       K_c, V_c rows                                     [l_p*Hkv/.. x batch]
@@ -47,6 +49,16 @@ __device__ __forceinline__ double dpp_f64(double x) {
   lo = __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, false);
   hi = __builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, false);
   return __hiloint2double(hi, lo);
+}
+
+// x plus that of the lane 16 or 32 away, in both.  (The swap of a register with itself leaves the lower group's value in both
+// groups of the first result, the upper one's in those of the second.)
+template <int AWAY>
+__device__ __forceinline__ double add_rows(double x) {
+  const uint32_t lo = (uint32_t)__double2loint(x), hi = (uint32_t)__double2hiint(x);
+  auto swap = [](uint32_t w) { return AWAY == 16 ? __builtin_amdgcn_permlane16_swap(w, w, false, false) : __builtin_amdgcn_permlane32_swap(w, w, false, false); };
+  const auto l = swap(lo), h = swap(hi);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -114,6 +126,24 @@ __global__ __launch_bounds__(T) void pool_query_kernel(View q, int64_t n_q, int 
     for (int w = 0; w < T / 64; ++w) sum += part[w][threadIdx.x];
     qpart[(((int64_t)b * hkv + v) * n_split + sp) * D + threadIdx.x] = sum;
   }
+}
+
+// The sums of four rows over the LPR lanes of each, a reduce-scatter: after the two exchanges inside a quad each lane holds
+// one row's sum over its quad, two rotations by 4 and 8 lanes finish it.  The last quad of a row's lanes (c >= LPR - 4) holds
+// complete sums, this lane that of row *u.  Every row takes the same summation tree (the adds commute), so identical rows get
+// identical scores.
+template <int LPR>
+__device__ __forceinline__ double reduce_rows(const double (&a)[4], int c, int* u) {
+  const bool odd1 = (c & 1) != 0, odd2 = (c & 2) != 0;
+  double keep0 = odd1 ? a[2] : a[0], keep1 = odd1 ? a[3] : a[1];
+  keep0 += dpp_f64<kDppXor1>(odd1 ? a[0] : a[2]);
+  keep1 += dpp_f64<kDppXor1>(odd1 ? a[1] : a[3]);
+  double acc = odd2 ? keep1 : keep0;
+  acc += dpp_f64<kDppXor2>(odd2 ? keep0 : keep1);
+  acc += dpp_f64<kDppRor4>(acc);
+  if (LPR == 16) acc += dpp_f64<kDppRor8>(acc);
+  *u = (odd1 ? 2 : 0) + (odd2 ? 1 : 0);
+  return acc;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -219,18 +249,8 @@ __global__ __launch_bounds__(256) void score_kernel(View k, int64_t L, const dou
       }
       a[u] = acc;
     }
-    // Reduce the four rows over the row's lanes as a reduce-scatter: after the two exchanges inside a quad each
-    // lane holds one row's sum over its quad, two rotations by 4 and 8 lanes finish it.  Every row takes the same
-    // summation tree (the adds commute), so identical rows get identical scores.
-    const bool odd1 = (c & 1) != 0, odd2 = (c & 2) != 0;
-    double keep0 = odd1 ? a[2] : a[0], keep1 = odd1 ? a[3] : a[1];
-    keep0 += dpp_f64<kDppXor1>(odd1 ? a[0] : a[2]);
-    keep1 += dpp_f64<kDppXor1>(odd1 ? a[1] : a[3]);
-    double acc = odd2 ? keep1 : keep0;
-    acc += dpp_f64<kDppXor2>(odd2 ? keep0 : keep1);
-    acc += dpp_f64<kDppRor4>(acc);
-    if (LPR == 16) acc += dpp_f64<kDppRor8>(acc);
-    const int u = (odd1 ? 2 : 0) + (odd2 ? 1 : 0);     // the row this lane ended up with
+    int u;                                             // the row this lane ends up with
+    const double acc = reduce_rows<LPR>(a, c, &u);
     const int64_t j = r0 + u * RPS + rsub;
     if (c >= LPR - 4 && j < r_end) {                   // the last quad of the row's lanes holds complete sums
       // written through to memory as the kernel runs (device-scope store): left to the write-back cache, the
@@ -773,6 +793,28 @@ constexpr int kMaxSelectParts = 16;
 static_assert(kLdsSortMax / kMaxSelectParts + 1 + (int64_t)kMaxBinRank <= kBins && 64 + (int64_t)kMaxBinRank <= kBins,
               "a part's share of the outputs and one bucket more fit sh.fill");
 
+// The exact path of a shared selection: every workgroup sorts the head's l_p largest and writes its share of the indices, outputs
+// [*first, *first + *n_out), which it returns.
+__device__ __forceinline__ const uint32_t* exact_share(const double* __restrict__ s, int64_t L, int64_t l_p, uint64_t* skeys, uint32_t* sidx,
+                                                       int32_t* __restrict__ idx, SelectShared& sh, int part, int n_parts, uint32_t* first, uint32_t* n_out) {
+  const int tid = threadIdx.x;
+  radix_collect<false>(s, L, l_p, skeys, sidx, sh);
+  int64_t n_sort = 1;
+  while (n_sort < l_p) n_sort <<= 1;
+  __syncthreads();
+  for (int64_t i = l_p + tid; i < n_sort; i += kSelectThreads) {   // padding sorts last
+    skeys[i] = 0;
+    sidx[i] = 0xffffffffu;
+  }
+  __syncthreads();
+  bitonic_sort(skeys, sidx, n_sort);
+  *first = (uint32_t)(l_p * part / n_parts);
+  *n_out = (uint32_t)(l_p * (part + 1) / n_parts) - *first;
+  const uint32_t* rows = sidx + *first;
+  for (uint32_t i = tid; i < *n_out; i += kSelectThreads) idx[*first + i] = (int32_t)rows[i];
+  return rows;
+}
+
 template <int D, int kPer>
 __global__ __launch_bounds__(kSelectThreads) void select_gather_kernel(const double* __restrict__ s_ws, View k, View v, int64_t L, int64_t l_p,
                                                                        int64_t cap, int32_t* __restrict__ idx_out, int hkv,
@@ -789,22 +831,8 @@ __global__ __launch_bounds__(kSelectThreads) void select_gather_kernel(const dou
   uint16_t* sbin = reinterpret_cast<uint16_t*>(sidx + cap);
   uint32_t first = 0, n_out = 0;
   const uint32_t* rows = sh.fill;
-  if (!bucket_rank_select<true, kPer>(s, L, l_p, cap, skeys, sidx, sbin, idx, sh, part, n_parts, &first, &n_out)) {
-    radix_collect<false>(s, L, l_p, skeys, sidx, sh);
-    int64_t n_sort = 1;
-    while (n_sort < l_p) n_sort <<= 1;
-    __syncthreads();
-    for (int64_t i = l_p + tid; i < n_sort; i += kSelectThreads) {   // padding sorts last
-      skeys[i] = 0;
-      sidx[i] = 0xffffffffu;
-    }
-    __syncthreads();
-    bitonic_sort(skeys, sidx, n_sort);
-    first = (uint32_t)(l_p * part / n_parts);
-    n_out = (uint32_t)(l_p * (part + 1) / n_parts) - first;
-    rows = sidx + first;
-    for (uint32_t i = tid; i < n_out; i += kSelectThreads) idx[first + i] = (int32_t)rows[i];
-  }
+  if (!bucket_rank_select<true, kPer>(s, L, l_p, cap, skeys, sidx, sbin, idx, sh, part, n_parts, &first, &n_out))
+    rows = exact_share(s, L, l_p, skeys, sidx, idx, sh, part, n_parts, &first, &n_out);
   __syncthreads();
   copy_rows<D>(k, v, rows, first, n_out, b, head, hkv, l_p, k_c, v_c);
 }
@@ -1115,6 +1143,129 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
   copy_rows<D>(k, v, rows, first, n_out, b, head, hkv, l_p, k_c, v_c);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Short blocks: pooled query, scores, selection and gather in one launch (compresses_at_once: where).  A launch that waits
+// for another costs more than what a unit's workgroup does in each step of a short block, so every workgroup adds up the
+// pooled query and scores all keys of its head itself, into LDS, and then shares the selection and the rows as above.  Bound
+// by the latencies of its steps and by what one unit's cache delivers, (probe rows + keys) * D * 2 bytes a workgroup.
+template <int D>
+__global__ __launch_bounds__(kSelectThreads, 8) void short_compress_kernel(View q, View k, View v, int L, int64_t l_p, int group, int hkv, double* __restrict__ s_out,
+                                                                        int32_t* __restrict__ idx_out, bf16_t* __restrict__ k_c, bf16_t* __restrict__ v_c) {
+  constexpr int LPR = D / 8;                   // lanes per row
+  constexpr int RPS = kSelectThreads / LPR;    // rows per step of the workgroup
+  constexpr int kWaves = kSelectThreads / 64;
+  constexpr int UNROLL = 4;
+  static_assert(LPR == 8 || LPR == 16, "the cross-lane reduction below is written for 8 or 16 lanes per row");
+  static_assert(kShortKeys == kSelectThreads, "one score a thread");
+  __shared__ SelectShared sh;
+  __shared__ double qs[D], scores[kShortKeys];
+  __shared__ __attribute__((aligned(16))) unsigned char buf[kWaves * D * 8 > kShortKeys * 14 ? kWaves * D * 8 : kShortKeys * 14];
+  double(*qpart)[D] = reinterpret_cast<double(*)[D]>(buf);                  // until the pooled query is complete
+  uint64_t* skeys = reinterpret_cast<uint64_t*>(buf);                       // from then on
+  uint32_t* sidx = reinterpret_cast<uint32_t*>(buf + kShortKeys * 8);
+  uint16_t* sbin = reinterpret_cast<uint16_t*>(buf + kShortKeys * 12);
+
+  const int part = blockIdx.x, n_parts = gridDim.x, head = blockIdx.y, b = blockIdx.z;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = tid % LPR, rsub = tid / LPR;
+  const bf16_t* kb = k.ptr + (int64_t)b * k.sb + (int64_t)head * k.sh + 8 * c;
+  auto load = [&](int r0, u32x4(&x)[UNROLL]) {
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      const int j = r0 + u * RPS + rsub;
+      x[u] = u32x4{0u, 0u, 0u, 0u};
+      if (j < L) x[u] = *reinterpret_cast<const u32x4*>(kb + (int64_t)j * k.st);
+    }
+  };
+  u32x4 x[UNROLL];
+  load(0, x);                                  // travel while the pooled query is added up
+
+  // ---- the pooled query: rows (t, g) in steps of RPS, which advance without divisions
+  {
+    const bf16_t* qb = q.ptr + (int64_t)b * q.sb + (int64_t)head * group * q.sh + 8 * c;
+    const int n_rows = (int)q.tokens * group, dt = RPS / group, dg = RPS % group;
+    int t = rsub / group, g = rsub % group;
+    double sum[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sum[e] = 0.0;
+    for (int r = rsub; r < n_rows; r += UNROLL * RPS) {
+      u32x4 y[UNROLL];
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        y[u] = u32x4{0u, 0u, 0u, 0u};
+        if (r + u * RPS < n_rows) y[u] = *reinterpret_cast<const u32x4*>(qb + (int64_t)t * q.st + (int64_t)g * q.sh);
+        t += dt;
+        g += dg;
+        if (g >= group) {
+          g -= group;
+          ++t;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u)
+        if (r + u * RPS < n_rows) {            // (whole waves without a row skip the additions)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            sum[2 * e] += bf16_to_f64(y[u][e] & 0xffffu);
+            sum[2 * e + 1] += bf16_to_f64(y[u][e] >> 16);
+          }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if (LPR == 8) sum[e] += dpp_f64<kDppRor8>(sum[e]);
+      sum[e] = add_rows<16>(sum[e]);
+      sum[e] = add_rows<32>(sum[e]);
+    }
+    if (lane < LPR) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qpart[wave][8 * c + e] = sum[e];
+    }
+    __syncthreads();
+    if (tid < D) {
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) s += qpart[w][tid];
+      qs[tid] = s;
+    }
+    __syncthreads();
+  }
+
+  // ---- the scores, by the same sums as score_kernel's
+  double qv[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) qv[e] = qs[8 * c + e];
+  for (int r0 = 0; r0 < L; r0 += RPS * UNROLL) {
+    double a[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      a[u] = 0.0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        a[u] = __builtin_fma(qv[2 * e], bf16_to_f64(x[u][e] & 0xffffu), a[u]);
+        a[u] = __builtin_fma(qv[2 * e + 1], bf16_to_f64(x[u][e] >> 16), a[u]);
+      }
+    }
+    load(r0 + RPS * UNROLL, x);
+    int u;
+    const double acc = reduce_rows<LPR>(a, c, &u);
+    const int j = r0 + u * RPS + rsub;
+    if (c >= LPR - 4 && j < L) scores[j] = acc;
+  }
+  __syncthreads();
+  const int64_t h = (int64_t)b * hkv + head;
+  if (s_out && part == 0 && tid < L) s_out[h * L + tid] = scores[tid];
+
+  // ---- selection and gather, as in select_gather_kernel
+  int32_t* idx = idx_out + h * l_p;
+  uint32_t first = 0, n_out = 0;
+  const uint32_t* rows = sh.fill;
+  if (!bucket_rank_select<true, 1>(scores, L, l_p, kShortKeys, skeys, sidx, sbin, idx, sh, part, n_parts, &first, &n_out))
+    rows = exact_share(scores, L, l_p, skeys, sidx, idx, sh, part, n_parts, &first, &n_out);
+  __syncthreads();
+  copy_rows<D>(k, v, rows, first, n_out, b, head, hkv, l_p, k_c, v_c);
+}
+
 // Scratch of the entry point that takes no workspace (apbv_compress_kv_noalloc): a fixed array in the code object,
 // one copy per GPU at that GPU's own address.  In host code the array's name is only a handle for the symbol lookup
 // below; kernels and launch code use the looked-up device address.
@@ -1199,6 +1350,12 @@ apbv_status launch_compress(const CompressParams& p_in, hipStream_t stream) {
     if (p.workspace_bytes < stats_off + stats_bytes) return APBV_ERR_WORKSPACE;
     const apbv_status st = launch_matrix_scores(p, scores, ws + stats_off, stream);
     if (st != APBV_OK) return st;
+  } else if (const int parts = compresses_at_once(p.q_probe.tokens * p.group, p.d, (int64_t)p.hkv * p.batch, p.L, p.l_p); parts > 0) {
+    auto compress = [&](auto kernel) {
+      launch(kernel, dim3((unsigned)parts, p.hkv, p.batch), dim3(kSelectThreads), 0, p.q_probe, p.k, p.v, (int)p.L, p.l_p, p.group, p.hkv, p.scores_out, p.idx_out, p.k_c, p.v_c);
+    };
+    p.d == 128 ? compress(short_compress_kernel<128>) : compress(short_compress_kernel<64>);
+    return launch.status();
   } else {
     const int64_t n_rows = p.q_probe.tokens * p.group;
     const bool pooled = pools_in_scores(n_rows, p.d, (int64_t)p.hkv * p.batch, p.L);

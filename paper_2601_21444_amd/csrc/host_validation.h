@@ -541,6 +541,23 @@ inline bool share_selection(int64_t heads, int64_t L, int64_t l_p, const Compres
          (w.n_sort < kLdsSortMax || l_p + kMaxBinRank <= w.n_sort || L <= w.n_sort);
 }
 
+// Workgroups a head of the compression in one launch (short_compress_kernel), 0 where it takes a launch per step.  More heads
+// than share a selection, whose compression is four launches, of up to kShortKeys keys: one launch while the pooled query and the
+// scores, which every workgroup repeats, cost less than the launches, and wherever the heads fill the chip by themselves.  Whole
+// call, a launch per step / one (us, graph replay; probe rows x head_dim, keys a head): 128 heads, 512 x 64, 256 15.8 / 10.0;
+// 480 heads 512 x 64, 512 31.4 / 20.4, 512 x 128, 1024 50.8 / 36.0; 32 heads, 448 x 128, 256 14.5 / 12.3; beyond the lines
+// 32 heads, 512 x 128, 512 15.3 / 16.0, 1024 16.6 / 24.2, 96 heads, 512 x 128, 829 19.4 / 19.8; with up to eight heads, two or
+// three launches, 16 x 64, 256 7.6 / 7.9, 512 x 128, 1024 11.6 / 17.1.
+constexpr int kShortKeys = 1024;               // keys whose scores a workgroup keeps in LDS, one a thread
+inline int compresses_at_once(int64_t n_rows, int head_dim, int64_t heads, int64_t L, int64_t l_p) {
+  const int64_t work = (2 * L + n_rows) * head_dim;
+  if (l_p < 1 || L > kShortKeys || n_rows > 1024 || heads <= kMaxSharedHeads) return 0;
+  if (work > (heads < 128 ? 110 << 10 : 256 << 10) && heads < 256) return 0;
+  int64_t parts = l_p / 32 < 16 ? l_p / 32 : 16;
+  parts = parts * heads <= 256 ? parts : 256 / heads;
+  return (int)(parts > 1 ? parts : 1);
+}
+
 // Long blocks, a few heads: the scores' histogram by n_hist workgroups a head, selection and gather by n_parts (compress.hip);
 // n_parts = 0: a workgroup per head and a gather launch.  The histograms take the place of the partial sums of the pooled
 // query, kPoolSplitMax * head_dim * 8 bytes a head, which bounds the length; every part reads all of a head's scores, which

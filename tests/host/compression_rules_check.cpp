@@ -107,6 +107,13 @@ int main() {
   for (int64_t rows : {1, 15, 16, 17, 64, 65, 160}) EXPECT(pools_in_scores(rows, 128, 2, 700));
   for (int64_t rows : {31, 33, 128, 129, 320}) EXPECT(pools_in_scores(rows, 64, 2, 700));
   EXPECT(!pools_in_scores(161, 128, 2, 700) && !pools_in_scores(321, 64, 2, 700));
+  // one launch for all steps (tests/test_gpu_short_blocks.py): its sizes on both sides of every line
+  EXPECT(compresses_at_once(1, 64, 9, 1, 1) == 1 && compresses_at_once(1, 64, 8, 1, 1) == 0);
+  EXPECT(compresses_at_once(129, 64, 12, 513, 100) == 3 && compresses_at_once(65, 128, 10, 257, 257) == 8 && compresses_at_once(264, 128, 12, 256, 96) == 3);
+  EXPECT(compresses_at_once(512, 128, 96, 829, 100) == 0 && compresses_at_once(112, 64, 9, 600, 400) == 12);
+  EXPECT(compresses_at_once(10, 64, 128, 1023, 33) == 1 && compresses_at_once(9, 128, 128, 700, 65) == 2 && compresses_at_once(4, 128, 256, 1024, 512) == 1);
+  EXPECT(compresses_at_once(1024, 64, 272, 1024, 40) == 1 && compresses_at_once(1025, 64, 272, 1024, 40) == 0);
+  EXPECT(compresses_at_once(2, 64, 256, 1025, 40) == 0 && compresses_at_once(2, 64, 256, 1024, 0) == 0);
   std::printf("compression rules ok\n");
   return 0;
 }
