@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -25,3 +26,10 @@ def pytest_collection_modifyitems(config, items):
     for item in items:
         if "gpu" in item.keywords:
             item.add_marker(skip)
+
+
+@pytest.fixture(autouse=True, scope="module")
+def collect_garbage():
+    """Tensors that earlier tests left in reference cycles (a traceback and its frame) are freed here, not while a test looks at
+    the memory that is allocated."""
+    gc.collect()
