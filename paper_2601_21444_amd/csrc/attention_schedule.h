@@ -87,21 +87,19 @@ APBV_HOST_DEVICE inline void decode_group_entry(const GroupSchedule& s, int entr
 
 // Which of an XCD's n work items, numbered heaviest first, its s-th workgroup takes.  Workgroups are dispatched to the 32
 // units in turn, so unit j gets numbers j, 32 + j, ... until it holds per_unit of them, and further ones go where one has
-// ended.  Items taken in that order would give unit 0 the heaviest of every round and unit 31 the lightest.  So
-//   - odd rounds run backwards, and where the last round is not full its units are those with the lightest items of the
-//     rounds before: what the units hold adds up to about the same;
-//   - up to one item more per unit than two fit (m > 0 of them): the lightest 3 m go to m units, three each, the lightest of
-//     them dispatched last.  In plain order the units' two workgroups could end together and take two of the last ones.
-// With more items than that the ends even out by themselves, and only the first rounds are arranged.  us, plain order / this:
-// 16 heads of 128 x 4 items, 1024 rows behind 283 keys (two workgroups of 128 rows a unit) 36.9 / 35.5, x 1160 rows (some
-// units three) 56.5 / 47.5, 8 heads of 128 with their own K/V x 3122 rows (64-row workgroups, some units two) 43.0 / 40.6, two
-// heads of 64, three problems of 16219 rows 240.6 / 225.1.  26 drawn launches of 513 to 768 workgroups of 128 rows: 1.06
-// times as fast on average, 3 of them 2 to 4 % slower.
+// ended.  Items taken in that order (kInTurn) would give unit 0 the heaviest of every round and unit 31 the lightest.  So
+//   - kFolded: odd rounds run backwards, and where the last round is not full its units are those with the lightest items of
+//     the rounds before: what the units hold adds up to about the same.  With more items than the units hold the ends even out
+//     by themselves, and only the first rounds are arranged;
+//   - kThrees: of up to one item more per unit than two fit (m > 0 of them) the lightest 3 m go to m units, three each, the
+//     lightest of them dispatched last.  In turn the units' two workgroups could end together and take two of the last ones.
+// arrangement_of() says which.
 constexpr int kUnitsPerXcd = 32;
-APBV_HOST_DEVICE inline int arrange_workgroup(int s, int n, int per_unit) {
+enum Arrangement { kFolded, kThrees, kInTurn };
+APBV_HOST_DEVICE inline int arrange_workgroup(int s, int n, int per_unit, int how = kThrees) {
   const int round = s / kUnitsPerXcd, unit = s % kUnitsPerXcd;
-  if (n <= kUnitsPerXcd) return s;
-  if (per_unit == 2 && n > 2 * kUnitsPerXcd && n <= 3 * kUnitsPerXcd) {
+  if (n <= kUnitsPerXcd || how == kInTurn) return s;
+  if (how == kThrees && per_unit == 2 && n > 2 * kUnitsPerXcd && n <= 3 * kUnitsPerXcd) {
     const int m = n - 2 * kUnitsPerXcd, pairs = kUnitsPerXcd - m;        // units with three items, with two
     if (round == 2) return n - m + unit;
     if (unit < pairs) return round == 0 ? unit : 2 * pairs - 1 - unit;
@@ -113,6 +111,21 @@ APBV_HOST_DEVICE inline int arrange_workgroup(int s, int n, int per_unit) {
   const int rank = unit >= more ? unit - more : unit + kUnitsPerXcd - more;
   if (round & 1) return round * kUnitsPerXcd + kUnitsPerXcd - 1 - rank;
   return round * kUnitsPerXcd + (round == last ? unit : rank);
+}
+// By the items' weights, weight(r) of the r-th heaviest of an XCD's n (two to a unit).  Folded where they lie far apart: the
+// pairs beside the threes would weigh more than a folded pair and one of the lightest, which are dispatched where one has
+// ended.  In turn for a few items beyond two a unit that weigh about as much as the others.  us, in turn / folded / threes:
+//   16 heads of 128, 5279 rows behind 570 keys 135.3 / 134.2 / 148.2     4430 behind 1500 134.6 / 140.8 / 129.5
+//   8 heads of 128 with their own K/V, 11179 rows behind 522 keys 252.7 / 250.7 / 286.2     8887 behind 1897 221.0 / 210.9 / 206.3
+//   (m = 3) 8526 behind 1500 203.2 / 195.9 / 194.8, behind 5000 307.1 / 331.9 / 336.9     (6) 8910 behind 5000 361.9 / 347.3 / 332.5
+//   28 heads of 128 (6) 2382 behind 1500 117.1 / 109.1 / 111.0, behind 5000 239.8 / 245.6 / 248.1, 2 x 1230 behind 1500 94.3 / 97.1 / 97.8
+// Not always right: 28 heads x 1088 rows in three problems 37.4 / 40.5 / 38.9.
+template <typename Weight>
+inline Arrangement arrangement_of(int n, Weight&& weight) {
+  const int m = n - 2 * kUnitsPerXcd, pairs = kUnitsPerXcd - m;
+  if (m <= 0 || pairs <= 0) return kThrees;
+  if (m <= 6 && (0.2 + 0.055 * m) * (double)weight(0) < (double)weight(n - 1)) return kInTurn;
+  return weight(2 * pairs - 1) <= weight(2 * kUnitsPerXcd - 1) + weight(2 * kUnitsPerXcd) ? kThrees : kFolded;
 }
 
 }  // namespace apbv
