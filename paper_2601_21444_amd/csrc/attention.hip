@@ -34,7 +34,7 @@
 // maxima, and O and the row sums are rescaled.  What is subtracted lies kReferenceBias above the reference, so that such a
 // logit's probability is 2 or more, and nothing but the probabilities has to be looked at: bit 14 of a bf16 says so, and
 // the words that hold a tile's are or-ed together (six instructions a tile; the maxima of the logits, which told it before,
-// took fourteen).  If a bit is set, the probabilities are formed again from the logits, which are kept until then.  bf16
+// took fourteen).  If a bit is set, the block's probabilities are formed again from the logits, which are kept until then.  bf16
 // and float32 have the exponents to spare: what underflows is 2^-121 of the row's maximum.  us, maxima of the logits / this:
 // 28 heads of 128, three problems of up to 16384 rows 6064 / 5910, 16 heads x 16384 rows behind 9216 keys 1859 / 1807, 2 x 28
 // heads x 3001 rows 181.1 / 179.4, 2 heads of 64, three problems of 16219 rows 255.5 / 247.3.  A probability equal to the
@@ -219,36 +219,54 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
 
   // ---- lazy rescaling: where a probability of a 16-row block is 2 or more, the references of the block's rows become their
   // largest logits of the tile, where these are larger, and the probabilities are formed again.  (A row that has not seen a
-  // visible key has kNoReference: hidden keys give exp2(-inf) = 0, the first visible one +inf.)  Both blocks take the same
-  // steps, the one that stays with its references as they are: branches around them take 40 bytes of scratch.
-  auto settle_reference = [&](const STile& s, PTile& pw) {
-    uint32_t any[kOwn], all = 0;
+  // visible key has kNoReference: hidden keys give exp2(-inf) = 0, the first visible one +inf.)
+  auto asks = [&](const u32x4& pw) {       // lanes with such a probability
+    return __builtin_amdgcn_ballot_w64(((pw[0] | pw[1] | pw[2] | pw[3]) & 0x40004000u) != 0);
+  };
+  auto tile_reference = [&](const STile& s, int nq) {      // the row's largest logit of the tile + kReferenceBias
+    float mx = s[0][nq][0];
 #pragma unroll
-    for (int nq = 0; nq < kOwn; ++nq) all |= any[nq] = pw[nq][0] | pw[nq][1] | pw[nq][2] | pw[nq][3];
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64((all & 0x40004000u) != 0) == 0, 1)) return;
+    for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-    for (int nq = 0; nq < kOwn; ++nq) {
-      const bool moves = __builtin_amdgcn_ballot_w64((any[nq] & 0x40004000u) != 0) != 0;
-      float mx = s[0][nq][0];
+      for (int r = (mb == 0 ? 1 : 0); r < 4; ++r) mx = __builtin_fmaxf(mx, s[mb][nq][r]);
+    {
+      auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+      mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    }
+    {
+      auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+      mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    }
+    return __builtin_fmaf(mx, p.scale_log2, kReferenceBias);
+  };
+  auto move_reference = [&](const STile& s, int nq, PTile& pw) {
+    const float m_new = fmaxf(m_sub[nq], tile_reference(s, nq));
+    const float alpha = __builtin_amdgcn_exp2f(m_sub[nq] - m_new);
+    m_sub[nq] = m_new;
+    l_run[nq][0] *= alpha;
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+    for (int d = 0; d < T::DBN; ++d) o[d][nq] *= alpha;
+    exp_block(s, nq, pw);
+  };
+  // Only the blocks that ask take these steps, behind a branch each.  In the hot loop these lie inside one for both, which is 1 %
+  // faster at 256 rows; the plain sequence, which is there several times, would take 20 to 52 bytes of scratch so.
+  // Both blocks stepping together, branch-free, and the first tile behind the branch too, as it was, against this (us; queries of
+  // 12 times unit variance, and of unit variance): 2 x 28 heads x 3001 rows 208.5 / 197.0, 175.8 / 174.8; 16 heads x 8192 rows behind
+  // 2560 keys 409.3 / 388.7, 357.9 / 357.9; 28 x 8192 behind 4096 908.0 / 871.1, 801.1 / 801.3; 8 heads of 64 x 8192 behind 1000
+  // 122.1 / 115.0, 104.3 / 104.2; of one tile, 23 blocks of a row x 28 heads of 128 10.6 / 10.0.
+  auto settle_reference = [&](auto hot, const STile& s, PTile& pw) {
+    if constexpr (decltype(hot)::value) {
+      uint64_t moves[kOwn], some = 0;
 #pragma unroll
-        for (int r = (mb == 0 ? 1 : 0); r < 4; ++r) mx = __builtin_fmaxf(mx, s[mb][nq][r]);
-      {
-        auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-      }
-      {
-        auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-      }
-      const float m_new = moves ? fmaxf(m_sub[nq], __builtin_fmaf(mx, p.scale_log2, kReferenceBias)) : m_sub[nq];
-      const float alpha = __builtin_amdgcn_exp2f(m_sub[nq] - m_new);
-      m_sub[nq] = m_new;
-      l_run[nq][0] *= alpha;
+      for (int nq = 0; nq < kOwn; ++nq) some |= moves[nq] = asks(pw[nq]);
+      if (__builtin_expect(some == 0, 1)) return;
 #pragma unroll
-      for (int d = 0; d < T::DBN; ++d) o[d][nq] *= alpha;
-      exp_block(s, nq, pw);
+      for (int nq = 0; nq < kOwn; ++nq)
+        if (moves[nq] != 0) move_reference(s, nq, pw);
+    } else {
+#pragma unroll
+      for (int nq = 0; nq < kOwn; ++nq)
+        if (__builtin_expect(asks(pw[nq]) != 0, 0)) move_reference(s, nq, pw);
     }
   };
 
@@ -279,7 +297,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     PTile pw;
 #pragma unroll
     for (int nq = 0; nq < kOwn; ++nq) exp_block(s, nq, pw);
-    settle_reference(s, pw);
+    settle_reference(std::false_type{}, s, pw);
     pv(vt, pw);
   };
 
@@ -351,7 +369,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
       });
     });
     stage_c(kPairs - 1);
-    settle_reference(sc, pw);
+    settle_reference(std::true_type{}, sc, pw);
     // ---- phase B: one slice per matrix instruction of O^T(t)
     constexpr int nB = kOwn * T::DBN, nK = kPrefetchK ? 2 * T::KSD : 0;
     static_for<nB>([&](auto I) {
@@ -403,7 +421,11 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     if (t_begin + 2 < n_tiles) kst.issue(ka[2]);
     vst.issue(va[0]);
     if (t_begin + 1 < n_tiles) vst.issue(va[1]);
-    if (t_begin < n_w) prepare(k_lds[0], t_begin, s_a);
+    if (t_begin < n_w) {
+      prepare(k_lds[0], t_begin, s_a);
+#pragma unroll
+      for (int nq = 0; nq < kOwn; ++nq) m_sub[nq] = fmaxf(m_sub[nq], tile_reference(s_a, nq));   // every row's first move: nothing to rescale
+    }
   }
   // loads of the two barrier intervals of a four-tile round that starts at tile t
   auto issue_first = [&](int t) {

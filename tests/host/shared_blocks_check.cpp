@@ -27,6 +27,9 @@ int main() {
   EXPECT(attention_shares_blocks(128, 1, 4, 40, 5000, false, 64) && !attention_shares_blocks(128, 1, 4, 40, 5000, false, 65));
 
   typedef AttentionKernel K;
+  // tests/test_gpu_reference_moves.py: waves of one 16-row block alone, of two in the batch
+  EXPECT(attention_kernel(64, 2, 1, 2, 545, 1000, true, 1) == K::kShared64 && attention_kernel(64, 2, 44, 2, 545, 1000, true, 1) == K::k128);
+  EXPECT(attention_kernel(128, 2, 1, 2, 545, 1000, true, 1) == K::kShared64 && attention_kernel(128, 2, 40, 2, 545, 1000, true, 1) == K::k256);
   struct { int hq, hkv, d; int64_t L, n_vis; int repeats; K alone, batch, group; } launches[] = {
       {2, 1, 64, 129, 0, 40, K::kShared64, K::kShared64, K::kShared64},   {2, 1, 64, 700, 128, 12, K::kShared64, K::kShared64, K::kShared64},
       {4, 1, 64, 300, 5000, 40, K::kShared64, K::k128, K::kShared64},     {8, 8, 64, 150, 1000, 30, K::kShared64, K::kShared64, K::kShared64},

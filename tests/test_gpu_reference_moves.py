@@ -1,6 +1,6 @@
 """GPU parity of attention where the rows' references move in the middle of the pipelined rounds: all rows of a block, one row of
 either 16-row block of a wave, the last row; keys whose norms grow along the key axis move them again and again.  Alone (waves
-of one 16-row block) and in a batch (waves of two), bit for bit, and with the fp64 oracle."""
+of one 16-row block) and in a batch (waves of two; tests/host/shared_blocks_check.cpp), bit for bit, and with the fp64 oracle."""
 import math
 
 import numpy as np
@@ -22,7 +22,7 @@ def dev(b):
 @pytest.mark.parametrize("rows", [slice(None), slice(0, 16), slice(31, 32), slice(272, 273), slice(544, 545)])
 def test_reference_moves(d, rows):
     rng = np.random.default_rng((31, d, rows.indices(545)[0]))
-    hq, hkv, L, n_p, repeats = 2, 1, 545, 1000, 40
+    hq, hkv, L, n_p, repeats = 2, 1, 545, 1000, 44 if d == 64 else 40
     q, kp, vp, k, v = (rng.standard_normal((n, h, d)).astype(np.float32) for n, h in ((L, hq), (n_p, hkv), (n_p, hkv), (L, hkv), (L, hkv)))
     q[rows] *= 12
     kp *= np.linspace(0.1, 2.0, n_p, dtype=np.float32)[:, None, None]
