@@ -94,7 +94,7 @@ struct AttnGroupParams {
   AttnParams item[kMaxGroupItems];
   GroupSchedule sched;
   int n_items;
-  int arrangement;     // attention_schedule.h
+  int arrangements;    // attention_schedule.h
 };
 apbv_status launch_host_attention_group(AttnGroupParams& gp, int head_dim, hipStream_t stream);
 

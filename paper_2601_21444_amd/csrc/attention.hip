@@ -537,27 +537,27 @@ __device__ __forceinline__ int deal(int row, int xcd, int period) {
 }
 
 // The place of this workgroup's item among its XCD's (rows of `group` workgroups, one item each), -1 without one: of the last
-// row some XCDs have no item, and arrange those they have (`arrangement`: that of all rows + 4 times that of all but one).
-__device__ __forceinline__ int arranged_slot(int group, int period, int n_items, int per_unit, int arrangement) {
-  const int s = blockIdx.x / kXcds, n_all = gridDim.x / kXcds;
+// row some XCDs have no item, and arrange those they have.
+template <int D, int W, int kOwn>
+__device__ __forceinline__ int arranged_slot(int slot, int group, int period, int n_items, int arrangements) {
+  const int n_all = gridDim.x / kXcds;
   const bool all = deal(n_all / group - 1, blockIdx.x % kXcds, period) < n_items;
   const int n = all ? n_all : n_all - group;
-  return s < n ? arrange_workgroup(s, n, per_unit, all ? arrangement % 4 : arrangement / 4) : -1;
-}
-
-template <int D, int W, int kOwn>
-__device__ constexpr int workgroups_per_unit() {      // by LDS with head_dim 128, by registers with 64
-  return D == 128 ? (W == 8 ? 1 : 2) : (W == 8 ? 1 : kOwn == 1 ? 4 : 3);
+  return slot < n ? arrange_workgroup(slot, n, workgroups_per_unit(D, W, kOwn), all ? arrangements % 4 : arrangements / 4) : -1;
 }
 
 // ---- workgroup -> (query tile, head, batch, key range); the heads of one KV group share an XCD
 template <int D, int W, int kOwn = 2>
 __global__ __launch_bounds__(64 * W, 2) void host_attention_kernel(const AttnParams p, const int n_qtiles,
-                                                                   const int n_items, const int arrangement) {
+                                                                   const int n_items, const int arrangements) {
   const int xcd = blockIdx.x % kXcds;
-  const int slot = arranged_slot(p.group, p.batch * p.hkv * p.n_splits, n_items, workgroups_per_unit<D, W, kOwn>(), arrangement);
-  if (slot < 0) return;
+  int slot = blockIdx.x / kXcds;
+  if (W != kWavesNarrow && arrangements != 0) {
+    slot = arranged_slot<D, W, kOwn>(slot, p.group, p.batch * p.hkv * p.n_splits, n_items, arrangements);
+    if (slot < 0) return;
+  }
   const int item_split = deal(slot / p.group, xcd, p.batch * p.hkv * p.n_splits);
+  if (item_split >= n_items) return;
   const int split = item_split % p.n_splits;     // key ranges of one item share nothing: spread them over the XCDs
   const int item = item_split / p.n_splits;
   const int g = slot % p.group;
@@ -575,9 +575,13 @@ template <int D, int W, int kOwn = 2>
 __global__ __launch_bounds__(64 * W, 2) void host_attention_group_kernel(const AttnGroupParams gp) {
   const int group = gp.item[0].group, hkv = gp.item[0].hkv;
   const int xcd = blockIdx.x % kXcds;
-  const int slot = arranged_slot(group, hkv, gp.sched.n_entries * hkv, workgroups_per_unit<D, W, kOwn>(), gp.arrangement);
-  if (slot < 0) return;
+  int slot = blockIdx.x / kXcds;
+  if (gp.arrangements != 0) {
+    slot = arranged_slot<D, W, kOwn>(slot, group, hkv, gp.sched.n_entries * hkv, gp.arrangements);
+    if (slot < 0) return;
+  }
   const int unit = deal(slot / group, xcd, hkv);
+  if (unit >= gp.sched.n_entries * hkv) return;
   const int g = slot % group;
   const int entry = unit / hkv, kvh = unit % hkv;
   int m, qt;
@@ -591,13 +595,6 @@ __global__ __launch_bounds__(64 * W, 2) void host_attention_group_kernel(const A
 
 }  // namespace
 
-constexpr int64_t kFixedKeys = 400;      // keys that take as long as the start and the end of a workgroup (20000 cycles, 52 a key)
-
-template <typename Weight>
-static int arrangements_of(int n, int group, Weight&& weight) {
-  return arrangement_of(n, weight) + 4 * arrangement_of(n - group, weight);
-}
-
 template <int W, int kOwn = 2>
 static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t stream) {
   constexpr int kRows = 16 * kOwn * W;
@@ -605,18 +602,16 @@ static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t
   const int64_t n_items = (int64_t)n_qtiles * p.batch * p.hkv * p.n_splits;
   const int64_t n_blocks = (n_items + kXcds - 1) / kXcds * kXcds * p.group;
   if (n_blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
-  const int arrangement = arrangements_of((int)(n_blocks / kXcds), p.group, [&](int r) {
-    const int64_t ahead = (int64_t)(r / p.group) * kXcds / ((int64_t)p.batch * p.hkv * p.n_splits);       // query tiles
-    const int64_t rows = p.s_kv > p.n_vis ? p.L - ahead * kRows : 0;
-    return kFixedKeys + p.n_vis + (rows > 0 ? rows : 0);
-  });
+  // (blocks of two waves have one or two query tiles, which weigh about the same)
+  const int arrangements = W == kWavesNarrow ? 0 : tile_arrangements(workgroups_per_unit(head_dim, W, kOwn), p.group, (int64_t)p.batch * p.hkv * p.n_splits,
+                                                                       kRows, p.L, p.n_vis, p.s_kv > p.n_vis);
   dim3 grid((unsigned)n_blocks);
   dim3 block(64 * W);
   Launcher launch(stream);
   if (head_dim == 128)
-    launch(host_attention_kernel<128, W, kOwn>, grid, block, 0, p, n_qtiles, (int)n_items, arrangement);
+    launch(host_attention_kernel<128, W, kOwn>, grid, block, 0, p, n_qtiles, (int)n_items, arrangements);
   else if (head_dim == 64)
-    launch(host_attention_kernel<64, W, kOwn>, grid, block, 0, p, n_qtiles, (int)n_items, arrangement);
+    launch(host_attention_kernel<64, W, kOwn>, grid, block, 0, p, n_qtiles, (int)n_items, arrangements);
   else
     return APBV_ERR_UNSUPPORTED;
   return launch.status();
@@ -641,12 +636,7 @@ static apbv_status launch_group_variant(AttnGroupParams& gp, int head_dim, const
   const int64_t n_units = (int64_t)gp.sched.n_entries * p0.hkv;
   const int64_t n_blocks = (n_units + kXcds - 1) / kXcds * kXcds * p0.group;
   if (n_blocks > 0x7fffffff) return APBV_ERR_UNSUPPORTED;
-  gp.arrangement = arrangements_of((int)(n_blocks / kXcds), p0.group, [&](int r) {
-    const int entry = (int)((int64_t)(r / p0.group) * kXcds / p0.hkv);
-    int m, qt;
-    decode_group_entry(gp.sched, entry < gp.sched.n_entries ? entry : gp.sched.n_entries - 1, m, qt);
-    return kFixedKeys + n_vis[m] + (int64_t)(qt + 1) * (16 * kOwn * W);
-  });
+  gp.arrangements = schedule_arrangements(workgroups_per_unit(head_dim, W, kOwn), p0.group, p0.hkv, 16 * kOwn * W, gp.sched, n_vis);
   Launcher launch(stream);
   if (head_dim == 128)
     launch(host_attention_group_kernel<128, W, kOwn>, dim3((unsigned)n_blocks), dim3(64 * W), 0, gp);

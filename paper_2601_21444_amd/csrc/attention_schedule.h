@@ -85,18 +85,23 @@ APBV_HOST_DEVICE inline void decode_group_entry(const GroupSchedule& s, int entr
   qt = level - s.level0[m];
 }
 
+// Workgroups of the attention kernel that a unit holds at once: of `waves` waves of `own` 16-row blocks each.  By LDS with
+// head_dim 128, by registers with 64.
+APBV_HOST_DEVICE constexpr int workgroups_per_unit(int head_dim, int waves, int own) {
+  return waves == 8 ? 1 : head_dim == 128 ? 2 : own == 1 ? 4 : 3;
+}
+
 // Which of an XCD's n work items, numbered heaviest first, its s-th workgroup takes.  Workgroups are dispatched to the 32
 // units in turn, so unit j gets numbers j, 32 + j, ... until it holds per_unit of them, and further ones go where one has
-// ended.  Items taken in that order (kInTurn) would give unit 0 the heaviest of every round and unit 31 the lightest.  So
-//   - kFolded: odd rounds run backwards, and where the last round is not full its units are those with the lightest items of
-//     the rounds before: what the units hold adds up to about the same.  With more items than the units hold the ends even out
-//     by themselves, and only the first rounds are arranged;
-//   - kThrees: of up to one item more per unit than two fit (m > 0 of them) the lightest 3 m go to m units, three each, the
-//     lightest of them dispatched last.  In turn the units' two workgroups could end together and take two of the last ones.
-// arrangement_of() says which.
+// ended.  Items taken in that order (kInTurn) give unit 0 the heaviest of every round and unit 31 the lightest.  So
+//   - kFolded: odd rounds run backwards, so that two rounds add up to about the same on every unit.  Where the last round is not
+//     full, its units are those with the lightest items of the round before, or, behind two rounds, units that have one item
+//     more than the others.  With more items than the units hold only the first rounds are arranged;
+//   - kThrees, with two a unit and up to one item more per unit than that (m > 0 of them): the lightest 3 m go to m units, three
+//     each, the lightest of them dispatched last.  In turn the units' two workgroups could end together and take two of the last.
 constexpr int kUnitsPerXcd = 32;
-enum Arrangement { kFolded, kThrees, kInTurn };
-APBV_HOST_DEVICE inline int arrange_workgroup(int s, int n, int per_unit, int how = kThrees) {
+enum Arrangement { kInTurn, kFolded, kThrees };
+APBV_HOST_DEVICE inline int arrange_workgroup(int s, int n, int per_unit, int how) {
   const int round = s / kUnitsPerXcd, unit = s % kUnitsPerXcd;
   if (n <= kUnitsPerXcd || how == kInTurn) return s;
   if (how == kThrees && per_unit == 2 && n > 2 * kUnitsPerXcd && n <= 3 * kUnitsPerXcd) {
@@ -112,20 +117,55 @@ APBV_HOST_DEVICE inline int arrange_workgroup(int s, int n, int per_unit, int ho
   if (round & 1) return round * kUnitsPerXcd + kUnitsPerXcd - 1 - rank;
   return round * kUnitsPerXcd + (round == last ? unit : rank);
 }
-// By the items' weights, weight(r) of the r-th heaviest of an XCD's n (two to a unit).  Folded where they lie far apart: the
-// pairs beside the threes would weigh more than a folded pair and one of the lightest, which are dispatched where one has
-// ended.  In turn for a few items beyond two a unit that weigh about as much as the others.  us, in turn / folded / threes:
-//   16 heads of 128, 5279 rows behind 570 keys 135.3 / 134.2 / 148.2     4430 behind 1500 134.6 / 140.8 / 129.5
-//   8 heads of 128 with their own K/V, 11179 rows behind 522 keys 252.7 / 250.7 / 286.2     8887 behind 1897 221.0 / 210.9 / 206.3
-//   (m = 3) 8526 behind 1500 203.2 / 195.9 / 194.8, behind 5000 307.1 / 331.9 / 336.9     (6) 8910 behind 5000 361.9 / 347.3 / 332.5
-//   28 heads of 128 (6) 2382 behind 1500 117.1 / 109.1 / 111.0, behind 5000 239.8 / 245.6 / 248.1, 2 x 1230 behind 1500 94.3 / 97.1 / 97.8
-// Not always right: 28 heads x 1088 rows in three problems 37.4 / 40.5 / 38.9.
+// By the number of items, what a unit holds, its rows (tile), whether all are of one problem, and the weights, weight(r) of the
+// r-th heaviest.  Which unit is free first is a matter of a few percent of a workgroup's time, and no estimate of it told the
+// orders apart, so the lines lie where an order is seldom behind plain order and ahead of it on average.  Drawn from 1540
+// launches of two and three a unit, each timed in all three.  Time in turn / as chosen, least and mean:
+//   64 rows, head_dim 128    33 to 64 items 0.983, 1.021
+//   128 rows, head_dim 128   33 to 64 0.988, 1.028 (always folded 0.927, 1.034)
+//                            65 to 128, one problem 0.941, 1.013, and 500 near the lines 0.934, 1.050; several 0.972, 1.022
+//                            65 to 96 always folded 0.926, 1.013; threes 0.878, 1.013; more than 128 folded 0.978, 0.996
+//   128 rows, head_dim 64    33 to 96 0.985, 1.049 (always folded 0.941, 1.048)    97 to 128 0.974, 1.033 (folded 0.943, 1.030)
+//                            more than 128 folded 0.973, 0.994
+// Four a unit, the 64-row workgroups of head_dim 64, stay in turn: folded 0.957, 1.002.  us, in turn / folded / threes, and what is taken:
+// 8 heads of 128 with their own K/V, 8910 rows behind 5000 keys 366 / 347 / 339, threes; 28 heads x 1034 rows in three problems 34.2 / 35.7 /
+// 36.9, in turn; 28 heads x 2382 behind 1500 119 / 109 / 115, threes.
 template <typename Weight>
-inline Arrangement arrangement_of(int n, Weight&& weight) {
-  const int m = n - 2 * kUnitsPerXcd, pairs = kUnitsPerXcd - m;
-  if (m <= 0 || pairs <= 0) return kThrees;
-  if (m <= 6 && (0.2 + 0.055 * m) * (double)weight(0) < (double)weight(n - 1)) return kInTurn;
-  return weight(2 * pairs - 1) <= weight(2 * kUnitsPerXcd - 1) + weight(2 * kUnitsPerXcd) ? kThrees : kFolded;
+inline Arrangement arrangement_of(int n, int per_unit, int tile, bool one, Weight&& weight) {
+  if (n <= kUnitsPerXcd || n > 4 * kUnitsPerXcd || per_unit == 1 || per_unit == 4) return kInTurn;
+  const int64_t heaviest = weight(0), lightest = weight(n - 1);
+  if (n <= kUnitsPerXcd * per_unit) return tile == 64 || 2 * lightest < heaviest ? kFolded : kInTurn;
+  if (per_unit == 2 && 2 * lightest < heaviest &&
+      (one ? n > 68 && n < 96 && 4 * lightest >= heaviest : n > 70 && n < 92 && 3 * lightest >= heaviest))
+    return kThrees;
+  if (per_unit == 2 && n > 70 && n < 89) return kInTurn;
+  return (one ? 4 : 3) * lightest < heaviest ? kFolded : kInTurn;
+}
+
+// The arrangements of a launch: of XCDs with an item in the last row of `group` workgroups each (n items), and, times four, of
+// those without.
+constexpr int64_t kFixedKeys = 400;      // keys that take as long as the start and the end of a workgroup (20000 cycles, 52 a key)
+template <typename Weight>
+inline int arrangements_of(int n, int group, int per_unit, int tile, bool one, Weight&& weight) {
+  return arrangement_of(n, per_unit, tile, one, weight) + 4 * arrangement_of(n - group, per_unit, tile, one, weight);
+}
+// One problem, `tile` of its n_rows a workgroup; period: the items of a query tile for each of the group's query heads.
+inline int tile_arrangements(int per_unit, int group, int64_t period, int tile, int64_t n_rows, int64_t n_vis, bool causal) {
+  const int64_t rows = ((n_rows + tile - 1) / tile * period + 7) / 8;
+  return arrangements_of((int)(rows * group), group, per_unit, tile, true, [&](int r) {
+    const int64_t seen = causal ? n_rows - (int64_t)(r / group) * 8 / period * tile : 0;
+    return kFixedKeys + n_vis + (seen > 0 ? seen : 0);
+  });
+}
+// The problems of a schedule.
+inline int schedule_arrangements(int per_unit, int group, int hkv, int tile, const GroupSchedule& s, const int64_t* n_vis) {
+  const int64_t rows = ((int64_t)s.n_entries * hkv + 7) / 8;
+  return arrangements_of((int)(rows * group), group, per_unit, tile, false, [&](int r) {
+    const int64_t entry = (int64_t)(r / group) * 8 / hkv;
+    int m, qt;
+    decode_group_entry(s, entry < s.n_entries ? (int)entry : s.n_entries - 1, m, qt);
+    return kFixedKeys + n_vis[m] + (int64_t)(qt + 1) * tile;
+  });
 }
 
 }  // namespace apbv
