@@ -608,20 +608,29 @@ static apbv_status launch_variant(const AttnParams& p, int head_dim, hipStream_t
   dim3 grid((unsigned)n_blocks);
   dim3 block(64 * W);
   Launcher launch(stream);
-  if (head_dim == 128)
-    launch(host_attention_kernel<128, W, kOwn>, grid, block, 0, p, n_qtiles, (int)n_items, arrangements);
-  else if (head_dim == 64)
+  if (head_dim == 64) {
     launch(host_attention_kernel<64, W, kOwn>, grid, block, 0, p, n_qtiles, (int)n_items, arrangements);
-  else
-    return APBV_ERR_UNSUPPORTED;
-  return launch.status();
+    return launch.status();
+  }
+  if constexpr (W != kWavesNarrow)
+    if (head_dim == 128) {
+      launch(host_attention_kernel<128, W, kOwn>, grid, block, 0, p, n_qtiles, (int)n_items, arrangements);
+      return launch.status();
+    }
+  return APBV_ERR_UNSUPPORTED;
 }
 
+// Blocks of at most kAttnNarrowMaxRows rows in more workgroups than leave SIMDs empty (kNarrow64): two waves of two blocks each,
+// which read K and V half as often as four of one, with head_dim 64; four with 128, where a wave of two blocks has a SIMD to
+// itself either way (64 KB of LDS a workgroup) and moves its O between vector and accumulation registers from round to round.
+// 150 launches (1 to 128 rows, up to 8000 workgroups), time of two waves over that of four: head_dim 128 1.24 on average, least
+// 1.01 (28 heads x 132 blocks of 64 rows 52.6 / 41.5 us); 64 1.09, but 0.83 where there are few keys (32 heads x 27 blocks of 21
+// rows 5.9 / 7.2).
 apbv_status launch_host_attention(const AttnParams& p, int head_dim, hipStream_t stream) {
   static_assert(kAttnQueryTile == kBM && kAttnNarrowQueryTile == 32 * kWavesNarrow, "tile sizes the host-side planning assumes");
   switch (attention_kernel(head_dim, p.group, p.batch, p.hq, p.L, p.n_vis, p.s_kv > p.n_vis, p.n_splits)) {
     case AttentionKernel::kShared64: return launch_variant<kWavesShort, 1>(p, head_dim, stream);
-    case AttentionKernel::kNarrow64: return launch_variant<kWavesNarrow>(p, head_dim, stream);
+    case AttentionKernel::kNarrow64: return head_dim == 64 ? launch_variant<kWavesNarrow>(p, head_dim, stream) : launch_variant<kWavesShort, 1>(p, head_dim, stream);
     case AttentionKernel::k128: return launch_variant<kWavesShort>(p, head_dim, stream);
     case AttentionKernel::k256: break;
   }

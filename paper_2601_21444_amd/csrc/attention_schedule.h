@@ -127,9 +127,9 @@ APBV_HOST_DEVICE inline int arrange_workgroup(int s, int n, int per_unit, int ho
 //                            65 to 96 always folded 0.926, 1.013; threes 0.878, 1.013; more than 128 folded 0.978, 0.996
 //   128 rows, head_dim 64    33 to 96 0.985, 1.049 (always folded 0.941, 1.048)    97 to 128 0.974, 1.033 (folded 0.943, 1.030)
 //                            more than 128 folded 0.973, 0.994
-// Four a unit, the 64-row workgroups of head_dim 64, stay in turn: folded 0.957, 1.002.  us, in turn / folded / threes, and what is taken:
-// 8 heads of 128 with their own K/V, 8910 rows behind 5000 keys 366 / 347 / 339, threes; 28 heads x 1034 rows in three problems 34.2 / 35.7 /
-// 36.9, in turn; 28 heads x 2382 behind 1500 119 / 109 / 115, threes.
+// Four a unit, the 64-row workgroups of head_dim 64, stay in turn: folded 0.957, 1.002.  us, in turn / folded / threes, the last taken:
+// 8 heads of 128 with their own K/V, 8910 rows behind 5000 keys 356 / 341 / 325; 4 x 16 heads x 1160 rows behind 283 56 / 53 / 47; 28
+// heads x 2382 behind 1500 116 / 109 / 111.
 template <typename Weight>
 inline Arrangement arrangement_of(int n, int per_unit, int tile, bool one, Weight&& weight) {
   if (n <= kUnitsPerXcd || n > 4 * kUnitsPerXcd || per_unit == 1 || per_unit == 4) return kInTurn;

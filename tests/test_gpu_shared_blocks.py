@@ -1,6 +1,7 @@
-"""GPU parity of attention where two waves share a block of 32 query rows (few workgroups) with the launches where one wave
-has it: every case runs alone and repeated in a batch large enough for the other kernels (tests/host/shared_blocks_check.cpp
-holds the rule to both); rows, log-sum-exps and the rows around them are compared bit for bit, and with the fp64 oracle."""
+"""GPU parity of attention where every wave has one 16-row block (few workgroups) with the launches where it has two: every case
+runs alone and repeated in a batch large enough for the other kernels (tests/host/shared_blocks_check.cpp holds the rule to both;
+blocks of at most 128 rows at head_dim 128 keep waves of one block in the batch too); rows, log-sum-exps and the rows around them
+are compared bit for bit, and with the fp64 oracle."""
 import math
 
 import numpy as np
