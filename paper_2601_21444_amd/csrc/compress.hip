@@ -1147,7 +1147,9 @@ __global__ __launch_bounds__(kSelectThreads) void long_select_gather_kernel(cons
 // Short blocks: pooled query, scores, selection and gather in one launch (compresses_at_once: where).  A launch that waits
 // for another costs more than what a unit's workgroup does in each step of a short block, so every workgroup adds up the
 // pooled query and scores all keys of its head itself, into LDS, and then shares the selection and the rows as above.  Bound
-// by the latencies of its steps and by what one unit's cache delivers, (probe rows + keys) * D * 2 bytes a workgroup.
+// by the latencies of its steps and by what one unit's cache delivers, (probe rows + keys) * D * 2 bytes a workgroup.  Two
+// workgroups a unit leave 64 registers, and 12 bytes a lane go to scratch; with the registers it asks for (70), one a unit, 447
+// calls take 1.09 times as long, 0.86 to 1.54 times.
 template <int D>
 __global__ __launch_bounds__(kSelectThreads, 8) void short_compress_kernel(View q, View k, View v, int L, int64_t l_p, int group, int hkv, double* __restrict__ s_out,
                                                                         int32_t* __restrict__ idx_out, bf16_t* __restrict__ k_c, bf16_t* __restrict__ v_c) {
@@ -1157,6 +1159,7 @@ __global__ __launch_bounds__(kSelectThreads, 8) void short_compress_kernel(View 
   constexpr int UNROLL = 4;
   static_assert(LPR == 8 || LPR == 16, "the cross-lane reduction below is written for 8 or 16 lanes per row");
   static_assert(kShortKeys == kSelectThreads, "one score a thread");
+  static_assert(kShortKeys + (int)kMaxBinRank <= kBins, "the outputs of a head's only part and one bucket more fit sh.fill");
   __shared__ SelectShared sh;
   __shared__ double qs[D], scores[kShortKeys];
   __shared__ __attribute__((aligned(16))) unsigned char buf[kWaves * D * 8 > kShortKeys * 14 ? kWaves * D * 8 : kShortKeys * 14];

@@ -547,12 +547,18 @@ inline bool share_selection(int64_t heads, int64_t L, int64_t l_p, const Compres
 // call, a launch per step / one (us, graph replay; probe rows x head_dim, keys a head): 128 heads, 512 x 64, 256 15.8 / 10.0;
 // 480 heads 512 x 64, 512 31.4 / 20.4, 512 x 128, 1024 50.8 / 36.0; 32 heads, 448 x 128, 256 14.5 / 12.3; beyond the lines
 // 32 heads, 512 x 128, 512 15.3 / 16.0, 1024 16.6 / 24.2, 96 heads, 512 x 128, 829 19.4 / 19.8; with up to eight heads, two or
-// three launches, 16 x 64, 256 7.6 / 7.9, 512 x 128, 1024 11.6 / 17.1.
+// three launches, 16 x 64, 256 7.6 / 7.9, 512 x 128, 1024 11.6 / 17.1.  Beyond
+// kShortBytes of rows read and written the memory decides, which a launch per step keeps busier with more waves, and a last round
+// of long workgroups weighs more (640 heads, 8 x 128, 768, all selected 120.3 / 134.7; 552 heads, 512 x 128, 962 147.2 / 160.6).
+// Of 11600 drawn calls within the lines a launch per step takes 1.34 times as long on average, and in 3 of 5800 with random
+// scores 2 to 4 % less; where all scores are equal, which every part of a head sorts, in one of a hundred, up to 7 % less.
 constexpr int kShortKeys = 1024;               // keys whose scores a workgroup keeps in LDS, one a thread
+constexpr int64_t kShortBytes = 576 << 20;
 inline int compresses_at_once(int64_t n_rows, int head_dim, int64_t heads, int64_t L, int64_t l_p) {
   const int64_t work = (2 * L + n_rows) * head_dim;
   if (l_p < 1 || L > kShortKeys || n_rows > 1024 || heads <= kMaxSharedHeads) return 0;
   if (work > (heads < 128 ? 110 << 10 : 256 << 10) && heads < 256) return 0;
+  if (heads * (n_rows + L + 4 * l_p) * head_dim * 2 > kShortBytes) return 0;
   int64_t parts = l_p / 32 < 16 ? l_p / 32 : 16;
   parts = parts * heads <= 256 ? parts : 256 / heads;
   return (int)(parts > 1 ? parts : 1);

@@ -114,6 +114,8 @@ int main() {
   EXPECT(compresses_at_once(10, 64, 128, 1023, 33) == 1 && compresses_at_once(9, 128, 128, 700, 65) == 2 && compresses_at_once(4, 128, 256, 1024, 512) == 1);
   EXPECT(compresses_at_once(1024, 64, 272, 1024, 40) == 1 && compresses_at_once(1025, 64, 272, 1024, 40) == 0);
   EXPECT(compresses_at_once(2, 64, 256, 1025, 40) == 0 && compresses_at_once(2, 64, 256, 1024, 0) == 0);
+  EXPECT(compresses_at_once(1, 64, 256, 1024, 1024) == 1 && compresses_at_once(2, 128, 256, 1024, 1024) == 1 && compresses_at_once(6, 64, 256, 1024, 1023) == 1);
+  EXPECT(compresses_at_once(768, 128, 640, 768, 537) == 1 && compresses_at_once(768, 128, 640, 768, 538) == 0);      // the memory line, 3686.4 rows a head
   std::printf("compression rules ok\n");
   return 0;
 }

@@ -22,6 +22,9 @@ CASES = [
     (128, 8, 16, 3, 3, 700, 65, "normal"),        # two
     (128, 16, 16, 2, 2, 1024, 512, "normal"),     # the most keys
     (64, 16, 17, 1024, 1, 1024, 40, "normal"),    # the most probe rows
+    (64, 16, 16, 1, 1, 1024, 1024, "normal"),     # one part with the most outputs
+    (128, 8, 32, 2, 1, 1024, 1024, "equal"),
+    (64, 16, 16, 3, 2, 1024, 1023, "pairs"),
     (64, 16, 16, 1, 2, 1025, 40, "normal"),       # one key more: a launch per step
 ]
 
