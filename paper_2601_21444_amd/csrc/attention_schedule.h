@@ -123,7 +123,7 @@ APBV_HOST_DEVICE inline int arrange_workgroup(int s, int n, int per_unit, int ho
 // launches of two and three a unit, each timed in all three.  Time in turn / as chosen, least and mean:
 //   64 rows, head_dim 128    33 to 64 items 0.983, 1.021
 //   128 rows, head_dim 128   33 to 64 0.988, 1.028 (always folded 0.927, 1.034)
-//                            65 to 128, one problem 0.941, 1.013, and 500 near the lines 0.934, 1.050; several 0.972, 1.022
+//                            65 to 128, one problem 0.941, 1.013, and 500 near the lines 0.934, 1.050; several 0.972, 1.024
 //                            65 to 96 always folded 0.926, 1.013; threes 0.878, 1.013; more than 128 folded 0.978, 0.996
 //   128 rows, head_dim 64    33 to 96 0.985, 1.049 (always folded 0.941, 1.048)    97 to 128 0.974, 1.033 (folded 0.943, 1.030)
 //                            more than 128 folded 0.973, 0.994
@@ -138,7 +138,7 @@ inline Arrangement arrangement_of(int n, int per_unit, int tile, bool one, Weigh
   if (per_unit == 2 && 2 * lightest < heaviest &&
       (one ? n > 68 && n < 96 && 4 * lightest >= heaviest : n > 70 && n < 92 && 3 * lightest >= heaviest))
     return kThrees;
-  if (per_unit == 2 && n > 70 && n < 89) return kInTurn;
+  if (per_unit == 2 && n > 72 && n < 89) return kInTurn;
   return (one ? 4 : 3) * lightest < heaviest ? kFolded : kInTurn;
 }
 

@@ -60,7 +60,7 @@ int main() {
         };
         EXPECT(of(1200) == kInTurn && of(600) == kInTurn);
         EXPECT(of(1200, 64) == (arranged && resident ? kFolded : kInTurn));
-        const bool gap = per_unit == 2 && n >= 71 && n <= 88;
+        const bool gap = per_unit == 2 && n >= 73 && n <= 88;
         const Arrangement between = per_unit == 2 && n >= (one ? 69 : 71) && n <= (one ? 95 : 91) ? kThrees : kInTurn, below = gap ? kInTurn : kFolded;
         for (const int64_t lightest : {599, 400, 399, 300, 299}) {
           Arrangement expected = kInTurn;
@@ -74,7 +74,8 @@ int main() {
   struct { int batch, hq, hkv, d; int64_t L, n_vis; K kernel; int per_unit, n, left, all, fewer; } singles[] = {
       {3, 6, 3, 128, 1654, 136, K::kShared64, 2, 60, 2, F, F},  {2, 16, 2, 128, 655, 4, K::kShared64, 2, 48, 4, F, F},
       {4, 6, 3, 128, 2674, 572, K::k128, 2, 64, 4, F, F},       {2, 6, 3, 128, 2756, 42, K::k128, 2, 34, 4, F, T},
-      {2, 16, 2, 128, 2111, 130, K::k128, 2, 72, 4, T, F},      {3, 16, 2, 128, 1381, 32, K::k128, 2, 72, 2, H, F},
+      {2, 16, 2, 128, 2111, 130, K::k128, 2, 72, 4, F, F},      {2, 16, 2, 128, 2324, 2, K::k128, 2, 80, 4, T, F},
+      {3, 16, 2, 128, 1381, 32, K::k128, 2, 72, 2, H, F},
       {3, 28, 4, 128, 806, 121, K::k128, 2, 77, 4, H, H},       {3, 16, 2, 128, 1610, 559, K::k128, 2, 80, 6, H, T},
       {3, 28, 4, 128, 794, 1731, K::k128, 2, 77, 4, T, T},      {3, 28, 4, 128, 1084, 36, K::k128, 2, 98, 4, T, H},
       {3, 16, 2, 128, 2125, 33, K::k128, 2, 104, 6, F, T},      {3, 16, 2, 128, 2605, 5, K::k128, 2, 128, 6, F, F},

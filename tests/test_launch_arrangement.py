@@ -27,7 +27,7 @@ def problem(g, batch, hq, hkv, d, L, n_p):
     (2, 8, 2, 64, 2900, 300),
     (3, 6, 3, 128, 1654, 136), (2, 16, 2, 128, 655, 4),                                # 64-row workgroups, two a unit: folded
     (4, 6, 3, 128, 2674, 572), (2, 6, 3, 128, 2756, 42),                               # 128 rows, two: folded; folded, in turn
-    (2, 16, 2, 128, 2111, 130), (3, 16, 2, 128, 1381, 32),                             # more: in turn, folded; threes, folded
+    (2, 16, 2, 128, 2111, 130), (2, 16, 2, 128, 2324, 2), (3, 16, 2, 128, 1381, 32),   # more: folded; in turn, folded; threes, folded
     (3, 28, 4, 128, 806, 121), (3, 16, 2, 128, 1610, 559), (3, 28, 4, 128, 794, 1731), # threes; threes, in turn; in turn
     (3, 28, 4, 128, 1084, 36), (3, 16, 2, 128, 2125, 33),                              # in turn, threes; folded, in turn
     (3, 16, 2, 128, 2605, 5), (3, 16, 2, 128, 2728, 47),                               # folded; in turn, folded
