@@ -66,7 +66,7 @@ typedef struct {
 const char* apbv_status_string(apbv_status s);
 
 /* Library version, major*10000 + minor*100 + patch: of this header, and (host, pure) of the library. */
-#define APBV_VERSION 217
+#define APBV_VERSION 218
 int apbv_version(void);
 
 /* Host, pure.  Bytes of workspace apbv_compress_kv needs for this shape (0 on invalid arguments).

@@ -40,14 +40,14 @@
 // heads x 3001 rows 181.1 / 179.4, 2 heads of 64, three problems of 16219 rows 255.5 / 247.3.  A probability equal to the
 // reference is not rounded, so the sooner it moves the closer the results: relative errors against float64 of 300 rows of
 // unit-variance logits with 2^2, 2^5, 2^8 1.86e-3, 2.03e-3, 2.11e-3 (2^8 for 32 rows at a time, as it was: 2.11e-3); every
-// move costs, and times grow from 2^4 down (28 heads of 128 as above, moves at 2^2 / 2^3 / 2^4 / 2^5 / 2^8: 6142 / 6077 / 6039 / 6036 / 6014).
+// move costs, and times grow from 2^4 down (28 heads of 128 as above, both blocks of a wave moving together, at 2^2 / 2^3 / 2^4 / 2^5 / 2^8: 6142 / 6077 / 6039 / 6036 / 6014).
 // Row sums are one more matrix instruction per query block and tile, with ones in place of V^T: it adds the probabilities
 // P^T of all 32 keys to what every lane of the row holds.  Eight two-element dot products on the vector ALU did it before,
 // of about 60 vector instructions a tile, and exchanges between the lane groups at the end.  us, dot products / this: 28
 // heads of 128, three problems of up to 16384 rows 6243 / 6188, 2 x 28 heads x 3001 rows 185.1 / 182.3, 2 heads of 64, three
 // problems of 16219 rows 270.5 / 258.6.
 //
-// Software pipeline.  The steps of a tile form a chain (S^T -> maximum -> exp -> P^T -> O^T); done tile
+// Software pipeline.  The steps of a tile form a chain (S^T -> exp -> P^T -> O^T); done tile
 // after tile a wave alternates between the matrix pipe and the vector ALU, and every LDS fragment read
 // is waited for where it is issued.  Here, while the matrix pipe computes S^T of tile t+1, the vector
 // ALU exponentiates tile t and the V^T operands of tile t are read; while it accumulates O^T of tile t,
@@ -80,8 +80,8 @@ constexpr int kRing = 4;           // K tiles, and V tiles, resident in LDS
 // wave alone on its SIMD does not overlap its matrix and vector instructions (16 + 4.2 n cycles for one 16x16x32 and n vector
 // instructions, measured), so its time is their sum, half of what it is with two.  Results are the same bit for bit.  Four
 // waves of one block, against two waves of two blocks / two waves that finish 16 rows each but form S^T of all 32 (as the
-// reference was one for a block before) / now (us): 16 heads of 128 x 1024 rows behind 224 keys 29.3 / 22.2 / 19.1, 2 heads
-// of 64 x 512 rows behind 160 12.8 / 10.9 / 9.4.
+// reference was one for a block before) / now (us): 16 heads of 128 x 1024 rows behind 224 keys 29.3 / 22.2 / 18.2, 2 heads
+// of 64 x 512 rows behind 160 12.8 / 10.9 / 9.0.
 template <int D, int W, int kOwn>
 __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const int qt, const int b, const int kvh,
                                                     const int g, const int split) {
@@ -132,7 +132,7 @@ __device__ __forceinline__ void attention_workgroup(const AttnParams& p, const i
     }
   }
 
-  // ---- online softmax state.  Per lane: kOwn queries; the four lane groups hold disjoint key subsets.
+  // ---- online softmax state.  Per lane: kOwn queries; the four lane groups hold different head-dim rows of O, and the same sums.
   f32x4 o[T::DBN][kOwn];
 #pragma unroll
   for (int d = 0; d < T::DBN; ++d)

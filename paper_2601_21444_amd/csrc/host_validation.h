@@ -200,14 +200,16 @@ inline int attention_rows(int head_dim, int group, double kv_heads, const Attent
   if (kv_bytes > 128e6 && attention_traffic(head_dim, group, t128, kv_bytes, qo_bytes) > reached * least) return 256;
   return 128;
 }
-// Whether a launch takes 64-row workgroups of four waves, two to a block of 32 rows (kShare in attention.hip), instead: up to
-// a workgroup per unit always, with head_dim 64 (three fit a unit) up to three, and with head_dim 128 up to two where the
-// estimates say so.  Beyond, every wave's own reads of K and V from LDS cost more than the sharing saves (16 heads of 128
-// x 2048 rows behind 704 keys 50.6 / 50.4 us, 28 x 1500 behind 400 46.0 / 53.4).  Drawn from 700 measured launches: where it
-// is taken 1.18 times as fast on average, in one of 517 launches 3 % slower; of 150 others at the upper end of the ranges
-// (250 workgroups and more) one is 3 % slower, and 32 heads of 64 with their own K/V x 1436 rows (736) 5 %.  Blocks of at most
-// kAttnNarrowMaxRows rows, which take 64 rows either way, up to 256 workgroups, or 512 with head_dim 64: 400 launches, 1.13
-// times as fast, none slower; of 150 others one 3 %.
+// Whether a launch takes 64-row workgroups of four waves, one 16-row block each (kOwn = 1 in attention.hip), instead: up to a
+// workgroup per unit always, with head_dim 64 (four fit a unit) up to three, and with head_dim 128 up to two where the
+// estimates say so.  Beyond, every wave's own reads of K and V from LDS cost more than the shorter steps save.  The lines, and the
+// estimate of such a launch, were drawn when two waves formed the S^T of 32 rows between them, and lie low for the kernel as it
+// is (us, 64 / 128 / 256 rows: 16 heads of 128 x 1024 rows behind 224 keys 18.2 / 26.2 / 36.3, x 2048 behind 704 41.0 / 49.2 / 68.9;
+// 28 x 1500 behind 400 40.4 / 38.4 / 51.8).  Of 740 measured launches 470 take it, 1.32 times as fast as the better of 128
+// and 256 rows on average, 0.996 at least.  With head_dim 128 the 47 others of 257 to 512 workgroups would be 1.16 times as
+// fast, 0.98 at least, 113 of 513 to 800 1.02, 0.84 at least; with 64 75 of 769 to 1100 1.07, 0.92 at least, 31 beyond 0.99.  Blocks of
+// at most kAttnNarrowMaxRows rows, which take 64 rows either way, up to 256 workgroups, or 512 with head_dim 64, where two waves
+// take 1.23 times as long (107 launches, 1.11 at least; 24 of 513 to 800 1.04, 0.94 at least).
 inline bool attention_shares_blocks(int head_dim, const AttentionTiles (&tiles)[3]) {
   const AttentionTiles& t = tiles[0];
   if (head_dim == 64) return t.n <= 768;
@@ -230,7 +232,7 @@ inline int attention_rows(int head_dim, int group, int batch, int n_q_heads, int
                         row * (double)n_rows, true);
 }
 
-// The workgroups of a launch: 64 rows by four waves, two to a block of 32, or by two waves; 128 or 256 rows.
+// The workgroups of a launch: 64 rows by four waves of 16, or in more workgroups than these are for (launch_host_attention); 128 or 256 rows.
 enum class AttentionKernel { kShared64, kNarrow64, k128, k256 };
 // One launch of batch * n_q_heads heads and n_splits key ranges, all of n_rows queries.
 inline AttentionKernel attention_kernel(int head_dim, int group, int batch, int n_q_heads, int64_t n_rows, int64_t n_vis, bool causal, int n_splits) {
